@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "uf_internal.h"
+#include "uf_pairs.h"
 #include "uf_split.h"
 
 namespace {
@@ -477,7 +478,12 @@ struct Plan {
     bool rowstats = false;
     int64_t kc = 0, nchunks = 0, kpad = 0;
     int64_t n_parts = 0;
-    size_t off_acc = 0, off_q = 0, off_chunk = 0, off_part = 0, off_rm = 0, off_m = 0, total = 0;
+    // touched-branch pair tiles: segment length, segments held side by side, elements
+    // of one plane of sums
+    bool pairs = false;
+    int64_t seg = 0, n_planes = 0, plane = 0;
+    size_t off_acc = 0, off_q = 0, off_chunk = 0, off_part = 0, off_rm = 0, off_m = 0,
+           off_planes = 0, total = 0;
 };
 
 // sp: the variant's split for the split precisions (ignored otherwise).
@@ -515,21 +521,29 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     const size_t elem = prec == UF_FP64 ? 8 : (mfma ? 1 : 4);
     p->n_parts = std::max<int64_t>(1, (p->sr + 255) / 256);
     const size_t acc_elem = (prec == UF_FP64) ? 8 : 4;
-    // workspace layout for a chunk of kc branches
-    auto layout = [&](int64_t kc) {
+    p->pairs = prec == UF_FP64 || (prec == UF_FP32 && !weighted);
+    p->seg = p->pairs ? ufx::pair_segment(n, nb) : 0;
+    p->plane = p->sr * n + n;
+    const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
+    // workspace layout for a chunk of kc branches; planes: segments held side by side
+    auto layout = [&](int64_t kc, int64_t planes) {
         p->kc = kc;
         p->nchunks = nb > 0 && kc > 0 ? (nb + kc - 1) / kc : 0;
         p->kpad = (kc + ufk::kGramKPad - 1) / ufk::kGramKPad * ufk::kGramKPad;
         Carver c;
-        p->off_acc = c.take(size_t(p->sr) * size_t(n) * acc_elem);
+        p->off_acc = c.take(size_t(p->pairs ? p->plane : p->sr * n) * acc_elem);
         p->off_q = rowstats ? c.take(size_t(p->sr) * size_t(n) * 8) : 0;
         if (mfma)
             p->off_chunk = c.take(size_t(n) * size_t(p->kpad));   // FP8 presence
+        else if (p->pairs)
+            p->off_chunk = c.take(kc > 0 ? ufx::pair_chunk(n, kc, elem).bytes : 0);
         else
             p->off_chunk = c.take(size_t(kc) * size_t(n) * elem);
         p->off_part = rowstats ? c.take(size_t(p->n_parts) * size_t(n) * 8) : 0;
         p->off_rm = rowstats ? c.take(size_t(n) * 8) : 0;
         p->off_m = split ? c.take(size_t(p->sr) * size_t(n) * 8) : 0;
+        p->n_planes = n_seg > 1 ? std::max<int64_t>(planes, 1) : 0;
+        p->off_planes = c.take(size_t(p->n_planes) * size_t(p->plane) * acc_elem);
         p->total = c.off + 256;
     };
     auto shape = [&](int64_t kc) {
@@ -538,28 +552,86 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         return std::min<int64_t>(kc, std::max<int64_t>(nb, 1));
     };
     if (fit > 0) {
-        // the chunk takes what the rest leaves (each carved piece may lose up to
-        // 255 bytes to alignment)
-        layout(0);
+        // A problem is taken when one chunk row of every sample for 32 branches (or all
+        // of them when fewer) fits beside the sums; the chunk takes what the rest leaves
+        // (each carved piece may lose up to 255 bytes to alignment).
+        const std::string too_large = "problem too large for the fixed scratch (" + std::to_string(fit) + " bytes)";
+        const bool pairs = p->pairs;
+        p->pairs = false;
+        layout(0, 0);
+        p->pairs = pairs;
         const size_t rest = p->total + 6 * 256;
         const size_t per = mfma ? size_t(n) : size_t(n) * elem;
         const int64_t room = rest < fit ? int64_t((fit - rest) / std::max<size_t>(per, 1)) : 0;
-        const int64_t kc = std::min<int64_t>(room, std::max<int64_t>(nb, 1));
-        if (mfma || kc < std::min<int64_t>(32, std::max<int64_t>(nb, 1)))
-            return fail(UF_ERR_RANGE, "problem too large for the fixed scratch (" +
-                                          std::to_string(fit) + " bytes)");
-        layout(kc);
-        if (p->total > fit)
-            return fail(UF_ERR_RANGE, "problem too large for the fixed scratch (" +
-                                          std::to_string(fit) + " bytes)");
+        int64_t kc = std::min<int64_t>(room, std::max<int64_t>(nb, 1));
+        if (mfma || kc < std::min<int64_t>(32, std::max<int64_t>(nb, 1))) return fail(UF_ERR_RANGE, too_large);
+        if (pairs) {
+            layout(std::max<int64_t>(nb, 1), n_seg);       // everything at once, if it fits
+            if (p->total <= fit) return UF_OK;
+        }
+        do layout(kc, 1);
+        while (p->total > fit && --kc > 0);
+        if (p->total > fit) return fail(UF_ERR_RANGE, too_large);
         return UF_OK;
     }
     int64_t kc = g_chunk_nodes.load();
     if (kc <= 0) {
         const double budget = 8.0 * 1024 * 1024 * 1024;
-        kc = static_cast<int64_t>(budget / (double(std::max<int64_t>(n, 1)) * double(elem)));
+        const int64_t cols = p->pairs ? (n + 63) / 64 * 64 : n;   // of a chunk row
+        kc = static_cast<int64_t>(budget / (double(std::max<int64_t>(cols, 1)) * double(elem)));
+        // whole segments per chunk, to run side by side
+        if (p->pairs && kc < nb && kc > p->seg) kc -= kc % p->seg;
     }
-    layout(shape(kc));
+    if (p->pairs) kc = std::min<int64_t>(kc, int64_t(1) << 22);   // 32-bit offsets inside a chunk
+    kc = shape(kc);
+    layout(kc, kc >= nb ? n_seg : kc / std::max<int64_t>(p->seg, 1));
+    return UF_OK;
+}
+
+// Plain dense part by touched-branch pair tiles: every branch, chunk by chunk, and
+// inside a chunk segment by segment.  Whole segments run side by side on their own
+// planes; a segment that a chunk boundary cuts continues on one plane.  Either way a
+// pair's sum is the sum, in order, of its segments' sums.
+template <typename T>
+uf_status run_pairs(const uf_embedding* e, const Plan& p, char* base, hipStream_t s) {
+    T* acc = reinterpret_cast<T*>(base + p.off_acc);
+    T* planes = reinterpret_cast<T*>(base + p.off_planes);
+    void* chunk = base + p.off_chunk;
+    const int64_t nb = e->nb;
+    const char* name = p.weighted ? (sizeof(T) == 8 ? "band_wn_f64" : "band_wn_f32")
+                                  : (sizeof(T) == 8 ? "band_uw_f64" : "band_uw_f32");
+    for (int64_t c = 0; c < p.nchunks; ++c) {
+        const int64_t k0 = c * p.kc, kc = std::min<int64_t>(p.kc, nb - k0);
+        {
+            ProfScope ps("embed_nm", s);
+            UF_HIP(ufx::pair_fill<T>(emb_view(*e), p.weighted, k0, kc, chunk, s));
+        }
+        ProfScope ps(name, s);
+        if (p.n_planes == 0) {
+            UF_HIP(ufx::pairs<T>(chunk, p.n, kc, 0, kc, kc, 1, p.sb, p.se, c > 0, acc, p.plane, s));
+            continue;
+        }
+        for (int64_t k = k0; k < k0 + kc;) {
+            const int64_t first_seg = k / p.seg, end = k0 + kc;
+            int64_t count = 0, to = k;   // whole segments from k on
+            while (k % p.seg == 0 && count < p.n_planes && to < end && std::min(to + p.seg, nb) <= end) {
+                to = std::min(to + p.seg, nb);
+                ++count;
+            }
+            if (count == 0) {
+                to = std::min((first_seg + 1) * p.seg, end);
+                UF_HIP(ufx::pairs<T>(chunk, p.n, kc, k - k0, to - k0, p.seg, 1, p.sb, p.se,
+                                     k % p.seg != 0, planes, p.plane, s));
+                if (to % p.seg == 0 || to == nb)
+                    UF_HIP(ufx::pair_planes<T>(planes, p.plane, 1, first_seg == 0, acc, s));
+            } else {
+                UF_HIP(ufx::pairs<T>(chunk, p.n, kc, k - k0, to - k0, p.seg, count, p.sb, p.se, 0,
+                                     planes, p.plane, s));
+                UF_HIP(ufx::pair_planes<T>(planes, p.plane, count, first_seg == 0, acc, s));
+            }
+            k = to;
+        }
+    }
     return UF_OK;
 }
 
@@ -600,28 +672,22 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
     const bool split = prec == UF_FP32_SPLIT || prec == UF_MFMA_SPLIT;
     const SplitCache* sp = split ? hold.get() : nullptr;
     // Dense part: node chunks (all branches, or the split's dense list) into acc.
-    for (int64_t c = 0; c < p.nchunks; ++c) {
+    if (p.pairs) {
+        st = prec == UF_FP64 ? run_pairs<double>(e, p, base, s) : run_pairs<float>(e, p, base, s);
+        if (st != UF_OK) return st;
+    }
+    for (int64_t c = 0; c < p.nchunks && !p.pairs; ++c) {
         const int64_t k0 = c * p.kc;
         const int64_t kc = std::min<int64_t>(p.kc, (sp ? sp->n_dense : nb) - k0);
         const int first = c == 0;
-        if (prec == UF_FP64) {
-            double* E = static_cast<double*>(chunk);
-            {
-                ProfScope ps("embed_nm", s);
-                UF_HIP(ufk::embed_node_major_f64(*e, k0, kc, weighted, E, s));
-            }
-            ProfScope ps(weighted ? "band_wn_f64" : "band_uw_f64", s);
-            UF_HIP(ufk::band_f64(E, e->len + k0, kc, p.n, p.sb, p.se, weighted, first,
-                                 static_cast<double*>(acc), s));
-        } else if (prec == UF_FP32) {
+        if (prec == UF_FP32) {
             float* E = static_cast<float*>(chunk);
             {
                 ProfScope ps("embed_nm", s);
-                UF_HIP(ufk::embed_node_major_f32(*e, k0, kc, weighted, E, s));
+                UF_HIP(ufk::embed_node_major_f32(*e, k0, kc, E, s));
             }
-            ProfScope ps(weighted ? "band_wn_f32" : "band_uw_f32", s);
-            UF_HIP(ufk::band_f32(E, e->len32 + k0, kc, p.n, p.sb, p.se, weighted, first,
-                                 static_cast<float*>(acc), s));
+            ProfScope ps("band_wn_f32", s);
+            UF_HIP(ufk::band_f32(E, kc, p.n, p.sb, p.se, first, static_cast<float*>(acc), s));
         } else if (prec == UF_FP32_SPLIT && sp->q_scale > 0.0) {
             uint32_t* E = static_cast<uint32_t*>(chunk);
             {
@@ -640,8 +706,7 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
                                            e->max_total < (int64_t(1) << 32), k0, kc, E, s));
             }
             ProfScope ps("band_wn_f32", s);
-            UF_HIP(ufk::band_f32(E, nullptr, kc, p.n, p.sb, p.se, 1, first,
-                                 static_cast<float*>(acc), s));
+            UF_HIP(ufk::band_f32(E, kc, p.n, p.sb, p.se, first, static_cast<float*>(acc), s));
         } else {
             const bool ms = prec == UF_MFMA_SPLIT;
             uint8_t* P = static_cast<uint8_t*>(chunk);
@@ -658,7 +723,7 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         }
     }
     if (p.nchunks == 0) {  // no (dense) branch: the dense part is 0
-        const int64_t words = p.sr * p.n * (prec == UF_FP64 ? 2 : 1);
+        const int64_t words = (p.pairs ? p.plane : p.sr * p.n) * (prec == UF_FP64 ? 2 : 1);
         UF_HIP(ufk::zero_u32(static_cast<unsigned*>(acc), words, s));
     }
     // Non-dense part of a split: exact fixed-point pair sums into M (every
@@ -675,10 +740,11 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         ProfScope ps("finalize", s);
         const bool fixed = sp && weighted && sp->q_scale > 0.0;
         const int acc_type = prec == UF_FP64 ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
-        UF_HIP(ufk::finalize(weighted ? 0 : 1, acc, acc_type, fixed ? 1.0 / sp->q_scale : 1.0, scal,
+        const void* diag = p.pairs && weighted ? static_cast<char*>(acc) + size_t(p.sr * p.n) * 8 : nullptr;
+        UF_HIP(ufk::finalize(diag ? 2 : weighted ? 0 : 1, acc, acc_type, fixed ? 1.0 / sp->q_scale : 1.0, scal,
                              p.n, p.sb, p.se, layout, odt == UF_OUT_F32 ? 1 : 0, out, q, s, M,
                              sp && weighted ? sp->sigma : nullptr,
-                             sp && weighted ? sp->unit : 0x1p-40));
+                             sp && weighted ? sp->unit : 0x1p-40, diag));
     }
     if (rowstats) {
         ProfScope ps("row_sums", s);

@@ -181,12 +181,9 @@ hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos,
                           const int32_t* tip_pos, const double* d64, const double* d32,
                           const double* dbf, hipStream_t st);
 
-// Node-major chunk E[k][s] for positions [k0, k0+kc): weighted -> T(l * c/T_s),
-// presence -> T(c > 0).
-hipError_t embed_node_major_f64(const uf_embedding& e, int64_t k0, int64_t kc, int weighted,
-                                double* out, hipStream_t st);
-hipError_t embed_node_major_f32(const uf_embedding& e, int64_t k0, int64_t kc, int weighted,
-                                float* out, hipStream_t st);
+// Node-major chunk E[k][s] = float(l * c/T_s) for positions [k0, k0+kc).
+hipError_t embed_node_major_f32(const uf_embedding& e, int64_t k0, int64_t kc, float* out,
+                                hipStream_t st);
 // Sample-major presence P[s][k]: FP8 e4m3 -2.0 (0xC0) where present, else 0, k < kpad (zero beyond
 // kc), for positions [k0, k0+kc), or for positions list[k0 .. k0+kc) when list is
 // non-null.  kpad is a multiple of kGramKPad.
@@ -194,12 +191,10 @@ hipError_t embed_presence_fp8(const uf_embedding& e, int64_t k0, int64_t kc, int
                               uint8_t* out, hipStream_t st, const int32_t* list = nullptr);
 
 // Band accumulation over one node chunk for stripes [sb, se):
-// weighted: acc += sum_k |E[k][i] - E[k][j]|;  unweighted: acc += sum_k l_k E[k][i] E[k][j].
-hipError_t band_f64(const double* E, const double* lenk, int64_t kc, int64_t n, int64_t sb,
-                    int64_t se, int weighted, int first, double* acc, hipStream_t st);
-hipError_t band_f32(const float* E, const float* lenk, int64_t kc, int64_t n, int64_t sb,
-                    int64_t se, int weighted, int first, float* acc, hipStream_t st);
-// Weighted only, 32-bit fixed point: acc += sum_k |E[k][i] - E[k][j]| (exact integers;
+// acc += sum_k |E[k][i] - E[k][j]|.
+hipError_t band_f32(const float* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
+                    float* acc, hipStream_t st);
+// The same in 32-bit fixed point: acc += sum_k |E[k][i] - E[k][j]| (exact integers;
 // the caller keeps the sum below 2^32).
 hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
                     uint32_t* acc, hipStream_t st);
@@ -218,11 +213,14 @@ hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, i
 // as in uf.h.  split_m (nullable, fixed point with step split_unit, sample-major:
 // M[i*(se-sb) + s-sb]) carries the non-dense branches: kind 0 adds sigma_i + sigma_j -
 // 2 M to the numerator, kind 1 adds M to the Gram value.
+// kind 2: weighted from m_ij = sum_v min(x_iv, x_jv), numerator (diag_i - m) +
+// (diag_j - m) with diag_i = sum_v x_iv in the accumulator's type.
 constexpr int kAccF32 = 0, kAccF64 = 1, kAccU32 = 2;
 hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, const double* scal,
                     int64_t n, int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
                     hipStream_t st, const unsigned long long* split_m = nullptr,
-                    const unsigned long long* sigma = nullptr, double split_unit = 0x1p-40);
+                    const unsigned long long* sigma = nullptr, double split_unit = 0x1p-40,
+                    const void* diag = nullptr);
 
 // Row sums of -d^2/2 over the distinct pairs of stripes [sb, se): two fixed-order stages.
 hipError_t row_sums(const double* q, int64_t n, int64_t sb, int64_t se, double* partial,

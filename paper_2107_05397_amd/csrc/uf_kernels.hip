@@ -2,9 +2,9 @@
 // 64-lane waves, 160 KB LDS per CU, MFMA matrix cores.
 //
 //   k_sample_scalars   per-sample FP64 scalars from the postorder leaf intervals
-//   k_embed_nm<T>      node-major chunk of the embedding (weighted or 0/1)
+//   k_embed_nm         node-major FP32 chunk of the embedding (weighted)
 //   k_embed_pres_fp8  sample-major FP8 (e4m3) 0/1 presence for the MFMA Gram path (merge)
-//   k_band<T, W>       stripe-band accumulation on the vector ALUs (LDS-tiled);
+//   k_band<T>          stripe-band accumulation on the vector ALUs (LDS-tiled);
 //                      T = uint32_t: weighted, 32-bit fixed point, one v_sad_u32
 //                      (|a - b| + acc) per update
 //   k_gram_mfma        unweighted Gram product on MFMA (split-precision lengths)
@@ -109,14 +109,13 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
 // an LDS tile, then written branch-row by branch-row (TS consecutive samples
 // per row: coalesced).
 // ----------------------------------------------------------------------------
-template <typename T>
 __global__ __launch_bounds__(256) void k_embed_nm(
-    int64_t n, int64_t k0, int64_t kc, int weighted, const int64_t* __restrict__ row_ptr,
+    int64_t n, int64_t k0, int64_t kc, const int64_t* __restrict__ row_ptr,
     const int32_t* __restrict__ rank, const int64_t* __restrict__ cum,
     const double* __restrict__ total, const int32_t* __restrict__ lo,
-    const int32_t* __restrict__ hi, const double* __restrict__ len, T* __restrict__ out) {
-    constexpr int TK = 256, TS = 256 / int(sizeof(T));   // FP32: 64 samples, FP64: 32
-    __shared__ T tile[TK][TS + 1];
+    const int32_t* __restrict__ hi, const double* __restrict__ len, float* __restrict__ out) {
+    constexpr int TK = 256, TS = 64;
+    __shared__ float tile[TK][TS + 1];
     const int tid = threadIdx.x;
     const int64_t kb = int64_t(blockIdx.x) * TK;
     const int64_t sb = int64_t(blockIdx.y) * TS;
@@ -131,17 +130,15 @@ __global__ __launch_bounds__(256) void k_embed_nm(
     }
     for (int j = 0; j < TS; ++j) {
         const int64_t s = sb + j;
-        T v = T(0);
+        float v = 0.0f;
         if (kin && s < n) {
             const int64_t c = embedded_count(row_ptr, rank, cum, s, lk, hk);
-            if (weighted) v = T(lv * (double(c) / total[s]));
-            else v = c > 0 ? T(1) : T(0);
+            v = float(lv * (double(c) / total[s]));
         }
         tile[tid][j] = v;
     }
     __syncthreads();
-    constexpr int ROWS_PER_PASS = 256 / TS;
-    for (int r = tid / TS; r < TK; r += ROWS_PER_PASS) {
+    for (int r = tid / TS; r < TK; r += 256 / TS) {
         const int64_t kk = kb + r;
         const int64_t s = sb + (tid % TS);
         if (kk < kc && s < n) out[kk * n + s] = tile[r][tid % TS];
@@ -228,9 +225,8 @@ __global__ __launch_bounds__(256) void k_embed_pres_fp8(
 // 255 partners.  Thread (ti, ts) keeps an 8x8 register tile: samples
 // i0+8ti+a, stripes s0+8ts+b; its partners are the 15 consecutive window
 // entries 8ti+8ts+(a+b).  Per branch and thread: 8+15 LDS reads for 64 pair
-// updates, each update two VALU ops
-//   weighted:   acc += |x_i - x_j|   with x = l * u prescaled in the embedding
-//   unweighted: acc += (l * a_i) * a_j  (Gram form, one FMA; 8 extra multiplies)
+// updates, acc += |x_i - x_j| with x = l * u prescaled in the embedding: two VALU
+// ops (FP32) or one at half rate (v_sad_u32).
 // Staging: KS branches at a time, double-buffered in LDS and filled by direct
 // global->LDS loads (no registers), issued for block b+1 before block b is
 // computed.  Column offsets (mod N) are computed once per thread.
@@ -243,10 +239,6 @@ struct BandCfg;
 template <>
 struct BandCfg<float> {
     static constexpr int KS = 16, MS = 8;
-};
-template <>
-struct BandCfg<double> {
-    static constexpr int KS = 8, MS = 8;
 };
 template <>
 struct BandCfg<uint32_t> {
@@ -315,7 +307,6 @@ template <typename T, int KS, int MS = 8>
 struct BandLds {
     T wi[2][KS][kBandI];
     T wj[2][KS][kBandI + 16 * MS];
-    T wl[2][KS];
 };
 
 // One band tile: samples [i0, i0+128) x stripes [s0, s0+16*MS) of a matrix with
@@ -323,10 +314,9 @@ struct BandLds {
 // (ti, ts) = (tid % 16, tid / 16) owns the 8 x MS register block of samples
 // i0 + 8ti + [0, 8) and stripes s0 + MS*ts + [0, MS); its partners are the
 // 8 + MS - 1 consecutive samples from i0 + s0 + 1 + 8ti + MS*ts.
-template <typename T, bool W, int KS, int MS = 8, bool SWZ = true>
-__device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __restrict__ E,
-                                          const T* __restrict__ lenk, int64_t kc, int64_t n,
-                                          int64_t sb, int64_t se, int64_t i0, int64_t s0,
+template <typename T, int KS, int MS = 8, bool SWZ = true>
+__device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __restrict__ E, int64_t kc,
+                                          int64_t n, int64_t sb, int64_t se, int64_t i0, int64_t s0,
                                           int first, T* __restrict__ acc) {
     constexpr int I = kBandI, WJ = kBandI + 16 * MS;
     constexpr int DW = int(sizeof(T) / 4);          // dwords per element
@@ -378,7 +368,6 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
                 for (int p = 0; p < SEG_J; ++p) dj[p * 64 + lane] = 0u;
             }
         }
-        if (!W && tid < KS) L.wl[buf][tid] = (k0 + tid < kc) ? lenk[k0 + tid] : T(0);
     };
 
     T r[8][MS];
@@ -392,9 +381,6 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
         }
     }
 
-    // FP64 tiles: one branch at a time (two in flight would take them past 256
-    // VGPRs and halve their occupancy)
-    constexpr int UNR = sizeof(T) == 8 ? 1 : 2;
     const int64_t nblk = (kc + KS - 1) / KS;
     stage(0, 0);
     __builtin_amdgcn_s_waitcnt(0);
@@ -402,7 +388,7 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
     for (int64_t blk = 0; blk < nblk; ++blk) {
         const int cur = int(blk & 1);
         if (blk + 1 < nblk) stage(cur ^ 1, (blk + 1) * KS);
-#pragma unroll UNR
+#pragma unroll 2
         for (int kk = 0; kk < KS; ++kk) {
             const uint32_t* rwi = reinterpret_cast<const uint32_t*>(&L.wi[cur][kk][0]);
             const uint32_t* rwj = reinterpret_cast<const uint32_t*>(&L.wj[cur][kk][0]);
@@ -421,19 +407,11 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
                 for (int a = 0; a < 8; ++a)
 #pragma unroll
                     for (int b = 0; b < MS; ++b) r[a][b] = sad_u32(xi[a], xj[a + b], r[a][b]);
-            } else if constexpr (W) {
+            } else {
 #pragma unroll
                 for (int a = 0; a < 8; ++a)
 #pragma unroll
                     for (int b = 0; b < MS; ++b) r[a][b] += fabs(xi[a] - xj[a + b]);
-            } else {
-                const T l = L.wl[cur][kk];
-#pragma unroll
-                for (int a = 0; a < 8; ++a) {
-                    const T li = l * xi[a];
-#pragma unroll
-                    for (int b = 0; b < MS; ++b) r[a][b] = fma(li, xj[a + b], r[a][b]);
-                }
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
@@ -452,11 +430,10 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
     }
 }
 
-template <typename T, bool W>
-__global__ __launch_bounds__(256) void k_band(const T* __restrict__ E,
-                                              const T* __restrict__ lenk, int64_t kc,
-                                              int64_t n, int64_t sb, int64_t se, int64_t n_iblk,
-                                              int first, T* __restrict__ acc) {
+template <typename T>
+__global__ __launch_bounds__(256) void k_band(const T* __restrict__ E, int64_t kc, int64_t n,
+                                              int64_t sb, int64_t se, int64_t n_iblk, int first,
+                                              T* __restrict__ acc) {
     constexpr int KS = BandCfg<T>::KS, MS = BandCfg<T>::MS, TS = 16 * MS;
     __shared__ __attribute__((aligned(16))) BandLds<T, KS, MS> L;
     const int64_t n_sblk = (se - sb + TS - 1) / TS;
@@ -465,7 +442,7 @@ __global__ __launch_bounds__(256) void k_band(const T* __restrict__ E,
     band_patch_tile(xcd_tile(blockIdx.x, n_tiles), n_iblk, n_sblk, &ib, &sblk);
     const int64_t i0 = ib * kBandI;
     const int64_t s0 = sb + sblk * TS;
-    band_tile<T, W, KS, MS, true>(L, E, lenk, kc, n, sb, se, i0, s0, first, acc);
+    band_tile<T, KS, MS, true>(L, E, kc, n, sb, se, i0, s0, first, acc);
 }
 
 // ----------------------------------------------------------------------------
@@ -773,6 +750,7 @@ struct FinIn {
     unsigned long long m;          // split: exact pair sum in the split's unit
     unsigned long long sg_i, sg_j; // weighted split: sigma of both samples
     double sc_i, sc_j;             // per-sample scalars
+    A dg_i, dg_j;                  // min form: sum_v x of both samples
 };
 
 // Loads only (no arithmetic on the loaded values, so that the loads of several
@@ -781,7 +759,8 @@ template <typename A>
 __device__ __forceinline__ FinIn<A> final_inputs(const A* __restrict__ acc,
                                                  const double* __restrict__ scal, int64_t n,
                                                  int64_t sb, int64_t s, int64_t i, int64_t j,
-                                                 const unsigned long long* __restrict__ sigma) {
+                                                 const unsigned long long* __restrict__ sigma,
+                                                 const A* __restrict__ diag) {
     FinIn<A> f;
     f.acc = acc[(s - sb) * n + i];
     f.m = 0ull;   // the split's sum comes from the LDS stage
@@ -789,6 +768,8 @@ __device__ __forceinline__ FinIn<A> final_inputs(const A* __restrict__ acc,
     f.sg_j = sigma ? sigma[j] : 0ull;
     f.sc_i = scal[i];
     f.sc_j = scal[j];
+    f.dg_i = diag ? diag[i] : A(0);
+    f.dg_j = diag ? diag[j] : A(0);
     return f;
 }
 
@@ -796,6 +777,9 @@ template <typename A>
 __device__ __forceinline__ double final_distance(int kind, const FinIn<A>& f, double acc_scale,
                                                  bool split, double split_unit) {
     double num = double(f.acc) * acc_scale;
+    // min form: both differences are sums of x - min(x, y) >= 0 taken in the same
+    // order, so neither is negative and equal samples give exactly 0
+    if (kind == 2) num = (double(f.dg_i) - num) + (double(f.dg_j) - num);
     if (split) {
         if (kind == 0) {
             const long long r = (long long)(f.sg_i + f.sg_j - 2ull * f.m);
@@ -804,7 +788,7 @@ __device__ __forceinline__ double final_distance(int kind, const FinIn<A>& f, do
             num += double(f.m) * split_unit;
         }
     }
-    if (kind == 0) {   // a sum of |x - y| over the sum of x + y: no clamp needed
+    if (kind != 1) {   // a sum of |x - y| over the sum of x + y: no clamp needed
         const double den = f.sc_i + f.sc_j;
         return den > 0.0 ? num / den : 0.0;
     }
@@ -825,7 +809,7 @@ __global__ __launch_bounds__(256) void k_finalize(int kind, const A* __restrict_
                                                   void* __restrict__ out, double* __restrict__ q,
                                                   const unsigned long long* __restrict__ split_m,
                                                   const unsigned long long* __restrict__ sigma,
-                                                  double split_unit) {
+                                                  const A* __restrict__ diag, double split_unit) {
     // row pitch 66 doubles: the run over s (step 66) has 4-way and the
     // anti-diagonal run (step -65) no LDS bank conflicts
     __shared__ double tile[kFinT][kFinT + 2];
@@ -868,7 +852,7 @@ __global__ __launch_bounds__(256) void k_finalize(int kind, const A* __restrict_
             for (int u = 0; u < 8; ++u) {
                 const int ls = (tid >> 6) + 4 * (8 * half + u);
                 const int64_t sc = s0 + ls < se ? s0 + ls : se - 1;
-                in[u] = final_inputs(acc, scal, n, sb, sc, ic, (ic + sc + 1) % n, sigma);
+                in[u] = final_inputs(acc, scal, n, sb, sc, ic, (ic + sc + 1) % n, sigma, diag);
                 if (split_m) in[u].m = (unsigned long long)__double_as_longlong(tile[ls][li]);
             }
 #pragma unroll
@@ -1022,8 +1006,8 @@ __global__ __launch_bounds__(256) void k_band_persistent_f32(
             const BatchTable t = tabs[it.x];
             const int64_t i0 = (int64_t(it.y) % t.n_iblk) * kBandI;
             const int64_t s0 = (int64_t(it.y) / t.n_iblk) * (16 * MS);
-            band_tile<float, true, KS, MS, false>(L, E + t.e_off, nullptr, kc, t.n, 0, t.n / 2, i0, s0,
-                                           first, acc + t.acc_off);
+            band_tile<float, KS, MS, false>(L, E + t.e_off, kc, t.n, 0, t.n / 2, i0, s0, first,
+                                            acc + t.acc_off);
         }
     }
 }
@@ -1050,26 +1034,15 @@ hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos, cons
     return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t embed_nm(const uf_embedding& e, int64_t k0, int64_t kc, int weighted, T* out,
-                           hipStream_t st) {
+hipError_t embed_node_major_f32(const uf_embedding& e, int64_t k0, int64_t kc, float* out,
+                                hipStream_t st) {
     if (kc <= 0 || e.n <= 0) return hipSuccess;
-    constexpr int TS = 256 / int(sizeof(T));
-    const int64_t gy = (e.n + TS - 1) / TS;
+    const int64_t gy = (e.n + 63) / 64;
     if (gy > 65535) return hipErrorInvalidValue;
     dim3 grid(unsigned((kc + 255) / 256), unsigned(gy));
-    hipLaunchKernelGGL(k_embed_nm<T>, grid, dim3(256), 0, st, e.n, k0, kc, weighted, e.row_ptr,
-                       e.rank, e.cum, e.total, e.lo, e.hi, e.len, out);
+    hipLaunchKernelGGL(k_embed_nm, grid, dim3(256), 0, st, e.n, k0, kc, e.row_ptr, e.rank, e.cum,
+                       e.total, e.lo, e.hi, e.len, out);
     return hipGetLastError();
-}
-
-hipError_t embed_node_major_f64(const uf_embedding& e, int64_t k0, int64_t kc, int weighted,
-                                double* out, hipStream_t st) {
-    return embed_nm<double>(e, k0, kc, weighted, out, st);
-}
-hipError_t embed_node_major_f32(const uf_embedding& e, int64_t k0, int64_t kc, int weighted,
-                                float* out, hipStream_t st) {
-    return embed_nm<float>(e, k0, kc, weighted, out, st);
 }
 
 hipError_t embed_presence_fp8(const uf_embedding& e, int64_t k0, int64_t kc, int64_t kpad,
@@ -1085,43 +1058,25 @@ hipError_t embed_presence_fp8(const uf_embedding& e, int64_t k0, int64_t kc, int
 }
 
 template <typename T>
-static hipError_t band(const T* E, const T* lenk, int64_t kc, int64_t n, int64_t sb, int64_t se,
-                       int weighted, int first, T* acc, hipStream_t st) {
+static hipError_t band(const T* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first, T* acc,
+                       hipStream_t st) {
     if (se <= sb || n <= 0) return hipSuccess;
     constexpr int64_t TS = 16 * BandCfg<T>::MS;
     const int64_t n_iblk = (n + kBandI - 1) / kBandI;
     const int64_t n_tiles = n_iblk * ((se - sb + TS - 1) / TS);
     if (n_tiles > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid{unsigned(n_tiles), 1u, 1u};
-    if (weighted)
-        hipLaunchKernelGGL((k_band<T, true>), grid, dim3(256), 0, st, E, lenk, kc, n, sb, se,
-                           n_iblk, first, acc);
-    else
-        hipLaunchKernelGGL((k_band<T, false>), grid, dim3(256), 0, st, E, lenk, kc, n, sb, se,
-                           n_iblk, first, acc);
+    hipLaunchKernelGGL(k_band<T>, dim3(unsigned(n_tiles)), dim3(256), 0, st, E, kc, n, sb, se, n_iblk,
+                       first, acc);
     return hipGetLastError();
 }
 
-hipError_t band_f64(const double* E, const double* lenk, int64_t kc, int64_t n, int64_t sb,
-                    int64_t se, int weighted, int first, double* acc, hipStream_t st) {
-    return band<double>(E, lenk, kc, n, sb, se, weighted, first, acc, st);
+hipError_t band_f32(const float* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
+                    float* acc, hipStream_t st) {
+    return band<float>(E, kc, n, sb, se, first, acc, st);
 }
-hipError_t band_f32(const float* E, const float* lenk, int64_t kc, int64_t n, int64_t sb,
-                    int64_t se, int weighted, int first, float* acc, hipStream_t st) {
-    return band<float>(E, lenk, kc, n, sb, se, weighted, first, acc, st);
-}
-
 hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
                     uint32_t* acc, hipStream_t st) {
-    if (se <= sb || n <= 0) return hipSuccess;
-    constexpr int64_t TS = 16 * BandCfg<uint32_t>::MS;
-    const int64_t n_iblk = (n + kBandI - 1) / kBandI;
-    const int64_t n_tiles = n_iblk * ((se - sb + TS - 1) / TS);
-    if (n_tiles > 0x7fffffff) return hipErrorInvalidValue;
-    const dim3 grid{unsigned(n_tiles), 1u, 1u};
-    hipLaunchKernelGGL((k_band<uint32_t, true>), grid, dim3(256), 0, st, E, nullptr, kc, n, sb, se,
-                       n_iblk, first, acc);
-    return hipGetLastError();
+    return band<uint32_t>(E, kc, n, sb, se, first, acc, st);
 }
 
 hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, int64_t kpad,
@@ -1140,7 +1095,7 @@ hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, i
 hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, const double* scal,
                     int64_t n, int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
                     hipStream_t st, const unsigned long long* split_m,
-                    const unsigned long long* sigma, double split_unit) {
+                    const unsigned long long* sigma, double split_unit, const void* diag) {
     if (se <= sb || n <= 0) return hipSuccess;
     const int64_t gx = (n + kFinT - 1) / kFinT;
     if (gx > 0x7fffffff) return hipErrorInvalidValue;
@@ -1148,15 +1103,15 @@ hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, c
     if (acc_type == kAccF64)
         hipLaunchKernelGGL(k_finalize<double>, grid, dim3(256), 0, st, kind,
                            static_cast<const double*>(acc), acc_scale, scal, n, sb, se, layout,
-                           out_f32, out, q, split_m, sigma, split_unit);
+                           out_f32, out, q, split_m, sigma, static_cast<const double*>(diag), split_unit);
     else if (acc_type == kAccU32)
         hipLaunchKernelGGL(k_finalize<uint32_t>, grid, dim3(256), 0, st, kind,
                            static_cast<const uint32_t*>(acc), acc_scale, scal, n, sb, se, layout,
-                           out_f32, out, q, split_m, sigma, split_unit);
+                           out_f32, out, q, split_m, sigma, static_cast<const uint32_t*>(diag), split_unit);
     else
         hipLaunchKernelGGL(k_finalize<float>, grid, dim3(256), 0, st, kind,
                            static_cast<const float*>(acc), acc_scale, scal, n, sb, se, layout,
-                           out_f32, out, q, split_m, sigma, split_unit);
+                           out_f32, out, q, split_m, sigma, static_cast<const float*>(diag), split_unit);
     return hipGetLastError();
 }
 

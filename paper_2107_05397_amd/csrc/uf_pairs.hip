@@ -1,0 +1,382 @@
+// Pair tiles over touched branches (gfx950): the FP64 and FP32 sums
+//   m_ij = sum_v min(x_iv, x_jv),
+// x = l u (weighted) or l a (unweighted, where the sum is the Gram value).  A term
+// is nonzero only where both samples touch v, and sum |x - y| = s_i + s_j - 2 m_ij,
+// so a tile of sample pairs only visits the branches that its rows and its
+// columns both touch.
+//
+// Chunk layout: samples in blocks of 64.  E[b][k][64] holds the block's values on
+// branch k of the chunk (row kc is all zeros), mask[b][k] the bit of every sample
+// of the block that touches it.
+//
+//   k_pair_zero    clears a chunk
+//   k_pair_fill    one walk over the branches every sample touches writes both
+//   k_pairs        the tiles
+//   k_pair_planes  adds the segments' sums in branch order
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+#include <utility>
+
+#include "uf_device.h"
+#include "uf_internal.h"
+#include "uf_pairs.h"
+
+namespace ufx {
+namespace {
+
+__global__ __launch_bounds__(256) void k_pair_zero(uint4* __restrict__ p, int64_t n16) {
+    const int64_t step = int64_t(gridDim.x) * 256;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n16; i += step)
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
+// One block per sample: every branch of [k0, k0 + kc) that the sample touches, once.
+// Weighted: x = l c / T with the exact count c (the sample's entries under branch v
+// of a walk are [ent, p2), and p2 only moves forward as the walk climbs);
+// unweighted: x = l.
+template <typename T, bool W>
+__global__ __launch_bounds__(256) void k_pair_fill(ufp::Emb e, int32_t k0, int32_t kc, int64_t kcp,
+                                                   T* __restrict__ E,
+                                                   unsigned long long* __restrict__ mask) {
+    const int64_t s = blockIdx.x;
+    const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
+    const double tot = e.total[s];
+    T* Es = E + (s >> 6) * (int64_t(kc) + 1) * 64 + (s & 63);
+    unsigned long long* ms = mask + (s >> 6) * kcp;
+    const unsigned long long bit = 1ull << (s & 63);
+    for (int64_t ent = a + threadIdx.x; ent < b; ent += 256) {
+        int64_t p2 = ent + 1;
+        ufd::for_each_branch(e, ent, a, [&](int32_t v) {
+            const int32_t k = v - k0;
+            if (k < 0 || k >= kc) return;
+            double x = e.len[v];
+            if constexpr (W) {
+                p2 = ufd::lower_bound_rank(e.rank, p2, b, e.hi[v]);
+                x *= double(e.cum[p2 + s] - e.cum[ent + s]) / tot;
+            }
+            Es[int64_t(k) * 64] = T(x);
+            atomicOr(&ms[k], bit);
+        });
+    }
+}
+
+// Tile t of the upper triangle of nblk x nblk blocks: super-tiles of G x G blocks,
+// super-row-major, the diagonal super-tile first in its super-row, row-major inside.
+// Workgroups are dealt to the 8 XCDs round-robin and XCD x takes the x-th eighth of
+// that order, so its CUs walk neighbouring tiles (shared rows and columns in its L2).
+constexpr int kGroup = 8;
+__device__ __forceinline__ bool tri_tile(int64_t b, int64_t nblk, int64_t& bi, int64_t& bj) {
+    constexpr int64_t G = kGroup;
+    const int64_t L = nblk * (nblk + 1) / 2;
+    const int64_t per = (L + 7) / 8;
+    int64_t v = (b & 7) * per + (b >> 3);
+    if ((b >> 3) >= per || v >= L) return false;
+    for (int64_t r0 = 0;;) {
+        const int64_t r = min(G, nblk - r0);
+        const int64_t diag = r * (r + 1) / 2, cnt = diag + r * (nblk - r0 - r);
+        if (v >= cnt) {
+            v -= cnt;
+            r0 += r;
+            continue;
+        }
+        if (v < diag) {
+            int64_t a = 0;
+            while (v >= r - a) {
+                v -= r - a;
+                ++a;
+            }
+            bi = r0 + a;
+            bj = bi + v;
+        } else {
+            v -= diag;
+            const int64_t c0 = r0 + r + (v / (r * G)) * G;
+            const int64_t c = min(G, nblk - c0);
+            const int64_t w = v % (r * G);
+            bi = r0 + w / c;
+            bj = c0 + w % c;
+        }
+        return true;
+    }
+}
+
+// whether the pairs [i0, i1) x [j0, j1), i < j, hold one of stripes [sb, se)
+__device__ __forceinline__ bool pairs_in_range(int64_t i0, int64_t i1, int64_t j0, int64_t j1,
+                                               int64_t n, int64_t sb, int64_t se) {
+    const int64_t S = n / 2;
+    const int64_t dlo = max<int64_t>(1, j0 - (i1 - 1)), dhi = j1 - 1 - i0;
+    if (dhi < dlo) return false;
+    // partner offset d = j - i; stripe d-1 if d <= S, else n-d-1
+    const int64_t a1 = max(dlo, sb + 1), b1 = min(dhi, min(se, S));
+    const int64_t a2 = max(dlo, max(n - se, S + 1)), b2 = min(dhi, n - 1 - sb);
+    return a1 <= b1 || a2 <= b2;
+}
+
+// value of lane L of the own 16-lane row
+template <int L, typename T>
+__device__ __forceinline__ T row_bcast(T v) {
+    if constexpr (sizeof(T) == 8) {
+        const long long b = __builtin_amdgcn_update_dpp(0ll, __double_as_longlong(v), 0x150 + L, 0xf, 0xf, true);
+        return __longlong_as_double(b);
+    } else {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + L, 0xf, 0xf, true));
+    }
+}
+
+// min of two non-negative finite values, one instruction (FP32: their bits as
+// integers, which order the same way)
+__device__ __forceinline__ double vmin(double a, double b) {
+    double d;
+    asm("v_min_f64 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ float vmin(float a, float b) {
+    return __uint_as_float(min(__float_as_uint(a), __float_as_uint(b)));
+}
+
+// descriptor over everything from p on (callers keep their offsets in range)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_of(const void* p) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, -4, 0x00027000);
+}
+template <typename T>
+__device__ __forceinline__ T buf_load(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff) {
+    T o;
+    if constexpr (sizeof(T) == 8) {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, int(voff), int(soff), 0);
+        __builtin_memcpy(&o, &v, 8);
+    } else {
+        const auto v = __builtin_amdgcn_raw_buffer_load_b32(r, int(voff), int(soff), 0);
+        __builtin_memcpy(&o, &v, 4);
+    }
+    return o;
+}
+
+template <class F, int... I>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// A wave owns A samples i x 64 samples j (one block).  Per window of kWin branches it
+// lists those that one of its i and one of its j touch (from the masks, in branch
+// order) in LDS, then runs the list in groups of U: lane l holds x_j of sample
+// j0 + l, and the A values x_i, loaded into the lanes of every 16-lane row, are
+// broadcast from there by DPP; an update is min and +.  Loads run one group ahead.
+// A listed branch adds exactly its terms and the others add zero, so the sums
+// are those over all branches in postorder, whichever tile a pair falls in.
+// Diagonal tiles also give sum_v x_iv (the pair (i, i)) by the same additions: it is
+// no smaller than any m_ij, and equal to it for equal samples.
+// blockIdx.y: segment [ka + seg*y, +seg) of the chunk, to its own plane of out.
+//
+// Why this shape.  A sample touches few branches (6% of a 20,000-tip tree at 300
+// tips, 3% of a 200,000-tip tree at 1,000), but 64 samples together touch most, so
+// a dense tile does mostly zeros: of the branches, 18% (8%) are touched on both sides
+// of an 8 x 64 tile, against 40% (20%) of a 64 x 64 one.  Groups of 4 or 16 samples i
+// were slower (1,500 samples, 20,000 tips: 1.91 and 2.14 ms against 1.67), the first
+// for its loads, the second for its longer lists.  It is bound about half by FP64
+// issue (min, +, and one broadcast per A-row) and by L2 misses of the rows read.
+// Measured with events, against an LDS-tiled kernel over all branches: 256 samples,
+// 1,000 tips 1,144 -> 29 us (two workgroups of 128 x 128 pairs there); 1,500 x 20,000
+// 23.4 -> 1.67 ms; 5,000 x 10,000 32.1 -> 10.9 ms.
+constexpr int kWin = kPairWin;
+template <typename T, int A>
+__global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
+                                               const unsigned long long* __restrict__ mask, int kc,
+                                               int64_t kcp, int n, int sb, int se, int ka, int kb,
+                                               int seg, int load, T* __restrict__ out,
+                                               int64_t plane) {
+    constexpr int SUB = 64 / (4 * A);
+    constexpr int PER = 16 / A;             // branches per load of x_i
+    constexpr int U = 8, NI = U / PER;
+    constexpr int ROW = 64 * int(sizeof(T));
+    __shared__ uint32_t queue[4][kWin + U];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t nblk = (n + 63) / 64;
+    int64_t bi, bj;
+    const int64_t tb = blockIdx.x;
+    if (!tri_tile(((tb >> 3) / SUB) * 8 + (tb & 7), nblk, bi, bj)) return;
+    const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;     // first i inside its block
+    const int i0 = int(bi) * 64 + ig, j0 = int(bj) * 64;
+    if (i0 >= n) return;
+    if (bi != bj && !pairs_in_range(i0, min(i0 + A, n), j0, min(j0 + 64, n), n, sb, se)) return;
+    const int k_lo = ka + seg * int(blockIdx.y), k_hi = min(kb, k_lo + seg);
+    out += int64_t(blockIdx.y) * plane;
+
+    const int S = n / 2, j = j0 + lane;
+    auto slot = [&](int a, int64_t* at, int64_t* dup) -> bool {
+        const int i = i0 + a;
+        *dup = -1;
+        if (i > j || j >= n) return false;
+        if (i == j) {
+            *at = int64_t(se - sb) * n + i;
+            return true;
+        }
+        const int d = j - i;
+        const int s = d <= S ? d - 1 : n - d - 1;
+        if (s < sb || s >= se) return false;
+        const int64_t row = int64_t(s - sb) * n;
+        *at = row + (d <= S ? i : j);
+        if (!(n & 1) && d == S) *dup = row + j;   // an even N's last stripe holds the pair twice
+        return true;
+    };
+    T r[A];
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+        int64_t at, dup;
+        r[a] = (load && slot(a, &at, &dup)) ? out[at] : T(0);
+    }
+    uint32_t* q = queue[wave];
+    const T* Ei = E + bi * (int64_t(kc) + 1) * 64;
+    const T* Ej = E + bj * (int64_t(kc) + 1) * 64;
+    const uint32_t* mi = reinterpret_cast<const uint32_t*>(mask + bi * kcp) + (ig >> 5);
+    const unsigned long long* mj = mask + bj * kcp;
+    const unsigned ibits = ((1u << A) - 1u) << (ig & 31);
+    const unsigned kl = unsigned(lane & 15) / A;
+    const unsigned oi = unsigned(ig + (lane & (A - 1))) * unsigned(sizeof(T));
+    const unsigned oj = unsigned(lane) * unsigned(sizeof(T));
+    struct Group {
+        T j[U], i[NI];
+    };
+    for (int w0 = k_lo; w0 < k_hi; w0 += kWin) {
+        // the window's list; padded to whole groups with the zero row
+        int cnt = 0;
+        uint32_t a_[kWin / 64];
+        unsigned long long b_[kWin / 64];
+#pragma unroll
+        for (int w = 0; w < kWin / 64; ++w) {
+            const int k = min(w0 + 64 * w + lane, kc - 1);
+            a_[w] = mi[2 * int64_t(k)];
+            b_[w] = mj[k];
+        }
+#pragma unroll
+        for (int w = 0; w < kWin / 64; ++w) {
+            const int k = 64 * w + lane;
+            const bool on = (a_[w] & ibits) != 0u && b_[w] != 0ull && w0 + k < k_hi;
+            const unsigned long long bal = __ballot(on);
+            const int at = cnt + int(__popcll(bal & ((1ull << lane) - 1ull)));
+            if (on) q[at] = uint32_t(k);
+            cnt += int(__popcll(bal));
+        }
+        if (lane < U) q[cnt + lane] = uint32_t(kc - w0);
+        wave_sync();
+        const __amdgpu_buffer_rsrc_t ri = buf_of(Ei + int64_t(w0) * 64);
+        const __amdgpu_buffer_rsrc_t rj = buf_of(Ej + int64_t(w0) * 64);
+        auto fetch = [&](int t) -> Group {
+            Group g;
+            const uint32_t ev = q[t * U + (lane & (U - 1))];
+#pragma unroll
+            for (int p = 0; p < NI; ++p)
+                g.i[p] = buf_load<T>(ri, q[t * U + p * PER + kl] * unsigned(ROW) + oi, 0u);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                g.j[u] = buf_load<T>(rj, oj, unsigned(__builtin_amdgcn_readlane(int(ev), u)) * unsigned(ROW));
+            return g;
+        };
+        auto use = [&](const Group& g) {
+            unrolled([&](auto u_) {
+                constexpr int u = decltype(u_)::value;
+                unrolled([&](auto a_) {
+                    constexpr int a = decltype(a_)::value;
+                    r[a] += vmin(row_bcast<(u % PER) * A + a>(g.i[u / PER]), g.j[u]);
+                }, std::make_integer_sequence<int, A>{});
+            }, std::make_integer_sequence<int, U>{});
+        };
+        const int ng = (cnt + U - 1) / U;
+        if (ng > 0) {
+            Group g0 = fetch(0), g1;
+            for (int t = 0; t < ng; t += 2) {   // fetches past the last group re-read it
+                g1 = fetch(min(t + 1, ng - 1));
+                use(g0);
+                g0 = fetch(min(t + 2, ng - 1));
+                if (t + 1 < ng) use(g1);
+            }
+        }
+        wave_sync();   // the list is rewritten next
+    }
+#pragma unroll
+    for (int a = 0; a < A; ++a) {
+        int64_t at, dup;
+        if (!slot(a, &at, &dup)) continue;
+        out[at] = r[a];
+        if (dup >= 0) out[dup] = r[a];
+    }
+}
+
+// acc (first: =, else +=) planes[0] + planes[1] + ..., in that order
+template <typename T>
+__global__ __launch_bounds__(256) void k_pair_planes(const T* __restrict__ planes, int64_t plane,
+                                                     int count, int first, T* __restrict__ acc) {
+    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (e >= plane) return;
+    T v = first ? planes[e] : acc[e] + planes[e];
+    for (int p = 1; p < count; ++p) v += planes[p * plane + e];
+    acc[e] = v;
+}
+
+}  // namespace
+
+template <typename T>
+hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, void* chunk,
+                     hipStream_t st) {
+    if (e.n <= 0 || kc <= 0) return hipSuccess;
+    const PairChunk c = pair_chunk(e.n, kc, sizeof(T));
+    T* E = static_cast<T*>(chunk);
+    auto* mask = reinterpret_cast<unsigned long long*>(static_cast<char*>(chunk) + c.off_mask);
+    const int64_t n16 = int64_t(c.bytes / 16);
+    const unsigned zb = unsigned(std::min<int64_t>((n16 + 255) / 256, 16384));
+    hipLaunchKernelGGL(k_pair_zero, dim3(zb), dim3(256), 0, st, static_cast<uint4*>(chunk), n16);
+    hipError_t er = hipGetLastError();
+    if (er != hipSuccess) return er;
+    if (weighted)
+        hipLaunchKernelGGL((k_pair_fill<T, true>), dim3(unsigned(e.n)), dim3(256), 0, st, e,
+                           int32_t(k0), int32_t(kc), c.kcp, E, mask);
+    else
+        hipLaunchKernelGGL((k_pair_fill<T, false>), dim3(unsigned(e.n)), dim3(256), 0, st, e,
+                           int32_t(k0), int32_t(kc), c.kcp, E, mask);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pairs(const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
+                 int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
+                 hipStream_t st) {
+    if (n <= 0 || kb <= ka) return hipSuccess;
+    const PairChunk c = pair_chunk(n, kc, sizeof(T));
+    const int64_t nblk = (n + 63) / 64;
+    constexpr int A = kPairA;
+    const int64_t blocks = 8 * (64 / (4 * A)) * ((nblk * (nblk + 1) / 2 + 7) / 8);
+    if (blocks > 0x7fffffff || n > 0x7fffff00 || kc > 0x3fffffff || count > 65535)
+        return hipErrorInvalidValue;
+    const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + c.off_mask);
+    hipLaunchKernelGGL((k_pairs<T, A>), dim3(unsigned(blocks), unsigned(count)), dim3(256), 0, st,
+                       static_cast<const T*>(chunk), mask, int(kc), c.kcp, int(n), int(sb), int(se),
+                       int(ka), int(kb), int(std::min<int64_t>(seg, 0x3fffffff)), load, out, plane);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pair_planes(const T* planes, int64_t plane, int64_t count, int first, T* acc,
+                       hipStream_t st) {
+    if (plane <= 0 || count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_pair_planes<T>, dim3(unsigned((plane + 255) / 256)), dim3(256), 0, st, planes,
+                       plane, int(count), first, acc);
+    return hipGetLastError();
+}
+
+template hipError_t pair_fill<double>(const ufp::Emb&, int, int64_t, int64_t, void*, hipStream_t);
+template hipError_t pair_fill<float>(const ufp::Emb&, int, int64_t, int64_t, void*, hipStream_t);
+template hipError_t pairs<double>(const void*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
+                                  int64_t, int64_t, int, double*, int64_t, hipStream_t);
+template hipError_t pairs<float>(const void*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
+                                 int64_t, int64_t, int, float*, int64_t, hipStream_t);
+template hipError_t pair_planes<double>(const double*, int64_t, int64_t, int, double*, hipStream_t);
+template hipError_t pair_planes<float>(const float*, int64_t, int64_t, int, float*, hipStream_t);
+
+}  // namespace ufx
