@@ -743,8 +743,10 @@ __global__ __launch_bounds__(512, 1) void k_gram_mfma(const uint8_t* __restrict_
 // and a 64-lane store covers at most two runs.
 constexpr int kFinT = 64;
 
-// Inputs of one (stripe, sample) element, loaded ahead of the arithmetic.
-template <typename A>
+// Inputs of one (stripe, sample) element, loaded ahead of the arithmetic.  KIND: the
+// form of the numerator (ufk::finalize); SPLIT: with the split's exact pair sums.  The
+// forms are compiled apart, so that each loads and holds only what it uses.
+template <typename A, int KIND, bool SPLIT>
 struct FinIn {
     A acc;                         // dense accumulator (unscaled)
     unsigned long long m;          // split: exact pair sum in the split's unit
@@ -755,40 +757,42 @@ struct FinIn {
 
 // Loads only (no arithmetic on the loaded values, so that the loads of several
 // elements stay in flight together).  Indices must be in range.
-template <typename A>
-__device__ __forceinline__ FinIn<A> final_inputs(const A* __restrict__ acc,
-                                                 const double* __restrict__ scal, int64_t n,
-                                                 int64_t sb, int64_t s, int64_t i, int64_t j,
-                                                 const unsigned long long* __restrict__ sigma,
-                                                 const A* __restrict__ diag) {
-    FinIn<A> f;
+template <typename A, int KIND, bool SPLIT>
+__device__ __forceinline__ FinIn<A, KIND, SPLIT> final_inputs(
+    const A* __restrict__ acc, const double* __restrict__ scal, int64_t n, int64_t sb, int64_t s,
+    int64_t i, int64_t j, const unsigned long long* __restrict__ sigma,
+    const A* __restrict__ diag) {
+    FinIn<A, KIND, SPLIT> f;
     f.acc = acc[(s - sb) * n + i];
-    f.m = 0ull;   // the split's sum comes from the LDS stage
-    f.sg_i = sigma ? sigma[i] : 0ull;
-    f.sg_j = sigma ? sigma[j] : 0ull;
+    if constexpr (SPLIT && KIND == 0) {
+        f.sg_i = sigma[i];
+        f.sg_j = sigma[j];
+    }
     f.sc_i = scal[i];
     f.sc_j = scal[j];
-    f.dg_i = diag ? diag[i] : A(0);
-    f.dg_j = diag ? diag[j] : A(0);
+    if constexpr (KIND == 2) {
+        f.dg_i = diag[i];
+        f.dg_j = diag[j];
+    }
     return f;
 }
 
-template <typename A>
-__device__ __forceinline__ double final_distance(int kind, const FinIn<A>& f, double acc_scale,
-                                                 bool split, double split_unit) {
+template <typename A, int KIND, bool SPLIT>
+__device__ __forceinline__ double final_distance(const FinIn<A, KIND, SPLIT>& f, double acc_scale,
+                                                 double split_unit) {
     double num = double(f.acc) * acc_scale;
     // min form: both differences are sums of x - min(x, y) >= 0 taken in the same
     // order, so neither is negative and equal samples give exactly 0
-    if (kind == 2) num = (double(f.dg_i) - num) + (double(f.dg_j) - num);
-    if (split) {
-        if (kind == 0) {
+    if constexpr (KIND == 2) num = (double(f.dg_i) - num) + (double(f.dg_j) - num);
+    if constexpr (SPLIT) {
+        if constexpr (KIND == 0) {
             const long long r = (long long)(f.sg_i + f.sg_j - 2ull * f.m);
             num += double(r) * split_unit;
         } else {
             num += double(f.m) * split_unit;
         }
     }
-    if (kind != 1) {   // a sum of |x - y| over the sum of x + y: no clamp needed
+    if constexpr (KIND != 1) {   // a sum of |x - y| over the sum of x + y: no clamp needed
         const double den = f.sc_i + f.sc_j;
         return den > 0.0 ? num / den : 0.0;
     }
@@ -801,9 +805,8 @@ __device__ __forceinline__ double final_distance(int kind, const FinIn<A>& f, do
     return fmin(fmax(d, 0.0), 1.0);
 }
 
-template <typename A>
-__global__ __launch_bounds__(256) void k_finalize(int kind, const A* __restrict__ acc,
-                                                  double acc_scale,
+template <typename A, int KIND, bool SPLIT>
+__global__ __launch_bounds__(256) void k_finalize(const A* __restrict__ acc, double acc_scale,
                                                   const double* __restrict__ scal, int64_t n,
                                                   int64_t sb, int64_t se, int layout, int out_f32,
                                                   void* __restrict__ out, double* __restrict__ q,
@@ -831,7 +834,7 @@ __global__ __launch_bounds__(256) void k_finalize(int kind, const A* __restrict_
         // (elements outside the range load from a clamped in-range element and are
         // not stored)
         const int64_t ic = i < n ? i : n - 1;
-        if (split_m) {
+        if constexpr (SPLIT) {
             // the split's sums are sample-major: stage the tile's 64 rows of 64
             // stripes through LDS with coalesced row reads (each element lands in
             // the cell its distance later takes, read back by the same thread)
@@ -847,21 +850,22 @@ __global__ __launch_bounds__(256) void k_finalize(int kind, const A* __restrict_
             __syncthreads();
         }
         for (int half = 0; half < 2; ++half) {
-            FinIn<A> in[8];
+            FinIn<A, KIND, SPLIT> in[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int ls = (tid >> 6) + 4 * (8 * half + u);
                 const int64_t sc = s0 + ls < se ? s0 + ls : se - 1;
-                in[u] = final_inputs(acc, scal, n, sb, sc, ic, (ic + sc + 1) % n, sigma, diag);
-                if (split_m) in[u].m = (unsigned long long)__double_as_longlong(tile[ls][li]);
+                const int64_t jc = ic + sc + 1;   // below 2 n
+                in[u] = final_inputs<A, KIND, SPLIT>(acc, scal, n, sb, sc, ic, jc < n ? jc : jc - n,
+                                                     sigma, diag);
+                if constexpr (SPLIT) in[u].m = (unsigned long long)__double_as_longlong(tile[ls][li]);
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 const int ls = (tid >> 6) + 4 * (8 * half + u);
                 const int64_t s = s0 + ls;
                 if (s >= se || i >= n) continue;
-                const double d = final_distance(kind, in[u], acc_scale, split_m != nullptr,
-                                                split_unit);
+                const double d = final_distance<A, KIND, SPLIT>(in[u], acc_scale, split_unit);
                 if (q) q[(s - sb) * n + i] = -0.5 * d * d;
                 if (condensed) tile[ls][li] = d;
                 else put((s - sb) * n + i, d);
@@ -1113,27 +1117,38 @@ hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, i
     return hipGetLastError();
 }
 
+template <typename A, int KIND, bool SPLIT>
+static hipError_t finalize_as(const void* acc, double acc_scale, const double* scal, int64_t n,
+                              int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
+                              hipStream_t st, const unsigned long long* split_m,
+                              const unsigned long long* sigma, double split_unit, const void* diag) {
+    const int64_t gx = (n + kFinT - 1) / kFinT;
+    if (gx > 0x7fffffff) return hipErrorInvalidValue;
+    dim3 grid(unsigned(gx), grid_y((se - sb + kFinT - 1) / kFinT));
+    hipLaunchKernelGGL((k_finalize<A, KIND, SPLIT>), grid, dim3(256), 0, st, static_cast<const A*>(acc),
+                       acc_scale, scal, n, sb, se, layout, out_f32, out, q, split_m, sigma,
+                       static_cast<const A*>(diag), split_unit);
+    return hipGetLastError();
+}
+
 hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, const double* scal,
                     int64_t n, int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
                     hipStream_t st, const unsigned long long* split_m,
                     const unsigned long long* sigma, double split_unit, const void* diag) {
     if (se <= sb || n <= 0) return hipSuccess;
-    const int64_t gx = (n + kFinT - 1) / kFinT;
-    if (gx > 0x7fffffff) return hipErrorInvalidValue;
-    dim3 grid(unsigned(gx), grid_y((se - sb + kFinT - 1) / kFinT));
-    if (acc_type == kAccF64)
-        hipLaunchKernelGGL(k_finalize<double>, grid, dim3(256), 0, st, kind,
-                           static_cast<const double*>(acc), acc_scale, scal, n, sb, se, layout,
-                           out_f32, out, q, split_m, sigma, static_cast<const double*>(diag), split_unit);
-    else if (acc_type == kAccU32)
-        hipLaunchKernelGGL(k_finalize<uint32_t>, grid, dim3(256), 0, st, kind,
-                           static_cast<const uint32_t*>(acc), acc_scale, scal, n, sb, se, layout,
-                           out_f32, out, q, split_m, sigma, static_cast<const uint32_t*>(diag), split_unit);
-    else
-        hipLaunchKernelGGL(k_finalize<float>, grid, dim3(256), 0, st, kind,
-                           static_cast<const float*>(acc), acc_scale, scal, n, sb, se, layout,
-                           out_f32, out, q, split_m, sigma, static_cast<const float*>(diag), split_unit);
-    return hipGetLastError();
+#define UF_FIN(T_, A_, K_, S_)                                                                       \
+    if (acc_type == T_ && kind == K_ && (split_m != nullptr) == S_)                                   \
+        return finalize_as<A_, K_, S_>(acc, acc_scale, scal, n, sb, se, layout, out_f32, out, q, st, \
+                                       split_m, sigma, split_unit, diag);
+    UF_FIN(kAccF64, double, 1, false)
+    UF_FIN(kAccF64, double, 2, false)
+    UF_FIN(kAccU32, uint32_t, 0, true)
+    UF_FIN(kAccF32, float, 0, false)
+    UF_FIN(kAccF32, float, 0, true)
+    UF_FIN(kAccF32, float, 1, false)
+    UF_FIN(kAccF32, float, 1, true)
+#undef UF_FIN
+    return hipErrorInvalidValue;
 }
 
 hipError_t row_sums(const double* q, int64_t n, int64_t sb, int64_t se, double* partial,
