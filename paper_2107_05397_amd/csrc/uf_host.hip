@@ -17,6 +17,7 @@
 #include <string>
 #include <vector>
 
+#include "uf_bits.h"
 #include "uf_internal.h"
 #include "uf_pairs.h"
 #include "uf_split.h"
@@ -482,6 +483,10 @@ struct Plan {
     // of one plane of sums
     bool pairs = false;
     int64_t seg = 0, n_planes = 0, plane = 0;
+    // Gram product on presence bits: length digits (4 or 8; 0: not taken), length kind,
+    // ranges of a chunk side by side
+    int digits = 0, len_kind = 0;
+    int64_t splits = 0;
     size_t off_acc = 0, off_q = 0, off_chunk = 0, off_part = 0, off_rm = 0, off_m = 0,
            off_planes = 0, total = 0;
 };
@@ -515,15 +520,22 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     p->prec = prec;
     p->rowstats = rowstats;
     const bool split = prec == UF_FP32_SPLIT || prec == UF_MFMA_SPLIT;
-    const bool mfma = prec == UF_MFMA_BF16X2 || prec == UF_MFMA_SPLIT;
+    // Unweighted, over all branches: the Gram product on presence bits, unless the
+    // lengths' range is too wide for its digits
+    p->len_kind = prec == UF_FP64 ? 0 : prec == UF_FP32 ? 1 : 2;
+    const bool bits = !weighted && !split && e->len_fixed[p->len_kind];
+    p->digits = bits ? (prec == UF_FP64 ? 8 : 4) : 0;
+    const bool mfma = (prec == UF_MFMA_BF16X2 && !bits) || prec == UF_MFMA_SPLIT;
     if (split && !sp) return fail(UF_ERR_ARG, "split precision without a split");
     const int64_t nb = split ? sp->n_dense : e->nb;
     const size_t elem = prec == UF_FP64 ? 8 : (mfma ? 1 : 4);
     p->n_parts = std::max<int64_t>(1, (p->sr + 255) / 256);
-    const size_t acc_elem = (prec == UF_FP64) ? 8 : 4;
-    p->pairs = prec == UF_FP64 || (prec == UF_FP32 && !weighted);
+    const size_t acc_elem = (prec == UF_FP64 || bits) ? 8 : 4;
+    p->pairs = !bits && (prec == UF_FP64 || (prec == UF_FP32 && !weighted));
     p->seg = p->pairs ? ufx::pair_segment(n, nb) : 0;
-    p->plane = p->sr * n + n;
+    // sums of one segment or range: with the pair tiles also sum_v x of every sample,
+    // with the bits one plane per four digits
+    p->plane = bits ? p->sr * n * (p->digits / 4) : p->pairs ? p->sr * n + n : p->sr * n;
     const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
     // workspace layout for a chunk of kc branches; planes: segments held side by side
     auto layout = [&](int64_t kc, int64_t planes) {
@@ -531,9 +543,11 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         p->nchunks = nb > 0 && kc > 0 ? (nb + kc - 1) / kc : 0;
         p->kpad = (kc + ufk::kGramKPad - 1) / ufk::kGramKPad * ufk::kGramKPad;
         Carver c;
-        p->off_acc = c.take(size_t(p->pairs ? p->plane : p->sr * n) * acc_elem);
+        p->off_acc = c.take(size_t(p->plane) * acc_elem);
         p->off_q = rowstats ? c.take(size_t(p->sr) * size_t(n) * 8) : 0;
-        if (mfma)
+        if (bits)
+            p->off_chunk = c.take(ufb::bits_plan(n, e->n_tips, kc).bytes);
+        else if (mfma)
             p->off_chunk = c.take(size_t(n) * size_t(p->kpad));   // FP8 presence
         else if (p->pairs)
             p->off_chunk = c.take(kc > 0 ? ufx::pair_chunk(n, kc, elem).bytes : 0);
@@ -542,7 +556,8 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         p->off_part = rowstats ? c.take(size_t(p->n_parts) * size_t(n) * 8) : 0;
         p->off_rm = rowstats ? c.take(size_t(n) * 8) : 0;
         p->off_m = split ? c.take(size_t(p->sr) * size_t(n) * 8) : 0;
-        p->n_planes = n_seg > 1 ? std::max<int64_t>(planes, 1) : 0;
+        p->splits = bits ? ufb::bits_splits(n, std::max<int64_t>(kc, 1)) : 0;
+        p->n_planes = n_seg > 1 ? std::max<int64_t>(planes, 1) : p->splits > 1 ? p->splits : 0;
         p->off_planes = c.take(size_t(p->n_planes) * size_t(p->plane) * acc_elem);
         p->total = c.off + 256;
     };
@@ -557,9 +572,10 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         // (each carved piece may lose up to 255 bytes to alignment).
         const std::string too_large = "problem too large for the fixed scratch (" + std::to_string(fit) + " bytes)";
         const bool pairs = p->pairs;
-        p->pairs = false;
+        const int64_t plane = p->plane;
+        p->plane = p->sr * n;
         layout(0, 0);
-        p->pairs = pairs;
+        p->plane = plane;
         const size_t rest = p->total + 6 * 256;
         const size_t per = mfma ? size_t(n) : size_t(n) * elem;
         const int64_t room = rest < fit ? int64_t((fit - rest) / std::max<size_t>(per, 1)) : 0;
@@ -577,12 +593,16 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     int64_t kc = g_chunk_nodes.load();
     if (kc <= 0) {
         const double budget = 8.0 * 1024 * 1024 * 1024;
-        const int64_t cols = p->pairs ? (n + 63) / 64 * 64 : n;   // of a chunk row
-        kc = static_cast<int64_t>(budget / (double(std::max<int64_t>(cols, 1)) * double(elem)));
+        // bytes of a chunk row
+        const double row = bits       ? double((n + 63) / 64 * 8)
+                           : p->pairs ? double((n + 63) / 64 * 64) * double(elem)
+                                      : double(n) * double(elem);
+        kc = static_cast<int64_t>(budget / std::max(row, 1.0));
         // whole segments per chunk, to run side by side
         if (p->pairs && kc < nb && kc > p->seg) kc -= kc % p->seg;
     }
-    if (p->pairs) kc = std::min<int64_t>(kc, int64_t(1) << 22);   // 32-bit offsets inside a chunk
+    // 32-bit offsets and sums inside a chunk
+    if (p->pairs || bits) kc = std::min<int64_t>(kc, int64_t(1) << 22);
     kc = shape(kc);
     layout(kc, kc >= nb ? n_seg : kc / std::max<int64_t>(p->seg, 1));
     return UF_OK;
@@ -635,6 +655,35 @@ uf_status run_pairs(const uf_embedding* e, const Plan& p, char* base, hipStream_
     return UF_OK;
 }
 
+// Unweighted dense part on presence bits.  Every sum is an exact integer (in FP64), so
+// chunks and ranges add in any order to the same value.
+uf_status run_bits(const uf_embedding* e, const Plan& p, uf_precision prec, char* base, hipStream_t s) {
+    double* acc = reinterpret_cast<double*>(base + p.off_acc);
+    double* planes = reinterpret_cast<double*>(base + p.off_planes);
+    void* ws = base + p.off_chunk;
+    const ufp::Emb ev = emb_view(*e);
+    if (p.nchunks > 0) {
+        ProfScope ps("embed_pres", s);
+        UF_HIP(ufb::tip_bits(ev, e->n_tips, ws, s));
+    }
+    for (int64_t c = 0; c < p.nchunks; ++c) {
+        const int64_t k0 = c * p.kc, kc = std::min<int64_t>(p.kc, e->nb - k0);
+        {
+            ProfScope ps("embed_pres", s);
+            UF_HIP(ufb::branch_bits(ev, e->n_tips, p.len_kind, e->len32, e->len_hi, e->len_lo,
+                                    std::ldexp(1.0, ufb::kDigitBits * p.digits - e->len_exp), k0, kc, ws, s));
+        }
+        ProfScope ps(prec == UF_FP64 ? "band_uw_f64" : prec == UF_FP32 ? "band_uw_f32" : "gram_mfma", s);
+        if (p.splits > 1) {
+            UF_HIP(ufb::gram_bits(p.digits, p.n, e->n_tips, kc, p.splits, p.sb, p.se, 0, planes, ws, s));
+            UF_HIP(ufx::pair_planes<double>(planes, p.plane, p.splits, c == 0, acc, s));
+        } else {
+            UF_HIP(ufb::gram_bits(p.digits, p.n, e->n_tips, kc, 1, p.sb, p.se, c > 0, acc, ws, s));
+        }
+    }
+    return UF_OK;
+}
+
 uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t sb, int64_t se,
                  int layout, uf_out_dtype odt, void* out, double* row_out, double* grand_mean,
                  bool full_means, void* ws, size_t ws_bytes, void* stream, bool fit_ws = false) {
@@ -672,11 +721,14 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
     const bool split = prec == UF_FP32_SPLIT || prec == UF_MFMA_SPLIT;
     const SplitCache* sp = split ? hold.get() : nullptr;
     // Dense part: node chunks (all branches, or the split's dense list) into acc.
-    if (p.pairs) {
+    if (p.digits) {
+        st = run_bits(e, p, prec, base, s);
+        if (st != UF_OK) return st;
+    } else if (p.pairs) {
         st = prec == UF_FP64 ? run_pairs<double>(e, p, base, s) : run_pairs<float>(e, p, base, s);
         if (st != UF_OK) return st;
     }
-    for (int64_t c = 0; c < p.nchunks && !p.pairs; ++c) {
+    for (int64_t c = 0; c < p.nchunks && !p.pairs && !p.digits; ++c) {
         const int64_t k0 = c * p.kc;
         const int64_t kc = std::min<int64_t>(p.kc, (sp ? sp->n_dense : nb) - k0);
         const int first = c == 0;
@@ -723,7 +775,7 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         }
     }
     if (p.nchunks == 0) {  // no (dense) branch: the dense part is 0
-        const int64_t words = (p.pairs ? p.plane : p.sr * p.n) * (prec == UF_FP64 ? 2 : 1);
+        const int64_t words = p.plane * (prec == UF_FP64 || p.digits ? 2 : 1);
         UF_HIP(ufk::zero_u32(static_cast<unsigned*>(acc), words, s));
     }
     // Non-dense part of a split: exact fixed-point pair sums into M (every
@@ -739,11 +791,16 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
     {
         ProfScope ps("finalize", s);
         const bool fixed = sp && weighted && sp->q_scale > 0.0;
-        const int acc_type = prec == UF_FP64 ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
-        const void* diag = p.pairs && weighted ? static_cast<char*>(acc) + size_t(p.sr * p.n) * 8 : nullptr;
-        UF_HIP(ufk::finalize(diag ? 2 : weighted ? 0 : 1, acc, acc_type, fixed ? 1.0 / sp->q_scale : 1.0, scal,
-                             p.n, p.sb, p.se, layout, odt == UF_OUT_F32 ? 1 : 0, out, q, s, M,
-                             sp && weighted ? sp->sigma : nullptr,
+        const int acc_type = prec == UF_FP64 || p.digits ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
+        const bool min_form = p.pairs && weighted, two_parts = p.digits == 8;
+        const int kind = min_form ? 2 : two_parts ? 3 : weighted ? 0 : 1;
+        const double scale = fixed      ? 1.0 / sp->q_scale
+                             : p.digits ? std::ldexp(1.0, e->len_exp - ufb::kDigitBits * p.digits)
+                                        : 1.0;
+        // after the sums: sum_v x of every sample, or the sums' lower part
+        const void* diag = min_form || two_parts ? static_cast<char*>(acc) + size_t(p.sr * p.n) * 8 : nullptr;
+        UF_HIP(ufk::finalize(kind, acc, acc_type, scale, scal, p.n, p.sb, p.se, layout,
+                             odt == UF_OUT_F32 ? 1 : 0, out, q, s, M, sp && weighted ? sp->sigma : nullptr,
                              sp && weighted ? sp->unit : 0x1p-40, diag));
     }
     if (rowstats) {
@@ -1088,6 +1145,7 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         e->n = n;
         e->nb = nb;
         e->nnz = nnz;
+        e->n_tips = t->n_tips;
         for (int64_t r = 0; r < n; ++r) e->max_total = std::max<int64_t>(e->max_total, tb->total[r]);
         char* b = static_cast<char*>(arena);
         e->row_ptr = reinterpret_cast<int64_t*>(b + o_rowptr);
@@ -1150,6 +1208,37 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         }
         rc = hipStreamSynchronize(s);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel"));
+        // Digits of the lengths: 28 bits below 2^len_exp (FP32-rounded and BF16 hi + lo
+        // lengths) or 56 (FP64).  Rounding changes a pair's sum by at most
+        // err = sum_v |l_v - rounded l_v|, and d by at most about err / w with w the
+        // smaller sample's total branch length.  Taken when that bound, over all branches
+        // and the smallest w, is at most 1e-5 and 1e-13 (worst cases; errors of opposite
+        // sign cancel in a pair's sum, and measured against 64 bits the distances are off
+        // by 2.5e-8, the rounding of FP32 results, and 7e-16).
+        double lmax = 0.0;
+        for (int64_t k = 0; k < nb; ++k) lmax = std::max({lmax, t->len[k], double(len32[k]), bf16_value(lhi[k]) + bf16_value(llo[k])});
+        while (e->len_exp < 1100 && lmax >= std::ldexp(1.0 - 0x1p-20, e->len_exp)) ++e->len_exp;
+        while (e->len_exp > -900 && lmax > 0.0 && lmax < std::ldexp(0.5 - 0x1p-20, e->len_exp)) --e->len_exp;
+        std::vector<double> hw(size_t(std::max<int64_t>(n, 1)), 0.0);
+        if (n > 0) rc = hipMemcpy(hw.data(), e->wu, size_t(n) * 8, hipMemcpyDeviceToHost);
+        if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalars"));
+        double w_min = 1e300;
+        for (double w : hw)
+            if (w > 0.0) w_min = std::min(w_min, w);
+        if (std::isfinite(lmax) && e->len_exp < 900 && e->len_exp > -800) {
+            const double q56 = std::ldexp(1.0, e->len_exp - 8 * ufb::kDigitBits), q28 = std::ldexp(1.0, e->len_exp - 4 * ufb::kDigitBits);
+            const double i56 = 1.0 / q56, i28 = 1.0 / q28;
+            double err[3] = {0.0, 0.0, 0.0};
+            auto off = [](double l, double iq, double q) { return std::fabs(l - std::nearbyint(l * iq) * q); };
+            for (int64_t k = 0; k < nb; ++k) {
+                err[0] += off(t->len[k], i56, q56);
+                err[1] += off(double(len32[k]), i28, q28);
+                err[2] += off(bf16_value(lhi[k]) + bf16_value(llo[k]), i28, q28);
+            }
+            e->len_fixed[0] = err[0] <= 1e-13 * w_min;
+            e->len_fixed[1] = err[1] <= 1e-5 * w_min;
+            e->len_fixed[2] = err[2] <= 1e-5 * w_min;
+        }
         *out = guard.release();
         return UF_OK;
     }

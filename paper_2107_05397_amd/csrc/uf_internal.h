@@ -99,6 +99,12 @@ struct uf_embedding {
     int64_t nb = 0;         // branches (non-root nodes) = positions [0, nb)
     int64_t nnz = 0;
     int64_t max_total = 0;  // largest sample total T_s (host copy)
+    int64_t n_tips = 0;     // of the tree
+    // fixed-point lengths of the unweighted Gram product on presence bits: every length
+    // is below 2^len_exp; len_fixed[kind] (FP64, FP32-rounded, BF16 hi + lo lengths) says
+    // that their rounding to the product's digits is negligible
+    int len_exp = 0;
+    bool len_fixed[3] = {false, false, false};
     // table
     int64_t* row_ptr = nullptr;   // [n+1]
     int32_t* rank = nullptr;      // [nnz]
@@ -213,6 +219,8 @@ hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, i
 // as in uf.h.  split_m (nullable, fixed point with step split_unit, sample-major:
 // M[i*(se-sb) + s-sb]) carries the non-dense branches: kind 0 adds sigma_i + sigma_j -
 // 2 M to the numerator, kind 1 adds M to the Gram value.
+// kind 3: kind 1 with the Gram value's upper part in acc (in units of 2^28) and its lower
+// part in diag (one element per accumulator element), both in units of acc_scale.
 // kind 2: weighted from m_ij = sum_v min(x_iv, x_jv), numerator (diag_i - m) +
 // (diag_j - m) with diag_i = sum_v x_iv in the accumulator's type.
 constexpr int kAccF32 = 0, kAccF64 = 1, kAccU32 = 2;

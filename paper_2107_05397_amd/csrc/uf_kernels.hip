@@ -752,7 +752,7 @@ struct FinIn {
     unsigned long long m;          // split: exact pair sum in the split's unit
     unsigned long long sg_i, sg_j; // weighted split: sigma of both samples
     double sc_i, sc_j;             // per-sample scalars
-    A dg_i, dg_j;                  // min form: sum_v x of both samples
+    A dg_i, dg_j;                  // min form: sum_v x of both samples; kind 3: lower part, -
 };
 
 // Loads only (no arithmetic on the loaded values, so that the loads of several
@@ -774,6 +774,7 @@ __device__ __forceinline__ FinIn<A, KIND, SPLIT> final_inputs(
         f.dg_i = diag[i];
         f.dg_j = diag[j];
     }
+    if constexpr (KIND == 3) f.dg_i = diag[(s - sb) * n + i];
     return f;
 }
 
@@ -781,6 +782,7 @@ template <typename A, int KIND, bool SPLIT>
 __device__ __forceinline__ double final_distance(const FinIn<A, KIND, SPLIT>& f, double acc_scale,
                                                  double split_unit) {
     double num = double(f.acc) * acc_scale;
+    if constexpr (KIND == 3) num = (double(f.acc) * 0x1p28 + double(f.dg_i)) * acc_scale;
     // min form: both differences are sums of x - min(x, y) >= 0 taken in the same
     // order, so neither is negative and equal samples give exactly 0
     if constexpr (KIND == 2) num = (double(f.dg_i) - num) + (double(f.dg_j) - num);
@@ -792,7 +794,7 @@ __device__ __forceinline__ double final_distance(const FinIn<A, KIND, SPLIT>& f,
             num += double(f.m) * split_unit;
         }
     }
-    if constexpr (KIND != 1) {   // a sum of |x - y| over the sum of x + y: no clamp needed
+    if constexpr (KIND == 0 || KIND == 2) {   // a sum of |x - y| over the sum of x + y: no clamp needed
         const double den = f.sc_i + f.sc_j;
         return den > 0.0 ? num / den : 0.0;
     }
@@ -1142,6 +1144,7 @@ hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, c
                                        split_m, sigma, split_unit, diag);
     UF_FIN(kAccF64, double, 1, false)
     UF_FIN(kAccF64, double, 2, false)
+    UF_FIN(kAccF64, double, 3, false)
     UF_FIN(kAccU32, uint32_t, 0, true)
     UF_FIN(kAccF32, float, 0, false)
     UF_FIN(kAccF32, float, 0, true)
