@@ -5,11 +5,14 @@
 // unit norm, r = sum_k x'_k y'_k, and a relabelling pi of the first matrix's
 // samples gives r_pi = sum_{i<j} y'_ij x'_{pi(i) pi(j)} (the multiset of x' and
 // so its mean and norm do not change).  x' is expanded to a full square matrix
-// S so that x'_{pi(i) pi(j)} lies in row pi(i).  One workgroup takes the rows i
-// and N-2-i (together N-1 partners) for a batch of permutations, one permutation
-// after another: it holds its partners' y'_ij and pi(j) in registers, stages
-// row pi(i) of S in LDS part by part (coalesced), and gathers from LDS, so each
-// permutation streams S once in order and the random access stays inside LDS.
+// S so that x'_{pi(i) pi(j)} lies in row pi(i).
+//
+// Rows of S that fit a CU's LDS stay there for every permutation (k_perm_lds): the
+// workgroup holding row r takes i = pi^-1(r) of each permutation, streams y'_ij and
+// pi(j), both coalesced, and gathers x' from LDS.  Longer rows go through LDS part
+// by part (k_perm_rows): one workgroup takes the rows i and N-2-i (together N-1
+// partners) for a batch of permutations, holds y'_ij and pi(j) in registers and
+// streams row pi(i) of S.
 // The observed statistic runs through the same kernel with the identity, so the
 // comparisons behind the p-value see identical arithmetic.  Every reduction runs
 // in a fixed order.
@@ -36,7 +39,9 @@ constexpr int kPB = 8;                 // permutations per batch
 constexpr int kRowThreads = 1024;      // threads of the permutation kernel
 constexpr int kJPT = 32;               // partners held in registers per thread
 constexpr int64_t kPartMax = 19456;    // LDS row part: 152 KiB, + 8 KiB for the reduction
-constexpr int64_t kChunk = 1 << 16;    // elements per partial sum
+constexpr int64_t kChunkMin = 4096;    // elements per partial sum, at least
+constexpr int64_t kChunkMost = 8192;   // partial sums, at most
+constexpr int kLdsU = 16;              // y' and pi loads in flight per lane
 constexpr int kScanBlock = 1024;       // elements per scan block (256 threads x 4)
 constexpr int kTile = 64;
 
@@ -56,19 +61,22 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
     return s;
 }
 
-// parts[b] = sum over chunk b of (v - shift)^power (power 1 or 2)
-__global__ __launch_bounds__(256) void k_chunk_sums(const double* __restrict__ v, int64_t m,
-                                                    double shift, int power,
-                                                    double* __restrict__ parts) {
+// parts[v][b] = sum over chunk b of (v - shift)^power (power 1 or 2), for v = x, y
+__global__ __launch_bounds__(256) void k_chunk_sums(const double* __restrict__ x,
+                                                    const double* __restrict__ y, int64_t m,
+                                                    int64_t chunk, double shift_x, double shift_y,
+                                                    int power, double* __restrict__ parts) {
     __shared__ double red[256];
-    const int64_t a = int64_t(blockIdx.x) * kChunk, b = min(m, a + kChunk);
+    const double* v = blockIdx.y ? y : x;
+    const double shift = blockIdx.y ? shift_y : shift_x;
+    const int64_t a = int64_t(blockIdx.x) * chunk, b = min(m, a + chunk);
     double s = 0.0;
     for (int64_t k = a + threadIdx.x; k < b; k += 256) {
         const double d = v[k] - shift;
         s += power == 2 ? d * d : d;
     }
     s = block_sum(s, red);
-    if (threadIdx.x == 0) parts[blockIdx.x] = s;
+    if (threadIdx.x == 0) parts[int64_t(blockIdx.y) * gridDim.x + blockIdx.x] = s;
 }
 
 // out[k] = (v[k] - mean) * scale
@@ -179,6 +187,72 @@ __global__ __launch_bounds__(kRowThreads) void k_perm_rows(const double* __restr
         }
         if (tid == 0) part[(b0 + q) * n_pairs + w] = red[0];
         __syncthreads();
+    }
+}
+
+// inv[b][pi_b(i)] = i (inv starts as -1); bad |= 1 for an entry outside [0, n), bad |= 2
+// where a row names a sample twice
+__global__ __launch_bounds__(256) void k_invert_perms(const int32_t* __restrict__ perm, int64_t total,
+                                                      int64_t n, int32_t* __restrict__ inv,
+                                                      uint32_t* __restrict__ bad) {
+    const int64_t k = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (k >= total) return;
+    const int64_t b = k / n, v = perm[k];
+    if (v < 0 || v >= n) atomicOr(bad, 1u);
+    else if (atomicExch(&inv[b * n + v], int32_t(k - b * n)) != -1) atomicOr(bad, 2u);
+}
+__global__ __launch_bounds__(256) void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n) p[i] = v;
+}
+
+// part[b][x] = sum over the rows r of block x (R rows from R x) of
+// sum_{j > i} y'_ij S[r][pi_b(j)], i = pi_b^-1(r), for the permutations of blockIdx.y's
+// share (b = n_perm: the identity).  The block's R rows of S stay in LDS; each wave
+// takes every 16th permutation and one row after another, kLdsU loads of y' and pi in
+// flight per lane, and adds up its lanes once per permutation.
+// Every permutation reads half of y' and pi from L2 instead of staging all of S:
+// 2,000 samples, 999 permutations 32.5 -> 1.85 ms (19,000 samples, 49: 36 -> 15 ms);
+// bound by reading y' (16 MB, beyond an
+// XCD's L2, once per permutation) and the LDS gather.
+__global__ __launch_bounds__(kRowThreads) void k_perm_lds(const double* __restrict__ S,
+                                                          const double* __restrict__ yv, int64_t n,
+                                                          const int32_t* __restrict__ perm,
+                                                          const int32_t* __restrict__ inv,
+                                                          int64_t n_perm, int64_t per, int R,
+                                                          int64_t n_part, double* __restrict__ part) {
+    extern __shared__ double rows[];   // [R][n]
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = int64_t(blockIdx.x) * R;
+    const int nr = int(min<int64_t>(R, n - r0));
+    for (int64_t k = threadIdx.x; k < nr * n; k += kRowThreads) rows[k] = S[r0 * n + k];
+    __syncthreads();
+    const int64_t b1 = min(n_perm + 1, (int64_t(blockIdx.y) + 1) * per);
+    for (int64_t b = int64_t(blockIdx.y) * per + wave; b < b1; b += kRowThreads / 64) {
+        const int32_t* pb = b < n_perm ? perm + b * n : nullptr;
+        double a = 0.0;
+        for (int q = 0; q < nr; ++q) {
+            const int64_t r = r0 + q;
+            const int64_t i = pb ? int64_t(inv[b * n + r]) : r;
+            const double* row = rows + int64_t(q) * n;
+            const double* yr = yv + (i * n - i * (i + 1) / 2 - i - 1);   // y'_ij at j
+            for (int64_t j0 = i + 1; j0 < n; j0 += 64 * kLdsU) {
+                double y[kLdsU];
+                int32_t p[kLdsU];
+#pragma unroll
+                for (int u = 0; u < kLdsU; ++u) {
+                    const int64_t j = j0 + 64 * u + lane;
+                    y[u] = j < n ? yr[j] : 0.0;
+                    p[u] = j < n ? (pb ? pb[j] : int32_t(j)) : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < kLdsU; ++u) a = fma(y[u], row[p[u]], a);
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
+        if (lane == 0) part[b * n_part + blockIdx.x] = a;
     }
 }
 
@@ -406,8 +480,9 @@ struct MantelPlan {
     int64_t n = 0, m = 0, n_pairs = 0, n_perm = 0;
     size_t off_sq = 0, off_y = 0, off_part = 0, off_tot = 0, off_cs = 0, off_rx = 0, off_ry = 0,
            off_ka = 0, off_kb = 0, off_ia = 0, off_ib = 0, off_z = 0, off_zp = 0, off_agg = 0,
-           off_first = 0, off_last = 0, off_h = 0, off_hs = 0, off_vary = 0, total = 0;
-    int64_t agg_len = 0, nblk = 0;
+           off_first = 0, off_last = 0, off_h = 0, off_hs = 0, off_vary = 0, off_inv = 0, total = 0;
+    int64_t agg_len = 0, nblk = 0, chunk = 0, n_chunks = 0;
+    bool lds = false;   // a row of S fits in LDS
 };
 
 size_t take(size_t& off, size_t bytes) {
@@ -425,9 +500,14 @@ MantelPlan mantel_plan(int64_t n, int method, int64_t n_perm) {
     size_t off = 0;
     p.off_sq = take(off, size_t(n) * size_t(n) * 8);
     p.off_y = take(off, size_t(p.m) * 8);
-    p.off_part = take(off, size_t(n_perm + 1) * size_t(p.n_pairs) * 8);
+    // partial sums: at most one per row
+    p.off_part = take(off, size_t(n_perm + 1) * size_t(n) * 8);
     p.off_tot = take(off, size_t(n_perm + 1) * 8);
-    p.off_cs = take(off, size_t((p.m + ufm::kChunk - 1) / ufm::kChunk + 1) * 8);
+    p.chunk = std::max(ufm::kChunkMin, (p.m + ufm::kChunkMost - 1) / ufm::kChunkMost);
+    p.n_chunks = (p.m + p.chunk - 1) / p.chunk;
+    p.off_cs = take(off, size_t(2 * p.n_chunks + 1) * 8);
+    p.lds = n <= ufm::kPartMax;
+    p.off_inv = take(off, p.lds ? size_t(n_perm) * size_t(n) * 4 : 0);
     if (method == UF_MANTEL_SPEARMAN) {
         p.off_rx = take(off, size_t(p.m) * 8);
         p.off_ry = take(off, size_t(p.m) * 8);
@@ -479,19 +559,21 @@ hipError_t scan_u32(const uint32_t* in, uint32_t* out, int64_t m, uint32_t* agg,
     return hipGetLastError();
 }
 
-// fixed-order sum of (v - shift)^power over m values (host finishes the chunk sums)
-uf_status chunk_sum(const double* v, int64_t m, double shift, int power, double* parts, hipStream_t s,
-                    double* out) {
-    const int64_t nb = (m + ufm::kChunk - 1) / ufm::kChunk;
-    hipLaunchKernelGGL(ufm::k_chunk_sums, dim3(unsigned(nb)), dim3(256), 0, s, v, m, shift, power,
-                       parts);
+// fixed-order sums of (v - shift)^power over the m values of x and of y (host finishes
+// the chunk sums)
+uf_status chunk_sums(const MantelPlan& p, const double* x, const double* y, double shift_x,
+                     double shift_y, int power, double* parts, hipStream_t s, double* sum_x,
+                     double* sum_y) {
+    hipLaunchKernelGGL(ufm::k_chunk_sums, dim3(unsigned(p.n_chunks), 2u), dim3(256), 0, s, x, y, p.m,
+                       p.chunk, shift_x, shift_y, power, parts);
     UFM_HIP(hipGetLastError());
-    std::vector<double> h(static_cast<size_t>(nb));
-    UFM_HIP(hipMemcpyAsync(h.data(), parts, size_t(nb) * 8, hipMemcpyDeviceToHost, s));
+    std::vector<double> h(static_cast<size_t>(2 * p.n_chunks));
+    UFM_HIP(hipMemcpyAsync(h.data(), parts, h.size() * 8, hipMemcpyDeviceToHost, s));
     UFM_HIP(hipStreamSynchronize(s));
-    double t = 0.0;
-    for (double x : h) t += x;
-    *out = t;
+    double t[2] = {0.0, 0.0};
+    for (size_t k = 0; k < h.size(); ++k) t[k >= size_t(p.n_chunks)] += h[k];
+    *sum_x = t[0];
+    *sum_y = t[1];
     return UF_OK;
 }
 
@@ -585,17 +667,28 @@ uf_status uf_mantel(const double* x, const double* y, int64_t n, int method, con
     double* part = reinterpret_cast<double*>(base + p.off_part);
     double* tot = reinterpret_cast<double*>(base + p.off_tot);
     double* cs = reinterpret_cast<double*>(base + p.off_cs);
+    int32_t* inv = reinterpret_cast<int32_t*>(base + p.off_inv);
     const int64_t m = p.m;
+    bool lds_rows = p.lds;
     if (n_perm > 0) {   // every permutation index must address a sample
         uint32_t* bad = reinterpret_cast<uint32_t*>(base + p.off_tot);
         UFM_HIP(hipMemsetAsync(bad, 0, 4, s));
-        hipLaunchKernelGGL(k_check_perms, dim3(grid_of(n_perm * n)), dim3(256), 0, s, perms, n_perm * n,
-                           n, bad);
+        if (p.lds) {
+            hipLaunchKernelGGL(k_fill_i32, dim3(grid_of(n_perm * n)), dim3(256), 0, s, inv, n_perm * n, -1);
+            UFM_HIP(hipGetLastError());
+            hipLaunchKernelGGL(k_invert_perms, dim3(grid_of(n_perm * n)), dim3(256), 0, s, perms,
+                               n_perm * n, n, inv, bad);
+        } else {
+            hipLaunchKernelGGL(k_check_perms, dim3(grid_of(n_perm * n)), dim3(256), 0, s, perms,
+                               n_perm * n, n, bad);
+        }
         UFM_HIP(hipGetLastError());
         uint32_t hbad = 0;
         UFM_HIP(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
         UFM_HIP(hipStreamSynchronize(s));
-        if (hbad) return fail(UF_ERR_ARG, "permutation entries must lie in [0, n)");
+        if (hbad & 1u) return fail(UF_ERR_ARG, "permutation entries must lie in [0, n)");
+        // a row that names a sample twice has no inverse: the general kernel takes it
+        lds_rows = p.lds && !hbad;
     }
 
     const double* xs = x;
@@ -612,11 +705,9 @@ uf_status uf_mantel(const double* x, const double* y, int64_t n, int method, con
     }
     // centre and scale both vectors to unit norm
     double sx = 0.0, sy = 0.0, qx = 0.0, qy = 0.0;
-    if ((st = chunk_sum(xs, m, 0.0, 1, cs, s, &sx)) != UF_OK) return st;
-    if ((st = chunk_sum(ys, m, 0.0, 1, cs, s, &sy)) != UF_OK) return st;
+    if ((st = chunk_sums(p, xs, ys, 0.0, 0.0, 1, cs, s, &sx, &sy)) != UF_OK) return st;
     const double mx = sx / double(m), my = sy / double(m);
-    if ((st = chunk_sum(xs, m, mx, 2, cs, s, &qx)) != UF_OK) return st;
-    if ((st = chunk_sum(ys, m, my, 2, cs, s, &qy)) != UF_OK) return st;
+    if ((st = chunk_sums(p, xs, ys, mx, my, 2, cs, s, &qx, &qy)) != UF_OK) return st;
     if (!(qx > 0.0) || !(qy > 0.0)) {   // a constant matrix: r undefined, reported as 0
         *stat = 0.0;
         *p_value = 1.0;
@@ -630,25 +721,42 @@ uf_status uf_mantel(const double* x, const double* y, int64_t n, int method, con
     hipLaunchKernelGGL(k_standardize, dim3(grid_of(m)), dim3(256), 0, s, ys, m, my, 1.0 / std::sqrt(qy),
                        yv);
     UFM_HIP(hipGetLastError());
-    // observed statistic (identity) in slot n_perm, then the permutations
-    const int64_t nparts = (n + kPartMax - 1) / kPartMax;
-    const int64_t part_len = (n + nparts - 1) / nparts;
-    const size_t lds = size_t(part_len + kRowThreads) * 8;
-    static const bool attr_ok =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&k_perm_rows),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            int((kPartMax + kRowThreads) * 8)) == hipSuccess;
+    // observed statistic (identity) in slot n_perm, beside the permutations
+    static const bool attr_ok = [] {
+        const int most = int((kPartMax + kRowThreads) * 8);
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_perm_rows),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void*>(&k_perm_lds),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess;
+    }();
     if (!attr_ok) return fail(UF_ERR_DEVICE, "cannot enable 160 KiB of LDS for the permutation kernel");
-    hipLaunchKernelGGL(k_perm_rows, dim3(unsigned(p.n_pairs)), dim3(kRowThreads), lds, s, S, yv, n,
-                       static_cast<const int32_t*>(nullptr), n_perm, 1, p.n_pairs, part_len, part);
-    UFM_HIP(hipGetLastError());
-    for (int64_t b0 = 0; b0 < n_perm; b0 += kPB) {
-        const int nb = int(std::min<int64_t>(kPB, n_perm - b0));
-        hipLaunchKernelGGL(k_perm_rows, dim3(unsigned(p.n_pairs)), dim3(kRowThreads), lds, s, S, yv, n,
-                           perms, b0, nb, p.n_pairs, part_len, part);
+    int64_t n_part = p.n_pairs;
+    if (lds_rows) {
+        // as many rows per block as give each of 256 CUs one block, if LDS holds them;
+        // few rows: the permutations in shares, at least one per wave
+        const int64_t R = std::max<int64_t>(1, std::min((n + 255) / 256, kPartMax / n));
+        n_part = (n + R - 1) / R;
+        const int64_t shares = std::max<int64_t>(1, std::min((n_perm + 16) / 16, 512 / n_part));
+        const int64_t per = (n_perm + shares) / shares;   // of n_perm + 1
+        hipLaunchKernelGGL(k_perm_lds, dim3(unsigned(n_part), unsigned((n_perm + per) / per)),
+                           dim3(kRowThreads), size_t(R * n) * 8, s, S, yv, n, perms, inv, n_perm, per,
+                           int(R), n_part, part);
         UFM_HIP(hipGetLastError());
+    } else {
+        const int64_t nparts = (n + kPartMax - 1) / kPartMax;
+        const int64_t part_len = (n + nparts - 1) / nparts;
+        const size_t lds = size_t(part_len + kRowThreads) * 8;
+        hipLaunchKernelGGL(k_perm_rows, dim3(unsigned(p.n_pairs)), dim3(kRowThreads), lds, s, S, yv, n,
+                           static_cast<const int32_t*>(nullptr), n_perm, 1, p.n_pairs, part_len, part);
+        UFM_HIP(hipGetLastError());
+        for (int64_t b0 = 0; b0 < n_perm; b0 += kPB) {
+            const int nb = int(std::min<int64_t>(kPB, n_perm - b0));
+            hipLaunchKernelGGL(k_perm_rows, dim3(unsigned(p.n_pairs)), dim3(kRowThreads), lds, s, S, yv, n,
+                               perms, b0, nb, p.n_pairs, part_len, part);
+            UFM_HIP(hipGetLastError());
+        }
     }
-    hipLaunchKernelGGL(k_perm_total, dim3(unsigned(n_perm + 1)), dim3(256), 0, s, part, p.n_pairs, tot);
+    hipLaunchKernelGGL(k_perm_total, dim3(unsigned(n_perm + 1)), dim3(256), 0, s, part, n_part, tot);
     UFM_HIP(hipGetLastError());
     std::vector<double> h(static_cast<size_t>(n_perm + 1));
     UFM_HIP(hipMemcpyAsync(h.data(), tot, h.size() * 8, hipMemcpyDeviceToHost, s));
