@@ -89,9 +89,10 @@ hipError_t topk_rows(const float* vals, int64_t rows, int64_t cols, int k, int32
                      float* val, hipStream_t st);
 hipError_t sparse_count(const Emb& e, int64_t* cnt, hipStream_t st);
 hipError_t sparse_fill(const Emb& e, const int64_t* off, int32_t* pos, double* val, hipStream_t st);
+// q_longest: the longest list of q; scratch: n_rows rows of nb doubles.
 hipError_t rerank(const SparseView& q, const SparseView& r, const int32_t* qids,
-                  const int32_t* cand, int64_t nq, int kc, int64_t nb, double* scratch,
-                  int64_t n_rows, double* out, hipStream_t st);
+                  const int32_t* cand, int64_t nq, int kc, int64_t nb, int64_t q_longest,
+                  double* scratch, int64_t n_rows, double* out, hipStream_t st);
 hipError_t zero_f64(double* p, int64_t n, hipStream_t st);
 hipError_t condensed_block(const void* c, int is_f32, int64_t n, int64_t row_off, int64_t n_rows,
                            int64_t col_off, int64_t n_cols, float* out, hipStream_t st);

@@ -12,7 +12,7 @@
 //   k_sqdist           FP32 pairwise squared distances (kNN)
 //   k_topk_rows        exact k smallest per row (radix select, ties by index)
 //   k_sparse_*         per-sample lists of (branch, l*u) for nonzero branches
-//   k_rerank           exact weighted-normalized distance across two tables
+//   k_rerank*          exact weighted-normalized distance across two tables
 //   k_condensed_block, k_gather_pairs   reads of a condensed matrix
 #include <hip/hip_runtime.h>
 
@@ -966,6 +966,115 @@ __global__ __launch_bounds__(256) void k_rerank(SparseView q, SparseView rf,
     }
 }
 
+// The same re-rank with the query's branches in LDS: a bit per branch, the number of
+// the query's branches below each 64-bit word, and the query's values in branch order
+// (in scratch when they do not fit).  A candidate's entry looks its bit up; where both
+// samples touch the branch, the count and the bits below give the value's place.
+// Groups of W waves take one candidate each, so nothing is reduced over the block for
+// every candidate.  blockIdx.y: a share of the candidates (few queries).
+// With a dense row of the query in memory instead, every entry was a gather of 8
+// bytes from a 1.6 MB row (200,000 branches): 1,500 queries x 100 candidates of 6,000
+// branches 6.5 -> 1.35 ms; bound by streaming the candidates' lists (12 bytes an
+// entry, 8 TB/s from L2 and beyond).
+constexpr int kRrThreads = 1024, kRrWaves = kRrThreads / 64, kRrU = 8;
+__global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, SparseView rf,
+                                                            const int32_t* __restrict__ qids,
+                                                            const int32_t* __restrict__ cand,
+                                                            int64_t nq, int kc, int share, int W,
+                                                            int words, int64_t nb, int vals_lds,
+                                                            double* __restrict__ scratch,
+                                                            double* __restrict__ out) {
+    extern __shared__ unsigned long long sh[];
+    __shared__ double red[kRrWaves];
+    __shared__ int wave_tot[kRrWaves];
+    unsigned long long* bits = sh;                                      // [words]
+    uint16_t* below = reinterpret_cast<uint16_t*>(sh + words);          // [words]
+    double* vals = vals_lds ? reinterpret_cast<double*>(sh + words + (words + 3) / 4)
+                            : scratch + int64_t(blockIdx.x) * nb;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int groups = kRrWaves / W, group = wave / W, part = wave % W;
+    const int c_lo = int(blockIdx.y) * share, c_hi = min(kc, c_lo + share);
+    for (int64_t qi = blockIdx.x; qi < nq; qi += gridDim.x) {
+        const int64_t qs = qids[qi];
+        const int64_t qa = q.off[qs], qb = q.off[qs + 1];
+        __syncthreads();                     // the previous query's tables are consumed
+        for (int w = tid; w < words; w += kRrThreads) bits[w] = 0ull;
+        __syncthreads();
+        for (int64_t t = qa + tid; t < qb; t += kRrThreads) {
+            const int32_t p = q.pos[t];
+            atomicOr(&bits[p >> 6], 1ull << (p & 63));
+        }
+        __syncthreads();
+        const int per = (words + kRrThreads - 1) / kRrThreads;
+        const int w0 = min(words, tid * per), w1 = min(words, w0 + per);
+        int own = 0;
+        for (int w = w0; w < w1; ++w) own += int(__popcll(bits[w]));
+        int inc = own;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(inc, off, 64);
+            if (lane >= off) inc += o;
+        }
+        if (lane == 63) wave_tot[wave] = inc;
+        __syncthreads();
+        int run = inc - own;
+        for (int w = 0; w < wave; ++w) run += wave_tot[w];
+        for (int w = w0; w < w1; ++w) {
+            below[w] = uint16_t(run);
+            run += int(__popcll(bits[w]));
+        }
+        __syncthreads();
+        auto place = [&](int32_t p, unsigned long long word) {
+            return int(below[p >> 6]) + int(__popcll(word & ((1ull << (p & 63)) - 1ull)));
+        };
+        for (int64_t t = qa + tid; t < qb; t += kRrThreads) {
+            const int32_t p = q.pos[t];
+            vals[place(p, bits[p >> 6])] = q.val[t];
+        }
+        __syncthreads();
+        for (int c0 = c_lo; c0 < c_hi; c0 += groups) {
+            const int c = c0 + group;
+            double acc = 0.0;
+            int64_t r = 0;
+            if (c < c_hi) {
+                r = cand[qi * kc + c];
+                const int64_t ra = rf.off[r], rb = rf.off[r + 1];
+                for (int64_t t0 = ra + part * 64; t0 < rb; t0 += 64 * W * kRrU) {
+                    int32_t p[kRrU];
+                    double v[kRrU];
+#pragma unroll
+                    for (int u = 0; u < kRrU; ++u) {
+                        const int64_t t = t0 + int64_t(64 * W) * u + lane;
+                        p[u] = t < rb ? rf.pos[t] : -1;
+                        v[u] = t < rb ? rf.val[t] : 0.0;
+                    }
+#pragma unroll
+                    for (int u = 0; u < kRrU; ++u) {
+                        if (p[u] < 0) continue;
+                        const unsigned long long word = bits[p[u] >> 6];
+                        if ((word >> (p[u] & 63)) & 1ull) acc += fmin(vals[place(p[u], word)], v[u]);
+                    }
+                }
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+            }
+            if (W > 1) {                     // block-uniform
+                if (lane == 0) red[wave] = acc;
+                __syncthreads();
+                acc = 0.0;
+                for (int w = 0; w < W; ++w) acc += red[group * W + w];
+                __syncthreads();
+            }
+            if (c < c_hi && part == 0 && lane == 0) {
+                const double den = q.s[qs] + rf.s[r];
+                const double d = den > 0.0 ? (den - 2.0 * acc) / den : 0.0;
+                out[qi * kc + c] = fmin(fmax(d, 0.0), 1.0);
+            }
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void k_zero_f64(double* __restrict__ p, int64_t n) {
     const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
     if (i < n) p[i] = 0.0;
@@ -1240,10 +1349,36 @@ hipError_t sparse_fill(const Emb& e, const int64_t* off, int32_t* pos, double* v
     return hipGetLastError();
 }
 
+// The tables of k_rerank_bits take the LDS of a CU or less when the tree has at most
+// about a million branches and no query touches 65,536 (16-bit counts); else the query
+// is laid out as a dense row in scratch.
 hipError_t rerank(const SparseView& q, const SparseView& r, const int32_t* qids,
-                  const int32_t* cand, int64_t nq, int kc, int64_t nb, double* scratch,
-                  int64_t n_rows, double* out, hipStream_t st) {
+                  const int32_t* cand, int64_t nq, int kc, int64_t nb, int64_t q_longest,
+                  double* scratch, int64_t n_rows, double* out, hipStream_t st) {
     if (nq <= 0 || kc <= 0) return hipSuccess;
+    const int64_t words = (nb + 63) / 64;
+    const size_t tables = size_t(words + (words + 3) / 4) * 8, with_vals = tables + size_t(q_longest) * 8;
+    constexpr size_t kMost = 158 * 1024;     // beside the static arrays
+    if (q_longest < 65536 && tables <= kMost) {
+        static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rerank_bits),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                        int(kMost)) == hipSuccess;
+        if (!attr_ok) return hipErrorInvalidValue;
+        const bool vals_lds = with_vals <= kMost;
+        // shares of the candidates while the queries alone leave CUs idle (each share lays
+        // the query out again, so at least 8 candidates)
+        const int64_t shares = vals_lds ? std::max<int64_t>(1, std::min<int64_t>((kc + 7) / 8, 512 / nq)) : 1;
+        const int share = int((kc + shares - 1) / shares);
+        int W = 1;
+        while (W < kRrWaves && share * W < kRrWaves) W *= 2;
+        const int64_t gx = vals_lds ? std::min<int64_t>(nq, 1 << 20) : std::min(nq, n_rows);
+        hipLaunchKernelGGL(k_rerank_bits, dim3(unsigned(gx), unsigned((kc + share - 1) / share)),
+                           dim3(kRrThreads), vals_lds ? with_vals : tables, st, q, r, qids, cand, nq, kc,
+                           share, W, int(words), nb, vals_lds ? 1 : 0, scratch, out);
+        return hipGetLastError();
+    }
+    hipError_t e = zero_f64(scratch, n_rows * nb, st);
+    if (e != hipSuccess) return e;
     const int64_t grid = nq < n_rows ? nq : n_rows;
     hipLaunchKernelGGL(k_rerank, dim3(unsigned(grid)), dim3(256), 0, st, q, r, qids, cand, nq, kc,
                        nb, scratch, out);

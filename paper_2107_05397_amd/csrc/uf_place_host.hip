@@ -81,7 +81,7 @@ struct uf_mlp {
 };
 
 struct uf_sparse {
-    int64_t n = 0, nb = 0, nnz = 0;
+    int64_t n = 0, nb = 0, nnz = 0, longest = 0;   // longest: of the samples' lists
     void* arena = nullptr;
     int64_t* off = nullptr;
     int32_t* pos = nullptr;
@@ -535,6 +535,7 @@ uf_status uf_sparse_build(const uf_embedding* emb, void* stream, uf_sparse** out
         sp->n = n;
         sp->nb = emb->nb;
         sp->nnz = run;
+        for (int64_t i = 0; i < n; ++i) sp->longest = std::max(sp->longest, soff[size_t(i + 1)] - soff[size_t(i)]);
         const size_t o_off = 0, o_pos = align256(size_t(n + 1) * 8);
         const size_t o_val = o_pos + align256(size_t(std::max<int64_t>(run, 1)) * 4);
         const size_t o_s = o_val + align256(size_t(std::max<int64_t>(run, 1)) * 8);
@@ -583,9 +584,8 @@ uf_status uf_dm_rerank_weighted_normalized(const uf_sparse* queries, const uf_sp
         hipStream_t s = static_cast<hipStream_t>(stream);
         double* scratch = reinterpret_cast<double*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
         const int64_t rows = rerank_rows(n_queries);
-        UF_HIP(ufp::zero_f64(scratch, rows * queries->nb, s));
         UF_HIP(ufp::rerank(queries->view(), refs->view(), query_ids, cand, n_queries, int(k),
-                           queries->nb, scratch, rows, out, s));
+                           queries->nb, queries->longest, scratch, rows, out, s));
         return UF_OK;
     });
 }
