@@ -974,8 +974,8 @@ __global__ __launch_bounds__(256) void k_rerank(SparseView q, SparseView rf,
 // every candidate.  blockIdx.y: a share of the candidates (few queries).
 // With a dense row of the query in memory instead, every entry was a gather of 8
 // bytes from a 1.6 MB row (200,000 branches): 1,500 queries x 100 candidates of 6,000
-// branches 6.5 -> 1.35 ms; bound by streaming the candidates' lists (12 bytes an
-// entry, 8 TB/s from L2 and beyond).
+// branches 6.5 -> 1.35 ms (zeroing of the rows included). What is left is one pass over
+// each candidate's list, 12 bytes an entry; its cache traffic was not counted.
 constexpr int kRrThreads = 1024, kRrWaves = kRrThreads / 64, kRrU = 8;
 __global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, SparseView rf,
                                                             const int32_t* __restrict__ qids,
