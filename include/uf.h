@@ -237,9 +237,9 @@ uf_status uf_dm_weighted_normalized_noalloc(const uf_embedding* emb, uf_precisio
 /* Many tables of uneven size on one tree -- e.g. rarefied replicates of a study
  * -- computed together: weighted normalized, FP32 accumulation, FP64 division,
  * condensed FP32 output per table.  Per node chunk, one kernel embeds every
- * table and one persistent kernel (#CU x wgs_per_cu resident blocks) drains
- * the (table, band tile) items of all tables from per-XCD atomic queues; the
- * whole sequence (all chunks, then finalize of every table) is captured once
+ * table and one launch runs the pair tiles of all tables (each over the branches
+ * that its samples touch); the whole sequence (all chunks, then the segments'
+ * sums and finalize of every table) is captured once
  * into a hipGraph and replayed with one launch.  Per-pair values are bitwise
  * equal to uf_dm_weighted_normalized(UF_FP32) on each table alone.
  *
@@ -260,19 +260,18 @@ uf_status uf_batch_plan_create(const uf_tree* tree, const uf_table* const* table
                                uf_batch** out);
 int64_t uf_batch_n_tables(const uf_batch* batch);
 uf_status uf_batch_workspace_size(const uf_batch* batch, size_t* bytes);
-/* Current launch configuration: branches staged per LDS block (8, 16 or 32),
- * resident blocks per CU, stripes per band tile (64, 128 or 256; a tile is 128
- * samples x that many stripes) and branches per chunk (each pointer nullable). */
+/* Current launch configuration: branches in flight per wave (8, 16 or 32), groups of
+ * 16 waves per CU (2 and more: as many as fit), pairs per tile (64, 128 or 256 stand
+ * for 4, 8 or 16 samples by 64) and branches per chunk (each pointer nullable). */
 uf_status uf_batch_config(const uf_batch* batch, int* stage_branches, int* wgs_per_cu,
                           int* tile_stripes, int64_t* chunk_nodes);
-/* Set the launch configuration.  Valid when that many blocks of the kernel for
- * (stage_branches, tile_stripes) fit on one CU (LDS and registers, as the HIP
- * occupancy query reports).  A new tile size rebuilds the work items
- * (synchronous).  Results do not depend on the configuration.
+/* Set the launch configuration.  wgs_per_cu may be 1 up to, for stage_branches 8: 5, 3
+ * and 2 (tile_stripes 64, 128, 256); 16: 3, 2 and 2; 32: 1.  Results do not depend on
+ * the configuration.
  * Errors: UF_ERR_ARG (NULL, invalid configuration), UF_ERR_DEVICE. */
 uf_status uf_batch_set_config(uf_batch* batch, int stage_branches, int wgs_per_cu,
                               int tile_stripes);
-/* Arithmetic of the batch: UF_FP32 (default; the persistent stripe kernel above)
+/* Arithmetic of the batch: UF_FP32 (default; the pair tiles above)
  * or UF_FP32_SPLIT: every table through the sparse-aware split of
  * uf_dm_weighted_normalized(UF_FP32_SPLIT) (results equal to that call on each
  * table alone).  The split mode builds one embedding and split per table here
@@ -293,9 +292,8 @@ uf_status uf_batch_set_precision(uf_batch* batch, uf_precision prec, const uf_ta
 uf_status uf_batch_run(uf_batch* batch, float* const* outs, int use_graph, void* ws,
                        size_t ws_bytes, void* hip_stream);
 /* The self-written tile/stripe autotuner: time every tile size (64, 128, 256
- * stripes) x stage size (8, 16, 32 branches) at the two highest resident-block
- * counts that configuration allows, on the first 2,048 branches of the batch's
- * first chunk; keep the fastest (results are identical for all) and record it
+ * stripes) x stage size (8, 16, 32 branches) at the two highest wgs_per_cu that
+ * configuration allows, on the first 16,384 branches of the batch's first chunk; keep the fastest (results are identical for all) and record it
  * in the JSON cache at tune_cache (nullable; else $UF_TUNE_CACHE; no file if
  * neither), keyed by the size bucket.
  * best_ms (nullable) receives the winner's time.  Synchronises hip_stream. */

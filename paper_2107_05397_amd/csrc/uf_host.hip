@@ -13,6 +13,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <new>
 #include <string>
 #include <vector>
@@ -482,6 +483,7 @@ struct Plan {
     // touched-branch pair tiles: segment length, segments held side by side, elements
     // of one plane of sums
     bool pairs = false;
+    int form = ufx::kPairMin;
     int64_t seg = 0, n_planes = 0, plane = 0;
     // Gram product on presence bits: length digits (4 or 8; 0: not taken), length kind,
     // ranges of a chunk side by side
@@ -528,14 +530,17 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     const bool mfma = (prec == UF_MFMA_BF16X2 && !bits) || prec == UF_MFMA_SPLIT;
     if (split && !sp) return fail(UF_ERR_ARG, "split precision without a split");
     const int64_t nb = split ? sp->n_dense : e->nb;
+    const bool fixed = prec == UF_FP32_SPLIT && sp->q_scale > 0.0;   // 32-bit fixed point
     const size_t elem = prec == UF_FP64 ? 8 : (mfma ? 1 : 4);
     p->n_parts = std::max<int64_t>(1, (p->sr + 255) / 256);
     const size_t acc_elem = (prec == UF_FP64 || bits) ? 8 : 4;
-    p->pairs = !bits && (prec == UF_FP64 || (prec == UF_FP32 && !weighted));
+    p->pairs = !bits && !mfma && !fixed;
+    p->form = weighted && prec != UF_FP64 ? ufx::kPairL1 : ufx::kPairMin;
     p->seg = p->pairs ? ufx::pair_segment(n, nb) : 0;
-    // sums of one segment or range: with the pair tiles also sum_v x of every sample,
-    // with the bits one plane per four digits
-    p->plane = bits ? p->sr * n * (p->digits / 4) : p->pairs ? p->sr * n + n : p->sr * n;
+    // sums of one segment or range: with the pair tiles' sums of minima also sum_v x of
+    // every sample, with the bits one plane per four digits
+    p->plane = bits ? p->sr * n * (p->digits / 4)
+                    : p->sr * n + (p->pairs && p->form == ufx::kPairMin ? n : 0);
     const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
     // workspace layout for a chunk of kc branches; planes: segments held side by side
     auto layout = [&](int64_t kc, int64_t planes) {
@@ -612,23 +617,21 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
 // inside a chunk segment by segment.  Whole segments run side by side on their own
 // planes; a segment that a chunk boundary cuts continues on one plane.  Either way a
 // pair's sum is the sum, in order, of its segments' sums.
-template <typename T>
-uf_status run_pairs(const uf_embedding* e, const Plan& p, char* base, hipStream_t s) {
+// nb branches; fill(k0, kc, chunk) writes the chunk of branches [k0, k0 + kc).
+template <typename T, typename F>
+uf_status run_pairs(const Plan& p, int64_t nb, const char* name, char* base, hipStream_t s, F&& fill) {
     T* acc = reinterpret_cast<T*>(base + p.off_acc);
     T* planes = reinterpret_cast<T*>(base + p.off_planes);
     void* chunk = base + p.off_chunk;
-    const int64_t nb = e->nb;
-    const char* name = p.weighted ? (sizeof(T) == 8 ? "band_wn_f64" : "band_wn_f32")
-                                  : (sizeof(T) == 8 ? "band_uw_f64" : "band_uw_f32");
     for (int64_t c = 0; c < p.nchunks; ++c) {
         const int64_t k0 = c * p.kc, kc = std::min<int64_t>(p.kc, nb - k0);
         {
             ProfScope ps("embed_nm", s);
-            UF_HIP(ufx::pair_fill<T>(emb_view(*e), p.weighted, k0, kc, chunk, s));
+            UF_HIP(fill(k0, kc, chunk));
         }
         ProfScope ps(name, s);
         if (p.n_planes == 0) {
-            UF_HIP(ufx::pairs<T>(chunk, p.n, kc, 0, kc, kc, 1, p.sb, p.se, c > 0, acc, p.plane, s));
+            UF_HIP(ufx::pairs<T>(p.form, chunk, p.n, kc, 0, kc, kc, 1, p.sb, p.se, c > 0, acc, p.plane, s));
             continue;
         }
         for (int64_t k = k0; k < k0 + kc;) {
@@ -640,12 +643,12 @@ uf_status run_pairs(const uf_embedding* e, const Plan& p, char* base, hipStream_
             }
             if (count == 0) {
                 to = std::min((first_seg + 1) * p.seg, end);
-                UF_HIP(ufx::pairs<T>(chunk, p.n, kc, k - k0, to - k0, p.seg, 1, p.sb, p.se,
+                UF_HIP(ufx::pairs<T>(p.form, chunk, p.n, kc, k - k0, to - k0, p.seg, 1, p.sb, p.se,
                                      k % p.seg != 0, planes, p.plane, s));
                 if (to % p.seg == 0 || to == nb)
                     UF_HIP(ufx::pair_planes<T>(planes, p.plane, 1, first_seg == 0, acc, s));
             } else {
-                UF_HIP(ufx::pairs<T>(chunk, p.n, kc, k - k0, to - k0, p.seg, count, p.sb, p.se, 0,
+                UF_HIP(ufx::pairs<T>(p.form, chunk, p.n, kc, k - k0, to - k0, p.seg, count, p.sb, p.se, 0,
                                      planes, p.plane, s));
                 UF_HIP(ufx::pair_planes<T>(planes, p.plane, count, first_seg == 0, acc, s));
             }
@@ -725,22 +728,32 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         st = run_bits(e, p, prec, base, s);
         if (st != UF_OK) return st;
     } else if (p.pairs) {
-        st = prec == UF_FP64 ? run_pairs<double>(e, p, base, s) : run_pairs<float>(e, p, base, s);
+        const ufp::Emb ev = emb_view(*e);
+        const char* name = prec == UF_FP64 ? (weighted ? "band_wn_f64" : "band_uw_f64")
+                                           : (weighted ? "band_wn_f32" : "band_uw_f32");
+        if (prec == UF_FP64)
+            st = run_pairs<double>(p, nb, name, base, s, [&](int64_t k0, int64_t kc, void* to) {
+                return ufx::pair_fill<double>(ev, weighted, k0, kc, to, s);
+            });
+        else if (!sp)
+            st = run_pairs<float>(p, nb, name, base, s, [&](int64_t k0, int64_t kc, void* to) {
+                return ufx::pair_fill<float>(ev, weighted, k0, kc, to, s);
+            });
+        else
+            st = run_pairs<float>(p, sp->n_dense, name, base, s, [&](int64_t k0, int64_t kc, void* to) {
+                const size_t at = ufx::pair_chunk(p.n, kc, sizeof(float)).off_mask;
+                return ufs::embed_list_f32(ev, sp->dense, sp->lo_ord, sp->n_dense,
+                                           e->max_total < (int64_t(1) << 32), k0, kc,
+                                           reinterpret_cast<unsigned long long*>(static_cast<char*>(to) + at),
+                                           static_cast<float*>(to), s);
+            });
         if (st != UF_OK) return st;
     }
     for (int64_t c = 0; c < p.nchunks && !p.pairs && !p.digits; ++c) {
         const int64_t k0 = c * p.kc;
         const int64_t kc = std::min<int64_t>(p.kc, (sp ? sp->n_dense : nb) - k0);
         const int first = c == 0;
-        if (prec == UF_FP32) {
-            float* E = static_cast<float*>(chunk);
-            {
-                ProfScope ps("embed_nm", s);
-                UF_HIP(ufk::embed_node_major_f32(*e, k0, kc, E, s));
-            }
-            ProfScope ps("band_wn_f32", s);
-            UF_HIP(ufk::band_f32(E, kc, p.n, p.sb, p.se, first, static_cast<float*>(acc), s));
-        } else if (prec == UF_FP32_SPLIT && sp->q_scale > 0.0) {
+        if (prec == UF_FP32_SPLIT) {
             uint32_t* E = static_cast<uint32_t*>(chunk);
             {
                 ProfScope ps("embed_nm", s);
@@ -750,15 +763,6 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
             }
             ProfScope ps("band_wn_u32", s);
             UF_HIP(ufk::band_u32(E, kc, p.n, p.sb, p.se, first, static_cast<uint32_t*>(acc), s));
-        } else if (prec == UF_FP32_SPLIT) {
-            float* E = static_cast<float*>(chunk);
-            {
-                ProfScope ps("embed_nm", s);
-                UF_HIP(ufs::embed_list_f32(emb_view(*e), sp->dense, sp->lo_ord, sp->n_dense,
-                                           e->max_total < (int64_t(1) << 32), k0, kc, E, s));
-            }
-            ProfScope ps("band_wn_f32", s);
-            UF_HIP(ufk::band_f32(E, kc, p.n, p.sb, p.se, first, static_cast<float*>(acc), s));
         } else {
             const bool ms = prec == UF_MFMA_SPLIT;
             uint8_t* P = static_cast<uint8_t*>(chunk);
@@ -792,7 +796,7 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         ProfScope ps("finalize", s);
         const bool fixed = sp && weighted && sp->q_scale > 0.0;
         const int acc_type = prec == UF_FP64 || p.digits ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
-        const bool min_form = p.pairs && weighted, two_parts = p.digits == 8;
+        const bool min_form = p.pairs && weighted && p.form == ufx::kPairMin, two_parts = p.digits == 8;
         const int kind = min_form ? 2 : two_parts ? 3 : weighted ? 0 : 1;
         const double scale = fixed      ? 1.0 / sp->q_scale
                              : p.digits ? std::ldexp(1.0, e->len_exp - ufb::kDigitBits * p.digits)
@@ -1424,18 +1428,17 @@ struct uf_batch {
     int64_t n_tables = 0;
     std::vector<BatchTable> tabs;        // host copy
     std::vector<int64_t> acc_elems;           // per table
-    int64_t n_items = 0, max_items = 0;
+    int64_t n_items = 0;
     int64_t kc = 0, n_chunks = 0;
-    int stage_branches = 16, wgs_per_cu = 2, tile_stripes = 128, n_cu = 256;
+    int stage_branches = 16, wgs_per_cu = 2, tile_stripes = 128;
     int64_t n_bucket = 0;
-    void* arena = nullptr;                    // descs, tab_of, items, queue bounds
+    void* arena = nullptr;                    // descs, tab_of, items
     BatchTable* d_tabs = nullptr;
     int32_t* d_tab_of = nullptr;
-    int2* d_items = nullptr;
-    int64_t* d_qbeg = nullptr;
-    int64_t* d_qend = nullptr;
-    int32_t* d_lo_chunks = nullptr;           // positions of each chunk ordered by lo
-    size_t off_E = 0, off_acc = 0, off_cnt = 0, ws_total = 0;
+    int4* d_items = nullptr;
+    int64_t max_plane = 0;
+    size_t off_mask = 0, chunk_bytes = 0;     // of a chunk of all tables
+    size_t off_E = 0, off_acc = 0, ws_total = 0;
     hipStream_t cap = nullptr;                // capture stream (default priority)
     hipEvent_t last_run = nullptr;            // recorded after every run's work
     hipGraph_t graph = nullptr;
@@ -1468,10 +1471,9 @@ namespace {
 const int kBatchStages[] = {8, 16, 32};
 const int kBatchTiles[] = {64, 128, 256};
 
-// (stage branches, resident blocks per CU, stripes per tile) is valid when the
-// kernel exists and that many of its blocks fit on a CU (LDS, registers)
+// (branches in flight, groups of waves per CU, tile) is one that recorded files may hold
 bool config_valid(int ks, int w, int ts) {
-    return w >= 1 && w <= ufk::band_persistent_max_blocks(ks, ts);
+    return w >= 1 && w <= ufx::batch_max_blocks(ks, ts);
 }
 
 std::string cache_key_arch() { return "gfx950"; }
@@ -1533,66 +1535,46 @@ bool write_tune_cache(const char* path, const std::map<int64_t, TuneEntry>& m) {
 
 const char* tune_path(const char* p) { return p ? p : std::getenv("UF_TUNE_CACHE"); }
 
-// Work items of the persistent kernel for tiles of ts stripes: (table, tile) with
-// the tile's i-block fastest, tables in order.
-std::vector<int2> batch_items(const std::vector<BatchTable>& tabs, int ts) {
-    std::vector<int2> items;
-    for (size_t r = 0; r < tabs.size(); ++r) {
+// Work items of the batch kernel: (table, segment, block of 64 samples i, block of 64
+// samples j >= i), a table's segments one after the other so that the items running
+// together read the same branches.  Item p runs on XCD p mod 8: every table's list is
+// cut in eighths, one per XCD (table -1: none), so that each XCD reads its own part
+// and has the same work; tables with the longest segments come first.
+std::vector<int4> batch_items(const std::vector<BatchTable>& tabs) {
+    std::vector<size_t> order(tabs.size());
+    std::iota(order.begin(), order.end(), size_t(0));
+    std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return tabs[x].seg > tabs[y].seg; });
+    std::vector<int4> items, own;
+    for (size_t r : order) {
         const BatchTable& t = tabs[r];
         if (t.n < 2) continue;
-        const int64_t n_sblk = (t.n / 2 + ts - 1) / ts;
-        for (int64_t tt = 0; tt < t.n_iblk * n_sblk; ++tt) items.push_back(make_int2(int(r), int(tt)));
+        const int64_t nblk = (t.n + 63) / 64;
+        own.clear();
+        for (int64_t g = 0; g < t.n_seg; ++g)
+            for (int64_t bi = 0; bi < nblk; ++bi)
+                for (int64_t bj = bi; bj < nblk; ++bj) own.push_back(make_int4(int(r), int(g), int(bi), int(bj)));
+        const size_t per = (own.size() + 7) / 8;
+        for (size_t p = 0; p < per; ++p)
+            for (size_t x = 0; x < 8; ++x)
+                items.push_back(x * per + p < own.size() ? own[x * per + p] : make_int4(-1, 0, 0, 0));
     }
     return items;
 }
 
-// Upload the items for tiles of ts stripes and the 8 queue bounds (synchronous).
-uf_status batch_set_tiles(uf_batch* b, int ts) {
-    const std::vector<int2> items = batch_items(b->tabs, ts);
-    // a run still in flight reads the current items
-    if (b->last_run) UF_HIP(hipEventSynchronize(b->last_run));
-    if (int64_t(items.size()) > b->max_items) return fail(UF_ERR_ARG, "tile size below the smallest");
-    b->n_items = int64_t(items.size());
-    std::vector<int64_t> qb(8), qe(8);
-    for (int q = 0; q < 8; ++q) {
-        qb[size_t(q)] = b->n_items * q / 8;
-        qe[size_t(q)] = b->n_items * (q + 1) / 8;
-    }
-    if (b->n_items)
-        UF_HIP(hipMemcpy(b->d_items, items.data(), sizeof(int2) * size_t(b->n_items), hipMemcpyHostToDevice));
-    UF_HIP(hipMemcpy(b->d_qbeg, qb.data(), 64, hipMemcpyHostToDevice));
-    UF_HIP(hipMemcpy(b->d_qend, qe.data(), 64, hipMemcpyHostToDevice));
-    b->tile_stripes = ts;
-    return UF_OK;
-}
-
-// node-major FP32 embedding of chunk [k0, k0+kc) of every table: forward merge
-// when every sample total is below 2^32, else binary searches (same values)
-hipError_t batch_embed(const uf_batch* b, int64_t k0, int64_t kc, float* E, hipStream_t s) {
-    const uf_embedding& e = *b->emb;
-    if (b->d_lo_chunks && e.max_total < (int64_t(1) << 32))
-        return ufs::embed_batch_merge_f32(emb_view(e), b->d_tabs, b->d_tab_of, b->d_lo_chunks + k0,
-                                          k0, kc, E, s);
-    return ufk::embed_batch_f32(e, b->d_tabs, b->d_tab_of, k0, kc, E, s);
-}
-
 // enqueue the whole batch on stream s (also used under graph capture)
 uf_status batch_enqueue(uf_batch* b, float* const* outs, char* base, hipStream_t s) {
-    float* E = reinterpret_cast<float*>(base + b->off_E);
+    void* chunk = base + b->off_E;
     float* acc = reinterpret_cast<float*>(base + b->off_acc);
-    unsigned* cnt = reinterpret_cast<unsigned*>(base + b->off_cnt);
     const uf_embedding& e = *b->emb;
-    const int nblk = b->n_cu * b->wgs_per_cu;
-    UF_HIP(ufk::zero_u32(cnt, std::max<int64_t>(b->n_chunks, 1) * 8, s));
     for (int64_t c = 0; c < b->n_chunks; ++c) {
         const int64_t k0 = c * b->kc;
         const int64_t kc = std::min<int64_t>(b->kc, e.nb - k0);
-        UF_HIP(batch_embed(b, k0, kc, E, s));
-        if (b->n_items > 0)
-            UF_HIP(ufk::band_persistent_f32(E, b->d_tabs, b->d_items, b->d_qbeg, b->d_qend,
-                                            cnt + c * 8, kc, c == 0, acc, b->stage_branches,
-                                            b->tile_stripes, nblk, s));
+        UF_HIP(ufx::batch_fill(emb_view(e), b->d_tabs, b->d_tab_of, k0, kc, chunk, b->off_mask,
+                               b->chunk_bytes, s));
+        UF_HIP(ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_items, k0, kc, acc,
+                                b->stage_branches, b->wgs_per_cu, b->tile_stripes, s));
     }
+    if (b->n_chunks > 0) UF_HIP(ufx::batch_planes(b->d_tabs, b->n_tables, b->max_plane, acc, s));
     for (int64_t r = 0; r < b->n_tables; ++r) {
         const BatchTable& t = b->tabs[r];
         if (t.n < 2) continue;
@@ -1729,20 +1711,17 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
         uf_status st = embed_impl(tree, &cat, stream, &b->emb);
         if (st != UF_OK) return st;
         b->n_tables = n_tables;
-        int dev = 0;
-        UF_HIP(hipGetDevice(&dev));
-        hipDeviceProp_t prop;
-        UF_HIP(hipGetDeviceProperties(&prop, dev));
-        b->n_cu = prop.multiProcessorCount;
         // chunk length: 16 GiB of embedding for all tables, or the process-wide setting
+        // (32-bit offsets inside a chunk)
         const int64_t n_all = std::max<int64_t>(cat.n_samples, 1);
         int64_t kc = g_chunk_nodes.load();
         if (kc <= 0) kc = int64_t(16.0 * 1024 * 1024 * 1024 / (double(n_all) * 4.0));
+        kc = std::min<int64_t>(kc, int64_t(1) << 22);
         kc = std::min<int64_t>(std::max<int64_t>(kc, 32), std::max<int64_t>(b->emb->nb, 1));
         b->kc = kc;
         b->n_chunks = b->emb->nb > 0 ? (b->emb->nb + kc - 1) / kc : 0;
         // per-table layout
-        int64_t off = 0, eoff = 0, aoff = 0;
+        int64_t off = 0, eoff = 0, moff = 0, aoff = 0;
         std::vector<int32_t> tab_of(size_t(n_all), 0);
         double mean_n = 0;
         for (int64_t r = 0; r < n_tables; ++r) {
@@ -1750,65 +1729,54 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
             t.n = tables[r]->n_samples;
             t.off = off;
             t.e_off = eoff;
+            t.m_off = moff;
+            t.plane = (t.n / 2) * t.n;
+            t.seg = ufx::pair_segment(t.n, b->emb->nb);
+            t.n_seg = (std::max<int64_t>(b->emb->nb, 1) + t.seg - 1) / t.seg;
+            const int64_t room = (t.plane + 63) / 64 * 64;
             t.acc_off = aoff;
-            t.n_iblk = (t.n + ufk::kBandI - 1) / ufk::kBandI;
+            aoff += room;
+            t.p_off = t.n_seg > 1 ? aoff : t.acc_off;
+            if (t.n_seg > 1) aoff += (t.n_seg * t.plane + 63) / 64 * 64;
             b->tabs.push_back(t);
+            b->max_plane = std::max(b->max_plane, t.n_seg > 1 ? t.plane : 0);
             for (int64_t i = 0; i < t.n; ++i) tab_of[size_t(off + i)] = int32_t(r);
-            const int64_t S = t.n / 2;
+            const int64_t nblk = (t.n + 63) / 64;
             off += t.n;
-            eoff += kc * t.n;
-            aoff += ((S * t.n + 63) / 64) * 64;
+            eoff += nblk * (kc + 1) * 64;
+            moff += nblk * kc;
             mean_n += double(t.n) / double(n_tables);
         }
-        // work items: the arena holds those of the smallest tile (the most)
-        b->max_items = int64_t(batch_items(b->tabs, kBatchTiles[0]).size());
+        const std::vector<int4> items = batch_items(b->tabs);
+        b->n_items = int64_t(items.size());
         b->n_bucket = mean_n > 1 ? int64_t(std::ceil(std::log2(mean_n))) : 0;
         Carver c;
         const size_t o_tabs = c.take(sizeof(BatchTable) * size_t(n_tables));
         const size_t o_tabof = c.take(size_t(n_all) * 4);
-        const size_t o_items = c.take(sizeof(int2) * size_t(std::max<int64_t>(b->max_items, 1)));
-        const size_t o_qb = c.take(8 * 8);
-        const size_t o_qe = c.take(8 * 8);
-        const int64_t nb = b->emb->nb;
-        const size_t o_lord = c.take(size_t(std::max<int64_t>(nb, 1)) * 4);
+        const size_t o_items = c.take(sizeof(int4) * size_t(std::max<int64_t>(b->n_items, 1)));
         if (hipMalloc(&b->arena, c.off + 256) != hipSuccess) return fail(UF_ERR_NOMEM, "batch descriptors");
         char* base = static_cast<char*>(b->arena);
         b->d_tabs = reinterpret_cast<BatchTable*>(base + o_tabs);
         b->d_tab_of = reinterpret_cast<int32_t*>(base + o_tabof);
-        b->d_items = reinterpret_cast<int2*>(base + o_items);
-        b->d_qbeg = reinterpret_cast<int64_t*>(base + o_qb);
-        b->d_qend = reinterpret_cast<int64_t*>(base + o_qe);
-        b->d_lo_chunks = reinterpret_cast<int32_t*>(base + o_lord);
-        {
-            // positions of each chunk [c kc, (c+1) kc) in ascending lo (stable)
-            std::vector<int32_t> ord(size_t(std::max<int64_t>(nb, 1)));
-            for (int64_t k = 0; k < nb; ++k) ord[size_t(k)] = int32_t(k);
-            for (int64_t k0 = 0; k0 < nb; k0 += kc) {
-                const auto first = ord.begin() + k0, last = ord.begin() + std::min<int64_t>(nb, k0 + kc);
-                std::stable_sort(first, last, [&](int32_t x, int32_t y) {
-                    return tree->lo[size_t(x)] < tree->lo[size_t(y)];
-                });
-            }
-            if (nb) UF_HIP(hipMemcpy(b->d_lo_chunks, ord.data(), size_t(nb) * 4, hipMemcpyHostToDevice));
-        }
+        b->d_items = reinterpret_cast<int4*>(base + o_items);
         UF_HIP(hipMemcpy(b->d_tabs, b->tabs.data(), sizeof(BatchTable) * size_t(n_tables), hipMemcpyHostToDevice));
+        if (b->n_items)
+            UF_HIP(hipMemcpy(b->d_items, items.data(), sizeof(int4) * items.size(), hipMemcpyHostToDevice));
         UF_HIP(hipMemcpy(b->d_tab_of, tab_of.data(), size_t(n_all) * 4, hipMemcpyHostToDevice));
         Carver w;
-        b->off_E = w.take(size_t(eoff) * 4);
+        b->off_mask = size_t(eoff) * 4;
+        b->chunk_bytes = (b->off_mask + size_t(moff) * 8 + 15) / 16 * 16;
+        b->off_E = w.take(b->chunk_bytes);
         b->off_acc = w.take(size_t(aoff) * 4);
-        b->off_cnt = w.take(size_t(std::max<int64_t>(b->n_chunks, 1)) * 8 * 4);
         b->ws_total = w.off + 256;
         // launch configuration from the tuning cache, if it has this size bucket
         auto cache = read_tune_cache(tune_path(tune_cache));
         auto it = cache.find(b->n_bucket);
-        int ts = 128;
         if (it != cache.end()) {
             b->stage_branches = it->second.ks;
             b->wgs_per_cu = it->second.w;
-            ts = it->second.ts;
+            b->tile_stripes = it->second.ts;
         }
-        st = batch_set_tiles(b, ts);
-        if (st != UF_OK) return st;
         UF_HIP(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
         UF_HIP(hipEventCreateWithFlags(&b->last_run, hipEventDisableTiming));
         *out = guard.release();
@@ -1860,12 +1828,9 @@ uf_status uf_batch_set_config(uf_batch* b, int stage_branches, int wgs_per_cu, i
         if (!b) return fail(UF_ERR_ARG, "batch is NULL");
         if (!config_valid(stage_branches, wgs_per_cu, tile_stripes))
             return fail(UF_ERR_ARG, "unsupported (stage_branches, wgs_per_cu, tile_stripes)");
-        if (tile_stripes != b->tile_stripes) {
-            const uf_status st = batch_set_tiles(b, tile_stripes);
-            if (st != UF_OK) return st;
-        }
         b->stage_branches = stage_branches;
         b->wgs_per_cu = wgs_per_cu;
+        b->tile_stripes = tile_stripes;
         if (b->exec) {
             (void)hipGraphExecDestroy(b->exec);
             (void)hipGraphDestroy(b->graph);
@@ -1998,15 +1963,15 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
             if (best_ms) *best_ms = best_t;
             return UF_OK;
         }
-        float* E = reinterpret_cast<float*>(base + b->off_E);
+        void* chunk = base + b->off_E;
         float* acc = reinterpret_cast<float*>(base + b->off_acc);
-        unsigned* cnt = reinterpret_cast<unsigned*>(base + b->off_cnt);
         const uf_embedding& e = *b->emb;
         if (b->n_chunks == 0 || b->n_items == 0) return UF_OK;
-        // timed on the first 2,048 branches of the first chunk: every configuration
+        // timed on the first 16,384 branches of the first chunk: every configuration
         // pays the same per-branch work, so a part of the chunk ranks them
-        const int64_t kc = std::min<int64_t>(std::min<int64_t>(b->kc, e.nb), 2048);
-        UF_HIP(batch_embed(b, 0, kc, E, s));
+        const int64_t kc = std::min<int64_t>(std::min<int64_t>(b->kc, e.nb), 16384);
+        UF_HIP(ufx::batch_fill(emb_view(e), b->d_tabs, b->d_tab_of, 0, kc, chunk, b->off_mask,
+                               b->chunk_bytes, s));
         hipEvent_t e0, e1;
         UF_HIP(hipEventCreate(&e0));
         UF_HIP(hipEventCreate(&e1));
@@ -2019,18 +1984,15 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
         } ev{e0, e1};
         TuneEntry best{b->stage_branches, b->wgs_per_cu, b->tile_stripes, 1e300};
         for (int ts : kBatchTiles) {
-            st = batch_set_tiles(b, ts);
-            if (st != UF_OK) return st;
             for (int ks : kBatchStages) {
                 // the two highest occupancies the configuration allows
-                const int wmax = ufk::band_persistent_max_blocks(ks, ts);
+                const int wmax = ufx::batch_max_blocks(ks, ts);
                 for (int w = std::max(1, wmax - 1); w <= wmax; ++w) {
                     double tmin = 1e300;
                     for (int rep = 0; rep < 2; ++rep) {
-                        UF_HIP(ufk::zero_u32(cnt, 8, s));
                         UF_HIP(hipEventRecord(e0, s));
-                        UF_HIP(ufk::band_persistent_f32(E, b->d_tabs, b->d_items, b->d_qbeg, b->d_qend,
-                                                        cnt, kc, 1, acc, ks, ts, b->n_cu * w, s));
+                        UF_HIP(ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_items, 0,
+                                                kc, acc, ks, w, ts, s));
                         UF_HIP(hipEventRecord(e1, s));
                         UF_HIP(hipEventSynchronize(e1));
                         float ms = 0;
@@ -2042,8 +2004,6 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
             }
         }
         if (best_ms) *best_ms = best.ms;
-        st = batch_set_tiles(b, best.ts);
-        if (st != UF_OK) return st;
         st = uf_batch_set_config(b, best.ks, best.w, best.ts);
         if (st != UF_OK) return st;
         const char* path = tune_path(tune_cache);

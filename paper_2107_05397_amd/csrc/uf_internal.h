@@ -165,9 +165,13 @@ class ProfGuard {
 struct BatchTable {
     int64_t n;        // samples
     int64_t off;      // first sample in the concatenated table
-    int64_t e_off;    // element offset of its node-major chunk block [kc][n]
+    int64_t e_off;    // element offset of its values in a chunk
+    int64_t m_off;    // element offset of its masks
     int64_t acc_off;  // element offset of its stripe-major accumulator [n/2][n]
-    int64_t n_iblk;   // 128-sample blocks
+    int64_t p_off;    // element offset of its segments' planes (n_seg == 1: acc_off)
+    int64_t plane;    // elements of a plane
+    int64_t seg;      // branches per segment
+    int64_t n_seg;
 };
 
 // ---------------------------------------------------------------------------
@@ -187,21 +191,14 @@ hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos,
                           const int32_t* tip_pos, const double* d64, const double* d32,
                           const double* dbf, hipStream_t st);
 
-// Node-major chunk E[k][s] = float(l * c/T_s) for positions [k0, k0+kc).
-hipError_t embed_node_major_f32(const uf_embedding& e, int64_t k0, int64_t kc, float* out,
-                                hipStream_t st);
 // Sample-major presence P[s][k]: FP8 e4m3 -2.0 (0xC0) where present, else 0, k < kpad (zero beyond
 // kc), for positions [k0, k0+kc), or for positions list[k0 .. k0+kc) when list is
 // non-null.  kpad is a multiple of kGramKPad.
 hipError_t embed_presence_fp8(const uf_embedding& e, int64_t k0, int64_t kc, int64_t kpad,
                               uint8_t* out, hipStream_t st, const int32_t* list = nullptr);
 
-// Band accumulation over one node chunk for stripes [sb, se):
-// acc += sum_k |E[k][i] - E[k][j]|.
-hipError_t band_f32(const float* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
-                    float* acc, hipStream_t st);
-// The same in 32-bit fixed point: acc += sum_k |E[k][i] - E[k][j]| (exact integers;
-// the caller keeps the sum below 2^32).
+// Band accumulation over one node chunk for stripes [sb, se), in 32-bit fixed point:
+// acc += sum_k |E[k][i] - E[k][j]| (exact integers; the caller keeps the sum below 2^32).
 hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
                     uint32_t* acc, hipStream_t st);
 
@@ -235,21 +232,6 @@ hipError_t row_sums(const double* q, int64_t n, int64_t sb, int64_t se, double* 
                     int64_t n_parts, double scale, double* out, hipStream_t st);
 hipError_t grand_mean(const double* row_means, int64_t n, double* out, hipStream_t st);
 
-// ---- batches (many tables on one tree, weighted normalized, FP32) --------
-// Node-major chunk of every table: table r's block at e_off, row stride n_r.
-hipError_t embed_batch_f32(const uf_embedding& e, const BatchTable* tabs, const int32_t* tab_of,
-                           int64_t k0, int64_t kc, float* out, hipStream_t st);
-// Persistent band kernel over (table, tile) items.  items: int32 pairs; queue q
-// holds items [qbeg[q], qend[q]) and its counter counters[q] (8 queues, one per
-// XCD; exhausted queues are stolen from).  stage_branches in {8, 16, 32};
-// tile_stripes in {64, 128, 256}: a tile is kBandI samples x tile_stripes
-// stripes, and item (r, t) is tile t of table r with its i-block fastest.
-hipError_t band_persistent_f32(const float* E, const BatchTable* tabs, const int2* items,
-                               const int64_t* qbeg, const int64_t* qend, unsigned* counters,
-                               int64_t kc, int first, float* acc, int stage_branches,
-                               int tile_stripes, int n_blocks, hipStream_t st);
-// Resident blocks per CU of that kernel (0 for an unknown configuration).
-int band_persistent_max_blocks(int stage_branches, int tile_stripes);
 // Zero n unsigned counters (a kernel, so that graph replays stay valid).
 hipError_t zero_u32(unsigned* p, int64_t n, hipStream_t st);
 

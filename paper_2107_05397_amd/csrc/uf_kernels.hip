@@ -2,10 +2,9 @@
 // 64-lane waves, 160 KB LDS per CU, MFMA matrix cores.
 //
 //   k_sample_scalars   per-sample FP64 scalars from the postorder leaf intervals
-//   k_embed_nm         node-major FP32 chunk of the embedding (weighted)
 //   k_embed_pres_fp8  sample-major FP8 (e4m3) 0/1 presence for the MFMA Gram path (merge)
-//   k_band<T>          stripe-band accumulation on the vector ALUs (LDS-tiled);
-//                      T = uint32_t: weighted, 32-bit fixed point, one v_sad_u32
+//   k_band             weighted stripe-band accumulation of a split's dense set on the
+//                      vector ALUs (LDS-tiled): 32-bit fixed point, one v_sad_u32
 //                      (|a - b| + acc) per update
 //   k_gram_mfma        unweighted Gram product on MFMA (split-precision lengths)
 //   k_finalize         FP64 division, output layouts, -d^2/2 for PCoA
@@ -19,14 +18,7 @@
 namespace ufk {
 namespace {
 
-// ----------------------------------------------------------------------------
-// Embedded count of sample s on the branch at postorder position k: the sum
-// of the sample's counts on the tips whose rank lies in [lo_k, hi_k).  Rows
-// are sorted by tip rank and carry an exclusive prefix of the counts, so the
-// count is a difference of two prefix values found by binary search.  This
-// equals the postorder sum of the children's counts (a subtree is a contiguous
-// run of postorder positions), exactly, in integers.
-// ----------------------------------------------------------------------------
+// first index in [a, b) whose tip rank is >= key
 __device__ __forceinline__ int64_t lower_bound_rank(const int32_t* __restrict__ rank, int64_t a,
                                                     int64_t b, int32_t key) {
     while (a < b) {
@@ -35,16 +27,6 @@ __device__ __forceinline__ int64_t lower_bound_rank(const int32_t* __restrict__ 
         else b = mid;
     }
     return a;
-}
-
-__device__ __forceinline__ int64_t embedded_count(const int64_t* __restrict__ row_ptr,
-                                                  const int32_t* __restrict__ rank,
-                                                  const int64_t* __restrict__ cum, int64_t s,
-                                                  int32_t lo, int32_t hi) {
-    const int64_t a = row_ptr[s], b = row_ptr[s + 1];
-    const int64_t p1 = lower_bound_rank(rank, a, b, lo);
-    const int64_t p2 = lower_bound_rank(rank, p1, b, hi);
-    return cum[p2 + s] - cum[p1 + s];
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -99,49 +81,6 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
         wu[s] = w;
         wu32[s] = w32;
         wub[s] = wb;
-    }
-}
-
-// ----------------------------------------------------------------------------
-// Node-major embedding chunk: out[k][s] for k in [0, kc), positions k0 + k.
-// A block covers 256 consecutive branches x TS samples.  The counts are found
-// sample by sample (all lanes search the same row, which stays in L1), kept in
-// an LDS tile, then written branch-row by branch-row (TS consecutive samples
-// per row: coalesced).
-// ----------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_embed_nm(
-    int64_t n, int64_t k0, int64_t kc, const int64_t* __restrict__ row_ptr,
-    const int32_t* __restrict__ rank, const int64_t* __restrict__ cum,
-    const double* __restrict__ total, const int32_t* __restrict__ lo,
-    const int32_t* __restrict__ hi, const double* __restrict__ len, float* __restrict__ out) {
-    constexpr int TK = 256, TS = 64;
-    __shared__ float tile[TK][TS + 1];
-    const int tid = threadIdx.x;
-    const int64_t kb = int64_t(blockIdx.x) * TK;
-    const int64_t sb = int64_t(blockIdx.y) * TS;
-    const int64_t k = kb + tid;
-    const bool kin = k < kc;
-    int32_t lk = 0, hk = 0;
-    double lv = 0.0;
-    if (kin) {
-        lk = lo[k0 + k];
-        hk = hi[k0 + k];
-        lv = len[k0 + k];
-    }
-    for (int j = 0; j < TS; ++j) {
-        const int64_t s = sb + j;
-        float v = 0.0f;
-        if (kin && s < n) {
-            const int64_t c = embedded_count(row_ptr, rank, cum, s, lk, hk);
-            v = float(lv * (double(c) / total[s]));
-        }
-        tile[tid][j] = v;
-    }
-    __syncthreads();
-    for (int r = tid / TS; r < TK; r += 256 / TS) {
-        const int64_t kk = kb + r;
-        const int64_t s = sb + (tid % TS);
-        if (kk < kc && s < n) out[kk * n + s] = tile[r][tid % TS];
     }
 }
 
@@ -963,82 +902,6 @@ __global__ __launch_bounds__(256) void k_grand_mean(const double* __restrict__ r
     if (threadIdx.x == 0) out[0] = red[0] / double(n);
 }
 
-// ----------------------------------------------------------------------------
-// Batches: many tables on one tree.
-// ----------------------------------------------------------------------------
-// Node-major chunk of every table; global sample g belongs to table tab_of[g].
-__global__ __launch_bounds__(256) void k_embed_batch_f32(
-    int64_t n_all, int64_t k0, int64_t kc, const BatchTable* __restrict__ tabs,
-    const int32_t* __restrict__ tab_of, const int64_t* __restrict__ row_ptr,
-    const int32_t* __restrict__ rank, const int64_t* __restrict__ cum,
-    const double* __restrict__ total, const int32_t* __restrict__ lo,
-    const int32_t* __restrict__ hi, const double* __restrict__ len, float* __restrict__ out) {
-    constexpr int TK = 256, TS = 64;
-    __shared__ float tile[TK][TS + 1];
-    const int tid = threadIdx.x;
-    const int64_t kb = int64_t(blockIdx.x) * TK;
-    const int64_t gb = int64_t(blockIdx.y) * TS;
-    const int64_t k = kb + tid;
-    const bool kin = k < kc;
-    int32_t lk = 0, hk = 0;
-    double lv = 0.0;
-    if (kin) {
-        lk = lo[k0 + k];
-        hk = hi[k0 + k];
-        lv = len[k0 + k];
-    }
-    for (int j = 0; j < TS; ++j) {
-        const int64_t g = gb + j;
-        float v = 0.0f;
-        if (kin && g < n_all) {
-            const int64_t c = embedded_count(row_ptr, rank, cum, g, lk, hk);
-            v = float(lv * (double(c) / total[g]));
-        }
-        tile[tid][j] = v;
-    }
-    __syncthreads();
-    for (int r = tid / TS; r < TK; r += 256 / TS) {
-        const int64_t kk = kb + r;
-        const int64_t g = gb + (tid % TS);
-        if (kk < kc && g < n_all) {
-            const BatchTable t = tabs[tab_of[g]];
-            out[t.e_off + kk * t.n + (g - t.off)] = tile[r][tid % TS];
-        }
-    }
-}
-
-// Persistent band kernel: the grid stays resident and pulls (table, tile)
-// items from per-XCD queues (block b runs on XCD b mod 8 and drains queue
-// b mod 8 first, then steals from the others).  Every queue is finite, so
-// every block exits once all queues are exhausted.
-template <int KS, int MS>
-__global__ __launch_bounds__(256) void k_band_persistent_f32(
-    const float* __restrict__ E, const BatchTable* __restrict__ tabs,
-    const int2* __restrict__ items, const int64_t* __restrict__ qbeg,
-    const int64_t* __restrict__ qend, unsigned* __restrict__ counters, int64_t kc, int first,
-    float* __restrict__ acc) {
-    __shared__ __attribute__((aligned(16))) BandLds<float, KS, MS> L;
-    __shared__ int64_t next_item;
-    const int xcd = int(blockIdx.x & 7);
-    for (int q = 0; q < 8; ++q) {
-        const int queue = (xcd + q) & 7;
-        const int64_t end = qend[queue];
-        for (;;) {
-            if (threadIdx.x == 0) next_item = qbeg[queue] + int64_t(atomicAdd(&counters[queue], 1u));
-            __syncthreads();
-            const int64_t item = next_item;
-            __syncthreads();
-            if (item >= end) break;
-            const int2 it = items[item];
-            const BatchTable t = tabs[it.x];
-            const int64_t i0 = (int64_t(it.y) % t.n_iblk) * kBandI;
-            const int64_t s0 = (int64_t(it.y) / t.n_iblk) * (16 * MS);
-            band_tile<float, KS, MS, false>(L, E + t.e_off, kc, t.n, 0, t.n / 2, i0, s0, first,
-                                            acc + t.acc_off);
-        }
-    }
-}
-
 __global__ void k_zero_u32(unsigned* __restrict__ p, int64_t n) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
@@ -1058,17 +921,6 @@ hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos, cons
     hipLaunchKernelGGL(k_sample_scalars, dim3(blocks), dim3(256), 0, st, e.n, e.row_ptr, e.rank,
                        e.cum, e.total, parent_pos, e.hi, tip_pos, d64, d32, dbf, e.sw, e.wu,
                        e.wu32, e.wub);
-    return hipGetLastError();
-}
-
-hipError_t embed_node_major_f32(const uf_embedding& e, int64_t k0, int64_t kc, float* out,
-                                hipStream_t st) {
-    if (kc <= 0 || e.n <= 0) return hipSuccess;
-    const int64_t gy = (e.n + 63) / 64;
-    if (gy > 65535) return hipErrorInvalidValue;
-    dim3 grid(unsigned((kc + 255) / 256), unsigned(gy));
-    hipLaunchKernelGGL(k_embed_nm, grid, dim3(256), 0, st, e.n, k0, kc, e.row_ptr, e.rank, e.cum,
-                       e.total, e.lo, e.hi, e.len, out);
     return hipGetLastError();
 }
 
@@ -1097,10 +949,6 @@ static hipError_t band(const T* E, int64_t kc, int64_t n, int64_t sb, int64_t se
     return hipGetLastError();
 }
 
-hipError_t band_f32(const float* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
-                    float* acc, hipStream_t st) {
-    return band<float>(E, kc, n, sb, se, first, acc, st);
-}
 hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
                     uint32_t* acc, hipStream_t st) {
     return band<uint32_t>(E, kc, n, sb, se, first, acc, st);
@@ -1169,58 +1017,6 @@ hipError_t row_sums(const double* q, int64_t n, int64_t sb, int64_t se, double* 
 
 hipError_t grand_mean(const double* row_means, int64_t n, double* out, hipStream_t st) {
     hipLaunchKernelGGL(k_grand_mean, dim3(1), dim3(256), 0, st, row_means, n, out);
-    return hipGetLastError();
-}
-
-hipError_t embed_batch_f32(const uf_embedding& e, const BatchTable* tabs, const int32_t* tab_of,
-                           int64_t k0, int64_t kc, float* out, hipStream_t st) {
-    if (kc <= 0 || e.n <= 0) return hipSuccess;
-    const int64_t gy = (e.n + 63) / 64;
-    if (gy > 65535) {
-        return hipErrorInvalidValue;
-    }
-    dim3 grid(unsigned((kc + 255) / 256), unsigned(gy));
-    hipLaunchKernelGGL(k_embed_batch_f32, grid, dim3(256), 0, st, e.n, k0, kc, tabs, tab_of,
-                       e.row_ptr, e.rank, e.cum, e.total, e.lo, e.hi, e.len, out);
-    return hipGetLastError();
-}
-
-// the persistent kernel for (branches per stage, stripes per tile)
-template <int KS, int MS>
-static const void* persistent_fn() {
-    return reinterpret_cast<const void*>(&k_band_persistent_f32<KS, MS>);
-}
-static const void* persistent_kernel(int stage_branches, int tile_stripes) {
-#define UF_PK(KS_)                                                           \
-    if (stage_branches == KS_) {                                             \
-        if (tile_stripes == 64) return persistent_fn<KS_, 4>();              \
-        if (tile_stripes == 128) return persistent_fn<KS_, 8>();             \
-        if (tile_stripes == 256) return persistent_fn<KS_, 16>();            \
-    }
-    UF_PK(8)
-    UF_PK(16)
-    UF_PK(32)
-#undef UF_PK
-    return nullptr;
-}
-
-int band_persistent_max_blocks(int stage_branches, int tile_stripes) {
-    const void* fn = persistent_kernel(stage_branches, tile_stripes);
-    if (!fn) return 0;
-    int blocks = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, fn, 256, 0) != hipSuccess) return 0;
-    return blocks;
-}
-
-hipError_t band_persistent_f32(const float* E, const BatchTable* tabs, const int2* items,
-                               const int64_t* qbeg, const int64_t* qend, unsigned* counters,
-                               int64_t kc, int first, float* acc, int stage_branches,
-                               int tile_stripes, int n_blocks, hipStream_t st) {
-    const void* fn = persistent_kernel(stage_branches, tile_stripes);
-    if (!fn || n_blocks < 1) return hipErrorInvalidValue;
-    void* args[] = {&E, &tabs, &items, &qbeg, &qend, &counters, &kc, &first, &acc};
-    const hipError_t e = hipLaunchKernel(fn, dim3(unsigned(n_blocks)), dim3(256), args, 0, st);
-    if (e != hipSuccess) return e;
     return hipGetLastError();
 }
 

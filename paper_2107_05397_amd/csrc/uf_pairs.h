@@ -7,12 +7,19 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "uf_internal.h"
 #include "uf_place.h"
 
 namespace ufx {
 
 constexpr int kPairA = 8;        // samples i per wave
 constexpr int kPairWin = 256;    // branches listed at a time
+constexpr int kPairU = 8;        // branches per group of loads
+constexpr int kPairMin = 0, kPairL1 = 1;   // sum of min(x, y); sum of |x - y|
+// From here on the L1 tiles take 16 samples i per wave: their rows no longer stay in
+// the caches, and each row of samples j read serves twice the pairs (5,000 samples, 40,000
+// branches 28.2 -> 19.7 ms; 2,500: 6.5 -> 7.1; 1,500: 2.05 -> 2.37).
+constexpr int64_t kPairWideN = 4096;
 
 // Workspace of one chunk of kc branches of n samples: values, then masks.
 struct PairChunk {
@@ -45,16 +52,37 @@ inline int64_t pair_segment(int64_t n, int64_t nb) {
 template <typename T>
 hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, void* chunk,
                      hipStream_t st);
-// m_ij of stripes [sb, se) over branches [ka, kb) of the chunk, `count` segments of
+// Sums of stripes [sb, se) over branches [ka, kb) of the chunk, `count` segments of
 // seg branches side by side, each into its own plane of out: [se-sb][n] stripe-major,
-// then sum_v x_iv of every sample i [n].  load: start from what out holds.
+// then (kPairMin) sum_v x_iv of every sample i [n].  load: start from what out holds.
+// form: kPairMin, or kPairL1 (FP32 only).
 template <typename T>
-hipError_t pairs(const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
+hipError_t pairs(int form, const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
                  int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
                  hipStream_t st);
 // acc (first: =, else +=) the planes in order.
 template <typename T>
 hipError_t pair_planes(const T* planes, int64_t plane, int64_t count, int first, T* acc,
                        hipStream_t st);
+
+// ---- batches: many tables on one tree, weighted, FP32 ----------------------
+// Chunk of every table (PairChunk's layout per table: values at e_off, masks at
+// off_mask + 8 m_off bytes), cleared (`bytes`) and filled.
+hipError_t batch_fill(const ufp::Emb& e, const BatchTable* tabs, const int32_t* tab_of, int64_t k0,
+                      int64_t kc, void* chunk, size_t off_mask, size_t bytes, hipStream_t st);
+// The L1 tiles of every table on the chunk [k0, k0 + kc), segments each to its own
+// plane at p_off.  items: (table, segment, block of 64 samples i, block of 64 samples
+// j >= i), eight at a time, item p for XCD p mod 8 (table -1: none).  Configuration: stage_branches (8, 16 or 32) branches in flight per wave;
+// wgs_per_cu groups of 16 waves per CU (two and more: as many as fit); tiles of
+// tile_stripes / 16 samples i (tile_stripes 64, 128 or 256) by 64 samples j.
+hipError_t batch_pairs(const void* chunk, size_t off_mask, const BatchTable* tabs, const int4* items,
+                       int64_t n_items, int64_t k0, int64_t kc, float* acc, int stage_branches,
+                       int wgs_per_cu, int tile_stripes, hipStream_t st);
+// The largest wgs_per_cu that a configuration may ask for (0: no such configuration): a
+// fixed table, so that recorded configurations stay valid.
+int batch_max_blocks(int stage_branches, int tile_stripes);
+// acc_off (=) the planes of each table, in order.
+hipError_t batch_planes(const BatchTable* tabs, int64_t n_tables, int64_t max_plane, float* acc,
+                        hipStream_t st);
 
 }  // namespace ufx

@@ -1,5 +1,5 @@
 // Pair tiles over touched branches (gfx950): the FP64 and FP32 sums
-//   m_ij = sum_v min(x_iv, x_jv),
+//   m_ij = sum_v min(x_iv, x_jv)   and, in FP32, sum_v |x_iv - x_jv|,
 // x = l u (weighted) or l a (unweighted, where the sum is the Gram value).  A term
 // is nonzero only where both samples touch v, and sum |x - y| = s_i + s_j - 2 m_ij,
 // so a tile of sample pairs only visits the branches that its rows and its
@@ -32,20 +32,29 @@ __global__ __launch_bounds__(256) void k_pair_zero(uint4* __restrict__ p, int64_
         p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// One block per sample: every branch of [k0, k0 + kc) that the sample touches, once.
+// One block per sample (tabs: of a batch of tables): every branch of [k0, k0 + kc) that the sample touches, once.
 // Weighted: x = l c / T with the exact count c (the sample's entries under branch v
 // of a walk are [ent, p2), and p2 only moves forward as the walk climbs);
 // unweighted: x = l.
 template <typename T, bool W>
 __global__ __launch_bounds__(256) void k_pair_fill(ufp::Emb e, int32_t k0, int32_t kc, int64_t kcp,
+                                                   const BatchTable* __restrict__ tabs,
+                                                   const int32_t* __restrict__ tab_of,
                                                    T* __restrict__ E,
                                                    unsigned long long* __restrict__ mask) {
     const int64_t s = blockIdx.x;
+    int64_t ls = s;      // in its table
+    if (tabs) {
+        const BatchTable t = tabs[tab_of[s]];
+        ls = s - t.off;
+        E += t.e_off;
+        mask += t.m_off;
+    }
     const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
     const double tot = e.total[s];
-    T* Es = E + (s >> 6) * (int64_t(kc) + 1) * 64 + (s & 63);
-    unsigned long long* ms = mask + (s >> 6) * kcp;
-    const unsigned long long bit = 1ull << (s & 63);
+    T* Es = E + (ls >> 6) * (int64_t(kc) + 1) * 64 + (ls & 63);
+    unsigned long long* ms = mask + (ls >> 6) * kcp;
+    const unsigned long long bit = 1ull << (ls & 63);
     for (int64_t ent = a + threadIdx.x; ent < b; ent += 256) {
         int64_t p2 = ent + 1;
         ufd::for_each_branch(e, ent, a, [&](int32_t v) {
@@ -172,6 +181,9 @@ __device__ __forceinline__ void wave_sync() {
 // are those over all branches in postorder, whichever tile a pair falls in.
 // Diagonal tiles also give sum_v x_iv (the pair (i, i)) by the same additions: it is
 // no smaller than any m_ij, and equal to it for equal samples.
+// L1: sums of |x_i - x_j| instead, over the branches that either side touches (a
+// difference of FP32 minima sums would lose the small distances), two VALU operations
+// an update with the broadcast in the first.
 // blockIdx.y: segment [ka + seg*y, +seg) of the chunk, to its own plane of out.
 //
 // Why this shape.  A sample touches few branches (6% of a 20,000-tip tree at 300
@@ -183,32 +195,20 @@ __device__ __forceinline__ void wave_sync() {
 // issue (min, +, and one broadcast per A-row) and by L2 misses of the rows read.
 // Measured with events, against an LDS-tiled kernel over all branches: 256 samples,
 // 1,000 tips 1,144 -> 29 us (two workgroups of 128 x 128 pairs there); 1,500 x 20,000
-// 23.4 -> 1.67 ms; 5,000 x 10,000 32.1 -> 10.9 ms.
+// 23.4 -> 1.67 ms; 5,000 x 10,000 32.1 -> 10.9 ms.  L1: 500 x 2,000 branches 658 -> 43 us;
+// 1,500 x 40,000 13.0 -> 2.03 ms; 5,000 x 10,000 7.5 -> 6.3 ms; 5,000 x 40,000 28.8 ->
+// 19.7 ms, there bound by the rows that miss the caches.
 constexpr int kWin = kPairWin;
-template <typename T, int A>
-__global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
-                                               const unsigned long long* __restrict__ mask, int kc,
-                                               int64_t kcp, int n, int sb, int se, int ka, int kb,
-                                               int seg, int load, T* __restrict__ out,
-                                               int64_t plane) {
-    constexpr int SUB = 64 / (4 * A);
+template <typename T, int A, int U, bool L1>
+__device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
+                                          const unsigned long long* __restrict__ mask, int kc,
+                                          int64_t kcp, int n, int64_t bi, int64_t bj, int ig, int k_lo,
+                                          int k_hi, int sb, int se, bool load, T* out) {
     constexpr int PER = 16 / A;             // branches per load of x_i
-    constexpr int U = 8, NI = U / PER;
+    constexpr int NI = U / PER;
     constexpr int ROW = 64 * int(sizeof(T));
-    __shared__ uint32_t queue[4][kWin + U];
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nblk = (n + 63) / 64;
-    int64_t bi, bj;
-    const int64_t tb = blockIdx.x;
-    if (!tri_tile(((tb >> 3) / SUB) * 8 + (tb & 7), nblk, bi, bj)) return;
-    const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;     // first i inside its block
     const int i0 = int(bi) * 64 + ig, j0 = int(bj) * 64;
-    if (i0 >= n) return;
-    if (bi != bj && !pairs_in_range(i0, min(i0 + A, n), j0, min(j0 + 64, n), n, sb, se)) return;
-    const int k_lo = ka + seg * int(blockIdx.y), k_hi = min(kb, k_lo + seg);
-    out += int64_t(blockIdx.y) * plane;
-
     const int S = n / 2, j = j0 + lane;
     auto slot = [&](int a, int64_t* at, int64_t* dup) -> bool {
         const int i = i0 + a;
@@ -216,7 +216,7 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
         if (i > j || j >= n) return false;
         if (i == j) {
             *at = int64_t(se - sb) * n + i;
-            return true;
+            return !L1;
         }
         const int d = j - i;
         const int s = d <= S ? d - 1 : n - d - 1;
@@ -232,7 +232,6 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
         int64_t at, dup;
         r[a] = (load && slot(a, &at, &dup)) ? out[at] : T(0);
     }
-    uint32_t* q = queue[wave];
     const T* Ei = E + bi * (int64_t(kc) + 1) * 64;
     const T* Ej = E + bj * (int64_t(kc) + 1) * 64;
     const uint32_t* mi = reinterpret_cast<const uint32_t*>(mask + bi * kcp) + (ig >> 5);
@@ -258,7 +257,8 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
 #pragma unroll
         for (int w = 0; w < kWin / 64; ++w) {
             const int k = 64 * w + lane;
-            const bool on = (a_[w] & ibits) != 0u && b_[w] != 0ull && w0 + k < k_hi;
+            const bool ti = (a_[w] & ibits) != 0u, tj = b_[w] != 0ull;
+            const bool on = (L1 ? ti || tj : ti && tj) && w0 + k < k_hi;
             const unsigned long long bal = __ballot(on);
             const int at = cnt + int(__popcll(bal & ((1ull << lane) - 1ull)));
             if (on) q[at] = uint32_t(k);
@@ -284,7 +284,9 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
                 constexpr int u = decltype(u_)::value;
                 unrolled([&](auto a_) {
                     constexpr int a = decltype(a_)::value;
-                    r[a] += vmin(row_bcast<(u % PER) * A + a>(g.i[u / PER]), g.j[u]);
+                    const T xi = row_bcast<(u % PER) * A + a>(g.i[u / PER]);
+                    if constexpr (L1) r[a] += fabs(xi - g.j[u]);
+                    else r[a] += vmin(xi, g.j[u]);
                 }, std::make_integer_sequence<int, A>{});
             }, std::make_integer_sequence<int, U>{});
         };
@@ -309,6 +311,74 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
     }
 }
 
+template <typename T, int A, bool L1>
+__global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
+                                               const unsigned long long* __restrict__ mask, int kc,
+                                               int64_t kcp, int n, int sb, int se, int ka, int kb,
+                                               int seg, int load, T* __restrict__ out,
+                                               int64_t plane) {
+    constexpr int SUB = 64 / (4 * A);
+    constexpr int U = kPairU;
+    __shared__ uint32_t queue[4][kWin + U];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t nblk = (n + 63) / 64;
+    int64_t bi, bj;
+    const int64_t tb = blockIdx.x;
+    if (!tri_tile(((tb >> 3) / SUB) * 8 + (tb & 7), nblk, bi, bj)) return;
+    const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;     // first i inside its block
+    const int i0 = int(bi) * 64 + ig, j0 = int(bj) * 64;
+    if (i0 >= n) return;
+    if (bi != bj && !pairs_in_range(i0, min(i0 + A, n), j0, min(j0 + 64, n), n, sb, se)) return;
+    const int k_lo = ka + seg * int(blockIdx.y), k_hi = min(kb, k_lo + seg);
+    pair_wave<T, A, U, L1>(queue[wave], E, mask, kc, kcp, n, bi, bj, ig, k_lo, k_hi, sb, se, load != 0,
+                           out + int64_t(blockIdx.y) * plane);
+}
+
+// The same tiles over every table of a batch in one launch: items of 64 x 64 pairs and one
+// segment, 64 / A waves each; block b runs on XCD b mod 8 and so does its item.
+// A segment that an earlier chunk began goes on from its plane.
+// Every table's segments together fill the chip, so that its launches do not queue up
+// behind small ones.  Eight tables of 300-1,500 samples x 20,000 branches, a whole call:
+// 8.15 ms with 128 x 128 LDS tiles over all branches (about one workgroup of four waves
+// per CU), now 4.1; three tables of 70-150 x 2,000: 0.77 -> 0.09 ms.  Waves that took
+// their tiles from counters instead spent 0.37 ms per 4,096 waves on them.  The items of
+// all tables in one list, cut in eighths by count: 7.5 ms (segments differ in length).
+template <int A, int U>
+__global__ __launch_bounds__(256) void k_batch_pairs(const float* __restrict__ E,
+                                                     const unsigned long long* __restrict__ mask,
+                                                     const BatchTable* __restrict__ tabs,
+                                                     const int4* __restrict__ items,
+                                                     int k0, int kc, float* __restrict__ acc) {
+    constexpr int SUB = 64 / (4 * A);       // workgroups per item
+    __shared__ uint32_t queue[4][kWin + U];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t tb = blockIdx.x;
+    const int4 it = items[((tb >> 3) / SUB) * 8 + (tb & 7)];   // table, segment, block of i, block of j
+    if (it.x < 0) return;
+    const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;
+    const BatchTable t = tabs[it.x];
+    const int n = int(t.n);
+    if (it.z * 64 + ig >= n) return;
+    const int64_t s0 = int64_t(it.y) * t.seg;       // the segment's part in this chunk
+    const int k_lo = int(max<int64_t>(s0 - k0, 0)), k_hi = int(min<int64_t>(s0 + t.seg - k0, kc));
+    if (k_lo >= k_hi) return;
+    pair_wave<float, A, U, true>(queue[wave], E + t.e_off, mask + t.m_off, kc, kc, n, it.z, it.w, ig, k_lo,
+                                 k_hi, 0, n / 2, s0 < k0, acc + t.p_off + it.y * t.plane);
+}
+
+// Every table's sums: its segments' planes in order (tables of one segment have their
+// sums there already).
+__global__ __launch_bounds__(256) void k_batch_planes(const BatchTable* __restrict__ tabs,
+                                                      float* __restrict__ acc) {
+    const BatchTable t = tabs[blockIdx.y];
+    if (t.n_seg < 2) return;
+    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < t.plane; e += int64_t(gridDim.x) * 256) {
+        float v = acc[t.p_off + e];
+        for (int64_t p = 1; p < t.n_seg; ++p) v += acc[t.p_off + p * t.plane + e];
+        acc[t.acc_off + e] = v;
+    }
+}
+
 // acc (first: =, else +=) planes[0] + planes[1] + ..., in that order
 template <typename T>
 __global__ __launch_bounds__(256) void k_pair_planes(const T* __restrict__ planes, int64_t plane,
@@ -329,6 +399,8 @@ hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, vo
     const PairChunk c = pair_chunk(e.n, kc, sizeof(T));
     T* E = static_cast<T*>(chunk);
     auto* mask = reinterpret_cast<unsigned long long*>(static_cast<char*>(chunk) + c.off_mask);
+    const BatchTable* no_tabs = nullptr;
+    const int32_t* no_tab_of = nullptr;
     const int64_t n16 = int64_t(c.bytes / 16);
     const unsigned zb = unsigned(std::min<int64_t>((n16 + 255) / 256, 16384));
     hipLaunchKernelGGL(k_pair_zero, dim3(zb), dim3(256), 0, st, static_cast<uint4*>(chunk), n16);
@@ -336,29 +408,112 @@ hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, vo
     if (er != hipSuccess) return er;
     if (weighted)
         hipLaunchKernelGGL((k_pair_fill<T, true>), dim3(unsigned(e.n)), dim3(256), 0, st, e,
-                           int32_t(k0), int32_t(kc), c.kcp, E, mask);
+                           int32_t(k0), int32_t(kc), c.kcp, no_tabs, no_tab_of, E, mask);
     else
         hipLaunchKernelGGL((k_pair_fill<T, false>), dim3(unsigned(e.n)), dim3(256), 0, st, e,
-                           int32_t(k0), int32_t(kc), c.kcp, E, mask);
+                           int32_t(k0), int32_t(kc), c.kcp, no_tabs, no_tab_of, E, mask);
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t pairs(const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
-                 int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
-                 hipStream_t st) {
-    if (n <= 0 || kb <= ka) return hipSuccess;
+template <typename T, int A, bool L1>
+static hipError_t pairs_as(const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
+                           int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
+                           hipStream_t st) {
     const PairChunk c = pair_chunk(n, kc, sizeof(T));
     const int64_t nblk = (n + 63) / 64;
-    constexpr int A = kPairA;
     const int64_t blocks = 8 * (64 / (4 * A)) * ((nblk * (nblk + 1) / 2 + 7) / 8);
     if (blocks > 0x7fffffff || n > 0x7fffff00 || kc > 0x3fffffff || count > 65535)
         return hipErrorInvalidValue;
     const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + c.off_mask);
-    hipLaunchKernelGGL((k_pairs<T, A>), dim3(unsigned(blocks), unsigned(count)), dim3(256), 0, st,
+    hipLaunchKernelGGL((k_pairs<T, A, L1>), dim3(unsigned(blocks), unsigned(count)), dim3(256), 0, st,
                        static_cast<const T*>(chunk), mask, int(kc), c.kcp, int(n), int(sb), int(se),
                        int(ka), int(kb), int(std::min<int64_t>(seg, 0x3fffffff)), load, out, plane);
     return hipGetLastError();
+}
+
+template <typename T>
+hipError_t pairs(int form, const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
+                 int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
+                 hipStream_t st) {
+    if (n <= 0 || kb <= ka) return hipSuccess;
+    if constexpr (std::is_same<T, float>::value)
+        if (form == kPairL1)
+            return n >= kPairWideN
+                       ? pairs_as<T, 2 * kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st)
+                       : pairs_as<T, kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
+    if (form != kPairMin) return hipErrorInvalidValue;
+    return pairs_as<T, kPairA, false>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
+}
+
+hipError_t batch_fill(const ufp::Emb& e, const BatchTable* tabs, const int32_t* tab_of, int64_t k0,
+                      int64_t kc, void* chunk, size_t off_mask, size_t bytes, hipStream_t st) {
+    if (e.n <= 0 || kc <= 0) return hipSuccess;
+    if (kc > 0x3fffffff) return hipErrorInvalidValue;
+    const int64_t n16 = int64_t((bytes + 15) / 16);
+    hipLaunchKernelGGL(k_pair_zero, dim3(unsigned(std::min<int64_t>((n16 + 255) / 256, 16384))), dim3(256),
+                       0, st, static_cast<uint4*>(chunk), n16);
+    const hipError_t er = hipGetLastError();
+    if (er != hipSuccess) return er;
+    hipLaunchKernelGGL((k_pair_fill<float, true>), dim3(unsigned(e.n)), dim3(256), 0, st, e, int32_t(k0),
+                       int32_t(kc), kc, tabs, tab_of, static_cast<float*>(chunk),
+                       reinterpret_cast<unsigned long long*>(static_cast<char*>(chunk) + off_mask));
+    return hipGetLastError();
+}
+
+int batch_max_blocks(int stage_branches, int tile_stripes) {
+    static const int limit[3][3] = {{5, 3, 2}, {3, 2, 2}, {1, 1, 1}};
+    const int k = stage_branches == 8 ? 0 : stage_branches == 16 ? 1 : stage_branches == 32 ? 2 : -1;
+    const int t = tile_stripes == 64 ? 0 : tile_stripes == 128 ? 1 : tile_stripes == 256 ? 2 : -1;
+    return k < 0 || t < 0 ? 0 : limit[k][t];
+}
+
+template <int A, int U>
+static hipError_t batch_pairs_as(const float* E, const unsigned long long* mask, const BatchTable* tabs,
+                                 const int4* items, int64_t n_items, int64_t k0, int64_t kc, float* acc,
+                                 int wgs_per_cu, hipStream_t st) {
+    const int64_t blocks = (64 / (4 * A)) * n_items;
+    if (blocks > 0x7fffffff || n_items % 8) return hipErrorInvalidValue;
+    // one group of 16 waves per CU: each of its four workgroups holds a quarter of the LDS
+    const unsigned lds = wgs_per_cu == 1 ? 34 * 1024 : 0;
+    hipLaunchKernelGGL((k_batch_pairs<A, U>), dim3(unsigned(blocks)), dim3(256), lds, st, E, mask, tabs, items,
+                       int(k0), int(kc), acc);
+    return hipGetLastError();
+}
+
+hipError_t batch_pairs(const void* chunk, size_t off_mask, const BatchTable* tabs, const int4* items,
+                       int64_t n_items, int64_t k0, int64_t kc, float* acc, int stage_branches,
+                       int wgs_per_cu, int tile_stripes, hipStream_t st) {
+    const auto* E = static_cast<const float*>(chunk);
+    const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + off_mask);
+    if (n_items < 1 || kc < 1) return hipSuccess;
+    if (wgs_per_cu < 1 || kc > 0x3fffffff) return hipErrorInvalidValue;
+#define UF_BP(KS_, TS_)                            \
+    if (stage_branches == KS_ && tile_stripes == TS_) \
+        return batch_pairs_as<TS_ / 16, KS_ / 2>(E, mask, tabs, items, n_items, k0, kc, acc, wgs_per_cu, st);
+    UF_BP(8, 64)
+    UF_BP(8, 128)
+    UF_BP(8, 256)
+    UF_BP(16, 64)
+    UF_BP(16, 128)
+    UF_BP(16, 256)
+    UF_BP(32, 64)
+    UF_BP(32, 128)
+    UF_BP(32, 256)
+#undef UF_BP
+    return hipErrorInvalidValue;
+}
+
+hipError_t batch_planes(const BatchTable* tabs, int64_t n_tables, int64_t max_plane, float* acc,
+                        hipStream_t st) {
+    if (n_tables < 1 || max_plane < 1) return hipSuccess;
+    const unsigned gx = unsigned(std::min<int64_t>((max_plane + 255) / 256, 4096));
+    for (int64_t r = 0; r < n_tables; r += 65535) {
+        const unsigned gy = unsigned(std::min<int64_t>(n_tables - r, 65535));
+        hipLaunchKernelGGL(k_batch_planes, dim3(gx, gy), dim3(256), 0, st, tabs + r, acc);
+        const hipError_t er = hipGetLastError();
+        if (er != hipSuccess) return er;
+    }
+    return hipSuccess;
 }
 
 template <typename T>
@@ -372,9 +527,9 @@ hipError_t pair_planes(const T* planes, int64_t plane, int64_t count, int first,
 
 template hipError_t pair_fill<double>(const ufp::Emb&, int, int64_t, int64_t, void*, hipStream_t);
 template hipError_t pair_fill<float>(const ufp::Emb&, int, int64_t, int64_t, void*, hipStream_t);
-template hipError_t pairs<double>(const void*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
+template hipError_t pairs<double>(int, const void*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
                                   int64_t, int64_t, int, double*, int64_t, hipStream_t);
-template hipError_t pairs<float>(const void*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
+template hipError_t pairs<float>(int, const void*, int64_t, int64_t, int64_t, int64_t, int64_t, int64_t,
                                  int64_t, int64_t, int, float*, int64_t, hipStream_t);
 template hipError_t pair_planes<double>(const double*, int64_t, int64_t, int, double*, hipStream_t);
 template hipError_t pair_planes<float>(const float*, int64_t, int64_t, int, float*, hipStream_t);

@@ -71,19 +71,14 @@ hipError_t entry_lengths(SlotEntry* se, int64_t n_entries, const int64_t* rl, hi
 // Node-major chunk E[k][s] over positions list[k0 .. k0+kc): x = l * c / T as FP32,
 // or as rint(x * q) in 32-bit fixed point.  merge (every T_s < 2^32) with lo_ord
 // (the n_list entries of list ordered by lo): two forward-merge passes; else one
-// binary search per element.  Same values either way.
+// binary search per element.  Same values either way.  The FP32 chunk has the layout
+// of the pair tiles (ufx::PairChunk): out its values, mask its masks.
 hipError_t embed_list_f32(const ufp::Emb& e, const int32_t* list, const int32_t* lo_ord,
-                          int64_t n_list, bool merge, int64_t k0, int64_t kc, float* out,
-                          hipStream_t st);
+                          int64_t n_list, bool merge, int64_t k0, int64_t kc,
+                          unsigned long long* mask, float* out, hipStream_t st);
 hipError_t embed_list_u32(const ufp::Emb& e, const int32_t* list, const int32_t* lo_ord,
                           int64_t n_list, bool merge, int64_t k0, int64_t kc, double q,
                           uint32_t* out, hipStream_t st);
-// The same two merge passes for a batch: every position of [k0, k0+kc) (FP32),
-// each sample's values into its table's block [kc][n_t] at e_off.  lo_ord_chunk:
-// the chunk's kc positions ordered by lo.  Every T_s must be below 2^32.
-hipError_t embed_batch_merge_f32(const ufp::Emb& e, const BatchTable* tabs, const int32_t* tab_of,
-                                 const int32_t* lo_ord_chunk, int64_t k0, int64_t kc, float* out,
-                                 hipStream_t st);
 // Per-list (hi+lo) branch length in fixed point, and the bf16 length parts of the
 // dense set gathered in order (zero beyond n_dense up to n_pad).
 hipError_t split_lengths(const int32_t* cls, int64_t nb, const int32_t* dense, int64_t n_dense,

@@ -297,11 +297,24 @@ __global__ __launch_bounds__(256) void k_sort_large(const int64_t* __restrict__ 
     }
 }
 
+// Where element (k - k0, s) of a chunk goes: fixed point row-major, [kc][n]; FP32 in the
+// layout of the pair tiles, blocks of 64 samples [kc + 1][64] whose last row is zero,
+// beside a mask per block and branch of the samples that hold a nonzero value.
+template <typename T>
+struct ChunkSlot {
+    static constexpr bool kBlocked = std::is_same<T, float>::value;
+    int64_t base, stride;
+    __device__ ChunkSlot(int64_t s, int64_t n, int64_t kc)
+        : base(kBlocked ? (s >> 6) * (kc + 1) * 64 + (s & 63) : s), stride(kBlocked ? 64 : n) {}
+    __device__ size_t at(int64_t kk) const { return size_t(base + kk * stride); }
+};
+
 // Node-major chunk over a list of branch positions (the dense set): x = l * c / T
 // as FP32, or as 32-bit fixed point rint(x * q) (T = uint32_t).
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_list(ufp::Emb e, const int32_t* __restrict__ list,
                                                     int64_t k0, int64_t kc, double q,
+                                                    unsigned long long* __restrict__ mask,
                                                     T* __restrict__ out) {
     constexpr int TK = 256, TS = 64;
     __shared__ T tile[TK][TS + 1];
@@ -318,6 +331,7 @@ __global__ __launch_bounds__(256) void k_embed_list(ufp::Emb e, const int32_t* _
         hk = e.hi[pos];
         lv = e.len[pos];
     }
+    unsigned long long on = 0;
     for (int j = 0; j < TS; ++j) {
         const int64_t s = sb + j;
         T v = T(0);
@@ -327,13 +341,17 @@ __global__ __launch_bounds__(256) void k_embed_list(ufp::Emb e, const int32_t* _
             else v = T(x);
         }
         tile[tid][j] = v;
+        on |= (unsigned long long)(v != T(0)) << j;
     }
+    const ChunkSlot<T> slot(sb + (tid % TS), e.n, kc);
+    if (slot.kBlocked && kin) mask[blockIdx.y * kc + k] = on;
     __syncthreads();
+    if (!slot.kBlocked && sb + (tid % TS) >= e.n) return;
     for (int r = tid / TS; r < TK; r += 256 / TS) {
         const int64_t kk = kb + r;
-        const int64_t s = sb + (tid % TS);
-        if (kk < kc && s < e.n) out[kk * e.n + s] = tile[r][tid % TS];
+        if (kk < kc) out[slot.at(kk)] = tile[r][tid % TS];
     }
+    if (slot.kBlocked && blockIdx.x == 0 && tid < TS) out[slot.at(kc)] = T(0);
 }
 
 // The same chunk by a forward merge, in two passes over the list (thread =
@@ -348,29 +366,10 @@ __global__ __launch_bounds__(256) void k_embed_list(ufp::Emb e, const int32_t* _
 // prefix is re-read only in lanes whose cursor moved.
 constexpr int kMergeQ = 64;
 
-// Where element (k - k0, s) of the chunk goes: row-major [kc][n] (tabs null), or
-// the block [kc][n_t] of the sample's table in a batch.
-struct ChunkSlot {
-    int64_t base, stride;
-    __device__ ChunkSlot(int64_t s, int64_t n, const BatchTable* tabs, const int32_t* tab_of) {
-        if (tabs) {
-            const BatchTable t = tabs[tab_of[s]];
-            base = t.e_off + (s - t.off);
-            stride = t.n;
-        } else {
-            base = s;
-            stride = n;
-        }
-    }
-    __device__ size_t at(int64_t kk) const { return size_t(base + kk * stride); }
-};
-
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_list_lo(ufp::Emb e, const int32_t* __restrict__ list,
                                                        const int32_t* __restrict__ lo_ord,
                                                        int64_t n_list, int64_t k0, int64_t kc,
-                                                       const BatchTable* __restrict__ tabs,
-                                                       const int32_t* __restrict__ tab_of,
                                                        T* __restrict__ out) {
     __shared__ int32_t qk[kMergeQ], ql[kMergeQ];
     const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
@@ -383,11 +382,11 @@ __global__ __launch_bounds__(256) void k_embed_list_lo(ufp::Emb e, const int32_t
         if (threadIdx.x < nq) {
             const int32_t k = lo_ord[t0 + threadIdx.x];
             qk[threadIdx.x] = k;
-            ql[threadIdx.x] = e.lo[list ? list[k] : k];
+            ql[threadIdx.x] = e.lo[list[k]];
         }
         __syncthreads();
         if (s >= e.n) continue;
-        const ChunkSlot slot(s, e.n, tabs, tab_of);
+        const ChunkSlot<T> slot(s, e.n, kc);
         const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
         int64_t cur = ufd::lower_bound_rank(e.rank, a, b, ql[0]);
         uint32_t below = uint32_t(e.cum[cur + s]);
@@ -409,29 +408,32 @@ __global__ __launch_bounds__(256) void k_embed_list_lo(ufp::Emb e, const int32_t
 template <typename T>
 __global__ __launch_bounds__(256) void k_embed_list_hi(ufp::Emb e, const int32_t* __restrict__ list,
                                                        int64_t k0, int64_t kc, double q,
-                                                       const BatchTable* __restrict__ tabs,
-                                                       const int32_t* __restrict__ tab_of,
+                                                       unsigned long long* __restrict__ mask,
                                                        T* __restrict__ out) {
+    static_assert(kMergeQ == 64, "one mask per lane");
     __shared__ int32_t qh[kMergeQ];
     __shared__ double qlen[kMergeQ];
     const int64_t s = int64_t(blockIdx.x) * 256 + threadIdx.x;
     const int64_t nseg = (kc + kMergeQ - 1) / kMergeQ;
-    const double tot = s < e.n ? e.total[s] : 1.0;
+    const bool in = s < e.n;
+    const double tot = in ? e.total[s] : 1.0;
+    const ChunkSlot<T> slot(s, e.n, kc);
     for (int64_t g = blockIdx.y; g < nseg; g += gridDim.y) {
         const int64_t t0 = k0 + g * kMergeQ;
         const int nq = k0 + kc - t0 < kMergeQ ? int(k0 + kc - t0) : kMergeQ;
         __syncthreads();
         if (threadIdx.x < nq) {
-            const int64_t pos = list ? int64_t(list[t0 + threadIdx.x]) : t0 + threadIdx.x;
+            const int32_t pos = list[t0 + threadIdx.x];
             qh[threadIdx.x] = e.hi[pos];
             qlen[threadIdx.x] = e.len[pos];
         }
         __syncthreads();
-        if (s >= e.n) continue;
-        const ChunkSlot slot(s, e.n, tabs, tab_of);
-        const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
+        // (the lanes past the last sample fill its block up with zeros)
+        if (slot.kBlocked ? (s & ~int64_t(63)) >= e.n : !in) continue;
+        const int64_t a = in ? e.row_ptr[s] : 0, b = in ? e.row_ptr[s + 1] : 0;
         int64_t cur = ufd::lower_bound_rank(e.rank, a, b, qh[0]);
-        uint32_t below = uint32_t(e.cum[cur + s]);
+        uint32_t below = in ? uint32_t(e.cum[cur + s]) : 0u;
+        unsigned long long mine = 0;
         int32_t nxt = cur < b ? e.rank[cur] : 0x7fffffff;   // rank at the cursor
         for (int t = 0; t < nq; ++t) {
             const int32_t h = qh[t];
@@ -442,12 +444,23 @@ __global__ __launch_bounds__(256) void k_embed_list_hi(ufp::Emb e, const int32_t
             }
             if (cur != from) below = uint32_t(e.cum[cur + s]);
             const size_t idx = slot.at(t0 + t - k0);
-            const int64_t c = int64_t(below - reinterpret_cast<const uint32_t*>(out)[idx]);
-            const double x = qlen[t] * (double(c) / tot);
-            T v;
-            if constexpr (std::is_same<T, uint32_t>::value) v = uint32_t(llrint(x * q));
-            else v = T(x);
+            T v = T(0);
+            if (!slot.kBlocked || in) {
+                const int64_t c = int64_t(below - reinterpret_cast<const uint32_t*>(out)[idx]);
+                const double x = qlen[t] * (double(c) / tot);
+                if constexpr (std::is_same<T, uint32_t>::value) v = uint32_t(llrint(x * q));
+                else v = T(x);
+            }
             out[idx] = v;
+            if constexpr (ChunkSlot<T>::kBlocked) {
+                const unsigned long long bal = __ballot(v != T(0));
+                if (int(threadIdx.x & 63) == t) mine = bal;
+            }
+        }
+        if constexpr (ChunkSlot<T>::kBlocked) {
+            const int64_t t = threadIdx.x & 63;
+            if (t < nq) mask[(s >> 6) * kc + (t0 - k0) + t] = mine;
+            if (g == 0) out[slot.at(kc)] = T(0);
         }
     }
 }
@@ -701,8 +714,8 @@ hipError_t entry_lengths(SlotEntry* se, int64_t n_entries, const int64_t* rl, hi
 
 template <typename T>
 static hipError_t embed_list(const ufp::Emb& e, const int32_t* list, const int32_t* lo_ord,
-                             int64_t n_list, bool merge, int64_t k0, int64_t kc, double q, T* out,
-                             hipStream_t st) {
+                             int64_t n_list, bool merge, int64_t k0, int64_t kc, double q,
+                             unsigned long long* mask, T* out, hipStream_t st) {
     if (kc <= 0 || e.n <= 0) return hipSuccess;
     if (merge && lo_ord && n_list >= k0 + kc) {
         const int64_t gx = (e.n + 255) / 256;
@@ -710,49 +723,30 @@ static hipError_t embed_list(const ufp::Emb& e, const int32_t* list, const int32
         const int64_t gy_hi = std::min<int64_t>((kc + kMergeQ - 1) / kMergeQ, 65535);
         if (gx > 0x7fffffff) return hipErrorInvalidValue;
         hipLaunchKernelGGL(k_embed_list_lo<T>, dim3(unsigned(gx), unsigned(gy_lo)), dim3(256), 0, st,
-                           e, list, lo_ord, n_list, k0, kc, static_cast<const BatchTable*>(nullptr),
-                           static_cast<const int32_t*>(nullptr), out);
+                           e, list, lo_ord, n_list, k0, kc, out);
         hipError_t rc = hipGetLastError();
         if (rc != hipSuccess) return rc;
         hipLaunchKernelGGL(k_embed_list_hi<T>, dim3(unsigned(gx), unsigned(gy_hi)), dim3(256), 0, st,
-                           e, list, k0, kc, q, static_cast<const BatchTable*>(nullptr),
-                           static_cast<const int32_t*>(nullptr), out);
+                           e, list, k0, kc, q, mask, out);
         return hipGetLastError();
     }
     const int64_t gy = (e.n + 63) / 64;
     if (gy > 65535) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_embed_list<T>, dim3(unsigned((kc + 255) / 256), unsigned(gy)), dim3(256), 0,
-                       st, e, list, k0, kc, q, out);
+                       st, e, list, k0, kc, q, mask, out);
     return hipGetLastError();
 }
 
 hipError_t embed_list_f32(const ufp::Emb& e, const int32_t* list, const int32_t* lo_ord,
-                          int64_t n_list, bool merge, int64_t k0, int64_t kc, float* out,
-                          hipStream_t st) {
-    return embed_list<float>(e, list, lo_ord, n_list, merge, k0, kc, 1.0, out, st);
+                          int64_t n_list, bool merge, int64_t k0, int64_t kc,
+                          unsigned long long* mask, float* out, hipStream_t st) {
+    return embed_list<float>(e, list, lo_ord, n_list, merge, k0, kc, 1.0, mask, out, st);
 }
 
 hipError_t embed_list_u32(const ufp::Emb& e, const int32_t* list, const int32_t* lo_ord,
                           int64_t n_list, bool merge, int64_t k0, int64_t kc, double q,
                           uint32_t* out, hipStream_t st) {
-    return embed_list<uint32_t>(e, list, lo_ord, n_list, merge, k0, kc, q, out, st);
-}
-
-hipError_t embed_batch_merge_f32(const ufp::Emb& e, const BatchTable* tabs, const int32_t* tab_of,
-                                 const int32_t* lo_ord_chunk, int64_t k0, int64_t kc, float* out,
-                                 hipStream_t st) {
-    if (kc <= 0 || e.n <= 0) return hipSuccess;
-    const int64_t gx = (e.n + 255) / 256;
-    const int64_t gy = std::min<int64_t>((kc + kMergeQ - 1) / kMergeQ, 65535);
-    if (gx > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_embed_list_lo<float>, dim3(unsigned(gx), unsigned(gy)), dim3(256), 0, st, e,
-                       static_cast<const int32_t*>(nullptr), lo_ord_chunk, kc, k0, kc, tabs, tab_of,
-                       out);
-    hipError_t rc = hipGetLastError();
-    if (rc != hipSuccess) return rc;
-    hipLaunchKernelGGL(k_embed_list_hi<float>, dim3(unsigned(gx), unsigned(gy)), dim3(256), 0, st, e,
-                       static_cast<const int32_t*>(nullptr), k0, kc, 1.0, tabs, tab_of, out);
-    return hipGetLastError();
+    return embed_list<uint32_t>(e, list, lo_ord, n_list, merge, k0, kc, q, nullptr, out, st);
 }
 
 hipError_t split_lengths(const int32_t* cls, int64_t nb, const int32_t* dense, int64_t n_dense,
