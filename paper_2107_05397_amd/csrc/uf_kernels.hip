@@ -159,30 +159,23 @@ __global__ __launch_bounds__(256) void k_embed_pres_fp8(
 // Stripe-band accumulation (vector ALU).
 //
 // A block owns a band tile: samples i in [i0, i0+128) times stripes s in
-// [s0, s0+128); the partner of (s, i) is j = (i+s+1) mod N.  For each branch
+// [s0, s0+256); the partner of (s, i) is j = (i+s+1) mod N.  For each branch
 // k of the chunk it needs E[k][i] for its 128 samples and E[k][j] for the
-// 255 partners.  Thread (ti, ts) keeps an 8x8 register tile: samples
-// i0+8ti+a, stripes s0+8ts+b; its partners are the 15 consecutive window
-// entries 8ti+8ts+(a+b).  Per branch and thread: 8+15 LDS reads for 64 pair
-// updates, acc += |x_i - x_j| with x = l * u prescaled in the embedding: two VALU
-// ops (FP32) or one at half rate (v_sad_u32).
+// 383 partners.  Thread (ti, ts) keeps an 8x16 register tile: samples
+// i0+8ti+a, stripes s0+16ts+b; its partners are the 23 consecutive window
+// entries 8ti+16ts+(a+b).  Per branch and thread: 8+23 LDS reads for 128 pair
+// updates, acc += |x_i - x_j| in one v_sad_u32.
 // Staging: KS branches at a time, double-buffered in LDS and filled by direct
-// global->LDS loads (no registers), issued for block b+1 before block b is
-// computed.  Column offsets (mod N) are computed once per thread.
-// Per-pair sums run over branches in postorder, independent of the tile
-// position, so any stripe range reproduces the full run bit for bit.
+// buffer loads to LDS (no registers; the row in the scalar offset, so no address
+// arithmetic either), issued for block b+1 before block b is computed.  Column
+// offsets (mod N) are computed once per thread.
+// Bound by the issue of v_sad_u32 (10,000 samples: the vector ALUs issue in 83% of
+// the cycles, seven eighths of it these).
 // ----------------------------------------------------------------------------
-template <typename T>
-struct BandCfg;
-// KS: branches per LDS stage; MS: stripes per thread (tile = 128 x 16*MS)
-template <>
-struct BandCfg<float> {
-    static constexpr int KS = 16, MS = 8;
-};
-template <>
-struct BandCfg<uint32_t> {
-    static constexpr int KS = 16, MS = 16;
-};
+constexpr int kBandKS = 16;                  // branches per LDS stage
+constexpr int kBandMS = 16;                  // stripes per thread
+constexpr int kBandTS = 16 * kBandMS;        // stripes per tile
+constexpr int kBandWgs = 512;                // two workgroups (64 KiB of LDS) on each of 256 CUs
 
 // |a - b| + c on unsigned 32-bit integers in one VALU op
 __device__ __forceinline__ uint32_t sad_u32(uint32_t a, uint32_t b, uint32_t c) {
@@ -220,86 +213,66 @@ __device__ __forceinline__ void band_patch_tile(int64_t l, int64_t n_iblk, int64
     *sblk = ps * kPatch + rem2 / wi;
 }
 
-// LDS of one band tile of 16*MS stripes: two staging buffers of KS branches.
-// With SWZ, rows are stored in 16-byte quads, quad q of a row at position band_swz(q):
-// the two low bits are flipped by bits 3 and 4, inside each group of four
-// quads.  The fragment reads of a wave start at even quads 2*DW*t (t = 0..15
-// for the sample window), which fall on the same banks for t and t+4 (t and
-// t+8 with 64 banks) when stored in place; with the flip, the first 8 and all
-// 16 of those quads use distinct banks.  The flip never leaves a 64-dword
-// segment, so each direct-to-LDS load still fills one segment, its lanes
-// taking the permuted source columns.  (Without SWZ, quads stay in place: the
-// batch kernel's 256-stripe tiles would need more than 256 VGPRs for the
-// permuted reads' offsets, halving their occupancy.)
-template <bool SWZ>
-__device__ __forceinline__ int band_swz(int q) {
-    return SWZ ? q ^ ((((q >> 3) ^ (q >> 4)) & 1) | ((q >> 2) & 2)) : q;
-}
-template <typename T>
-__device__ __forceinline__ T band_from_dw(const uint32_t* d) {
-    if constexpr (sizeof(T) == 8) return __hiloint2double(int(d[1]), int(d[0]));
-    else if constexpr (std::is_same<T, float>::value) return __uint_as_float(d[0]);
-    else return d[0];
-}
+// Two staging buffers of KS branches.  Rows are stored in 16-byte quads, quad q of a row
+// at position band_swz(q): the two low bits are flipped by bits 3 and 4, inside each
+// group of four quads.  The fragment reads of a wave start at even quads 2*t (t = 0..15
+// for the sample window), which fall on the same banks for t and t+4 (t and t+8 with 64
+// banks) when stored in place; with the flip, the first 8 and all 16 of those quads use
+// distinct banks.  The flip never leaves a 64-dword segment, so each direct-to-LDS load
+// still fills one segment, its lanes taking the permuted source columns.
+__device__ __forceinline__ int band_swz(int q) { return q ^ ((((q >> 3) ^ (q >> 4)) & 1) | ((q >> 2) & 2)); }
 
-template <typename T, int KS, int MS = 8>
 struct BandLds {
-    T wi[2][KS][kBandI];
-    T wj[2][KS][kBandI + 16 * MS];
+    uint32_t wi[2][kBandKS][kBandI];
+    uint32_t wj[2][kBandKS][kBandI + kBandTS];
 };
 
-// One band tile: samples [i0, i0+128) x stripes [s0, s0+16*MS) of a matrix with
-// n samples, over the kc branches of node-major E (row stride n).  Thread
-// (ti, ts) = (tid % 16, tid / 16) owns the 8 x MS register block of samples
-// i0 + 8ti + [0, 8) and stripes s0 + MS*ts + [0, MS); its partners are the
-// 8 + MS - 1 consecutive samples from i0 + s0 + 1 + 8ti + MS*ts.
-template <typename T, int KS, int MS = 8, bool SWZ = true>
-__device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __restrict__ E, int64_t kc,
-                                          int64_t n, int64_t sb, int64_t se, int64_t i0, int64_t s0,
-                                          int first, T* __restrict__ acc) {
-    constexpr int I = kBandI, WJ = kBandI + 16 * MS;
-    constexpr int DW = int(sizeof(T) / 4);          // dwords per element
-    constexpr int EPS = 64 / DW;                    // elements per 64-dword segment
-    constexpr int SEG_I = I / EPS, SEG_J = WJ / EPS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// One band tile: samples [i0, i0+128) x stripes [s0, s0+256) of a matrix with n samples,
+// over the branches [ka, kb) of node-major E (row stride n).  Thread (ti, ts) = (tid % 16,
+// tid / 16) owns the 8 x MS register block of samples i0 + 8ti + [0, 8) and stripes
+// s0 + MS*ts + [0, MS); its partners are the 8 + MS - 1 consecutive samples from
+// i0 + s0 + 1 + 8ti + MS*ts.  mode: store the sums, add to what acc holds, or (a part of
+// the tile's branches) add atomically.
+constexpr int kBandStore = 0, kBandAdd = 1, kBandAtomic = 2;
+__device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict__ E, int64_t ka,
+                                          int64_t kb, int64_t n, int64_t sb, int64_t se, int64_t i0,
+                                          int64_t s0, int mode, uint32_t* __restrict__ acc) {
+    constexpr int KS = kBandKS, MS = kBandMS;
+    constexpr int SEG_I = kBandI / 64, SEG_J = (kBandI + kBandTS) / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ti = tid & 15, ts = tid >> 4;
 
-    // lane -> the dword of segment p it fills (its quad at band_swz), as
-    // (element of the segment, dword of that element)
-    auto seg_dword = [&](int p) { return 4 * (band_swz<SWZ>(16 * p + (lane >> 2)) - 16 * p) + (lane & 3); };
-    int64_t coli[SEG_I], colj[SEG_J];
+    // lane -> the element of segment p it fills (its quad at band_swz)
+    auto seg_elem = [&](int p) { return 4 * band_swz(16 * p + (lane >> 2)) + (lane & 3); };
+    int coli[SEG_I], colj[SEG_J];   // in bytes
 #pragma unroll
-    for (int p = 0; p < SEG_I; ++p) {
-        const int dl = seg_dword(p);
-        coli[p] = ((i0 + p * EPS + dl / DW) % n) * DW + dl % DW;
-    }
+    for (int p = 0; p < SEG_I; ++p) coli[p] = 4 * int((i0 + seg_elem(p)) % n);
 #pragma unroll
-    for (int p = 0; p < SEG_J; ++p) {
-        const int dl = seg_dword(p);
-        colj[p] = ((i0 + s0 + 1 + p * EPS + dl / DW) % n) * DW + dl % DW;
-    }
-    // this thread's fragment quads: 2*DW from its 8 samples, NQJ from its 7+MS partners
-    constexpr int NQI = 2 * DW, NQJ = ((7 + MS) * DW + 3) / 4;
+    for (int p = 0; p < SEG_J; ++p) colj[p] = 4 * int((i0 + s0 + 1 + seg_elem(p)) % n);
+    // this thread's fragment quads: 2 from its 8 samples, NQJ from its 7+MS partners
+    constexpr int NQI = 2, NQJ = (7 + MS + 3) / 4;
     int oi[NQI], oj[NQJ];
 #pragma unroll
-    for (int q = 0; q < NQI; ++q) oi[q] = 4 * band_swz<SWZ>(2 * DW * ti + q);
+    for (int q = 0; q < NQI; ++q) oi[q] = 4 * band_swz(2 * ti + q);
 #pragma unroll
-    for (int q = 0; q < NQJ; ++q) oj[q] = 4 * band_swz<SWZ>((ti * 8 + ts * MS) * DW / 4 + q);
+    for (int q = 0; q < NQJ; ++q) oj[q] = 4 * band_swz((ti * 8 + ts * MS) / 4 + q);
 
     auto stage = [&](int buf, int64_t k0) {
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(E + k0 * n), 0, -4, 0x00027000);
 #pragma unroll
         for (int kk = wave; kk < KS; kk += 4) {
             const int64_t row = k0 + kk;
-            uint32_t* di = reinterpret_cast<uint32_t*>(&L.wi[buf][kk][0]);
-            uint32_t* dj = reinterpret_cast<uint32_t*>(&L.wj[buf][kk][0]);
-            if (row < kc) {
-                const uint32_t* src = reinterpret_cast<const uint32_t*>(E + row * n);
+            uint32_t* di = &L.wi[buf][kk][0];
+            uint32_t* dj = &L.wj[buf][kk][0];
+            if (row < kb) {
+                const int so = kk * int(n) * 4;
 #pragma unroll
                 for (int p = 0; p < SEG_I; ++p)
-                    __builtin_amdgcn_global_load_lds(src + coli[p], di + p * 64, 4, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, di + p * 64, 4, coli[p], so, 0, 0);
 #pragma unroll
                 for (int p = 0; p < SEG_J; ++p)
-                    __builtin_amdgcn_global_load_lds(src + colj[p], dj + p * 64, 4, 0, 0);
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dj + p * 64, 4, colj[p], so, 0, 0);
             } else {
 #pragma unroll
                 for (int p = 0; p < SEG_I; ++p) di[p * 64 + lane] = 0u;
@@ -309,54 +282,41 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
         }
     };
 
-    T r[8][MS];
+    uint32_t r[8][MS];
 #pragma unroll
     for (int b = 0; b < MS; ++b) {
         const int64_t s = s0 + ts * MS + b;
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
             const int64_t i = i0 + ti * 8 + a;
-            r[a][b] = (!first && s < se && i < n) ? acc[(s - sb) * n + i] : T(0);
+            r[a][b] = (mode == kBandAdd && s < se && i < n) ? acc[(s - sb) * n + i] : 0u;
         }
     }
 
-    const int64_t nblk = (kc + KS - 1) / KS;
-    stage(0, 0);
+    const int64_t nblk = (kb - ka + KS - 1) / KS;
+    stage(0, ka);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     for (int64_t blk = 0; blk < nblk; ++blk) {
         const int cur = int(blk & 1);
-        if (blk + 1 < nblk) stage(cur ^ 1, (blk + 1) * KS);
+        if (blk + 1 < nblk) stage(cur ^ 1, ka + (blk + 1) * KS);
 #pragma unroll 2
         for (int kk = 0; kk < KS; ++kk) {
-            const uint32_t* rwi = reinterpret_cast<const uint32_t*>(&L.wi[cur][kk][0]);
-            const uint32_t* rwj = reinterpret_cast<const uint32_t*>(&L.wj[cur][kk][0]);
-            uint32_t bi[4 * NQI], bj[4 * NQJ];
+            const uint32_t* rwi = &L.wi[cur][kk][0];
+            const uint32_t* rwj = &L.wj[cur][kk][0];
+            uint32_t xi[4 * NQI], xj[4 * NQJ];
 #pragma unroll
-            for (int q = 0; q < NQI; ++q) *reinterpret_cast<uint4*>(bi + 4 * q) = *reinterpret_cast<const uint4*>(rwi + oi[q]);
+            for (int q = 0; q < NQI; ++q) *reinterpret_cast<uint4*>(xi + 4 * q) = *reinterpret_cast<const uint4*>(rwi + oi[q]);
 #pragma unroll
-            for (int q = 0; q < NQJ; ++q) *reinterpret_cast<uint4*>(bj + 4 * q) = *reinterpret_cast<const uint4*>(rwj + oj[q]);
-            T xi[8], xj[8 + MS];
+            for (int q = 0; q < NQJ; ++q) *reinterpret_cast<uint4*>(xj + 4 * q) = *reinterpret_cast<const uint4*>(rwj + oj[q]);
 #pragma unroll
-            for (int a = 0; a < 8; ++a) xi[a] = band_from_dw<T>(bi + a * DW);
+            for (int a = 0; a < 8; ++a)
 #pragma unroll
-            for (int c = 0; c < 7 + MS; ++c) xj[c] = band_from_dw<T>(bj + c * DW);
-            if constexpr (std::is_same<T, uint32_t>::value) {
-#pragma unroll
-                for (int a = 0; a < 8; ++a)
-#pragma unroll
-                    for (int b = 0; b < MS; ++b) r[a][b] = sad_u32(xi[a], xj[a + b], r[a][b]);
-            } else {
-#pragma unroll
-                for (int a = 0; a < 8; ++a)
-#pragma unroll
-                    for (int b = 0; b < MS; ++b) r[a][b] += fabs(xi[a] - xj[a + b]);
-            }
+                for (int b = 0; b < MS; ++b) r[a][b] = sad_u32(xi[a], xj[a + b], r[a][b]);
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
     }
-
 #pragma unroll
     for (int b = 0; b < MS; ++b) {
         const int64_t s = s0 + ts * MS + b;
@@ -364,24 +324,50 @@ __device__ __forceinline__ void band_tile(BandLds<T, KS, MS>& L, const T* __rest
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
             const int64_t i = i0 + ti * 8 + a;
-            if (i < n) acc[(s - sb) * n + i] = r[a][b];
+            if (i >= n) continue;
+            if (mode == kBandAtomic) atomicAdd(&acc[(s - sb) * n + i], r[a][b]);
+            else acc[(s - sb) * n + i] = r[a][b];
         }
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_band(const T* __restrict__ E, int64_t kc, int64_t n,
+// kBandWgs resident workgroups.  Whole rounds of tiles are theirs one by one; the tiles
+// left over, fewer than there are workgroups, are cut along the branches into as many
+// equal shares (multiples of 4 stages), so that every workgroup ends at about the same
+// time.  The sums are integers: a tile's parts add up in any order to the same bits.
+// One workgroup per tile left CUs empty in the last (or only) round: 300 samples x 2,912
+// branches 1,030 -> 109 us, 1,000 x 3,838 1.36 -> 0.67 ms, 3,333 x 6,849 2.44 -> 1.68,
+// 10,000 x 14,873 27.5 -> 25.4.  On touched-branch pair tiles (min and add) these took
+// 2.2 (3,333) and 56 ms: most of a split's dense branches are touched in every tile.
+__global__ __launch_bounds__(256, 2) void k_band(const uint32_t* __restrict__ E, int64_t kc, int64_t n,
                                               int64_t sb, int64_t se, int64_t n_iblk, int first,
-                                              T* __restrict__ acc) {
-    constexpr int KS = BandCfg<T>::KS, MS = BandCfg<T>::MS, TS = 16 * MS;
-    __shared__ __attribute__((aligned(16))) BandLds<T, KS, MS> L;
-    const int64_t n_sblk = (se - sb + TS - 1) / TS;
-    const int64_t n_tiles = n_iblk * n_sblk;
-    int64_t ib = 0, sblk = 0;
-    band_patch_tile(xcd_tile(blockIdx.x, n_tiles), n_iblk, n_sblk, &ib, &sblk);
-    const int64_t i0 = ib * kBandI;
-    const int64_t s0 = sb + sblk * TS;
-    band_tile<T, KS, MS, true>(L, E, kc, n, sb, se, i0, s0, first, acc);
+                                              uint32_t* __restrict__ acc) {
+    __shared__ __attribute__((aligned(16))) BandLds L;
+    const int64_t n_sblk = (se - sb + kBandTS - 1) / kBandTS;
+    const int64_t n_tiles = n_iblk * n_sblk, whole = n_tiles / kBandWgs * kBandWgs;
+    const int64_t stages = (kc + kBandKS - 1) / kBandKS, work = (n_tiles - whole) * stages;
+    const int64_t rank = int64_t(blockIdx.x & 7) * (kBandWgs / 8) + (blockIdx.x >> 3);
+    const int64_t end = rank + 1 == kBandWgs ? work : ((rank + 1) * work / kBandWgs) & ~int64_t(3);
+    int64_t w = (rank * work / kBandWgs) & ~int64_t(3), l = blockIdx.x;
+    for (;;) {
+        int64_t t, ka = 0, kb = kc;
+        if (w < end) {                           // a part of a tile
+            const int64_t g = w % stages, cnt = min(stages - g, end - w);
+            t = whole + w / stages;
+            ka = g * kBandKS;
+            kb = min(kc, (g + cnt) * kBandKS);
+            w += cnt;
+        } else if (l < whole) {
+            t = xcd_tile(l, whole);
+            l += kBandWgs;
+        } else {
+            break;
+        }
+        int64_t ib = 0, sblk = 0;
+        band_patch_tile(t, n_iblk, n_sblk, &ib, &sblk);
+        const int mode = kb - ka < kc ? kBandAtomic : first ? kBandStore : kBandAdd;
+        band_tile(L, E, ka, kb, n, sb, se, ib * kBandI, sb + sblk * kBandTS, mode, acc);
+    }
 }
 
 // ----------------------------------------------------------------------------
@@ -936,22 +922,18 @@ hipError_t embed_presence_fp8(const uf_embedding& e, int64_t k0, int64_t kc, int
     return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t band(const T* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first, T* acc,
-                       hipStream_t st) {
-    if (se <= sb || n <= 0) return hipSuccess;
-    constexpr int64_t TS = 16 * BandCfg<T>::MS;
-    const int64_t n_iblk = (n + kBandI - 1) / kBandI;
-    const int64_t n_tiles = n_iblk * ((se - sb + TS - 1) / TS);
-    if (n_tiles > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_band<T>, dim3(unsigned(n_tiles)), dim3(256), 0, st, E, kc, n, sb, se, n_iblk,
-                       first, acc);
-    return hipGetLastError();
-}
-
 hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
                     uint32_t* acc, hipStream_t st) {
-    return band<uint32_t>(E, kc, n, sb, se, first, acc, st);
+    if (se <= sb || n <= 0) return hipSuccess;
+    const int64_t n_iblk = (n + kBandI - 1) / kBandI;
+    const int64_t n_tiles = n_iblk * ((se - sb + kBandTS - 1) / kBandTS);
+    if (n_tiles > 0x7fffffff) return hipErrorInvalidValue;
+    if (first && n_tiles % kBandWgs) {   // the tiles cut in parts add to it
+        const hipError_t er = zero_u32(acc, (se - sb) * n, st);
+        if (er != hipSuccess) return er;
+    }
+    hipLaunchKernelGGL(k_band, dim3(kBandWgs), dim3(256), 0, st, E, kc, n, sb, se, n_iblk, first, acc);
+    return hipGetLastError();
 }
 
 hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, int64_t kpad,
