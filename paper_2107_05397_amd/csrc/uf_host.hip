@@ -838,6 +838,38 @@ void prof_end(ProfHandle* h) { delete h; }
 // =========================================================================
 // C ABI
 // =========================================================================
+namespace {
+// Digits of the lengths: 28 bits below 2^len_exp (FP32-rounded and BF16 hi + lo lengths)
+// or 56 (FP64).  Rounding changes a pair's sum by at most len_err = sum_v |l_v - rounded
+// l_v| and a distance by at most about len_err / (the smaller sample's total length).
+void length_digits(uf_tree* t) {
+    const int64_t nb = t->n_nodes - 1;
+    double lmax = 0.0;
+    for (int64_t k = 0; k < nb; ++k) lmax = std::max(lmax, t->len[size_t(k)]);
+    lmax *= 1.0 + 0x1p-16;   // the rounded lengths are no longer than this
+    int ex = 0;
+    while (ex < 1100 && lmax >= std::ldexp(1.0 - 0x1p-20, ex)) ++ex;
+    while (ex > -900 && lmax > 0.0 && lmax < std::ldexp(0.5 - 0x1p-20, ex)) --ex;
+    t->len_exp = ex;
+    if (!std::isfinite(lmax) || ex >= 900 || ex <= -800) return;
+    const double q56 = std::ldexp(1.0, ex - 8 * ufb::kDigitBits), i56 = 1.0 / q56;
+    const double q28 = std::ldexp(1.0, ex - 4 * ufb::kDigitBits), i28 = 1.0 / q28;
+    // (adding 2^52 rounds a value below it; one above is whole)
+    auto off = [](double l, double iq, double q) {
+        const double v = l * iq, r = v < 0x1p52 ? (v + 0x1p52) - 0x1p52 : v;
+        return std::fabs(l - r * q);
+    };
+    double err[3] = {0.0, 0.0, 0.0};
+    for (int64_t k = 0; k < nb; ++k) {
+        const double l = t->len[size_t(k)], hi = bf16_value(bf16_bits(l));
+        err[0] += off(l, i56, q56);
+        err[1] += off(double(static_cast<float>(l)), i28, q28);
+        err[2] += off(hi + bf16_value(bf16_bits(l - hi)), i28, q28);
+    }
+    std::copy(err, err + 3, t->len_err);
+}
+}  // namespace
+
 extern "C" {
 
 const char* uf_status_string(uf_status s) {
@@ -1003,6 +1035,7 @@ uf_status uf_tree_load(int64_t m, const int64_t* parent, const double* length, u
             t->hi[k] = int32_t(tips_before[k + 1]);
         }
         t->n_tips = tips_before[m];
+        length_digits(t);
         *out = guard.release();
         return UF_OK;
     });
@@ -1212,37 +1245,20 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         }
         rc = hipStreamSynchronize(s);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel"));
-        // Digits of the lengths: 28 bits below 2^len_exp (FP32-rounded and BF16 hi + lo
-        // lengths) or 56 (FP64).  Rounding changes a pair's sum by at most
-        // err = sum_v |l_v - rounded l_v|, and d by at most about err / w with w the
-        // smaller sample's total branch length.  Taken when that bound, over all branches
-        // and the smallest w, is at most 1e-5 and 1e-13 (worst cases; errors of opposite
+        // The digits serve when the bound err / w on a distance, with w the smallest sample's
+        // total branch length, is at most 1e-5 and 1e-13 (worst cases; errors of opposite
         // sign cancel in a pair's sum, and measured against 64 bits the distances are off
         // by 2.5e-8, the rounding of FP32 results, and 7e-16).
-        double lmax = 0.0;
-        for (int64_t k = 0; k < nb; ++k) lmax = std::max({lmax, t->len[k], double(len32[k]), bf16_value(lhi[k]) + bf16_value(llo[k])});
-        while (e->len_exp < 1100 && lmax >= std::ldexp(1.0 - 0x1p-20, e->len_exp)) ++e->len_exp;
-        while (e->len_exp > -900 && lmax > 0.0 && lmax < std::ldexp(0.5 - 0x1p-20, e->len_exp)) --e->len_exp;
         std::vector<double> hw(size_t(std::max<int64_t>(n, 1)), 0.0);
         if (n > 0) rc = hipMemcpy(hw.data(), e->wu, size_t(n) * 8, hipMemcpyDeviceToHost);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalars"));
         double w_min = 1e300;
         for (double w : hw)
             if (w > 0.0) w_min = std::min(w_min, w);
-        if (std::isfinite(lmax) && e->len_exp < 900 && e->len_exp > -800) {
-            const double q56 = std::ldexp(1.0, e->len_exp - 8 * ufb::kDigitBits), q28 = std::ldexp(1.0, e->len_exp - 4 * ufb::kDigitBits);
-            const double i56 = 1.0 / q56, i28 = 1.0 / q28;
-            double err[3] = {0.0, 0.0, 0.0};
-            auto off = [](double l, double iq, double q) { return std::fabs(l - std::nearbyint(l * iq) * q); };
-            for (int64_t k = 0; k < nb; ++k) {
-                err[0] += off(t->len[k], i56, q56);
-                err[1] += off(double(len32[k]), i28, q28);
-                err[2] += off(bf16_value(lhi[k]) + bf16_value(llo[k]), i28, q28);
-            }
-            e->len_fixed[0] = err[0] <= 1e-13 * w_min;
-            e->len_fixed[1] = err[1] <= 1e-5 * w_min;
-            e->len_fixed[2] = err[2] <= 1e-5 * w_min;
-        }
+        e->len_exp = t->len_exp;
+        e->len_fixed[0] = t->len_err[0] <= 1e-13 * w_min;
+        e->len_fixed[1] = t->len_err[1] <= 1e-5 * w_min;
+        e->len_fixed[2] = t->len_err[2] <= 1e-5 * w_min;
         *out = guard.release();
         return UF_OK;
     }

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <memory>
@@ -31,6 +32,10 @@ struct uf_tree {
     std::vector<int32_t> lo, hi;      // tip-rank interval under position k
     std::vector<int32_t> tip_rank;    // by node id, -1 for internal nodes
     std::vector<int32_t> tip_pos;     // position of the tip with rank r
+    // lengths in fixed point (FP64, FP32-rounded, BF16 hi + lo): every one is below
+    // 2^len_exp, and rounding them to the digits of their kind is off by len_err in all
+    int len_exp = 0;
+    double len_err[3] = {HUGE_VAL, HUGE_VAL, HUGE_VAL};
 };
 
 // A validated table: per sample, its nonzero entries sorted by tip rank.
@@ -181,7 +186,6 @@ struct BatchTable {
 namespace ufk {
 
 constexpr int kBandI = 128;       // samples per band tile
-constexpr int kBandS = 128;       // stripes per band tile
 constexpr int kGramT = 256;       // square tile of the MFMA Gram kernel
 constexpr int kGramK = 128;        // K step of the MFMA Gram kernel
 constexpr int kGramKPad = 256;    // K of its presence matrix is padded to this (steps go in pairs)
