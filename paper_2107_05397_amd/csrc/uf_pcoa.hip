@@ -9,17 +9,20 @@
 // eigenpairs come from randomized subspace iteration with a Rayleigh-Ritz
 // projection (Halko, Martinsson, Tropp 2011): Y = B Omega, then orthonormal
 // bases of B Q, and T = Q^T B Q, whose small eigenproblem gives the Ritz pairs.
-// Orthonormalisation is SVQB (Stathopoulos and Wu 2002): from the Gram matrix
-// G = Y^T Y = U S U^T, Q = Y U S^{-1/2} over the directions with S above a
-// relative floor (so rank-deficient B is handled), applied twice.  The small
-// symmetric eigenproblems (at most 48 x 48) are solved on the host by cyclic
-// Jacobi rotations.  All reductions over samples run in a fixed order.
+// Orthonormalisation is Cholesky QR, applied twice: from the Gram matrix G = Y^T Y =
+// R^T R, Q = Y R^-1, leaving out columns that depend on others up to a relative floor
+// (so rank-deficient B is handled).  All of it runs on the device; only the last
+// eigenproblem, Q^T B Q, is solved on the host, by cyclic Jacobi rotations.  All
+// reductions over samples run in a fixed order.  One call, 6,000 samples, 20 columns, 3
+// iterations: 2.09 ms with SVQB (Stathopoulos and Wu 2002; the basis PCA still uses it)
+// and its eigenproblems on the host, now 0.83; 300 samples 605 -> 237 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 #include "uf.h"
@@ -28,121 +31,12 @@
 namespace ufq {
 namespace {
 
-constexpr int kRB = 64;          // rows per block of the A X kernel
+constexpr int kRB = 32;          // rows per block of the A X kernel
 constexpr int kMaxCols = 48;     // columns of the test matrix (LDS: 33 KiB + up to 24 KiB)
 constexpr int kSegs = 8;         // column-block segments of the A X kernel
 
-__device__ __forceinline__ int64_t cidx(int64_t n, int64_t a, int64_t b) {   // a < b
-    return a * n - a * (a + 1) / 2 + (b - a - 1);
-}
 
-// P[seg][i][c] = sum over j in the segment's column blocks, j != i, of
-// (-d_ij^2 / 2) X[j][c].  Block (ib, seg); 256 threads; tile 64 x 64 of A in
-// LDS transposed (At[j][r]) so the inner loop reads consecutive rows.  The next
-// tile is loaded into registers while the current one is multiplied.
-template <int CPT>
-__global__ __launch_bounds__(256) void k_ax(const double* __restrict__ dm, int64_t n,
-                                            const double* __restrict__ X, int cols,
-                                            int64_t nblk, double* __restrict__ P) {
-    constexpr int kPer = kRB * kRB / 256;                 // tile elements per thread
-    constexpr int kW = 4 * CPT;                           // X columns, zero-padded
-    constexpr int kXPer = (kRB * kW + 255) / 256;         // X elements per thread
-    __shared__ double At[kRB][kRB + 1];
-    __shared__ double Xs[kRB][kW];
-    const int tid = threadIdx.x;
-    const int64_t ib = blockIdx.x, seg = blockIdx.y;
-    const int64_t i0 = ib * kRB;
-    const int64_t jb0 = nblk * seg / kSegs, jb1 = nblk * (seg + 1) / kSegs;
-    const int r = tid & 63, cg = tid >> 6;      // output row; columns cg*CPT ..
-    double acc[CPT];
-#pragma unroll
-    for (int k = 0; k < CPT; ++k) acc[k] = 0.0;
-    // One tile's distances and X rows, all loads in flight at once: element u of
-    // this thread is e = tid + 256 u, taken along the contiguous side of the
-    // condensed rows (row i fixed and j consecutive above the diagonal, row j
-    // fixed and i consecutive below it).  Zero outside the matrix and on it.
-    double va[kPer], vx[kXPer];
-    auto load = [&](int64_t jb) {
-        const int64_t j0 = jb * kRB;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int e = tid + 256 * u;
-            const int rr = jb >= ib ? e / kRB : e % kRB;
-            const int cc = jb >= ib ? e % kRB : e / kRB;
-            const int64_t i = i0 + rr, j = j0 + cc;
-            va[u] = 0.0;
-            if (i < n && j < n && i != j) va[u] = i < j ? dm[cidx(n, i, j)] : dm[cidx(n, j, i)];
-        }
-#pragma unroll
-        for (int u = 0; u < kXPer; ++u) {
-            const int e = tid + 256 * u;
-            const int c = e % kW;
-            const int64_t j = j0 + e / kW;
-            vx[u] = (e < kRB * kW && c < cols && j < n) ? X[j * cols + c] : 0.0;
-        }
-    };
-    auto store = [&](int64_t jb) {
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int e = tid + 256 * u;
-            const int rr = jb >= ib ? e / kRB : e % kRB;
-            const int cc = jb >= ib ? e % kRB : e / kRB;
-            At[cc][rr] = 0.0 - 0.5 * va[u] * va[u];   // +0 where the distance is absent
-        }
-#pragma unroll
-        for (int u = 0; u < kXPer; ++u) {
-            const int e = tid + 256 * u;
-            if (e < kRB * kW) Xs[e / kW][e % kW] = vx[u];
-        }
-    };
-    if (jb0 < jb1) load(jb0);
-    for (int64_t jb = jb0; jb < jb1; ++jb) {
-        __syncthreads();
-        store(jb);
-        if (jb + 1 < jb1) load(jb + 1);          // next tile in flight during the FMAs
-        __syncthreads();
-        for (int jj = 0; jj < kRB; ++jj) {
-            const double a = At[jj][r];
-#pragma unroll
-            for (int k = 0; k < CPT; ++k) acc[k] = fma(a, Xs[jj][cg * CPT + k], acc[k]);
-        }
-    }
-    const int64_t i = i0 + r;
-    if (i < n) {
-#pragma unroll
-        for (int k = 0; k < CPT; ++k) {
-            const int c = cg * CPT + k;
-            if (c < cols) P[(seg * n + i) * cols + c] = acc[k];
-        }
-    }
-}
-
-// k_ax for `cols` test columns: CPT = ceil(cols / 4) columns per thread.
-template <int CPT>
-hipError_t launch_ax_cpt(dim3 g, hipStream_t s, const double* dm, int64_t n, const double* X,
-                         int cols, int64_t nblk, double* P) {
-    hipLaunchKernelGGL(k_ax<CPT>, g, dim3(256), 0, s, dm, n, X, cols, nblk, P);
-    return hipGetLastError();
-}
-
-hipError_t launch_ax(dim3 g, hipStream_t s, const double* dm, int64_t n, const double* X, int cols,
-                     int64_t nblk, double* P) {
-    switch ((cols + 3) / 4) {
-        case 1: return launch_ax_cpt<1>(g, s, dm, n, X, cols, nblk, P);
-        case 2: return launch_ax_cpt<2>(g, s, dm, n, X, cols, nblk, P);
-        case 3: return launch_ax_cpt<3>(g, s, dm, n, X, cols, nblk, P);
-        case 4: return launch_ax_cpt<4>(g, s, dm, n, X, cols, nblk, P);
-        case 5: return launch_ax_cpt<5>(g, s, dm, n, X, cols, nblk, P);
-        case 6: return launch_ax_cpt<6>(g, s, dm, n, X, cols, nblk, P);
-        case 7: return launch_ax_cpt<7>(g, s, dm, n, X, cols, nblk, P);
-        case 8: return launch_ax_cpt<8>(g, s, dm, n, X, cols, nblk, P);
-        case 9: return launch_ax_cpt<9>(g, s, dm, n, X, cols, nblk, P);
-        case 10: return launch_ax_cpt<10>(g, s, dm, n, X, cols, nblk, P);
-        case 11: return launch_ax_cpt<11>(g, s, dm, n, X, cols, nblk, P);
-        case 12: return launch_ax_cpt<12>(g, s, dm, n, X, cols, nblk, P);
-        default: return hipErrorInvalidValue;
-    }
-}
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 // Fixed-order block reduction of 256 doubles held one per thread.
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -157,12 +51,10 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
     return s;
 }
 
-// sums[c] = sum_i X[i][c], sums[cols + c] = sum_i r_i X[i][c] (one block per column)
-__global__ __launch_bounds__(256) void k_colsums(const double* __restrict__ X, int cols, int64_t n,
-                                                 const double* __restrict__ rmean,
-                                                 double* __restrict__ sums) {
-    __shared__ double red[256];
-    const int c = blockIdx.x;
+// sums[c] = sum_i X[i][c], sums[cols + c] = sum_i r_i X[i][c], by one block
+__device__ __forceinline__ void col_sums(const double* __restrict__ X, int cols, int c, int64_t n,
+                                         const double* __restrict__ rmean, double* __restrict__ sums,
+                                         double* red) {
     double s = 0.0, t = 0.0;
     for (int64_t i = threadIdx.x; i < n; i += 256) {
         const double x = X[i * cols + c];
@@ -177,20 +69,336 @@ __global__ __launch_bounds__(256) void k_colsums(const double* __restrict__ X, i
     }
 }
 
-// Y = sum_seg P[seg] - r (1^T X) - 1 (r^T X) + g 1 (1^T X)
-__global__ __launch_bounds__(256) void k_centre(const double* __restrict__ P, int64_t n, int cols,
+// P[seg][i][c] = sum over j in the segment, j != i, of (-d_ij^2 / 2) X[j][c], on
+// v_mfma_f64_16x16x4_f64.  Block (ib, seg): 32 rows; its four waves take a quarter of
+// the segment's steps of 16 columns j each and are added up in order at the end.  Lane l
+// holds row l mod 16 of each 16-row group and columns 4 (l / 16) + t of the step (t = 0..3,
+// one MFMA each), straight from the condensed matrix: above the diagonal its four
+// values are consecutive, below it the 16 lanes' are.  Two to three waves
+// a SIMD hide each other's loads.  NB: 16-column groups of X (zero past `cols`).  Blocks past the rows
+// (grid.x > nblk) give the column sums of X (col_sums).
+// Bound by reading the matrix, each element from both its row's and its column's block
+// (6,000 samples: 288 MB, 3.8 TB/s; the MFMAs with 17-32 columns take 30 us of it).
+// 6,000 samples, 20 columns: 138 us with the tile of A in LDS and FMAs from there, now
+// 76; holding a step's values in registers over the next one's loads 84 (fewer waves).
+constexpr int kAxWaves = 4;
+constexpr int kAbove = 0, kBelow = 1, kAny = 2;
+template <int NB>
+__global__ __launch_bounds__(64 * kAxWaves, NB < 3 ? 2 : 1) void k_ax(const double* __restrict__ dm, int64_t n,
+                                                      const double* __restrict__ X, int cols,
+                                                      int64_t nblk, const double* __restrict__ rmean,
+                                                      double* __restrict__ P, double* __restrict__ sums) {
+    constexpr int RG = kRB / 16;
+    __shared__ double red[kRB][NB * 16 + 1];
+    if (int64_t(blockIdx.x) >= nblk) {
+        const int c = int(blockIdx.x - nblk) * kSegs + int(blockIdx.y);
+        if (c < cols) col_sums(X, cols, c, n, rmean, sums, &red[0][0]);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane & 15, grp = lane >> 4;
+    const int64_t i0 = int64_t(blockIdx.x) * kRB;
+    const int64_t nj = (n + 15) / 16, parts = int64_t(kSegs) * kAxWaves, part = int64_t(blockIdx.y) * kAxWaves + wave;
+    const int64_t j_lo = nj * part / parts * 16, j_hi = nj * (part + 1) / parts * 16;
+    v4d acc[RG][NB];
+#pragma unroll
+    for (int r = 0; r < RG; ++r)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[r][b] = v4d{0.0, 0.0, 0.0, 0.0};
+    struct Step {
+        double a[RG][4], x[NB][4];
+    };
+    // element (i, j) of the condensed matrix, i < j, is dm[at(i) + j]
+    auto at = [&](int64_t i) { return i * n - i * (i + 1) / 2 - i - 1; };
+    int64_t base[RG];
+#pragma unroll
+    for (int r = 0; r < RG; ++r) base[r] = at(min(i0 + 16 * r + row, n - 1));
+    // mode: every column of the step above the diagonal of every row, below it, or any
+    auto fetch = [&](auto mode_, int64_t j0) -> Step {
+        constexpr int mode = decltype(mode_)::value;
+        Step f;
+#pragma unroll
+        for (int r = 0; r < RG; ++r) {
+            const int64_t i_first = i0 + 16 * r;
+            if constexpr (mode == kAbove) {
+                const double* from = dm + base[r] + j0 + 4 * grp;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) f.a[r][t] = from[t];
+            } else if constexpr (mode == kBelow) {
+                const double* from = dm + at(j0 + 4 * grp) + min(i_first + row, n - 1);
+                const int64_t step = n - 2 - (j0 + 4 * grp);     // at(j + 1) - at(j), one less each time
+#pragma unroll
+                for (int t = 0; t < 4; ++t) f.a[r][t] = from[t * step - t * (t - 1) / 2];
+            } else {
+                const int64_t i = i_first + row;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int64_t j = j0 + 4 * grp + t;
+                    f.a[r][t] = i < n && j < n && i != j ? dm[i < j ? at(i) + j : at(j) + i] : 0.0;
+                }
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int64_t j = j0 + 4 * grp + t, jc = mode == kAny ? min(j, n - 1) : j;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const double x = X[jc * cols + min(16 * b + row, cols - 1)];
+                f.x[b][t] = mode != kAny || j < n ? x : 0.0;
+            }
+        }
+        return f;
+    };
+    bool col[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) col[b] = 16 * b + row < cols;
+    auto use = [&](const Step& g) {   // (nothing reads a loaded value before this)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < RG; ++r) {
+                const double a = 0.0 - 0.5 * g.a[r][t] * g.a[r][t];   // +0 where the distance is absent
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+                    acc[r][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, col[b] ? g.x[b][t] : 0.0, acc[r][b], 0, 0, 0);
+            }
+    };
+    auto run = [&](auto mode_, int64_t lo, int64_t hi) {
+        for (int64_t j0 = lo; j0 < hi; j0 += 16) use(fetch(mode_, j0));
+    };
+    const int64_t d_lo = min(max(i0, j_lo), j_hi);
+    run(std::integral_constant<int, kBelow>{}, j_lo, d_lo);
+    for (int64_t j0 = d_lo; j0 < min(i0 + kRB, j_hi); j0 += 16) use(fetch(std::integral_constant<int, kAny>{}, j0));
+    const int64_t u_lo = max(j_lo, i0 + kRB), u_hi = min(j_hi, n / 16 * 16);
+    run(std::integral_constant<int, kAbove>{}, u_lo, u_hi);
+    for (int64_t j0 = max(u_lo, u_hi); j0 < j_hi; j0 += 16) use(fetch(std::integral_constant<int, kAny>{}, j0));
+    for (int w = 0; w < kAxWaves; ++w) {
+        if (wave == w) {
+#pragma unroll
+            for (int r = 0; r < RG; ++r)
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        double& to = red[16 * r + grp + 4 * q][16 * b + row];
+                        to = w == 0 ? acc[r][b][q] : to + acc[r][b][q];
+                    }
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < kRB * cols; e += 64 * kAxWaves) {
+        const int64_t i = i0 + e / cols;
+        if (i < n) P[(int64_t(blockIdx.y) * n + i) * cols + e % cols] = red[e / cols][e % cols];
+    }
+}
+
+hipError_t launch_ax(hipStream_t s, const double* dm, int64_t n, const double* X, int cols, int64_t nblk,
+                     const double* rmean, double* P, double* sums) {
+    const dim3 g{unsigned(nblk + (rmean ? (cols + kSegs - 1) / kSegs : 0)), unsigned(kSegs)};
+    const dim3 t{64 * kAxWaves};
+    if (cols <= 16) hipLaunchKernelGGL(k_ax<1>, g, t, 0, s, dm, n, X, cols, nblk, rmean, P, sums);
+    else if (cols <= 32) hipLaunchKernelGGL(k_ax<2>, g, t, 0, s, dm, n, X, cols, nblk, rmean, P, sums);
+    else if (cols <= kMaxCols) hipLaunchKernelGGL(k_ax<3>, g, t, 0, s, dm, n, X, cols, nblk, rmean, P, sums);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+// r_i = (sum_seg P[seg][i]) / n (one column of ones)
+__global__ __launch_bounds__(256) void k_row_means(const double* __restrict__ P, int64_t n,
+                                                   double* __restrict__ r) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    double v = 0.0;
+    for (int s = 0; s < kSegs; ++s) v += P[s * n + i];
+    r[i] = v / double(n);
+}
+
+__global__ __launch_bounds__(256) void k_fill(double* __restrict__ p, int64_t n, double v) {
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < n) p[i] = v;
+}
+
+// Rows of a Gram block: 64-row tiles, at most kMaxGramBlocks blocks.
+constexpr int kGT = 64;
+constexpr int64_t kMaxGramBlocks = 128;
+inline int64_t gram_rows(int64_t n) {
+    const int64_t tiles = (n + kGT - 1) / kGT;
+    return (tiles + kMaxGramBlocks - 1) / kMaxGramBlocks * kGT;
+}
+inline int64_t gram_blocks(int64_t n) { return (n + gram_rows(n) - 1) / gram_rows(n); }
+
+// Gram entries of one tile in LDS (A^T B over its rows), added to the thread's; entry
+// tid + 256 u of the c x c matrix
+constexpr int kGE = (kMaxCols * kMaxCols + 255) / 256;
+__device__ __forceinline__ void gram_tile(const double (*A)[kMaxCols + 1], const double (*B)[kMaxCols + 1],
+                                          int c, double* g) {
+#pragma unroll
+    for (int u = 0; u < kGE; ++u) {
+        const int e = threadIdx.x + 256 * u;
+        if (e >= c * c) break;
+        const int x = e / c, y = e % c;
+        double v = g[u];
+#pragma unroll 8
+        for (int r = 0; r < kGT; ++r) v = fma(A[r][x], B[r][y], v);
+        g[u] = v;
+    }
+}
+
+// Y = sum_seg P[seg] - r (1^T X) - 1 (r^T X) + g 1 (1^T X), and the block's part of
+// L^T Y (L null: Y^T Y) to Gp[block]
+__global__ __launch_bounds__(256) void k_centre(const double* __restrict__ P, int64_t n, int c,
                                                 const double* __restrict__ rmean,
                                                 const double* __restrict__ gmean,
-                                                const double* __restrict__ sums,
-                                                double* __restrict__ Y) {
-    const int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (e >= n * cols) return;
-    const int64_t i = e / cols;
-    const int c = int(e % cols);
+                                                const double* __restrict__ sums, int64_t rows,
+                                                const double* __restrict__ L, double* __restrict__ Y,
+                                                double* __restrict__ Gp) {
+    __shared__ double ty[kGT][kMaxCols + 1], tl[kGT][kMaxCols + 1];
+    const int64_t r0 = int64_t(blockIdx.x) * rows, r1 = min(n, r0 + rows);
+    const double gm = gmean[0];
+    double g[kGE];
+#pragma unroll
+    for (int u = 0; u < kGE; ++u) g[u] = 0.0;
+    for (int64_t t0 = r0; t0 < r1; t0 += kGT) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < kGT * c; e += 256) {
+            const int r = e / c, k = e % c;
+            const int64_t i = t0 + r;
+            double y = 0.0, l = 0.0;
+            if (i < r1) {
+                double p[kSegs];
+#pragma unroll
+                for (int s = 0; s < kSegs; ++s) p[s] = P[(s * n + i) * c + k];
+                double v = 0.0;
+#pragma unroll
+                for (int s = 0; s < kSegs; ++s) v += p[s];
+                y = v - rmean[i] * sums[k] - sums[c + k] + gm * sums[k];
+                if (L) l = L[i * c + k];
+                Y[i * c + k] = y;
+            }
+            ty[r][k] = y;
+            if (L) tl[r][k] = l;
+        }
+        __syncthreads();
+        gram_tile(L ? tl : ty, ty, c, g);
+    }
+#pragma unroll
+    for (int u = 0; u < kGE; ++u)
+        if (threadIdx.x + 256 * u < c * c) Gp[int64_t(blockIdx.x) * c * c + threadIdx.x + 256 * u] = g[u];
+}
+
+// Q = Y M (M c x c), and the block's part of Q^T Q to Gp[block] (Gp null: none)
+__global__ __launch_bounds__(256) void k_basis(const double* __restrict__ Y, int64_t n, int c,
+                                               const double* __restrict__ M, int64_t rows,
+                                               double* __restrict__ Q, double* __restrict__ Gp) {
+    __shared__ double ty[kGT][kMaxCols + 1], tq[kGT][kMaxCols + 1], m[kMaxCols][kMaxCols + 1];
+    const int64_t r0 = int64_t(blockIdx.x) * rows, r1 = min(n, r0 + rows);
+    for (int e = threadIdx.x; e < c * c; e += 256) m[e / c][e % c] = M[e];
+    double g[kGE];
+#pragma unroll
+    for (int u = 0; u < kGE; ++u) g[u] = 0.0;
+    for (int64_t t0 = r0; t0 < r1; t0 += kGT) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < kGT * c; e += 256)
+            ty[e / c][e % c] = t0 + e / c < r1 ? Y[t0 * c + e] : 0.0;
+        __syncthreads();
+        for (int e = threadIdx.x; e < kGT * c; e += 256) {
+            const int r = e / c, k = e % c;
+            double v = 0.0;
+            for (int t = 0; t < c; ++t) v = fma(ty[r][t], m[t][k], v);
+            tq[r][k] = v;
+            if (t0 + r < r1) Q[t0 * c + e] = v;
+        }
+        if (!Gp) continue;
+        __syncthreads();
+        gram_tile(tq, tq, c, g);
+    }
+    if (!Gp) return;
+#pragma unroll
+    for (int u = 0; u < kGE; ++u)
+        if (threadIdx.x + 256 * u < c * c) Gp[int64_t(blockIdx.x) * c * c + threadIdx.x + 256 * u] = g[u];
+}
+
+// entry e of the sum of the c x c parts [b, e_b), in order
+__device__ __forceinline__ double sum_parts(const double* __restrict__ Gp, int64_t b, int64_t b_end, int cc,
+                                            int e) {
     double v = 0.0;
-    for (int s = 0; s < kSegs; ++s) v += P[s * n * cols + e];
-    const double g = gmean[0];
-    Y[e] = v - rmean[i] * sums[c] - sums[cols + c] + g * sums[c];
+    for (; b < b_end; b += 16) {
+        double p[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) p[u] = Gp[min<int64_t>(b + u, b_end - 1) * cc + e];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v += b + u < b_end ? p[u] : 0.0;
+    }
+    return v;
+}
+__global__ __launch_bounds__(256) void k_sum_parts(const double* __restrict__ Gp, int64_t nb, int cc,
+                                                   double* __restrict__ T) {
+    const int e = int(blockIdx.x) * 256 + threadIdx.x;
+    if (e < cc) T[e] = sum_parts(Gp, 0, nb, cc, e);
+}
+
+// M (c x c, upper triangular) with (Y M)^T (Y M) = I but for the columns of Y that depend
+// on earlier ones, which M makes zero (kept[j] = 0, else 1): from G = Y^T Y (nb parts) by
+// Cholesky, G = R^T R, leaving out columns whose remaining norm is below a relative floor,
+// and M = R^-1.  One block; one wave factorises, lane = column.  A chain of c steps, bound
+// by their latency.  (The eigenvectors of G, found on the host, span the same space but
+// cost two synchronisations and a Jacobi iteration each time: about 100 us with 20
+// columns; this kernel 24.)
+__global__ __launch_bounds__(1024) void k_chol(const double* __restrict__ Gp, int64_t nb, int c,
+                                               double* __restrict__ M, double* __restrict__ kept) {
+    __shared__ double G[kMaxCols][kMaxCols + 1], R[kMaxCols + 4][kMaxCols + 1], X[kMaxCols + 4][kMaxCols + 1];
+    const int cc = c * c, half = cc <= 512 ? 512 : 0;   // two threads an entry where that fits
+    for (int e = threadIdx.x; e < (kMaxCols + 4) * (kMaxCols + 1); e += 1024) (&R[0][0])[e] = (&X[0][0])[e] = 0.0;
+    if (half) {
+        const int e = threadIdx.x & 511;
+        const bool second = threadIdx.x >= 512;
+        const int64_t mid = (nb + 1) / 2;
+        const double v = e < cc ? sum_parts(Gp, second ? mid : 0, second ? nb : mid, cc, e) : 0.0;
+        if (!second && e < cc) G[e / c][e % c] = v;
+        __syncthreads();
+        if (second && e < cc) G[e / c][e % c] += v;
+    } else {
+        for (int e = threadIdx.x; e < cc; e += 1024) G[e / c][e % c] = sum_parts(Gp, 0, nb, cc, e);
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        auto wave_sync = [] {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        };
+        const int j = threadIdx.x, jc = min(j, kMaxCols - 1);
+        double top = j < c ? G[j][j] : 0.0;
+        const bool finite = __all(top < HUGE_VAL);      // else (also not a number) nothing is kept
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) top = fmax(top, __shfl_xor(top, o, 64));
+        unsigned long long have = 0;
+        for (int s = 0; s < c; ++s) {
+            double v = j < c ? G[s][jc] : 0.0;
+            for (int t = 0; t < s; t += 4)              // (rows past s are still zero)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v = fma(-R[t + u][s], R[t + u][jc], v);
+            const double d = __shfl(v, s, 64);
+            if (finite && d > 1e-14 * top) {
+                have |= 1ull << s;
+                if (j >= s && j < c) R[s][j] = v / sqrt(d);
+            }
+            wave_sync();
+        }
+        // column j of R^-1 from its end, over the columns kept
+        for (int r = c - 1; r >= 0; --r) {
+            if (!(have >> r & 1)) continue;
+            double v = j == r ? 1.0 : 0.0;
+            for (int t = r + 1; t < c; t += 4)          // (rows past c are zero)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v = fma(-R[r][min(t + u, kMaxCols)], X[t + u][jc], v);
+            if (j < c && (have >> j & 1)) X[r][j] = v / R[r][r];
+        }
+        if (j < c) kept[j] = double(have >> j & 1);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < cc; e += 1024) M[e] = X[e / c][e % c];
 }
 
 // G_part[b][x][y] = sum over rows of block b (kGramRows rows) of Y[i][x] Z[i][y]
@@ -303,7 +511,7 @@ void jacobi_eig(std::vector<double> a, int m, std::vector<double>& w, std::vecto
 struct Plan {
     int64_t n = 0, nblk = 0;
     int cols = 0;
-    size_t off_p = 0, off_y = 0, off_q = 0, off_z = 0, off_sums = 0, off_gp = 0, off_m = 0,
+    size_t off_p = 0, off_y = 0, off_q = 0, off_z = 0, off_sums = 0, off_gp = 0, off_m = 0, off_t = 0,
            off_r = 0, off_g = 0, off_one = 0, total = 0;
 };
 
@@ -325,8 +533,9 @@ Plan make_plan(int64_t n, int cols) {
     p.off_q = take(off, nc);
     p.off_z = take(off, nc);
     p.off_sums = take(off, size_t(2 * cols) * 8);
-    p.off_gp = take(off, size_t((n + kGramRows - 1) / kGramRows) * cols * cols * 8);
-    p.off_m = take(off, size_t(cols) * cols * 8);
+    p.off_gp = take(off, size_t(gram_blocks(n)) * cols * cols * 8);
+    p.off_m = take(off, size_t(cols) * kMaxCols * 8);
+    p.off_t = take(off, size_t(cols * cols + cols + 1) * 8);
     p.off_r = take(off, size_t(n) * 8);
     p.off_g = take(off, 8);
     p.off_one = take(off, size_t(n) * 8);
@@ -530,8 +739,8 @@ uf_status uf_pcoa(const double* dm, int64_t n, const double* row_means, const do
     double* sums = reinterpret_cast<double*>(base + p.off_sums);
     double* Gp = reinterpret_cast<double*>(base + p.off_gp);
     double* Md = reinterpret_cast<double*>(base + p.off_m);
-    const int64_t nbg = (n + kGramRows - 1) / kGramRows;
-    const dim3 gax{unsigned(p.nblk), unsigned(kSegs)};
+    double* Td = reinterpret_cast<double*>(base + p.off_t);   // Q^T B Q, columns kept (1 or 0), mean of A
+    const int64_t nbg = gram_blocks(n), rows = gram_rows(n);
 
     // row means of A and grand mean: given, or A 1 / n and its mean
     const double* rm = row_means;
@@ -540,90 +749,34 @@ uf_status uf_pcoa(const double* dm, int64_t n, const double* row_means, const do
         double* r = reinterpret_cast<double*>(base + p.off_r);
         double* g = reinterpret_cast<double*>(base + p.off_g);
         double* one = reinterpret_cast<double*>(base + p.off_one);
-        std::vector<double> h1(static_cast<size_t>(n), 1.0);
-        UFQ_HIP(hipMemcpyAsync(one, h1.data(), size_t(n) * 8, hipMemcpyHostToDevice, s));
-        UFQ_HIP(launch_ax(gax, s, dm, n, one, 1, p.nblk, P));
-        // r = (sum_seg P) / n via k_centre with zero means: reuse Y as scratch
-        UFQ_HIP(hipMemsetAsync(sums, 0, size_t(2 * cols) * 8, s));
-        UFQ_HIP(hipMemsetAsync(g, 0, 8, s));
-        UFQ_HIP(hipMemsetAsync(Y, 0, size_t(n) * 8, s));
-        hipLaunchKernelGGL(k_centre, dim3(unsigned((n + 255) / 256)), dim3(256), 0, s, P, n, 1, Y, g,
-                           sums, r);
+        const dim3 gn{unsigned((n + 255) / 256)};
+        hipLaunchKernelGGL(k_fill, gn, dim3(256), 0, s, one, n, 1.0);
         UFQ_HIP(hipGetLastError());
-        std::vector<double> hr(static_cast<size_t>(n));
-        UFQ_HIP(hipMemcpyAsync(hr.data(), r, size_t(n) * 8, hipMemcpyDeviceToHost, s));
-        UFQ_HIP(hipStreamSynchronize(s));
-        double tot = 0.0;
-        for (int64_t i = 0; i < n; ++i) {
-            hr[size_t(i)] /= double(n);
-            tot += hr[size_t(i)];
-        }
-        const double hg = tot / double(n);
-        UFQ_HIP(hipMemcpyAsync(r, hr.data(), size_t(n) * 8, hipMemcpyHostToDevice, s));
-        UFQ_HIP(hipMemcpyAsync(g, &hg, 8, hipMemcpyHostToDevice, s));
-        UFQ_HIP(hipStreamSynchronize(s));   // host sources go out of scope
+        UFQ_HIP(launch_ax(s, dm, n, one, 1, p.nblk, nullptr, P, sums));
+        hipLaunchKernelGGL(k_row_means, gn, dim3(256), 0, s, P, n, r);
+        UFQ_HIP(hipGetLastError());
+        UFQ_HIP(ufk::grand_mean(r, n, g, s));
         rm = r;
         gm = g;
     }
 
-    // X (n x c) -> B X into out
-    auto bx = [&](const double* X, int c, double* out) -> uf_status {
-        UFQ_HIP(launch_ax(gax, s, dm, n, X, c, p.nblk, P));
-        hipLaunchKernelGGL(k_colsums, dim3(unsigned(c)), dim3(256), 0, s, X, c, n, rm, sums);
-        UFQ_HIP(hipGetLastError());
-        hipLaunchKernelGGL(k_centre, dim3(unsigned((n * c + 255) / 256)), dim3(256), 0, s, P, n, c, rm,
-                           gm, sums, out);
+    // B X (n x cols) into out, and the parts of L^T out (L null: out^T out)
+    auto bx = [&](const double* X, const double* L, double* out) -> uf_status {
+        UFQ_HIP(launch_ax(s, dm, n, X, cols, p.nblk, rm, P, sums));
+        hipLaunchKernelGGL(k_centre, dim3(unsigned(nbg)), dim3(256), 0, s, P, n, cols, rm, gm, sums, rows, L,
+                           out, Gp);
         UFQ_HIP(hipGetLastError());
         return UF_OK;
     };
-    // host copy of the fixed-order sum of Y^T Z (cy x cz)
-    auto gram = [&](const double* A, int ca, const double* B, int cb, std::vector<double>& G) -> uf_status {
-        hipLaunchKernelGGL(k_gram, dim3(unsigned(nbg)), dim3(256), 0, s, A, ca, B, cb, n, Gp);
+    // out = the columns of Yin (whose Gram parts are in Gp) made orthonormal; again: leave
+    // the Gram parts of out in Gp
+    auto orth = [&](const double* Yin, double* out, bool again) -> uf_status {
+        hipLaunchKernelGGL(k_chol, dim3(1), dim3(1024), 0, s, Gp, nbg, cols, Md, Td + cols * cols);
         UFQ_HIP(hipGetLastError());
-        std::vector<double> part(size_t(nbg) * ca * cb);
-        UFQ_HIP(hipMemcpyAsync(part.data(), Gp, part.size() * 8, hipMemcpyDeviceToHost, s));
-        UFQ_HIP(hipStreamSynchronize(s));
-        G.assign(size_t(ca) * cb, 0.0);
-        for (int64_t b = 0; b < nbg; ++b)
-            for (size_t e = 0; e < G.size(); ++e) G[e] += part[size_t(b) * G.size() + e];
-        return UF_OK;
-    };
-    // SVQB: out = Yin U S^{-1/2} over the directions of Yin above the floor; returns
-    // the number of columns kept
-    auto svqb = [&](const double* Yin, int c, double* out, int* kept) -> uf_status {
-        std::vector<double> G, w, v;
-        uf_status e = gram(Yin, c, Yin, c, G);
-        if (e != UF_OK) return e;
-        jacobi_eig(G, c, w, v);
-        std::vector<int> order(static_cast<size_t>(c));
-        std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return w[a] > w[b]; });
-        const double top = c > 0 ? w[size_t(order[0])] : 0.0;
-        int k = 0;
-        while (k < c && top > 0.0 && w[size_t(order[size_t(k)])] > 1e-14 * top) ++k;
-        std::vector<double> M(size_t(c) * std::max(k, 1), 0.0);
-        for (int j = 0; j < k; ++j) {
-            const int o = order[size_t(j)];
-            const double sc = 1.0 / std::sqrt(w[size_t(o)]);
-            for (int r = 0; r < c; ++r) M[size_t(r) * k + j] = v[size_t(r) * c + o] * sc;
-        }
-        *kept = k;
-        if (k == 0) return UF_OK;
-        UFQ_HIP(hipMemcpyAsync(Md, M.data(), M.size() * 8, hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(k_rightmul, dim3(unsigned((n * k + 255) / 256)), dim3(256), 0, s, Yin, c, n,
-                           Md, k, out);
+        hipLaunchKernelGGL(k_basis, dim3(unsigned(nbg)), dim3(256), 0, s, Yin, n, cols, Md, rows, out,
+                           again ? Gp : nullptr);
         UFQ_HIP(hipGetLastError());
-        UFQ_HIP(hipStreamSynchronize(s));   // M is reused by the next call
         return UF_OK;
-    };
-    auto orth = [&](double* Yin, int c, double* out, int* kept) -> uf_status {
-        int k1 = 0;
-        uf_status e = svqb(Yin, c, Z, &k1);   // Z as scratch
-        if (e != UF_OK || k1 == 0) {
-            *kept = k1;
-            return e;
-        }
-        return svqb(Z, k1, out, kept);
     };
 
     // Omega is n x l0; a narrower basis (l0 > n) keeps its first `cols` columns
@@ -638,30 +791,34 @@ uf_status uf_pcoa(const double* dm, int64_t n, const double* row_means, const do
         UFQ_HIP(hipStreamSynchronize(s));   // hs goes out of scope
         Om = Q;
     }
-    st = bx(Om, cols, Y);
-    if (st != UF_OK) return st;
-    int k = 0;
-    st = orth(Y, cols, Q, &k);
-    if (st != UF_OK) return st;
-    for (int it = 0; it < power_iters && k > 0; ++it) {
-        st = bx(Q, k, Y);
+    // Columns that a rank-deficient basis lacks are zero, and stay so.
+    st = bx(Om, nullptr, Y);
+    for (int it = 0; st == UF_OK; ++it) {
+        st = orth(Y, Z, true);
+        if (st == UF_OK) st = orth(Z, Q, false);
         if (st != UF_OK) return st;
-        st = orth(Y, k, Q, &k);
-        if (st != UF_OK) return st;
+        st = bx(Q, it < power_iters ? nullptr : Q, Y);
+        if (it == power_iters) break;
     }
+    if (st != UF_OK) return st;
+    hipLaunchKernelGGL(k_sum_parts, dim3(unsigned((cols * cols + 255) / 256)), dim3(256), 0, s, Gp, nbg,
+                       cols * cols, Td);
+    UFQ_HIP(hipGetLastError());
+    UFQ_HIP(hipMemcpyAsync(Td + cols * cols + cols, gm, 8, hipMemcpyDeviceToDevice, s));
+    std::vector<double> ht(size_t(cols) * cols + cols + 1);
+    UFQ_HIP(hipMemcpyAsync(ht.data(), Td, ht.size() * 8, hipMemcpyDeviceToHost, s));
+    UFQ_HIP(hipStreamSynchronize(s));
+    std::vector<int> have;   // columns of the basis
+    for (int j = 0; j < cols; ++j)
+        if (ht[size_t(cols) * cols + j] != 0.0) have.push_back(j);
+    const int k = int(have.size());
     std::vector<double> lam(size_t(dims), 0.0);
-    std::vector<double> W(size_t(std::max(k, 1)) * dims, 0.0);   // k x dims, scaled
     if (k > 0) {
-        st = bx(Q, k, Y);   // Y = B Q
-        if (st != UF_OK) return st;
-        std::vector<double> T, w, v;
-        st = gram(Q, k, Y, k, T);
-        if (st != UF_OK) return st;
+        std::vector<double> W(size_t(cols) * dims, 0.0);   // cols x dims, scaled
+        std::vector<double> T(size_t(k) * k), w, v;
         for (int a = 0; a < k; ++a)
-            for (int b = a + 1; b < k; ++b) {
-                const double m = 0.5 * (T[size_t(a) * k + b] + T[size_t(b) * k + a]);
-                T[size_t(a) * k + b] = T[size_t(b) * k + a] = m;
-            }
+            for (int b = 0; b < k; ++b)
+                T[size_t(a) * k + b] = 0.5 * (ht[size_t(have[a]) * cols + have[b]] + ht[size_t(have[b]) * cols + have[a]]);
         jacobi_eig(T, k, w, v);
         std::vector<int> order(static_cast<size_t>(k));
         std::iota(order.begin(), order.end(), 0);
@@ -670,10 +827,10 @@ uf_status uf_pcoa(const double* dm, int64_t n, const double* row_means, const do
             const int o = order[size_t(j)];
             lam[size_t(j)] = w[size_t(o)];
             const double sc = std::sqrt(std::max(w[size_t(o)], 0.0));
-            for (int r = 0; r < k; ++r) W[size_t(r) * dims + j] = v[size_t(r) * k + o] * sc;
+            for (int r = 0; r < k; ++r) W[size_t(have[r]) * dims + j] = v[size_t(r) * k + o] * sc;
         }
         UFQ_HIP(hipMemcpyAsync(Md, W.data(), W.size() * 8, hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(k_rightmul, dim3(unsigned((n * dims + 255) / 256)), dim3(256), 0, s, Q, k, n,
+        hipLaunchKernelGGL(k_rightmul, dim3(unsigned((n * dims + 255) / 256)), dim3(256), 0, s, Q, cols, n,
                            Md, int(dims), coords);
         UFQ_HIP(hipGetLastError());
         hipLaunchKernelGGL(k_signs, dim3(unsigned(dims)), dim3(256), 0, s, coords, int(dims), n);
@@ -681,15 +838,10 @@ uf_status uf_pcoa(const double* dm, int64_t n, const double* row_means, const do
         UFQ_HIP(hipStreamSynchronize(s));   // W goes out of scope
     } else {
         UFQ_HIP(hipMemsetAsync(coords, 0, size_t(n) * dims * 8, s));
+        UFQ_HIP(hipStreamSynchronize(s));
     }
     std::memcpy(eigvals, lam.data(), size_t(dims) * 8);
-    if (trace) {
-        double hg = 0.0;
-        UFQ_HIP(hipMemcpyAsync(&hg, gm, 8, hipMemcpyDeviceToHost, s));
-        UFQ_HIP(hipStreamSynchronize(s));
-        *trace = -double(n) * hg;
-    }
-    UFQ_HIP(hipStreamSynchronize(s));
+    if (trace) *trace = -double(n) * ht[size_t(cols) * cols + cols];
     return UF_OK;
 }
 
