@@ -39,9 +39,102 @@ __device__ __forceinline__ void for_each_branch(const ufp::Emb& e, int64_t entry
     const int32_t r = e.rank[entry];
     const int32_t prev = entry > row_start ? e.rank[entry - 1] : -1;
     int32_t v = e.tip_pos[r];
-    while (v < e.root_pos && e.lo[v] > prev) {
+    int4 nd = e.nodes[v];
+    while (v < e.root_pos && nd.x > prev) {
+        const int4 up = e.nodes[nd.z];
         f(v);
-        v = e.parent_pos[v];
+        v = nd.z;
+        nd = up;
+    }
+}
+
+// A sample's row (tip ranks, exclusive prefix of the counts) in LDS.  Rows of up to
+// kRowCap entries are staged there: the walks below search them at every branch, and
+// from memory each probe of a search was a round trip of its own.
+constexpr int kRowCap = 1024;
+struct RowLds {
+    int64_t cum[kRowCap + 1];
+    int32_t rank[kRowCap];
+};
+__device__ __forceinline__ bool row_stage(const ufp::Emb& e, int64_t s, int64_t a, int64_t b, RowLds& L) {
+    if (b - a > kRowCap) return false;
+    const int m = int(b - a);
+    for (int t = threadIdx.x; t <= m; t += blockDim.x) {
+        L.cum[t] = e.cum[a + s + t];
+        if (t < m) L.rank[t] = e.rank[a + t];
+    }
+    return true;
+}
+
+// The same branches with the sample's exact count on each where asked for: f(v, record,
+// count()).  The sample's entries under a branch v of a walk are [entry, p2): none before
+// lies under v (v does not cover the previous tip), and p2, the first entry at rank >=
+// hi_v, only moves forward as the walk climbs, mostly by little, so it is searched for in
+// steps of 1, 2, 4, ...  The parent's record is loaded while the branch is worked on.
+// nodes: lo, hi, parent and a field of the caller's per position (one line a step).  LDS:
+// the row is in L.
+template <bool LDS, typename F>
+__device__ __forceinline__ void for_each_counted_branch(const ufp::Emb& e, const int4* __restrict__ nodes,
+                                                        const RowLds& L, int64_t s, int64_t a, int64_t b,
+                                                        int entry, F&& f) {
+    const int m = int(b - a);
+    const int32_t* __restrict__ gr = e.rank + a;
+    const int64_t* __restrict__ gc = e.cum + a + s;
+    auto rank = [&](int t) -> int32_t {
+        if constexpr (LDS) return L.rank[t];
+        else return gr[t];
+    };
+    auto cum = [&](int t) -> int64_t {
+        if constexpr (LDS) return L.cum[t];
+        else return gc[t];
+    };
+    const int32_t prev = entry > 0 ? rank(entry - 1) : -1;
+    int32_t v = e.tip_pos[rank(entry)];
+    if (v >= e.root_pos) return;
+    int4 nd = nodes[v];
+    int p2 = entry + 1;
+    while (nd.x > prev) {
+        const int4 up = nodes[min(nd.z, e.root_pos - 1)];
+        f(v, nd, [&]() -> int64_t {
+            const int32_t hi = nd.y;
+            if (p2 < m && rank(p2) < hi) {
+                int from = p2 + 1, to = m;
+                for (int w = 1;; w *= 2) {
+                    const int t = from + w - 1;
+                    if (t >= m) break;
+                    if (rank(t) >= hi) {
+                        to = t;
+                        break;
+                    }
+                    from = t + 1;
+                }
+                while (from < to) {
+                    const int mid = (from + to) >> 1;
+                    if (rank(mid) < hi) from = mid + 1;
+                    else to = mid;
+                }
+                p2 = from;
+            }
+            return cum(p2) - cum(entry);
+        });
+        v = nd.z;
+        if (v >= e.root_pos) break;
+        nd = up;
+    }
+}
+
+// f over the walks of all entries of the row, by the block's threads.
+template <typename F>
+__device__ __forceinline__ void for_each_counted_row_branch(const ufp::Emb& e, const int4* __restrict__ nodes,
+                                                            RowLds& L, int64_t s, F&& f) {
+    const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
+    const bool staged = row_stage(e, s, a, b, L);
+    __syncthreads();
+    const int m = int(b - a), step = int(blockDim.x);
+    if (staged) {
+        for (int t = threadIdx.x; t < m; t += step) for_each_counted_branch<true>(e, nodes, L, s, a, b, t, f);
+    } else {
+        for (int t = threadIdx.x; t < m; t += step) for_each_counted_branch<false>(e, nodes, L, s, a, b, t, f);
     }
 }
 

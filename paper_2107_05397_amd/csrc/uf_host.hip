@@ -191,6 +191,7 @@ ufp::Emb emb_view(const uf_embedding& e) {
     v.hi = e.hi;
     v.len = e.len;
     v.parent_pos = e.parent_pos;
+    v.nodes = e.nodes;
     v.tip_pos = e.tip_pos;
     v.root_pos = int32_t(e.nb);
     return v;
@@ -1168,6 +1169,7 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         const size_t o_wu32 = c.take(size_t(std::max<int64_t>(n, 1)) * 8);
         const size_t o_wub = c.take(size_t(std::max<int64_t>(n, 1)) * 8);
         const size_t o_ppos = c.take(size_t(m) * 4);
+        const size_t o_nodes = c.take(size_t(m) * 16);
         const size_t o_tpos = c.take(size_t(std::max<int64_t>(t->n_tips, 1)) * 4);
         const size_t o_d64 = c.take(size_t(m) * 8);
         const size_t o_d32 = c.take(size_t(m) * 8);
@@ -1202,6 +1204,7 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         int32_t* ppos = reinterpret_cast<int32_t*>(b + o_ppos);
         int32_t* tpos = reinterpret_cast<int32_t*>(b + o_tpos);
         e->parent_pos = ppos;
+        e->nodes = reinterpret_cast<int4*>(b + o_nodes);
         e->tip_pos = tpos;
         // first position of each position's subtree: its leftmost tip's
         e->sub_first.resize(size_t(nb));
@@ -1239,6 +1242,8 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         if (rc == hipSuccess) rc = H2D(dd32, d32.data(), size_t(m) * 8);
         if (rc == hipSuccess) rc = H2D(ddbf, dbf.data(), size_t(m) * 8);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "upload of the embedding inputs"));
+        rc = ufk::pack_nodes(*e, s);
+        if (rc != hipSuccess) return cleanup(hip_fail(rc, "node record kernel launch"));
         if (n > 0) {
             rc = ufk::sample_scalars(*e, ppos, tpos, dd64, dd32, ddbf, s);
             if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel launch"));

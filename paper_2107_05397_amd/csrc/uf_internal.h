@@ -134,6 +134,7 @@ struct uf_embedding {
     SplitScratch split_tmp;
     std::mutex split_mu;
     int32_t* parent_pos = nullptr;  // [nb+1], -1 for the root
+    int4* nodes = nullptr;          // [nb+1] lo, hi, parent_pos, 0
     int32_t* tip_pos = nullptr;     // [n_tips] position of the tip with rank r
     std::vector<int32_t> sub_first; // host, [nb]: first position of each position's subtree
     // root distances by position for the three length roundings (per-sample scalars)
@@ -191,6 +192,7 @@ constexpr int kGramK = 128;        // K step of the MFMA Gram kernel
 constexpr int kGramKPad = 256;    // K of its presence matrix is padded to this (steps go in pairs)
 
 // Per-sample scalars from the postorder leaf intervals (one wave per sample).
+hipError_t pack_nodes(const uf_embedding& e, hipStream_t st);   // fills e.nodes
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos,
                           const int32_t* tip_pos, const double* d64, const double* d32,
                           const double* dbf, hipStream_t st);

@@ -888,6 +888,15 @@ __global__ __launch_bounds__(256) void k_grand_mean(const double* __restrict__ r
     if (threadIdx.x == 0) out[0] = red[0] / double(n);
 }
 
+// One 16-byte record a position, so that a step of a walk up the tree touches one line.
+__global__ __launch_bounds__(256) void k_pack_nodes(const int32_t* __restrict__ lo,
+                                                    const int32_t* __restrict__ hi,
+                                                    const int32_t* __restrict__ parent, int64_t m,
+                                                    int4* __restrict__ nodes) {
+    const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (v < m) nodes[v] = make_int4(lo[v], hi[v], parent[v], 0);
+}
+
 __global__ void k_zero_u32(unsigned* __restrict__ p, int64_t n) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
@@ -900,6 +909,13 @@ inline unsigned grid_y(int64_t v) { return unsigned(v < 65535 ? (v < 1 ? 1 : v) 
 // ============================================================================
 // launchers
 // ============================================================================
+hipError_t pack_nodes(const uf_embedding& e, hipStream_t st) {
+    const int64_t m = e.nb + 1;
+    hipLaunchKernelGGL(k_pack_nodes, dim3(unsigned((m + 255) / 256)), dim3(256), 0, st, e.lo, e.hi,
+                       e.parent_pos, m, e.nodes);
+    return hipGetLastError();
+}
+
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos, const int32_t* tip_pos,
                           const double* d64, const double* d32, const double* dbf,
                           hipStream_t st) {

@@ -22,6 +22,7 @@ struct Emb {
     const int32_t* hi;
     const double* len;
     const int32_t* parent_pos;
+    const int4* nodes;       // lo, hi and parent of a position together, for the walks
     const int32_t* tip_pos;
     int32_t root_pos;
 };

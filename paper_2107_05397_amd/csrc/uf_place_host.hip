@@ -47,6 +47,7 @@ ufp::Emb view(const uf_embedding& e) {
     v.hi = e.hi;
     v.len = e.len;
     v.parent_pos = e.parent_pos;
+    v.nodes = e.nodes;
     v.tip_pos = e.tip_pos;
     v.root_pos = int32_t(e.nb);
     return v;

