@@ -825,6 +825,7 @@ namespace ufh {
 uf_status fail(uf_status st, const std::string& msg) { return ::fail(st, msg); }
 uf_status hip_fail(hipError_t e, const char* what) { return ::hip_fail(e, what); }
 uf_status check_device(int* dev_out) { return ::check_device(dev_out); }
+char* embedding_scratch(uf_embedding* e, size_t bytes, uf_status* st) { return ::split_scratch(e, bytes, st); }
 struct ProfHandle {
     ProfScope scope;
     ProfHandle(const char* name, hipStream_t s) : scope(name, s) {}
@@ -1037,6 +1038,7 @@ uf_status uf_tree_load(int64_t m, const int64_t* parent, const double* length, u
         }
         t->n_tips = tips_before[m];
         length_digits(t);
+        t->node_at32.assign(t->node_at.begin(), t->node_at.end());
         *out = guard.release();
         return UF_OK;
     });

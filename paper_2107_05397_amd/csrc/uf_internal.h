@@ -26,6 +26,7 @@ struct uf_tree {
     int64_t n_nodes = 0;
     int64_t n_tips = 0;
     std::vector<int64_t> node_at;     // node id at position k
+    std::vector<int32_t> node_at32;   // the same, as uploaded by the projection
     std::vector<int64_t> pos_of;      // position of node id
     std::vector<int32_t> parent_pos;  // parent position, -1 for the root
     std::vector<double> len;          // branch length at position (root: 0)
@@ -84,8 +85,8 @@ struct SplitCache {
     }
 };
 
-// Device temporaries of a split build, kept per embedding and grown on demand so
-// that rebuilding a split does not allocate again (guarded by split_mu).
+// Device temporaries of a split build or a projection, kept per embedding and grown on
+// demand so that the next one does not allocate again (guarded by split_mu).
 struct SplitScratch {
     void* buf = nullptr;
     size_t bytes = 0;
@@ -150,6 +151,8 @@ namespace ufh {
 uf_status fail(uf_status st, const std::string& msg);
 uf_status hip_fail(hipError_t e, const char* what);
 uf_status check_device(int* dev_out);
+// The embedding's grow-only device scratch (the caller holds split_mu).
+char* embedding_scratch(uf_embedding* e, size_t bytes, uf_status* st);
 // Timing of the launches enqueued on s during the guard's lifetime, under a
 // kernel name of uf_profile_read (events recorded only while profiling is on).
 struct ProfHandle;

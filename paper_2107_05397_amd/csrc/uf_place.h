@@ -35,8 +35,11 @@ struct SparseView {
     const double* s;     // per-sample sum_v l_v u_sv
 };
 
-hipError_t project(const Emb& e, const int32_t* dims, const int8_t* signs, int per_node,
-                   int out_dim, double scale, uint16_t* out, hipStream_t st);
+// dims, signs: [n_nodes][per_node] by node id, on the device; node_at: the node id of each
+// position; entries: scratch of n_nodes * per_node.
+hipError_t project(const Emb& e, const int32_t* dims, const int8_t* signs, const int32_t* node_at,
+                   int64_t n_nodes, int per_node, int32_t* entries, int out_dim, double scale,
+                   uint16_t* out, hipStream_t st);
 // la/lb: 0 = row layout (k contiguous), 1 = column layout (row index contiguous).
 // part: device FP32 scratch of part_elems floats for split-K partial sums
 // (nullable: no split; 16-byte aligned).  Requires 16-byte aligned A and B, lda

@@ -57,13 +57,23 @@ __device__ __forceinline__ int64_t count_in(const int64_t* __restrict__ row_ptr,
     return cum[p2 + s] - cum[p1 + s];
 }
 
+// The projection's entries by position: 2 dim + (sign > 0) of each of a node's outputs.
+__global__ __launch_bounds__(256) void k_project_entries(const int32_t* __restrict__ dims,
+                                                         const int8_t* __restrict__ signs,
+                                                         const int32_t* __restrict__ node_at, int64_t m,
+                                                         int per_node, int32_t* __restrict__ entries) {
+    const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (t >= m * per_node) return;
+    const int64_t from = int64_t(node_at[t / per_node]) * per_node + t % per_node;
+    entries[t] = 2 * dims[from] + (signs[from] > 0);
+}
+
 // x[s] = sum_v l_v u_sv * sign/2 at dims: one block per sample, int64 fixed
 // point (2^-40) sums in LDS so the result does not depend on atomic order.  Bound by the
 // walks' scattered reads: 3,000 samples x 500 tips, 200,000 branches 1,285 us with a
 // search of the whole row in memory at every branch, now 713.
-__global__ __launch_bounds__(256) void k_project(Emb e, const int32_t* __restrict__ dims,
-                                                 const int8_t* __restrict__ signs, int per_node,
-                                                 int out_dim, double scale,
+__global__ __launch_bounds__(256) void k_project(Emb e, const int32_t* __restrict__ entries,
+                                                 int per_node, int out_dim, double scale,
                                                  uint16_t* __restrict__ out) {
     extern __shared__ unsigned long long acc[];
     __shared__ ufd::RowLds row;
@@ -74,8 +84,8 @@ __global__ __launch_bounds__(256) void k_project(Emb e, const int32_t* __restric
         const double y = e.len[v] * (double(count()) * inv_t) * 0.5 * scale;
         const long long q = llrint(y * 1099511627776.0);   // 2^40
         for (int j = 0; j < per_node; ++j) {
-            const long long sq = signs[int64_t(v) * per_node + j] > 0 ? q : -q;
-            atomicAdd(&acc[dims[int64_t(v) * per_node + j]], (unsigned long long)sq);
+            const int32_t en = entries[int64_t(v) * per_node + j];
+            atomicAdd(&acc[en >> 1], (unsigned long long)(en & 1 ? q : -q));
         }
     });
     __syncthreads();
@@ -1094,12 +1104,18 @@ __global__ __launch_bounds__(256) void k_gather_pairs(const V* __restrict__ c, i
 // ============================================================================
 // launchers
 // ============================================================================
-hipError_t project(const Emb& e, const int32_t* dims, const int8_t* signs, int per_node,
-                   int out_dim, double scale, uint16_t* out, hipStream_t st) {
+hipError_t project(const Emb& e, const int32_t* dims, const int8_t* signs, const int32_t* node_at,
+                   int64_t n_nodes, int per_node, int32_t* entries, int out_dim, double scale,
+                   uint16_t* out, hipStream_t st) {
     if (e.n <= 0) return hipSuccess;
+    const int64_t cnt = n_nodes * per_node;
+    hipLaunchKernelGGL(k_project_entries, dim3(unsigned((cnt + 255) / 256)), dim3(256), 0, st, dims, signs,
+                       node_at, n_nodes, per_node, entries);
+    const hipError_t er = hipGetLastError();
+    if (er != hipSuccess) return er;
     const size_t lds = size_t(out_dim) * 8;
-    hipLaunchKernelGGL(k_project, dim3(unsigned(e.n)), dim3(256), lds, st, e, dims, signs,
-                       per_node, out_dim, scale, out);
+    hipLaunchKernelGGL(k_project, dim3(unsigned(e.n)), dim3(256), lds, st, e, entries, per_node, out_dim,
+                       scale, out);
     return hipGetLastError();
 }
 
