@@ -1451,7 +1451,7 @@ struct uf_batch {
     int64_t n_tables = 0;
     std::vector<BatchTable> tabs;        // host copy
     std::vector<int64_t> acc_elems;           // per table
-    int64_t n_items = 0;
+    int64_t n_items = 0, n_wide = 0;          // of them, of wide tables (first)
     int64_t kc = 0, n_chunks = 0;
     int stage_branches = 16, wgs_per_cu = 2, tile_stripes = 128;
     int64_t n_bucket = 0;
@@ -1560,28 +1560,45 @@ const char* tune_path(const char* p) { return p ? p : std::getenv("UF_TUNE_CACHE
 
 // Work items of the batch kernel: (table, segment, block of 64 samples i, block of 64
 // samples j >= i), a table's segments one after the other so that the items running
-// together read the same branches.  Item p runs on XCD p mod 8: every table's list is
-// cut in eighths, one per XCD (table -1: none), so that each XCD reads its own part
-// and has the same work; tables with the longest segments come first.
-std::vector<int4> batch_items(const std::vector<BatchTable>& tabs) {
+// together read the same branches, and inside a segment in super-tiles of 8 x 8 blocks
+// (row by row, three tables of 4,500-9,000 samples were slower by a quarter).  Item p runs
+// on XCD p mod 8: every table's list is cut in eighths, one per XCD (table -1: none), so
+// that each XCD reads its own part and has the same work; tables with the longest
+// segments come first.  wide: the tables of ufx::kPairWideN samples and more, else the rest.
+std::vector<int4> batch_items(const std::vector<BatchTable>& tabs, bool wide) {
+    constexpr int64_t G = 8;
     std::vector<size_t> order(tabs.size());
     std::iota(order.begin(), order.end(), size_t(0));
     std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) { return tabs[x].seg > tabs[y].seg; });
     std::vector<int4> items, own;
     for (size_t r : order) {
         const BatchTable& t = tabs[r];
-        if (t.n < 2) continue;
+        if (t.n < 2 || (t.n >= ufx::kPairWideN) != wide) continue;
         const int64_t nblk = (t.n + 63) / 64;
         own.clear();
         for (int64_t g = 0; g < t.n_seg; ++g)
-            for (int64_t bi = 0; bi < nblk; ++bi)
-                for (int64_t bj = bi; bj < nblk; ++bj) own.push_back(make_int4(int(r), int(g), int(bi), int(bj)));
+            for (int64_t r0 = 0; r0 < nblk; r0 += G)
+                for (int64_t c0 = r0; c0 < nblk; c0 += G)
+                    for (int64_t bi = r0; bi < std::min(nblk, r0 + G); ++bi)
+                        for (int64_t bj = std::max(bi, c0); bj < std::min(nblk, c0 + G); ++bj)
+                            own.push_back(make_int4(int(r), int(g), int(bi), int(bj)));
         const size_t per = (own.size() + 7) / 8;
         for (size_t p = 0; p < per; ++p)
             for (size_t x = 0; x < 8; ++x)
                 items.push_back(x * per + p < own.size() ? own[x * per + p] : make_int4(-1, 0, 0, 0));
     }
     return items;
+}
+
+// The pair tiles of every table on one chunk: the wide tables (first in d_items) with 16
+// samples i a wave, as single calls take them, the others as configured.
+hipError_t batch_tiles(const uf_batch* b, const void* chunk, int64_t k0, int64_t kc, float* acc, int ks, int w,
+                       int ts, hipStream_t s) {
+    const hipError_t er = ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_wide, k0, kc, acc,
+                                           ks, w, 256, s);
+    if (er != hipSuccess) return er;
+    return ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items + b->n_wide, b->n_items - b->n_wide, k0,
+                            kc, acc, ks, w, ts, s);
 }
 
 // enqueue the whole batch on stream s (also used under graph capture)
@@ -1594,8 +1611,7 @@ uf_status batch_enqueue(uf_batch* b, float* const* outs, char* base, hipStream_t
         const int64_t kc = std::min<int64_t>(b->kc, e.nb - k0);
         UF_HIP(ufx::batch_fill(emb_view(e), b->d_tabs, b->d_tab_of, k0, kc, chunk, b->off_mask,
                                b->chunk_bytes, s));
-        UF_HIP(ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_items, k0, kc, acc,
-                                b->stage_branches, b->wgs_per_cu, b->tile_stripes, s));
+        UF_HIP(batch_tiles(b, chunk, k0, kc, acc, b->stage_branches, b->wgs_per_cu, b->tile_stripes, s));
     }
     if (b->n_chunks > 0) UF_HIP(ufx::batch_planes(b->d_tabs, b->n_tables, b->max_plane, acc, s));
     for (int64_t r = 0; r < b->n_tables; ++r) {
@@ -1770,7 +1786,10 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
             moff += nblk * kc;
             mean_n += double(t.n) / double(n_tables);
         }
-        const std::vector<int4> items = batch_items(b->tabs);
+        std::vector<int4> items = batch_items(b->tabs, true);
+        b->n_wide = int64_t(items.size());
+        const std::vector<int4> rest = batch_items(b->tabs, false);
+        items.insert(items.end(), rest.begin(), rest.end());
         b->n_items = int64_t(items.size());
         b->n_bucket = mean_n > 1 ? int64_t(std::ceil(std::log2(mean_n))) : 0;
         Carver c;
@@ -2014,8 +2033,7 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
                     double tmin = 1e300;
                     for (int rep = 0; rep < 2; ++rep) {
                         UF_HIP(hipEventRecord(e0, s));
-                        UF_HIP(ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_items, 0,
-                                                kc, acc, ks, w, ts, s));
+                        UF_HIP(batch_tiles(b, chunk, 0, kc, acc, ks, w, ts, s));
                         UF_HIP(hipEventRecord(e1, s));
                         UF_HIP(hipEventSynchronize(e1));
                         float ms = 0;

@@ -18,7 +18,8 @@ constexpr int kPairU = 8;        // branches per group of loads
 constexpr int kPairMin = 0, kPairL1 = 1;   // sum of min(x, y); sum of |x - y|
 // From here on the L1 tiles take 16 samples i per wave: their rows no longer stay in
 // the caches, and each row of samples j read serves twice the pairs (5,000 samples, 40,000
-// branches 28.2 -> 19.7 ms; 2,500: 6.5 -> 7.1; 1,500: 2.05 -> 2.37).
+// branches 28.2 -> 19.7 ms; 2,500: 6.5 -> 7.1; 1,500: 2.05 -> 2.37).  A batch runs such
+// tables in a launch of their own.
 constexpr int64_t kPairWideN = 4096;
 
 // Workspace of one chunk of kc branches of n samples: values, then masks.
