@@ -331,13 +331,16 @@ __device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict
     }
 }
 
-// kBandWgs resident workgroups.  Whole rounds of tiles are theirs one by one; the tiles
-// left over, fewer than there are workgroups, are cut along the branches into as many
-// equal shares (multiples of 4 stages), so that every workgroup ends at about the same
-// time.  The sums are integers: a tile's parts add up in any order to the same bits.
+// Whole rounds of kBandWgs tiles take a workgroup a tile, dispatched as workgroups end (so
+// that those running are neighbours, whose windows share the L2).  The tiles left over,
+// fewer than a round, are cut along the branches into kBandWgs equal shares (multiples of
+// 4 stages), taken first by as many workgroups, so that all end at about the same time.
+// The sums are integers: a tile's parts add up in any order to the same bits.
 // One workgroup per tile left CUs empty in the last (or only) round: 300 samples x 2,912
 // branches 1,030 -> 109 us, 1,000 x 3,838 1.36 -> 0.67 ms, 3,333 x 6,849 2.44 -> 1.68,
-// 10,000 x 14,873 27.5 -> 25.4.  On touched-branch pair tiles (min and add) these took
+// 10,000 x 14,873 27.5 -> 23.7; 30,000 samples, 200,000 tips 209 -> 198 (resident
+// workgroups that took whole tiles in a fixed order: 25.4, and 603 ms instead of 562 at
+// 50,000 samples).  On touched-branch pair tiles (min and add) these took
 // 2.2 (3,333) and 56 ms: most of a split's dense branches are touched in every tile.
 __global__ __launch_bounds__(256, 2) void k_band(const uint32_t* __restrict__ E, int64_t kc, int64_t n,
                                               int64_t sb, int64_t se, int64_t n_iblk, int first,
@@ -346,22 +349,22 @@ __global__ __launch_bounds__(256, 2) void k_band(const uint32_t* __restrict__ E,
     const int64_t n_sblk = (se - sb + kBandTS - 1) / kBandTS;
     const int64_t n_tiles = n_iblk * n_sblk, whole = n_tiles / kBandWgs * kBandWgs;
     const int64_t stages = (kc + kBandKS - 1) / kBandKS, work = (n_tiles - whole) * stages;
+    const int64_t shares = n_tiles > whole ? kBandWgs : 0;      // (a multiple of 8: XCDs as below)
+    const bool share = int64_t(blockIdx.x) < shares;
     const int64_t rank = int64_t(blockIdx.x & 7) * (kBandWgs / 8) + (blockIdx.x >> 3);
-    const int64_t end = rank + 1 == kBandWgs ? work : ((rank + 1) * work / kBandWgs) & ~int64_t(3);
-    int64_t w = (rank * work / kBandWgs) & ~int64_t(3), l = blockIdx.x;
-    for (;;) {
+    int64_t w = share ? (rank * work / kBandWgs) & ~int64_t(3) : 0;
+    const int64_t end = !share ? 1 : rank + 1 == kBandWgs ? work : ((rank + 1) * work / kBandWgs) & ~int64_t(3);
+    while (w < end) {
         int64_t t, ka = 0, kb = kc;
-        if (w < end) {                           // a part of a tile
+        if (share) {                             // a part of a tile
             const int64_t g = w % stages, cnt = min(stages - g, end - w);
             t = whole + w / stages;
             ka = g * kBandKS;
             kb = min(kc, (g + cnt) * kBandKS);
             w += cnt;
-        } else if (l < whole) {
-            t = xcd_tile(l, whole);
-            l += kBandWgs;
         } else {
-            break;
+            t = xcd_tile(int64_t(blockIdx.x) - shares, whole);
+            w = end;
         }
         int64_t ib = 0, sblk = 0;
         band_patch_tile(t, n_iblk, n_sblk, &ib, &sblk);
@@ -943,12 +946,14 @@ hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_
     if (se <= sb || n <= 0) return hipSuccess;
     const int64_t n_iblk = (n + kBandI - 1) / kBandI;
     const int64_t n_tiles = n_iblk * ((se - sb + kBandTS - 1) / kBandTS);
-    if (n_tiles > 0x7fffffff) return hipErrorInvalidValue;
+    if (n_tiles > 0x7ffff000) return hipErrorInvalidValue;
     if (first && n_tiles % kBandWgs) {   // the tiles cut in parts add to it
         const hipError_t er = zero_u32(acc, (se - sb) * n, st);
         if (er != hipSuccess) return er;
     }
-    hipLaunchKernelGGL(k_band, dim3(kBandWgs), dim3(256), 0, st, E, kc, n, sb, se, n_iblk, first, acc);
+    const int64_t whole = n_tiles / kBandWgs * kBandWgs;
+    const unsigned blocks = unsigned(whole + (n_tiles > whole ? kBandWgs : 0));
+    hipLaunchKernelGGL(k_band, dim3(blocks), dim3(256), 0, st, E, kc, n, sb, se, n_iblk, first, acc);
     return hipGetLastError();
 }
 
