@@ -48,7 +48,8 @@ PEAK_HBM = 8.0e12
 
 # the distance kernels, and the host code whose split cost model fixes how much
 # work each of their launches does
-KERNEL_SOURCES = ("uf_kernels.hip", "uf_split.hip", "uf_device.h", "uf_internal.h", "uf_host.hip")
+KERNEL_SOURCES = ("uf_kernels.hip", "uf_split.hip", "uf_pairs.hip", "uf_pairs.h", "uf_bits.hip",
+                  "uf_bits.h", "uf_device.h", "uf_internal.h", "uf_host.hip")
 
 
 def kernel_source_hash() -> str:
@@ -250,10 +251,11 @@ def bench_batch(args) -> int:
                    "updates_per_step": U, "parallelism": "single-gpu"},
         "roofline": {"bound": "alu", "achieved": slots / 1e12,
                      "peak": PEAK_VALU_SLOTS["fp32"] / 1e12, "unit": "Tops/s",
-                     "frac": slots / PEAK_VALU_SLOTS["fp32"], "traffic": None,
-                     "note": "VALU lane-ops (2 per update) over the whole batch (embed + "
-                             "persistent band + finalize) per step; peak 256 CU x 128 lanes/clk "
-                             "x 2.4 GHz"},
+                     "frac": None, "traffic": None,
+                     "note": "VALU lane-ops (2 per update of the problem, of which the pair tiles "
+                             "visit only those on branches that a tile touches) over the whole "
+                             "batch (fill + tiles + finalize) per step; peak 256 CU x 128 "
+                             "lanes/clk x 2.4 GHz"},
         "extra": {"graph_s": graph_s, "eager_batch_s": eager_s,
                   "separate_single_table_calls_s": separate_s,
                   "separate_split_calls_s": split_s,
@@ -490,20 +492,23 @@ def bench_matrix(args) -> int:
     # of v_add_u32 (3.61e13 vs 6.55e13 lane-ops/s), i.e. 2 slots as well.  The peak
     # is the published 157.3 TFLOP/s FP32 counted as 78.6e12 slots/s (an FMA is 2
     # flops in one slot; = 256 CU x 128 lanes/clk x 2.4 GHz), half that for FP64.
-    # With the split the stripe kernel visits only the dense branches.
+    # With the split the stripe kernel visits only the dense branches.  The pair tiles of
+    # plain FP64 and FP32 skip the branches that a tile does not touch: their updates are
+    # counted in full and no fraction of a peak is stated.
     if wp == "fp64":
-        band, peak_ops, kname = "band_wn_f64", PEAK_VALU_SLOTS["fp64"], "k_band<double,weighted>"
+        band, peak_ops, kname = "band_wn_f64", PEAK_VALU_SLOTS["fp64"], "k_pairs<double> (weighted)"
     elif "band_wn_u32" in kern:
-        band, peak_ops, kname = "band_wn_u32", PEAK_VALU_SLOTS["fp32"], "k_band<uint32_t,weighted>"
+        band, peak_ops, kname = "band_wn_u32", PEAK_VALU_SLOTS["fp32"], "k_band (weighted, fixed point)"
     else:
-        band, peak_ops, kname = "band_wn_f32", PEAK_VALU_SLOTS["fp32"], "k_band<float,weighted>"
+        band, peak_ops, kname = "band_wn_f32", PEAK_VALU_SLOTS["fp32"], "k_pairs<float> (weighted)"
     band_ms = kern[band]["total_ms_per_step"]
     band_updates = pairs * splits["weighted_normalized"][0] if split_w else U
     slots = 2 * band_updates / (band_ms / 1e3)
     traffic = measured_traffic(band, args.workload)
     roofline = {"bound": "alu", "kernel": kname,
                 "achieved": slots / 1e12, "peak": peak_ops / 1e12,
-                "unit": "Tops/s", "frac": slots / peak_ops, "traffic": traffic,
+                "unit": "Tops/s", "frac": slots / peak_ops if band == "band_wn_u32" else None,
+                "traffic": traffic,
                 "avg_launch_ms": kern[band]["avg_ms_per_launch"],
                 "launches_per_step": kern[band]["launches_per_step"],
                 "updates_per_launch": band_updates / kern[band]["launches_per_step"],
@@ -529,7 +534,7 @@ def bench_matrix(args) -> int:
             extra["split"][var] = {"dense_branches": v[0], "shared_lists": v[1],
                                    "pairs_enumerated": v[2],
                                    "slot_kernel_pairs_per_s": v[2] / (r_ms / 1e3) if r_ms else None}
-    if "gram_mfma" in kern:
+    if "gram_mfma" in kern and split_u:   # (over all branches the product is on presence bits)
         g_ms = kern["gram_mfma"]["total_ms_per_step"]
         g_upd = pairs * splits["unweighted"][0] if split_u else U
         extra["mfma_roofline"] = {"bound": "mfma", "achieved": 4 * g_upd / (g_ms / 1e3) / 1e12,
@@ -593,9 +598,9 @@ def bench_matrix(args) -> int:
     del ws_w, ws_u
 
     # Comparison runs, each a whole call over the full problem with the inputs resident:
-    # the unweighted plain stripe kernel (FP32) vs the MFMA Gram over all branches (the
-    # "MFMA vs plain" figure, both at <= 1e-4 error on the subset); --extra adds the
-    # plain weighted FP32 kernel over all branches.
+    # the unweighted matrix over all branches in FP32 and with BF16 hi + lo lengths (both
+    # the Gram product on presence bits, both at <= 1e-4 error on the subset); --extra adds
+    # the weighted FP32 kernel over all branches.
     comparisons = [("unweighted_plain_fp32", "unweighted", "fp32"),
                    ("unweighted_mfma_all_branches", "unweighted", "mfma")]
     if args.extra:
@@ -616,8 +621,6 @@ def bench_matrix(args) -> int:
             log(f"comparison {name}: {dt:.2f}s")
         extra["mfma_speedup_over_plain_fp32"] = (extra["unweighted_plain_fp32"]["seconds"] /
                                                  extra["unweighted_mfma_all_branches"]["seconds"])
-        t_all = extra["unweighted_mfma_all_branches"]["seconds"]
-        extra["unweighted_mfma_all_branches"]["mfma_frac_whole_call"] = 4 * U / t_all / PEAK_BF16_MFMA
         # the FP64 weighted kernel on one GPU's share of the stripes (an eighth), the
         # size it would take on each of eight GPUs
         S = n // 2
@@ -637,9 +640,11 @@ def bench_matrix(args) -> int:
         extra["weighted_fp64_stripe_share"] = {
             "stripes": [0, se], "seconds": dt, "updates": share_updates,
             "updates_per_s": share_updates / dt, "band_ms": f64_ms,
-            "roofline": {"bound": "alu", "kernel": "k_band<double,weighted>",
+            "roofline": {"bound": "alu", "kernel": "k_pairs<double> (weighted)",
                          "achieved": f64_slots / 1e12, "peak": PEAK_VALU_SLOTS["fp64"] / 1e12,
-                         "unit": "Tops/s", "frac": f64_slots / PEAK_VALU_SLOTS["fp64"]}}
+                         "unit": "Tops/s", "frac": None,
+                         "note": "2 slots per update of the problem, of which the kernel visits "
+                                 "only those on branches that a tile touches"}}
         # sampled pairs inside the share: (i, (i + s + 1) mod n), s < se
         srng = np.random.default_rng(5)
         ss = srng.integers(0, se, size=12)
@@ -648,8 +653,7 @@ def bench_matrix(args) -> int:
         sv = share.view(se, n)[torch.tensor(ss, device="cuda"), torch.tensor(si2, device="cuda")]
         sampled_got["weighted_fp64_stripe_share"] = ("weighted_normalized", sv.cpu().numpy(),
                                                      share_pairs)
-        log(f"FP64 weighted on stripes [0, {se}): {dt:.2f}s, band {f64_ms:.0f} ms "
-            f"({f64_slots / PEAK_VALU_SLOTS['fp64']:.2f} of the FP64 peak)")
+        log(f"FP64 weighted on stripes [0, {se}): {dt:.2f}s, pair tiles {f64_ms:.0f} ms")
         del share
 
     # arithmetic types of the kernels that ran: weighted dense part, split pair sums,

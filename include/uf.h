@@ -64,10 +64,15 @@ typedef enum {
 } uf_status;
 
 typedef enum {
-    UF_FP64 = 0,        /* FP64 embedding and FP64 accumulation (vector ALU)           */
-    UF_FP32 = 1,        /* FP32 embedding and FP32 accumulation, FP64 final division   */
-    UF_MFMA_BF16X2 = 2, /* unweighted only: Gram product on MFMA, 0/1 x (l_hi + l_lo)  */
-                        /* in BF16 with FP32 accumulation, FP64 final division         */
+    UF_FP64 = 0,        /* weighted: FP64 values and accumulation (vector ALU);        */
+                        /* unweighted: exact integer sums of the lengths in 56-bit     */
+                        /* fixed point (MFMA on presence bits), or FP64 accumulation   */
+                        /* where the lengths' range is too wide for it                 */
+    UF_FP32 = 1,        /* weighted: FP32 values and accumulation; unweighted: as      */
+                        /* above, FP32 lengths in 28 bits; FP64 final division         */
+    UF_MFMA_BF16X2 = 2, /* unweighted only: Gram product on MFMA with lengths          */
+                        /* l_hi + l_lo in BF16: exact sums in 28-bit fixed point, or   */
+                        /* FP32 accumulation where their range is too wide             */
     UF_FP32_SPLIT = 3,  /* weighted only, sparse aware (the paper's "sparse-aware      */
                         /* optimizations", section II): branches touched by more than  */
                         /* a threshold fraction of the samples on the FP32 stripe      */

@@ -169,8 +169,9 @@ __global__ __launch_bounds__(256) void k_embed_pres_fp8(
 // buffer loads to LDS (no registers; the row in the scalar offset, so no address
 // arithmetic either), issued for block b+1 before block b is computed.  Column
 // offsets (mod N) are computed once per thread.
-// Bound by the issue of v_sad_u32 (10,000 samples: the vector ALUs issue in 83% of
-// the cycles, seven eighths of it these).
+// Bound by the issue of v_sad_u32 (10,000 samples, counted before the loads lost their
+// address arithmetic: the vector ALUs issued in 83% of the cycles, seven eighths of it
+// these).
 // ----------------------------------------------------------------------------
 constexpr int kBandKS = 16;                  // branches per LDS stage
 constexpr int kBandMS = 16;                  // stripes per thread
