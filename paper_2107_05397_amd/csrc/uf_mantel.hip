@@ -13,9 +13,10 @@
 // by part (k_perm_rows): one workgroup takes the rows i and N-2-i (together N-1
 // partners) for a batch of permutations, holds y'_ij and pi(j) in registers and
 // streams row pi(i) of S.
-// The observed statistic runs through the same kernel with the identity, so the
-// comparisons behind the p-value see identical arithmetic.  Every reduction runs
-// in a fixed order.
+// The observed statistic runs through the same kernel with the identity, and sums are
+// added by i, in an order that the permutation has no part in (as long as a row of S
+// fits in LDS, up to 19,456 samples), so the comparisons behind the p-value see identical
+// arithmetic: a permutation that leaves x unchanged gives the observed statistic bit for bit.
 //
 // Ranks (Spearman): a stable LSD radix sort of the order-preserving 64-bit
 // images of the values, 8 bits per pass (per-block digit histograms, their
@@ -206,21 +207,27 @@ __global__ __launch_bounds__(256) void k_fill_i32(int32_t* __restrict__ p, int64
     if (i < n) p[i] = v;
 }
 
-// part[b][x] = sum over the rows r of block x (R rows from R x) of
-// sum_{j > i} y'_ij S[r][pi_b(j)], i = pi_b^-1(r), for the permutations of blockIdx.y's
-// share (b = n_perm: the identity).  The block's R rows of S stay in LDS; each wave
-// takes every 16th permutation and one row after another, kLdsU loads of y' and pi in
-// flight per lane, and adds up its lanes once per permutation.
-// Every permutation reads half of y' and pi from L2 instead of staging all of S:
-// 2,000 samples, 999 permutations 32.5 -> 1.85 ms (19,000 samples, 49: 36 -> 15 ms);
-// bound by reading y' (16 MB, beyond an
-// XCD's L2, once per permutation) and the LDS gather.
+// part[b][i] = sum_{j > i} y'_ij S[r][pi_b(j)], i = pi_b^-1(r), for the rows r of block x
+// (R rows from R x) and the permutations of blockIdx.y's share (b = n_perm: the identity).
+// The block's R rows of S stay in LDS; each wave takes every 16th permutation and one row
+// after another, kLdsU loads of y' and pi in flight per lane.  A row's sum is a function of
+// i and of the terms alone, and the rows are added by i (k_perm_total), so that a pi which
+// leaves x unchanged (equal samples exchanged, groups of a 0/1 matrix relabelled) gives the
+// observed statistic bit for bit, as the comparisons behind the p-value need.  (Adding the
+// rows of a block here, in the order of r, saved the reductions but made such ties a matter
+// of rounding.)  Four rows are reduced over the lanes together, with the tree of a plain
+// reduction.
+// Every permutation reads half of y' and pi from L2 instead of staging all of S: a call
+// with 2,000 samples, 999 permutations 33.2 -> 2.04 ms (2.02 with the sums in the order of
+// r; 19,000 samples, 49 permutations, so summed: 36 -> 15 ms).  Bound by reading y' (16 MB,
+// beyond an XCD's L2, once per permutation) and the LDS gather.
+constexpr int kRowSet = 4;
 __global__ __launch_bounds__(kRowThreads) void k_perm_lds(const double* __restrict__ S,
                                                           const double* __restrict__ yv, int64_t n,
                                                           const int32_t* __restrict__ perm,
                                                           const int32_t* __restrict__ inv,
                                                           int64_t n_perm, int64_t per, int R,
-                                                          int64_t n_part, double* __restrict__ part) {
+                                                          double* __restrict__ part) {
     extern __shared__ double rows[];   // [R][n]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -231,12 +238,13 @@ __global__ __launch_bounds__(kRowThreads) void k_perm_lds(const double* __restri
     const int64_t b1 = min(n_perm + 1, (int64_t(blockIdx.y) + 1) * per);
     for (int64_t b = int64_t(blockIdx.y) * per + wave; b < b1; b += kRowThreads / 64) {
         const int32_t* pb = b < n_perm ? perm + b * n : nullptr;
-        double a = 0.0;
-        for (int q = 0; q < nr; ++q) {
+        // the sum of row q over the lane's j; *at: its i
+        auto row_sum = [&](int q, int64_t* at) -> double {
             const int64_t r = r0 + q;
             const int64_t i = pb ? int64_t(inv[b * n + r]) : r;
             const double* row = rows + int64_t(q) * n;
             const double* yr = yv + (i * n - i * (i + 1) / 2 - i - 1);   // y'_ij at j
+            double a = 0.0;
             for (int64_t j0 = i + 1; j0 < n; j0 += 64 * kLdsU) {
                 double y[kLdsU];
                 int32_t p[kLdsU];
@@ -249,10 +257,29 @@ __global__ __launch_bounds__(kRowThreads) void k_perm_lds(const double* __restri
 #pragma unroll
                 for (int u = 0; u < kLdsU; ++u) a = fma(y[u], row[p[u]], a);
             }
-        }
+            *at = i;
+            return a;
+        };
+        for (int q0 = 0; q0 < nr; q0 += kRowSet) {
+            double a[kRowSet];
+            int64_t at[kRowSet];
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-        if (lane == 0) part[b * n_part + blockIdx.x] = a;
+            for (int t = 0; t < kRowSet; ++t) {
+                a[t] = 0.0;
+                at[t] = -1;
+                if (q0 + t < nr) a[t] = row_sum(q0 + t, &at[t]);
+            }
+            // lanes 16 t to 16 t + 15 end up with row t: steps of 32, 16, 8, 4, 2, 1 lanes for
+            // each, the first two of them on the rows that the lane keeps
+            const bool h = (lane & 32) != 0, g = (lane & 16) != 0;
+            const double x0 = (h ? a[2] : a[0]) + __shfl_xor(h ? a[0] : a[2], 32, 64);
+            const double x1 = (h ? a[3] : a[1]) + __shfl_xor(h ? a[1] : a[3], 32, 64);
+            double v = (g ? x1 : x0) + __shfl_xor(g ? x0 : x1, 16, 64);
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+            const int64_t i = h ? (g ? at[3] : at[2]) : (g ? at[1] : at[0]);
+            if ((lane & 15) == 0 && i >= 0) part[b * n + i] = v;
+        }
     }
 }
 
@@ -735,12 +762,13 @@ uf_status uf_mantel(const double* x, const double* y, int64_t n, int method, con
         // as many rows per block as give each of 256 CUs one block, if LDS holds them;
         // few rows: the permutations in shares, at least one per wave
         const int64_t R = std::max<int64_t>(1, std::min((n + 255) / 256, kPartMax / n));
-        n_part = (n + R - 1) / R;
-        const int64_t shares = std::max<int64_t>(1, std::min((n_perm + 16) / 16, 512 / n_part));
+        const int64_t n_blk = (n + R - 1) / R;
+        n_part = n;
+        const int64_t shares = std::max<int64_t>(1, std::min((n_perm + 16) / 16, 512 / n_blk));
         const int64_t per = (n_perm + shares) / shares;   // of n_perm + 1
-        hipLaunchKernelGGL(k_perm_lds, dim3(unsigned(n_part), unsigned((n_perm + per) / per)),
+        hipLaunchKernelGGL(k_perm_lds, dim3(unsigned(n_blk), unsigned((n_perm + per) / per)),
                            dim3(kRowThreads), size_t(R * n) * 8, s, S, yv, n, perms, inv, n_perm, per,
-                           int(R), n_part, part);
+                           int(R), part);
         UFM_HIP(hipGetLastError());
     } else {
         const int64_t nparts = (n + kPartMax - 1) / kPartMax;
