@@ -1476,18 +1476,34 @@ struct uf_batch {
     std::vector<hipStream_t> streams;         // kMaxBatchStreams, default priority
     std::vector<hipEvent_t> events;           // fork + one join event per stream
 
-    ~uf_batch() {
-        if (exec) (void)hipGraphExecDestroy(exec);
-        if (graph) (void)hipGraphDestroy(graph);
-        if (cap) (void)hipStreamDestroy(cap);
-        if (last_run) (void)hipEventDestroy(last_run);
-        for (hipStream_t q : streams) (void)hipStreamDestroy(q);
-        for (hipEvent_t ev : events) (void)hipEventDestroy(ev);
-        for (uf_embedding* t : tembs) uf_free_embedding(t);
-        if (arena) (void)hipFree(arena);
-        uf_free_embedding(emb);
-    }
+    ~uf_batch();
 };
+
+namespace {
+// Give up the captured graph.  Runs are asynchronous: a replay still in flight is waited
+// for first, since it executes what is destroyed here.
+void drop_graph(uf_batch* b) {
+    if (b->exec) {
+        if (b->last_run && hipEventSynchronize(b->last_run) != hipSuccess) (void)hipGetLastError();
+        (void)hipGraphExecDestroy(b->exec);
+    }
+    if (b->graph) (void)hipGraphDestroy(b->graph);
+    b->exec = nullptr;
+    b->graph = nullptr;
+    b->graph_key.clear();
+}
+}  // namespace
+
+uf_batch::~uf_batch() {
+    drop_graph(this);
+    if (cap) (void)hipStreamDestroy(cap);
+    if (last_run) (void)hipEventDestroy(last_run);
+    for (hipStream_t q : streams) (void)hipStreamDestroy(q);
+    for (hipEvent_t ev : events) (void)hipEventDestroy(ev);
+    for (uf_embedding* t : tembs) uf_free_embedding(t);
+    if (arena) (void)hipFree(arena);
+    uf_free_embedding(emb);
+}
 
 namespace {
 
@@ -1657,14 +1673,6 @@ uf_status batch_split_enqueue(uf_batch* b, float* const* outs, char* base, hipSt
 
 uf_status batch_enqueue_any(uf_batch* b, float* const* outs, char* base, hipStream_t s) {
     return b->split ? batch_split_enqueue(b, outs, base, s) : batch_enqueue(b, outs, base, s);
-}
-
-void drop_graph(uf_batch* b) {
-    if (b->exec) (void)hipGraphExecDestroy(b->exec);
-    if (b->graph) (void)hipGraphDestroy(b->graph);
-    b->exec = nullptr;
-    b->graph = nullptr;
-    b->graph_key.clear();
 }
 
 }  // namespace
@@ -1873,13 +1881,7 @@ uf_status uf_batch_set_config(uf_batch* b, int stage_branches, int wgs_per_cu, i
         b->stage_branches = stage_branches;
         b->wgs_per_cu = wgs_per_cu;
         b->tile_stripes = tile_stripes;
-        if (b->exec) {
-            (void)hipGraphExecDestroy(b->exec);
-            (void)hipGraphDestroy(b->graph);
-            b->exec = nullptr;
-            b->graph = nullptr;
-            b->graph_key.clear();
-        }
+        drop_graph(b);
         return UF_OK;
     });
 }
@@ -1916,12 +1918,7 @@ uf_status uf_batch_run(uf_batch* b, float* const* outs, int use_graph, void* ws,
         key.push_back(reinterpret_cast<uintptr_t>(base));
         for (int64_t r = 0; r < b->n_tables; ++r) key.push_back(reinterpret_cast<uintptr_t>(outs[r]));
         if (!b->exec || key != b->graph_key) {
-            if (b->exec) {
-                (void)hipGraphExecDestroy(b->exec);
-                (void)hipGraphDestroy(b->graph);
-                b->exec = nullptr;
-                b->graph = nullptr;
-            }
+            drop_graph(b);
             UF_HIP(hipStreamBeginCapture(b->cap, hipStreamCaptureModeRelaxed));
             uf_status est = batch_enqueue_any(b, outs, base, b->cap);
             hipGraph_t g = nullptr;
