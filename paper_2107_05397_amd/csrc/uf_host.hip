@@ -536,12 +536,10 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     p->n_parts = std::max<int64_t>(1, (p->sr + 255) / 256);
     const size_t acc_elem = (prec == UF_FP64 || bits) ? 8 : 4;
     p->pairs = !bits && !mfma && !fixed;
-    p->form = weighted && prec != UF_FP64 ? ufx::kPairL1 : ufx::kPairMin;
+    p->form = weighted ? ufx::kPairL1 : ufx::kPairMin;
     p->seg = p->pairs ? ufx::pair_segment(n, nb) : 0;
-    // sums of one segment or range: with the pair tiles' sums of minima also sum_v x of
-    // every sample, with the bits one plane per four digits
-    p->plane = bits ? p->sr * n * (p->digits / 4)
-                    : p->sr * n + (p->pairs && p->form == ufx::kPairMin ? n : 0);
+    // sums of one segment or range: with the bits one plane per four digits
+    p->plane = bits ? p->sr * n * (p->digits / 4) : p->sr * n;
     const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
     // workspace layout for a chunk of kc branches; planes: segments held side by side
     auto layout = [&](int64_t kc, int64_t planes) {
@@ -577,17 +575,13 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         // of them when fewer) fits beside the sums; the chunk takes what the rest leaves
         // (each carved piece may lose up to 255 bytes to alignment).
         const std::string too_large = "problem too large for the fixed scratch (" + std::to_string(fit) + " bytes)";
-        const bool pairs = p->pairs;
-        const int64_t plane = p->plane;
-        p->plane = p->sr * n;
         layout(0, 0);
-        p->plane = plane;
         const size_t rest = p->total + 6 * 256;
         const size_t per = mfma ? size_t(n) : size_t(n) * elem;
         const int64_t room = rest < fit ? int64_t((fit - rest) / std::max<size_t>(per, 1)) : 0;
         int64_t kc = std::min<int64_t>(room, std::max<int64_t>(nb, 1));
         if (mfma || kc < std::min<int64_t>(32, std::max<int64_t>(nb, 1))) return fail(UF_ERR_RANGE, too_large);
-        if (pairs) {
+        if (p->pairs) {
             layout(std::max<int64_t>(nb, 1), n_seg);       // everything at once, if it fits
             if (p->total <= fit) return UF_OK;
         }
@@ -797,13 +791,13 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         ProfScope ps("finalize", s);
         const bool fixed = sp && weighted && sp->q_scale > 0.0;
         const int acc_type = prec == UF_FP64 || p.digits ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
-        const bool min_form = p.pairs && weighted && p.form == ufx::kPairMin, two_parts = p.digits == 8;
-        const int kind = min_form ? 2 : two_parts ? 3 : weighted ? 0 : 1;
+        const bool two_parts = p.digits == 8;
+        const int kind = two_parts ? 3 : weighted ? 0 : 1;
         const double scale = fixed      ? 1.0 / sp->q_scale
                              : p.digits ? std::ldexp(1.0, e->len_exp - ufb::kDigitBits * p.digits)
                                         : 1.0;
-        // after the sums: sum_v x of every sample, or the sums' lower part
-        const void* diag = min_form || two_parts ? static_cast<char*>(acc) + size_t(p.sr * p.n) * 8 : nullptr;
+        // after the sums: their lower part
+        const void* diag = two_parts ? static_cast<char*>(acc) + size_t(p.sr * p.n) * 8 : nullptr;
         UF_HIP(ufk::finalize(kind, acc, acc_type, scale, scal, p.n, p.sb, p.se, layout,
                              odt == UF_OUT_F32 ? 1 : 0, out, q, s, M, sp && weighted ? sp->sigma : nullptr,
                              sp && weighted ? sp->unit : 0x1p-40, diag));

@@ -227,8 +227,6 @@ hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, i
 // 2 M to the numerator, kind 1 adds M to the Gram value.
 // kind 3: kind 1 with the Gram value's upper part in acc (in units of 2^28) and its lower
 // part in diag (one element per accumulator element), both in units of acc_scale.
-// kind 2: weighted from m_ij = sum_v min(x_iv, x_jv), numerator (diag_i - m) +
-// (diag_j - m) with diag_i = sum_v x_iv in the accumulator's type.
 constexpr int kAccF32 = 0, kAccF64 = 1, kAccU32 = 2;
 hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, const double* scal,
                     int64_t n, int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,

@@ -681,7 +681,7 @@ struct FinIn {
     unsigned long long m;          // split: exact pair sum in the split's unit
     unsigned long long sg_i, sg_j; // weighted split: sigma of both samples
     double sc_i, sc_j;             // per-sample scalars
-    A dg_i, dg_j;                  // min form: sum_v x of both samples; kind 3: lower part, -
+    A dg_i;                        // kind 3: lower part
 };
 
 // Loads only (no arithmetic on the loaded values, so that the loads of several
@@ -699,10 +699,6 @@ __device__ __forceinline__ FinIn<A, KIND, SPLIT> final_inputs(
     }
     f.sc_i = scal[i];
     f.sc_j = scal[j];
-    if constexpr (KIND == 2) {
-        f.dg_i = diag[i];
-        f.dg_j = diag[j];
-    }
     if constexpr (KIND == 3) f.dg_i = diag[(s - sb) * n + i];
     return f;
 }
@@ -712,9 +708,6 @@ __device__ __forceinline__ double final_distance(const FinIn<A, KIND, SPLIT>& f,
                                                  double split_unit) {
     double num = double(f.acc) * acc_scale;
     if constexpr (KIND == 3) num = (double(f.acc) * 0x1p28 + double(f.dg_i)) * acc_scale;
-    // min form: both differences are sums of x - min(x, y) >= 0 taken in the same
-    // order, so neither is negative and equal samples give exactly 0
-    if constexpr (KIND == 2) num = (double(f.dg_i) - num) + (double(f.dg_j) - num);
     if constexpr (SPLIT) {
         if constexpr (KIND == 0) {
             const long long r = (long long)(f.sg_i + f.sg_j - 2ull * f.m);
@@ -723,7 +716,7 @@ __device__ __forceinline__ double final_distance(const FinIn<A, KIND, SPLIT>& f,
             num += double(f.m) * split_unit;
         }
     }
-    if constexpr (KIND == 0 || KIND == 2) {   // a sum of |x - y| over the sum of x + y: no clamp needed
+    if constexpr (KIND == 0) {   // a sum of |x - y| over the sum of x + y: no clamp needed
         const double den = f.sc_i + f.sc_j;
         return den > 0.0 ? num / den : 0.0;
     }
@@ -994,8 +987,8 @@ hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, c
     if (acc_type == T_ && kind == K_ && (split_m != nullptr) == S_)                                   \
         return finalize_as<A_, K_, S_>(acc, acc_scale, scal, n, sb, se, layout, out_f32, out, q, st, \
                                        split_m, sigma, split_unit, diag);
+    UF_FIN(kAccF64, double, 0, false)
     UF_FIN(kAccF64, double, 1, false)
-    UF_FIN(kAccF64, double, 2, false)
     UF_FIN(kAccF64, double, 3, false)
     UF_FIN(kAccU32, uint32_t, 0, true)
     UF_FIN(kAccF32, float, 0, false)

@@ -17,9 +17,9 @@ constexpr int kPairWin = 256;    // branches listed at a time
 constexpr int kPairU = 8;        // branches per group of loads
 constexpr int kPairMin = 0, kPairL1 = 1;   // sum of min(x, y); sum of |x - y|
 // From here on the L1 tiles take 16 samples i per wave: their rows no longer stay in
-// the caches, and each row of samples j read serves twice the pairs (5,000 samples, 40,000
-// branches 28.2 -> 19.7 ms; 2,500: 6.5 -> 7.1; 1,500: 2.05 -> 2.37).  A batch runs such
-// tables in a launch of their own.
+// the caches, and each row of samples j read serves twice the pairs (FP32, 5,000 samples,
+// 40,000 branches 28.2 -> 19.7 ms; 2,500: 6.5 -> 7.1; 1,500: 2.05 -> 2.37; FP64, 3,500:
+// 17.8 -> 17.4, 2,500: 10.0 -> 11.2).  A batch runs such tables in a launch of their own.
 constexpr int64_t kPairWideN = 4096;
 
 // Workspace of one chunk of kc branches of n samples: values, then masks.
@@ -54,9 +54,8 @@ template <typename T>
 hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, void* chunk,
                      hipStream_t st);
 // Sums of stripes [sb, se) over branches [ka, kb) of the chunk, `count` segments of
-// seg branches side by side, each into its own plane of out: [se-sb][n] stripe-major,
-// then (kPairMin) sum_v x_iv of every sample i [n].  load: start from what out holds.
-// form: kPairMin, or kPairL1 (FP32 only).
+// seg branches side by side, each into its own plane of out: [se-sb][n] stripe-major.
+// load: start from what out holds.
 template <typename T>
 hipError_t pairs(int form, const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
                  int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,

@@ -1,9 +1,10 @@
-// Pair tiles over touched branches (gfx950): the FP64 and FP32 sums
-//   m_ij = sum_v min(x_iv, x_jv)   and, in FP32, sum_v |x_iv - x_jv|,
-// x = l u (weighted) or l a (unweighted, where the sum is the Gram value).  A term
-// is nonzero only where both samples touch v, and sum |x - y| = s_i + s_j - 2 m_ij,
-// so a tile of sample pairs only visits the branches that its rows and its
-// columns both touch.
+// Pair tiles over touched branches (gfx950), FP64 and FP32:
+//   weighted    sum_v |x_iv - x_jv|    x = l u: branches that the tile's rows or columns touch
+//   unweighted  sum_v min(x_iv, x_jv)  x = l a (the Gram value): branches that both touch
+// so a tile of sample pairs leaves out the branches that add zero to all its pairs.
+// (Weighted sums of minima, s_i + s_j - 2 m_ij, would need the shorter list too, but are a
+// difference of large numbers: two samples of equal depth that differ on a few branches,
+// d = 3e-9, are off by 2e-8 of their distance in FP64, and by all of it in FP32.)
 //
 // Chunk layout: samples in blocks of 64.  E[b][k][64] holds the block's values on
 // branch k of the chunk (row kc is all zeros), mask[b][k] the bit of every sample
@@ -186,25 +187,24 @@ __device__ __forceinline__ void wave_sync() {
 // broadcast from there by DPP; an update is min and +.  Loads run one group ahead.
 // A listed branch adds exactly its terms and the others add zero, so the sums
 // are those over all branches in postorder, whichever tile a pair falls in.
-// Diagonal tiles also give sum_v x_iv (the pair (i, i)) by the same additions: it is
-// no smaller than any m_ij, and equal to it for equal samples.
-// L1: sums of |x_i - x_j| instead, over the branches that either side touches (a
-// difference of FP32 minima sums would lose the small distances), two VALU operations
-// an update with the broadcast in the first.
+// L1: sums of |x_i - x_j|, over the branches that either side touches; in FP32 two VALU
+// operations an update with the broadcast in the first.
 // blockIdx.y: segment [ka + seg*y, +seg) of the chunk, to its own plane of out.
 //
 // Why this shape.  A sample touches few branches (6% of a 20,000-tip tree at 300
 // tips, 3% of a 200,000-tip tree at 1,000), but 64 samples together touch most, so
 // a dense tile does mostly zeros: of the branches, 18% (8%) are touched on both sides
-// of an 8 x 64 tile, against 40% (20%) of a 64 x 64 one.  Groups of 4 or 16 samples i
-// were slower (1,500 samples, 20,000 tips: 1.91 and 2.14 ms against 1.67), the first
-// for its loads, the second for its longer lists.  It is bound about half by FP64
-// issue (min, +, and one broadcast per A-row) and by L2 misses of the rows read.
-// Measured with events, against an LDS-tiled kernel over all branches: 256 samples,
-// 1,000 tips 1,144 -> 29 us (two workgroups of 128 x 128 pairs there); 1,500 x 20,000
-// 23.4 -> 1.67 ms; 5,000 x 10,000 32.1 -> 10.9 ms.  L1: 500 x 2,000 branches 658 -> 43 us;
-// 1,500 x 40,000 13.0 -> 2.03 ms; 5,000 x 10,000 7.5 -> 6.3 ms; 5,000 x 40,000 28.8 ->
-// 19.7 ms, there bound by the rows that miss the caches.
+// of an 8 x 64 tile, and 56% (32%) on either side.  For minima, groups of 4 or 16
+// samples i were slower (1,500 samples, 20,000 tips: 1.91 and 2.14 ms against 1.67), the
+// first for its loads, the second for its longer lists.  Bound about half by FP64 issue
+// (min, + or -, |+|, and one broadcast per A-row) and by L2 misses of the rows read.
+// Measured with events as whole calls, against an LDS-tiled kernel over all branches
+// (two workgroups of 128 x 128 pairs at 256 samples).  FP64 |x - y|: 256 samples, 1,000 tips
+// 1.23 -> 0.083 ms; 1,500 x 20,000 24.9 -> 3.7; 5,000 x 5,000 17.5 -> 11.8; 8,000 x 5,000,
+// most branches touched, 35.1 -> 31.6 (as sums of minima 0.076, 1.9, 8.9 and 40.1).  FP32:
+// 500 x 2,000 branches 658 -> 43 us; 1,500 x 40,000 14.4 -> 2.15 ms; 5,000 x 10,000 8.8 ->
+// 6.4 ms; 5,000 x 40,000 33.5 -> 16.5 ms, there bound by the rows that miss the caches;
+// 10,000 x 2,000 5.4 -> 5.4.
 constexpr int kWin = kPairWin;
 template <typename T, int A, int U, bool L1>
 __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
@@ -220,11 +220,7 @@ __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
     auto slot = [&](int a, int64_t* at, int64_t* dup) -> bool {
         const int i = i0 + a;
         *dup = -1;
-        if (i > j || j >= n) return false;
-        if (i == j) {
-            *at = int64_t(se - sb) * n + i;
-            return !L1;
-        }
+        if (i >= j || j >= n) return false;
         const int d = j - i;
         const int s = d <= S ? d - 1 : n - d - 1;
         if (s < sb || s >= se) return false;
@@ -335,7 +331,7 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
     const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;     // first i inside its block
     const int i0 = int(bi) * 64 + ig, j0 = int(bj) * 64;
     if (i0 >= n) return;
-    if (bi != bj && !pairs_in_range(i0, min(i0 + A, n), j0, min(j0 + 64, n), n, sb, se)) return;
+    if (!pairs_in_range(i0, min(i0 + A, n), j0, min(j0 + 64, n), n, sb, se)) return;
     const int k_lo = ka + seg * int(blockIdx.y), k_hi = min(kb, k_lo + seg);
     pair_wave<T, A, U, L1>(queue[wave], E, mask, kc, kcp, n, bi, bj, ig, k_lo, k_hi, sb, se, load != 0,
                            out + int64_t(blockIdx.y) * plane);
@@ -448,11 +444,10 @@ hipError_t pairs(int form, const void* chunk, int64_t n, int64_t kc, int64_t ka,
                  int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
                  hipStream_t st) {
     if (n <= 0 || kb <= ka) return hipSuccess;
-    if constexpr (std::is_same<T, float>::value)
-        if (form == kPairL1)
-            return n >= kPairWideN
-                       ? pairs_as<T, 2 * kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st)
-                       : pairs_as<T, kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
+    if (form == kPairL1)
+        return n >= kPairWideN
+                   ? pairs_as<T, 2 * kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st)
+                   : pairs_as<T, kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
     if (form != kPairMin) return hipErrorInvalidValue;
     return pairs_as<T, kPairA, false>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
 }
