@@ -65,14 +65,17 @@ typedef enum {
 
 typedef enum {
     UF_FP64 = 0,        /* weighted: FP64 values and accumulation (vector ALU);        */
-                        /* unweighted: exact integer sums of the lengths in 56-bit     */
-                        /* fixed point (MFMA on presence bits), or FP64 accumulation   */
-                        /* where the lengths' range is too wide for it                 */
+                        /* unweighted: exact integer sums of the lengths rounded to 56 */
+                        /* bits (MFMA on presence bits; distances within 2^-50 of      */
+                        /* those of the unrounded lengths), or FP64 accumulation where */
+                        /* the lengths' range is too wide for that bound               */
     UF_FP32 = 1,        /* weighted: FP32 values and accumulation; unweighted: as      */
-                        /* above, FP32 lengths in 28 bits; FP64 final division         */
+                        /* above, FP32 lengths in 28 or 56 bits (distances within      */
+                        /* 2^-22); FP64 final division                                 */
     UF_MFMA_BF16X2 = 2, /* unweighted only: Gram product on MFMA with lengths          */
-                        /* l_hi + l_lo in BF16: exact sums in 28-bit fixed point, or   */
-                        /* FP32 accumulation where their range is too wide             */
+                        /* l_hi + l_lo in BF16: exact sums of these in 28 or 56 bits   */
+                        /* (within 2^-22), or FP32 accumulation where their range is   */
+                        /* too wide                                                    */
     UF_FP32_SPLIT = 3,  /* weighted only, sparse aware (the paper's "sparse-aware      */
                         /* optimizations", section II): branches touched by more than  */
                         /* a threshold fraction of the samples on the FP32 stripe      */

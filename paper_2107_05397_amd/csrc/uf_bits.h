@@ -57,10 +57,10 @@ hipError_t tip_bits(const ufp::Emb& e, int64_t n_tips, void* ws, hipStream_t st)
 hipError_t branch_bits(const ufp::Emb& e, int64_t n_tips, int kind, const float* len32,
                        const uint16_t* len_hi, const uint16_t* len_lo, double inv_q, int64_t k0,
                        int64_t kc, void* ws, hipStream_t st);
-// G_ij / q of stripes [sb, se) over the chunk's branches as exact integers in FP64
-// planes [se-sb][n], stripe-major: nd = 4: one plane (digits 0-3); nd = 8: the plane of
-// digits 4-7 (in units of 2^28), then that of digits 0-3.  Split y writes its own planes
-// at out + y * (planes of one split); load: add to what out holds.
+// G_ij / q of stripes [sb, se) and w_i / q = G_ii / q over the chunk's branches as exact
+// integers in FP64 planes [se-sb+1][n], stripe-major, w last: nd = 4: one plane (digits
+// 0-3); nd = 8: the plane of digits 4-7 (in units of 2^28), then that of digits 0-3.  Split
+// y writes its own planes at out + y * (planes of one split); load: add to what out holds.
 hipError_t gram_bits(int nd, int64_t n, int64_t n_tips, int64_t kc, int64_t splits, int64_t sb,
                      int64_t se, int load, double* out, const void* ws, hipStream_t st);
 

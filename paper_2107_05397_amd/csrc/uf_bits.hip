@@ -200,7 +200,8 @@ __global__ __launch_bounds__(256, 2) void k_gram_bits(const u64* __restrict__ an
         const int64_t dlo = max<int64_t>(1, j0 - (min(i0 + 64, n) - 1)), dhi = min(j0 + 64, n) - 1 - i0;
         const int64_t a1 = max(dlo, sb + 1), b1 = min(dhi, min(se, S));
         const int64_t a2 = max(dlo, max(n - se, S + 1)), b2 = min(dhi, n - 1 - sb);
-        if (dhi < dlo || !(a1 <= b1 || a2 <= b2)) return;
+        // (a diagonal tile also gives its samples' own sums)
+        if (bi != bj && (dhi < dlo || !(a1 <= b1 || a2 <= b2))) return;
     }
     const int ih = wave & 1, hh = wave >> 1;   // half of the i's; of the j's (nd 4) or digits (nd 8)
     const int jb0 = ND == 8 ? 0 : hh;
@@ -308,18 +309,18 @@ __global__ __launch_bounds__(256, 2) void k_gram_bits(const u64* __restrict__ an
 
     // D of a 32 x 32 block: lane holds column lane % 32, rows 8 (e / 4) + 4 (lane / 32) + e % 4
     const int64_t S = n / 2, sr = se - sb;
-    out += int64_t(blockIdx.y) * (ND / 4) * sr * n;
-    if (ND == 8 && hh == 0) out += sr * n;
+    out += int64_t(blockIdx.y) * (ND / 4) * (sr + 1) * n;
+    if (ND == 8 && hh == 0) out += (sr + 1) * n;
 #pragma unroll
     for (int y = 0; y < NB; ++y)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int64_t i = bi * 64 + 32 * ih + 8 * (e >> 2) + 4 * g + (e & 3);
             const int64_t j = bj * 64 + 32 * (jb0 + y) + r;
-            if (!(i < j && j < n)) continue;
+            if (!(i <= j && j < n)) continue;
             const int64_t d = j - i;
-            const int64_t s = d <= S ? d - 1 : n - d - 1;
-            if (s < sb || s >= se) continue;
+            const int64_t s = d == 0 ? se : d <= S ? d - 1 : n - d - 1;   // (w follows the stripes)
+            if (d != 0 && (s < sb || s >= se)) continue;
             long long v = 0;
 #pragma unroll
             for (int q = 3; q >= 0; --q) v = (v << kDigitBits) + (long long)c[y][q][e];

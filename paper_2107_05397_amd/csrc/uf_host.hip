@@ -526,8 +526,8 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     // Unweighted, over all branches: the Gram product on presence bits, unless the
     // lengths' range is too wide for its digits
     p->len_kind = prec == UF_FP64 ? 0 : prec == UF_FP32 ? 1 : 2;
-    const bool bits = !weighted && !split && e->len_fixed[p->len_kind];
-    p->digits = bits ? (prec == UF_FP64 ? 8 : 4) : 0;
+    p->digits = weighted || split ? 0 : e->len_digits[p->len_kind];
+    const bool bits = p->digits > 0;
     const bool mfma = (prec == UF_MFMA_BF16X2 && !bits) || prec == UF_MFMA_SPLIT;
     if (split && !sp) return fail(UF_ERR_ARG, "split precision without a split");
     const int64_t nb = split ? sp->n_dense : e->nb;
@@ -538,8 +538,9 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     p->pairs = !bits && !mfma && !fixed;
     p->form = weighted ? ufx::kPairL1 : ufx::kPairMin;
     p->seg = p->pairs ? ufx::pair_segment(n, nb) : 0;
-    // sums of one segment or range: with the bits one plane per four digits
-    p->plane = bits ? p->sr * n * (p->digits / 4) : p->sr * n;
+    // sums of one segment or range: with the bits one plane per four digits, each with the
+    // samples' own sums after the pairs'
+    p->plane = bits ? (p->sr + 1) * n * (p->digits / 4) : p->sr * n;
     const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
     // workspace layout for a chunk of kc branches; planes: segments held side by side
     auto layout = [&](int64_t kc, int64_t planes) {
@@ -791,16 +792,10 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
         ProfScope ps("finalize", s);
         const bool fixed = sp && weighted && sp->q_scale > 0.0;
         const int acc_type = prec == UF_FP64 || p.digits ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
-        const bool two_parts = p.digits == 8;
-        const int kind = two_parts ? 3 : weighted ? 0 : 1;
-        const double scale = fixed      ? 1.0 / sp->q_scale
-                             : p.digits ? std::ldexp(1.0, e->len_exp - ufb::kDigitBits * p.digits)
-                                        : 1.0;
-        // after the sums: their lower part
-        const void* diag = two_parts ? static_cast<char*>(acc) + size_t(p.sr * p.n) * 8 : nullptr;
-        UF_HIP(ufk::finalize(kind, acc, acc_type, scale, scal, p.n, p.sb, p.se, layout,
+        const int kind = p.digits == 8 ? 3 : p.digits ? 2 : weighted ? 0 : 1;
+        UF_HIP(ufk::finalize(kind, acc, acc_type, fixed ? 1.0 / sp->q_scale : 1.0, scal, p.n, p.sb, p.se, layout,
                              odt == UF_OUT_F32 ? 1 : 0, out, q, s, M, sp && weighted ? sp->sigma : nullptr,
-                             sp && weighted ? sp->unit : 0x1p-40, diag));
+                             sp && weighted ? sp->unit : 0x1p-40));
     }
     if (rowstats) {
         ProfScope ps("row_sums", s);
@@ -835,34 +830,34 @@ void prof_end(ProfHandle* h) { delete h; }
 // C ABI
 // =========================================================================
 namespace {
-// Digits of the lengths: 28 bits below 2^len_exp (FP32-rounded and BF16 hi + lo lengths)
-// or 56 (FP64).  Rounding changes a pair's sum by at most len_err = sum_v |l_v - rounded
-// l_v| and a distance by at most about len_err / (the smaller sample's total length).
-void length_digits(uf_tree* t) {
-    const int64_t nb = t->n_nodes - 1;
+// Every length of the tree is below 2^len_exp, also as FP32 or BF16 hi + lo.
+void length_exponent(uf_tree* t) {
     double lmax = 0.0;
-    for (int64_t k = 0; k < nb; ++k) lmax = std::max(lmax, t->len[size_t(k)]);
+    for (int64_t k = 0; k < t->n_nodes - 1; ++k) lmax = std::max(lmax, t->len[size_t(k)]);
     lmax *= 1.0 + 0x1p-16;   // the rounded lengths are no longer than this
     int ex = 0;
     while (ex < 1100 && lmax >= std::ldexp(1.0 - 0x1p-20, ex)) ++ex;
     while (ex > -900 && lmax > 0.0 && lmax < std::ldexp(0.5 - 0x1p-20, ex)) --ex;
     t->len_exp = ex;
-    if (!std::isfinite(lmax) || ex >= 900 || ex <= -800) return;
-    const double q56 = std::ldexp(1.0, ex - 8 * ufb::kDigitBits), i56 = 1.0 / q56;
-    const double q28 = std::ldexp(1.0, ex - 4 * ufb::kDigitBits), i28 = 1.0 / q28;
-    // (adding 2^52 rounds a value below it; one above is whole)
-    auto off = [](double l, double iq, double q) {
-        const double v = l * iq, r = v < 0x1p52 ? (v + 0x1p52) - 0x1p52 : v;
-        return std::fabs(l - r * q);
-    };
-    double err[3] = {0.0, 0.0, 0.0};
-    for (int64_t k = 0; k < nb; ++k) {
-        const double l = t->len[size_t(k)], hi = bf16_value(bf16_bits(l));
-        err[0] += off(l, i56, q56);
-        err[1] += off(double(static_cast<float>(l)), i28, q28);
-        err[2] += off(hi + bf16_value(bf16_bits(l - hi)), i28, q28);
-    }
-    std::copy(err, err + 3, t->len_err);
+}
+
+// Digits of the unweighted product's lengths: multiples of q = 2^(len_exp - 7 digits).  A
+// length is off by q/2 at most, and a distance, whose sums over one or both samples'
+// branches (K_i and K_j of them) are all taken from the rounded lengths, by (K_i + K_j) q/2
+// over the length of their union: at most q / mean, with the smallest mean length of a
+// sample's branches.  With a mean of 2^(len_exp - 6) or more that is 2^-50 with 8 digits and
+// 2^-22 with 4, no more than sums in FP64 and FP32 over thousands of lengths are off by
+// (random trees of 5,000 and 20,000 tips, against 80-bit sums: 1.7e-15 and 9.9e-7 at most;
+// from the digits 1.6e-16 and 1.6e-9, the rounding errors having either sign).  Lengths of
+// random trees reach 12 to 25 times their mean.  With a longer range, 8 digits serve FP32
+// and hi + lo lengths while the bound is 2^-24; beyond that, and for FP64, sums of the
+// lengths themselves do.
+void choose_digits(uf_embedding* e, double mean_min) {
+    const int ex = e->len_exp;
+    const bool f64 = ex < 900 && ex > -800, f32 = ex < 128 && ex > -100;   // (no infinities)
+    const bool near = mean_min >= std::ldexp(1.0, ex - 6), far = mean_min >= std::ldexp(1.0, ex - 32);
+    e->len_digits[0] = f64 && near ? 8 : 0;
+    e->len_digits[1] = e->len_digits[2] = f32 && near ? 4 : f32 && far ? 8 : 0;
 }
 }  // namespace
 
@@ -1031,7 +1026,7 @@ uf_status uf_tree_load(int64_t m, const int64_t* parent, const double* length, u
             t->hi[k] = int32_t(tips_before[k + 1]);
         }
         t->n_tips = tips_before[m];
-        length_digits(t);
+        length_exponent(t);
         t->node_at32.assign(t->node_at.begin(), t->node_at.end());
         *out = guard.release();
         return UF_OK;
@@ -1140,13 +1135,16 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
             lhi[k] = bf16_bits(t->len[k]);
             llo[k] = bf16_bits(t->len[k] - bf16_value(lhi[k]));
         }
-        // root distances by position for the three length roundings (FP64 sums)
+        // root distances by position for the three length roundings (FP64 sums), and
+        // branches of nonzero length on the way
         std::vector<double> d64(m, 0.0), d32(m, 0.0), dbf(m, 0.0);
+        std::vector<int32_t> above(m, 0);
         for (int64_t k = m - 2; k >= 0; --k) {
             const int32_t p = t->parent_pos[k];
             d64[k] = d64[p] + t->len[k];
             d32[k] = d32[p] + double(len32[k]);
             dbf[k] = dbf[p] + (bf16_value(lhi[k]) + bf16_value(llo[k]));
+            above[k] = above[p] + (t->len[k] > 0.0);
         }
         // one device allocation for everything
         Carver c;
@@ -1170,6 +1168,8 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         const size_t o_d64 = c.take(size_t(m) * 8);
         const size_t o_d32 = c.take(size_t(m) * 8);
         const size_t o_dbf = c.take(size_t(m) * 8);
+        const size_t o_above = c.take(size_t(m) * 4);
+        const size_t o_mean = c.take(8);
         void* arena = nullptr;
         hipError_t he = hipMalloc(&arena, c.off + 256);
         if (he != hipSuccess) return fail(UF_ERR_NOMEM, "device allocation of the embedding failed");
@@ -1238,28 +1238,25 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         if (rc == hipSuccess) rc = H2D(dd32, d32.data(), size_t(m) * 8);
         if (rc == hipSuccess) rc = H2D(ddbf, dbf.data(), size_t(m) * 8);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "upload of the embedding inputs"));
-        rc = ufk::pack_nodes(*e, s);
+        int32_t* dabove = reinterpret_cast<int32_t*>(b + o_above);
+        unsigned long long* mean_min = reinterpret_cast<unsigned long long*>(b + o_mean);
+        const double infinite = HUGE_VAL;   // no sample touches a branch of nonzero length
+        rc = H2D(dabove, above.data(), size_t(m) * 4);
+        if (rc == hipSuccess) rc = H2D(mean_min, &infinite, 8);
+        if (rc != hipSuccess) return cleanup(hip_fail(rc, "upload of the embedding inputs"));
+        rc = ufk::pack_nodes(*e, dabove, s);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "node record kernel launch"));
         if (n > 0) {
-            rc = ufk::sample_scalars(*e, ppos, tpos, dd64, dd32, ddbf, s);
+            rc = ufk::sample_scalars(*e, ppos, tpos, dd64, dd32, ddbf, mean_min, s);
             if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel launch"));
         }
         rc = hipStreamSynchronize(s);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel"));
-        // The digits serve when the bound err / w on a distance, with w the smallest sample's
-        // total branch length, is at most 1e-5 and 1e-13 (worst cases; errors of opposite
-        // sign cancel in a pair's sum, and measured against 64 bits the distances are off
-        // by 2.5e-8, the rounding of FP32 results, and 7e-16).
-        std::vector<double> hw(size_t(std::max<int64_t>(n, 1)), 0.0);
-        if (n > 0) rc = hipMemcpy(hw.data(), e->wu, size_t(n) * 8, hipMemcpyDeviceToHost);
+        double mean = 0.0;
+        rc = hipMemcpy(&mean, mean_min, 8, hipMemcpyDeviceToHost);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalars"));
-        double w_min = 1e300;
-        for (double w : hw)
-            if (w > 0.0) w_min = std::min(w_min, w);
         e->len_exp = t->len_exp;
-        e->len_fixed[0] = t->len_err[0] <= 1e-13 * w_min;
-        e->len_fixed[1] = t->len_err[1] <= 1e-5 * w_min;
-        e->len_fixed[2] = t->len_err[2] <= 1e-5 * w_min;
+        choose_digits(e, mean);
         *out = guard.release();
         return UF_OK;
     }
@@ -1296,7 +1293,7 @@ uf_status uf_embedding_prepare(const uf_embedding* ce, int what, void* stream) {
         hipStream_t s = static_cast<hipStream_t>(stream);
         if ((what & UF_PREP_SCALARS) && e->n > 0) {
             ProfScope ps("sample_scalars", s);
-            UF_HIP(ufk::sample_scalars(*e, e->parent_pos, e->tip_pos, e->d64, e->d32, e->dbf, s));
+            UF_HIP(ufk::sample_scalars(*e, e->parent_pos, e->tip_pos, e->d64, e->d32, e->dbf, nullptr, s));
         }
         const bool sw = (what & UF_PREP_SPLIT_WEIGHTED) != 0, su = (what & UF_PREP_SPLIT_UNWEIGHTED) != 0;
         if (sw || su) {

@@ -4,7 +4,6 @@
 
 #include <hip/hip_runtime.h>
 
-#include <cmath>
 #include <cstddef>
 #include <cstdint>
 #include <memory>
@@ -33,10 +32,7 @@ struct uf_tree {
     std::vector<int32_t> lo, hi;      // tip-rank interval under position k
     std::vector<int32_t> tip_rank;    // by node id, -1 for internal nodes
     std::vector<int32_t> tip_pos;     // position of the tip with rank r
-    // lengths in fixed point (FP64, FP32-rounded, BF16 hi + lo): every one is below
-    // 2^len_exp, and rounding them to the digits of their kind is off by len_err in all
-    int len_exp = 0;
-    double len_err[3] = {HUGE_VAL, HUGE_VAL, HUGE_VAL};
+    int len_exp = 0;                  // every length is below 2^len_exp, also FP32- and BF16-rounded
 };
 
 // A validated table: per sample, its nonzero entries sorted by tip rank.
@@ -107,10 +103,10 @@ struct uf_embedding {
     int64_t max_total = 0;  // largest sample total T_s (host copy)
     int64_t n_tips = 0;     // of the tree
     // fixed-point lengths of the unweighted Gram product on presence bits: every length
-    // is below 2^len_exp; len_fixed[kind] (FP64, FP32-rounded, BF16 hi + lo lengths) says
-    // that their rounding to the product's digits is negligible
+    // is below 2^len_exp; len_digits[kind] (FP64, FP32-rounded, BF16 hi + lo lengths) 7-bit
+    // digits below that serve (0: none do)
     int len_exp = 0;
-    bool len_fixed[3] = {false, false, false};
+    int len_digits[3] = {0, 0, 0};
     // table
     int64_t* row_ptr = nullptr;   // [n+1]
     int32_t* rank = nullptr;      // [nnz]
@@ -135,7 +131,7 @@ struct uf_embedding {
     SplitScratch split_tmp;
     std::mutex split_mu;
     int32_t* parent_pos = nullptr;  // [nb+1], -1 for the root
-    int4* nodes = nullptr;          // [nb+1] lo, hi, parent_pos, 0
+    int4* nodes = nullptr;          // [nb+1] lo, hi, parent_pos, branches of nonzero length up to the root
     int32_t* tip_pos = nullptr;     // [n_tips] position of the tip with rank r
     std::vector<int32_t> sub_first; // host, [nb]: first position of each position's subtree
     // root distances by position for the three length roundings (per-sample scalars)
@@ -194,11 +190,14 @@ constexpr int kGramT = 256;       // square tile of the MFMA Gram kernel
 constexpr int kGramK = 128;        // K step of the MFMA Gram kernel
 constexpr int kGramKPad = 256;    // K of its presence matrix is padded to this (steps go in pairs)
 
-// Per-sample scalars from the postorder leaf intervals (one wave per sample).
-hipError_t pack_nodes(const uf_embedding& e, hipStream_t st);   // fills e.nodes
+// e.nodes; above: branches of nonzero length from each position to the root.
+hipError_t pack_nodes(const uf_embedding& e, const int32_t* above, hipStream_t st);
+// Per-sample scalars from the postorder leaf intervals (one wave per sample).  mean_min
+// (nullable): lowered to the smallest mean length of the branches a sample touches (those
+// of nonzero length), as the bits of a double.
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos,
                           const int32_t* tip_pos, const double* d64, const double* d32,
-                          const double* dbf, hipStream_t st);
+                          const double* dbf, unsigned long long* mean_min, hipStream_t st);
 
 // Sample-major presence P[s][k]: FP8 e4m3 -2.0 (0xC0) where present, else 0, k < kpad (zero beyond
 // kc), for positions [k0, k0+kc), or for positions list[k0 .. k0+kc) when list is
@@ -225,14 +224,14 @@ hipError_t gram_mfma(const uint8_t* P, const uint16_t* hi, const uint16_t* lo, i
 // as in uf.h.  split_m (nullable, fixed point with step split_unit, sample-major:
 // M[i*(se-sb) + s-sb]) carries the non-dense branches: kind 0 adds sigma_i + sigma_j -
 // 2 M to the numerator, kind 1 adds M to the Gram value.
-// kind 3: kind 1 with the Gram value's upper part in acc (in units of 2^28) and its lower
-// part in diag (one element per accumulator element), both in units of acc_scale.
+// kind 2: unweighted from exact integers (FP64): acc holds the Gram values [se-sb][n], then
+// w of every sample [n] from the same lengths; kind 3: two such parts, the upper one (in
+// units of 2^28) and the lower.
 constexpr int kAccF32 = 0, kAccF64 = 1, kAccU32 = 2;
 hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, const double* scal,
                     int64_t n, int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
                     hipStream_t st, const unsigned long long* split_m = nullptr,
-                    const unsigned long long* sigma = nullptr, double split_unit = 0x1p-40,
-                    const void* diag = nullptr);
+                    const unsigned long long* sigma = nullptr, double split_unit = 0x1p-40);
 
 // Row sums of -d^2/2 over the distinct pairs of stripes [sb, se): two fixed-order stages.
 hipError_t row_sums(const double* q, int64_t n, int64_t sb, int64_t se, double* partial,

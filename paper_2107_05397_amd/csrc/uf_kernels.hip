@@ -42,19 +42,24 @@ __device__ __forceinline__ double wave_sum(double v) {
 //      = sum_k D(t_k) - sum_k D(lca(t_k, t_{k+1}))  for tips in rank order,
 // which is sum_v l_v a_v.  D is the root distance with FP64, FP32-rounded or
 // BF16 hi+lo lengths.  Lane sums and the wave reduction run in a fixed order.
+//   MEAN: *mean_min = min(itself, w / touched branches of nonzero length), likewise from
+// the numbers of such branches up to the root (nodes[v].w); as bits, which order as the
+// values do.
 // ----------------------------------------------------------------------------
+template <bool MEAN>
 __global__ __launch_bounds__(256) void k_sample_scalars(
     int64_t n, const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ rank,
     const int64_t* __restrict__ cum, const double* __restrict__ total,
     const int32_t* __restrict__ parent_pos, const int32_t* __restrict__ hi,
     const int32_t* __restrict__ tip_pos, const double* __restrict__ d64,
     const double* __restrict__ d32, const double* __restrict__ dbf, double* __restrict__ sw,
-    double* __restrict__ wu, double* __restrict__ wu32, double* __restrict__ wub) {
+    double* __restrict__ wu, double* __restrict__ wu32, double* __restrict__ wub,
+    const int4* __restrict__ nodes, unsigned long long* __restrict__ mean_min) {
     const int lane = threadIdx.x & 63;
     const int64_t s = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (s >= n) return;
     const int64_t a = row_ptr[s], b = row_ptr[s + 1];
-    double x = 0.0, w = 0.0, w32 = 0.0, wb = 0.0;
+    double x = 0.0, w = 0.0, w32 = 0.0, wb = 0.0, k = 0.0;
     for (int64_t e = a + lane; e < b; e += 64) {
         const int32_t r = rank[e];
         const int32_t tp = tip_pos[r];
@@ -63,6 +68,7 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
         w += d64[tp];
         w32 += d32[tp];
         wb += dbf[tp];
+        if constexpr (MEAN) k += nodes[tp].w;
         if (e + 1 < b) {
             const int32_t r2 = rank[e + 1];
             int32_t p = tp;
@@ -70,6 +76,7 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
             w -= d64[p];
             w32 -= d32[p];
             wb -= dbf[p];
+            if constexpr (MEAN) k -= nodes[p].w;
         }
     }
     x = wave_sum(x);
@@ -81,6 +88,11 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
         wu[s] = w;
         wu32[s] = w32;
         wub[s] = wb;
+    }
+    if constexpr (MEAN) {
+        k = wave_sum(k);
+        if (lane == 0 && k > 0.0)
+            atomicMin(mean_min, (unsigned long long)__double_as_longlong(fmax(w, 0.0) / k));
     }
 }
 
@@ -681,33 +693,53 @@ struct FinIn {
     unsigned long long m;          // split: exact pair sum in the split's unit
     unsigned long long sg_i, sg_j; // weighted split: sigma of both samples
     double sc_i, sc_j;             // per-sample scalars
-    A dg_i;                        // kind 3: lower part
+    A w_i, w_j;                    // kinds 2, 3: sums of both samples (of the upper part)
+    A lo, wl_i, wl_j;              // kind 3: the same of the lower part
 };
 
 // Loads only (no arithmetic on the loaded values, so that the loads of several
 // elements stay in flight together).  Indices must be in range.
 template <typename A, int KIND, bool SPLIT>
 __device__ __forceinline__ FinIn<A, KIND, SPLIT> final_inputs(
-    const A* __restrict__ acc, const double* __restrict__ scal, int64_t n, int64_t sb, int64_t s,
-    int64_t i, int64_t j, const unsigned long long* __restrict__ sigma,
-    const A* __restrict__ diag) {
+    const A* __restrict__ acc, const double* __restrict__ scal, int64_t n, int64_t sb, int64_t se,
+    int64_t s, int64_t i, int64_t j, const unsigned long long* __restrict__ sigma) {
     FinIn<A, KIND, SPLIT> f;
     f.acc = acc[(s - sb) * n + i];
     if constexpr (SPLIT && KIND == 0) {
         f.sg_i = sigma[i];
         f.sg_j = sigma[j];
     }
-    f.sc_i = scal[i];
-    f.sc_j = scal[j];
-    if constexpr (KIND == 3) f.dg_i = diag[(s - sb) * n + i];
+    if constexpr (KIND < 2) {
+        f.sc_i = scal[i];
+        f.sc_j = scal[j];
+    } else {
+        const A* w = acc + (se - sb) * n;
+        f.w_i = w[i];
+        f.w_j = w[j];
+        if constexpr (KIND == 3) {
+            f.lo = w[n + (s - sb) * n + i];
+            f.wl_i = w[n + (se - sb) * n + i];
+            f.wl_j = w[n + (se - sb) * n + j];
+        }
+    }
     return f;
 }
 
 template <typename A, int KIND, bool SPLIT>
 __device__ __forceinline__ double final_distance(const FinIn<A, KIND, SPLIT>& f, double acc_scale,
                                                  double split_unit) {
+    if constexpr (KIND >= 2) {
+        // integers: exact differences in each part (below 2^53), one rounding where the parts
+        // meet; 0 <= xr <= orr, and equal samples give exactly 0
+        double orr = f.w_i + f.w_j - f.acc, xr = orr - f.acc;
+        if constexpr (KIND == 3) {
+            const double ol = f.wl_i + f.wl_j - f.lo, xl = ol - f.lo;
+            orr = fma(orr, 0x1p28, ol);
+            xr = fma(xr, 0x1p28, xl);
+        }
+        return orr > 0.0 ? xr / orr : 0.0;
+    }
     double num = double(f.acc) * acc_scale;
-    if constexpr (KIND == 3) num = (double(f.acc) * 0x1p28 + double(f.dg_i)) * acc_scale;
     if constexpr (SPLIT) {
         if constexpr (KIND == 0) {
             const long long r = (long long)(f.sg_i + f.sg_j - 2ull * f.m);
@@ -736,7 +768,7 @@ __global__ __launch_bounds__(256) void k_finalize(const A* __restrict__ acc, dou
                                                   void* __restrict__ out, double* __restrict__ q,
                                                   const unsigned long long* __restrict__ split_m,
                                                   const unsigned long long* __restrict__ sigma,
-                                                  const A* __restrict__ diag, double split_unit) {
+                                                  double split_unit) {
     // row pitch 66 doubles: the run over s (step 66) has 4-way and the
     // anti-diagonal run (step -65) no LDS bank conflicts
     __shared__ double tile[kFinT][kFinT + 2];
@@ -780,8 +812,8 @@ __global__ __launch_bounds__(256) void k_finalize(const A* __restrict__ acc, dou
                 const int ls = (tid >> 6) + 4 * (8 * half + u);
                 const int64_t sc = s0 + ls < se ? s0 + ls : se - 1;
                 const int64_t jc = ic + sc + 1;   // below 2 n
-                in[u] = final_inputs<A, KIND, SPLIT>(acc, scal, n, sb, sc, ic, jc < n ? jc : jc - n,
-                                                     sigma, diag);
+                in[u] = final_inputs<A, KIND, SPLIT>(acc, scal, n, sb, se, sc, ic, jc < n ? jc : jc - n,
+                                                     sigma);
                 if constexpr (SPLIT) in[u].m = (unsigned long long)__double_as_longlong(tile[ls][li]);
             }
 #pragma unroll
@@ -888,10 +920,11 @@ __global__ __launch_bounds__(256) void k_grand_mean(const double* __restrict__ r
 // One 16-byte record a position, so that a step of a walk up the tree touches one line.
 __global__ __launch_bounds__(256) void k_pack_nodes(const int32_t* __restrict__ lo,
                                                     const int32_t* __restrict__ hi,
-                                                    const int32_t* __restrict__ parent, int64_t m,
+                                                    const int32_t* __restrict__ parent,
+                                                    const int32_t* __restrict__ above, int64_t m,
                                                     int4* __restrict__ nodes) {
     const int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (v < m) nodes[v] = make_int4(lo[v], hi[v], parent[v], 0);
+    if (v < m) nodes[v] = make_int4(lo[v], hi[v], parent[v], above[v]);
 }
 
 __global__ void k_zero_u32(unsigned* __restrict__ p, int64_t n) {
@@ -906,20 +939,20 @@ inline unsigned grid_y(int64_t v) { return unsigned(v < 65535 ? (v < 1 ? 1 : v) 
 // ============================================================================
 // launchers
 // ============================================================================
-hipError_t pack_nodes(const uf_embedding& e, hipStream_t st) {
+hipError_t pack_nodes(const uf_embedding& e, const int32_t* above, hipStream_t st) {
     const int64_t m = e.nb + 1;
     hipLaunchKernelGGL(k_pack_nodes, dim3(unsigned((m + 255) / 256)), dim3(256), 0, st, e.lo, e.hi,
-                       e.parent_pos, m, e.nodes);
+                       e.parent_pos, above, m, e.nodes);
     return hipGetLastError();
 }
 
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos, const int32_t* tip_pos,
                           const double* d64, const double* d32, const double* dbf,
-                          hipStream_t st) {
+                          unsigned long long* mean_min, hipStream_t st) {
     const unsigned blocks = unsigned((e.n + 3) / 4);
-    hipLaunchKernelGGL(k_sample_scalars, dim3(blocks), dim3(256), 0, st, e.n, e.row_ptr, e.rank,
-                       e.cum, e.total, parent_pos, e.hi, tip_pos, d64, d32, dbf, e.sw, e.wu,
-                       e.wu32, e.wub);
+    hipLaunchKernelGGL(mean_min ? k_sample_scalars<true> : k_sample_scalars<false>, dim3(blocks), dim3(256),
+                       0, st, e.n, e.row_ptr, e.rank, e.cum, e.total, parent_pos, e.hi, tip_pos, d64, d32,
+                       dbf, e.sw, e.wu, e.wu32, e.wub, e.nodes, mean_min);
     return hipGetLastError();
 }
 
@@ -968,27 +1001,27 @@ template <typename A, int KIND, bool SPLIT>
 static hipError_t finalize_as(const void* acc, double acc_scale, const double* scal, int64_t n,
                               int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
                               hipStream_t st, const unsigned long long* split_m,
-                              const unsigned long long* sigma, double split_unit, const void* diag) {
+                              const unsigned long long* sigma, double split_unit) {
     const int64_t gx = (n + kFinT - 1) / kFinT;
     if (gx > 0x7fffffff) return hipErrorInvalidValue;
     dim3 grid(unsigned(gx), grid_y((se - sb + kFinT - 1) / kFinT));
     hipLaunchKernelGGL((k_finalize<A, KIND, SPLIT>), grid, dim3(256), 0, st, static_cast<const A*>(acc),
-                       acc_scale, scal, n, sb, se, layout, out_f32, out, q, split_m, sigma,
-                       static_cast<const A*>(diag), split_unit);
+                       acc_scale, scal, n, sb, se, layout, out_f32, out, q, split_m, sigma, split_unit);
     return hipGetLastError();
 }
 
 hipError_t finalize(int kind, const void* acc, int acc_type, double acc_scale, const double* scal,
                     int64_t n, int64_t sb, int64_t se, int layout, int out_f32, void* out, double* q,
                     hipStream_t st, const unsigned long long* split_m,
-                    const unsigned long long* sigma, double split_unit, const void* diag) {
+                    const unsigned long long* sigma, double split_unit) {
     if (se <= sb || n <= 0) return hipSuccess;
 #define UF_FIN(T_, A_, K_, S_)                                                                       \
     if (acc_type == T_ && kind == K_ && (split_m != nullptr) == S_)                                   \
         return finalize_as<A_, K_, S_>(acc, acc_scale, scal, n, sb, se, layout, out_f32, out, q, st, \
-                                       split_m, sigma, split_unit, diag);
+                                       split_m, sigma, split_unit);
     UF_FIN(kAccF64, double, 0, false)
     UF_FIN(kAccF64, double, 1, false)
+    UF_FIN(kAccF64, double, 2, false)
     UF_FIN(kAccF64, double, 3, false)
     UF_FIN(kAccU32, uint32_t, 0, true)
     UF_FIN(kAccF32, float, 0, false)
