@@ -151,7 +151,9 @@ uf_status uf_embedding_prepare(const uf_embedding* emb, int what, void* hip_stre
 /* Bytes of device workspace needed by a uf_dm_* call with the same
  * arguments.  weighted: 1 for the weighted-normalized variant, 0 for
  * unweighted.  want_row_stats: non-zero if the call will request row sums /
- * means.  The node-chunk length follows uf_set_chunk_nodes(). */
+ * means.  The node-chunk length follows uf_set_chunk_nodes(); UF_FP64, UF_FP32
+ * and UF_MFMA_BF16X2 of the unweighted variant also hold the presence bits of all
+ * tips, about N x tips / 7.5 bytes. */
 uf_status uf_workspace_size(const uf_embedding* emb, int weighted, uf_precision precision,
                             int64_t stripe_begin, int64_t stripe_end, int want_row_stats,
                             size_t* bytes);

@@ -487,9 +487,9 @@ struct Plan {
     int form = ufx::kPairMin;
     int64_t seg = 0, n_planes = 0, plane = 0;
     // Gram product on presence bits: length digits (4 or 8; 0: not taken), length kind,
-    // ranges of a chunk side by side
+    // ranges of a chunk side by side, stripes taken at a time
     int digits = 0, len_kind = 0;
-    int64_t splits = 0;
+    int64_t splits = 0, sr_part = 0;
     size_t off_acc = 0, off_q = 0, off_chunk = 0, off_part = 0, off_rm = 0, off_m = 0,
            off_planes = 0, total = 0;
 };
@@ -538,9 +538,16 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     p->pairs = !bits && !mfma && !fixed;
     p->form = weighted ? ufx::kPairL1 : ufx::kPairMin;
     p->seg = p->pairs ? ufx::pair_segment(n, nb) : 0;
-    // sums of one segment or range: with the bits one plane per four digits, each with the
-    // samples' own sums after the pairs'
-    p->plane = bits ? (p->sr + 1) * n * (p->digits / 4) : p->sr * n;
+    // sums of one segment or range: with the bits one plane of FP64 integers per four digits,
+    // each with the samples' own sums after the pairs'.  That is two to four times the FP64
+    // or FP32 sums, so where it comes to more than 1 GiB the stripes are taken in as many
+    // parts as keep the whole to their size (FP64 from 11,600 samples on).
+    p->sr_part = p->sr;
+    auto bits_plane = [&] { return (p->sr_part + 1) * n * (p->digits / 4); };
+    const double most = std::max(double(p->sr * n) * (prec == UF_FP64 ? 8 : 4), 0x1p30) + double(2 * n * p->digits * 2);
+    for (int64_t parts = 2; bits && p->sr_part > 1 && double(bits_plane()) * 8 > most; ++parts)
+        p->sr_part = (p->sr + parts - 1) / parts;
+    p->plane = bits ? bits_plane() : p->sr * n;
     const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
     // workspace layout for a chunk of kc branches; planes: segments held side by side
     auto layout = [&](int64_t kc, int64_t planes) {
@@ -598,7 +605,9 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         const double row = bits       ? double((n + 63) / 64 * 8)
                            : p->pairs ? double((n + 63) / 64 * 64) * double(elem)
                                       : double(n) * double(elem);
-        kc = static_cast<int64_t>(budget / std::max(row, 1.0));
+        // (the bits of the tips, which the chunks are made from, count too)
+        const double fixed_part = bits ? std::min(double(ufb::bits_plan(n, e->n_tips, 0).off_any), 0.875 * budget) : 0.0;
+        kc = static_cast<int64_t>((budget - fixed_part) / std::max(row, 1.0));
         // whole segments per chunk, to run side by side
         if (p->pairs && kc < nb && kc > p->seg) kc -= kc % p->seg;
     }
@@ -654,30 +663,34 @@ uf_status run_pairs(const Plan& p, int64_t nb, const char* name, char* base, hip
     return UF_OK;
 }
 
-// Unweighted dense part on presence bits.  Every sum is an exact integer (in FP64), so
-// chunks and ranges add in any order to the same value.
-uf_status run_bits(const uf_embedding* e, const Plan& p, uf_precision prec, char* base, hipStream_t s) {
+// Unweighted dense part on presence bits, stripes [sb, se).  Every sum is an exact integer
+// (in FP64), so chunks and ranges add in any order to the same value.
+uf_status run_bits(const uf_embedding* e, const Plan& p, uf_precision prec, int64_t sb, int64_t se, char* base,
+                   hipStream_t s) {
     double* acc = reinterpret_cast<double*>(base + p.off_acc);
     double* planes = reinterpret_cast<double*>(base + p.off_planes);
     void* ws = base + p.off_chunk;
     const ufp::Emb ev = emb_view(*e);
-    if (p.nchunks > 0) {
+    const bool begun = sb > p.sb;     // the tips' bits, and those of a lone chunk, are there
+    const int64_t plane = (se - sb + 1) * p.n * (p.digits / 4);
+    if (p.nchunks == 0) UF_HIP(ufk::zero_u32(reinterpret_cast<unsigned*>(acc), 2 * plane, s));
+    if (p.nchunks > 0 && !begun) {
         ProfScope ps("embed_pres", s);
         UF_HIP(ufb::tip_bits(ev, e->n_tips, ws, s));
     }
     for (int64_t c = 0; c < p.nchunks; ++c) {
         const int64_t k0 = c * p.kc, kc = std::min<int64_t>(p.kc, e->nb - k0);
-        {
+        if (!begun || p.nchunks > 1) {
             ProfScope ps("embed_pres", s);
             UF_HIP(ufb::branch_bits(ev, e->n_tips, p.len_kind, e->len32, e->len_hi, e->len_lo,
                                     std::ldexp(1.0, ufb::kDigitBits * p.digits - e->len_exp), k0, kc, ws, s));
         }
         ProfScope ps(prec == UF_FP64 ? "band_uw_f64" : prec == UF_FP32 ? "band_uw_f32" : "gram_mfma", s);
         if (p.splits > 1) {
-            UF_HIP(ufb::gram_bits(p.digits, p.n, e->n_tips, kc, p.splits, p.sb, p.se, 0, planes, ws, s));
-            UF_HIP(ufx::pair_planes<double>(planes, p.plane, p.splits, c == 0, acc, s));
+            UF_HIP(ufb::gram_bits(p.digits, p.n, e->n_tips, kc, p.splits, sb, se, 0, planes, ws, s));
+            UF_HIP(ufx::pair_planes<double>(planes, plane, p.splits, c == 0, acc, s));
         } else {
-            UF_HIP(ufb::gram_bits(p.digits, p.n, e->n_tips, kc, 1, p.sb, p.se, c > 0, acc, ws, s));
+            UF_HIP(ufb::gram_bits(p.digits, p.n, e->n_tips, kc, 1, sb, se, c > 0, acc, ws, s));
         }
     }
     return UF_OK;
@@ -721,8 +734,15 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
     const SplitCache* sp = split ? hold.get() : nullptr;
     // Dense part: node chunks (all branches, or the split's dense list) into acc.
     if (p.digits) {
-        st = run_bits(e, p, prec, base, s);
-        if (st != UF_OK) return st;
+        for (int64_t b = sb; b < se; b += p.sr_part) {
+            const int64_t to = std::min(se, b + p.sr_part), done = (b - sb) * p.n;
+            st = run_bits(e, p, prec, b, to, base, s);
+            if (st != UF_OK) return st;
+            ProfScope ps("finalize", s);
+            char* part = static_cast<char*>(out) + (layout == UF_STRIPES ? done * (odt == UF_OUT_F32 ? 4 : 8) : 0);
+            UF_HIP(ufk::finalize(p.digits == 8 ? 3 : 2, acc, ufk::kAccF64, 1.0, nullptr, p.n, b, to, layout,
+                                 odt == UF_OUT_F32 ? 1 : 0, part, q ? q + done : nullptr, s));
+        }
     } else if (p.pairs) {
         const ufp::Emb ev = emb_view(*e);
         const char* name = prec == UF_FP64 ? (weighted ? "band_wn_f64" : "band_uw_f64")
@@ -774,8 +794,8 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
                                   p.se, first, static_cast<float*>(acc), s));
         }
     }
-    if (p.nchunks == 0) {  // no (dense) branch: the dense part is 0
-        const int64_t words = p.plane * (prec == UF_FP64 || p.digits ? 2 : 1);
+    if (p.nchunks == 0 && !p.digits) {  // no (dense) branch: the dense part is 0
+        const int64_t words = p.plane * (prec == UF_FP64 ? 2 : 1);
         UF_HIP(ufk::zero_u32(static_cast<unsigned*>(acc), words, s));
     }
     // Non-dense part of a split: exact fixed-point pair sums into M (every
@@ -788,12 +808,11 @@ uf_status run_dm(const uf_embedding* e, int weighted, uf_precision prec, int64_t
     }
     const double* scal = weighted ? e->sw
                                   : (prec == UF_FP64 ? e->wu : (prec == UF_FP32 ? e->wu32 : e->wub));
-    {
+    if (!p.digits) {
         ProfScope ps("finalize", s);
         const bool fixed = sp && weighted && sp->q_scale > 0.0;
-        const int acc_type = prec == UF_FP64 || p.digits ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
-        const int kind = p.digits == 8 ? 3 : p.digits ? 2 : weighted ? 0 : 1;
-        UF_HIP(ufk::finalize(kind, acc, acc_type, fixed ? 1.0 / sp->q_scale : 1.0, scal, p.n, p.sb, p.se, layout,
+        const int acc_type = prec == UF_FP64 ? ufk::kAccF64 : (fixed ? ufk::kAccU32 : ufk::kAccF32);
+        UF_HIP(ufk::finalize(weighted ? 0 : 1, acc, acc_type, fixed ? 1.0 / sp->q_scale : 1.0, scal, p.n, p.sb, p.se, layout,
                              odt == UF_OUT_F32 ? 1 : 0, out, q, s, M, sp && weighted ? sp->sigma : nullptr,
                              sp && weighted ? sp->unit : 0x1p-40));
     }

@@ -1,0 +1,64 @@
+"""Workspace of large unweighted matrices and of batches of very many tables: bounded by the
+results and the chunk, and the parts that they are then taken in give the same bits."""
+import numpy as np
+import pytest
+
+import paper_2107_05397_amd as uf
+import synth
+
+from ._util import random_rows, table as make_table
+
+pytestmark = pytest.mark.gpu
+
+GIB = 1 << 30
+
+
+def _embedding(n, n_tips, seed):
+    import torch  # noqa: F401
+    rng = np.random.default_rng(seed)
+    tree = synth.gen_tree(n_tips, 0.05, seed)
+    some = random_rows(rng, np.arange(n_tips), 500, max_nnz=n_tips // 6)
+    table = make_table([some[k] for k in rng.integers(0, 500, n)])
+    t = uf.Tree(tree.parent, tree.length)
+    return uf.Embedding(t, uf.Table(t, table.indptr, table.tips, table.counts))
+
+
+def test_unweighted_workspace_holds_one_sum_per_pair():
+    n = 60000
+    emb = _embedding(n, 60, 1)
+    for precision, elem in (("fp64", 8), ("fp32", 4), ("mfma", 4)):
+        for means in (False, True):
+            got = uf.workspace_size(emb, "unweighted", precision, row_stats=means)
+            assert got <= (elem + 8 * means) * (n // 2) * n + (9 + 2 * means) * GIB, (precision, means)
+    few = uf.workspace_size(_embedding(300, 60, 2), "unweighted", "fp64")
+    assert few <= 64 << 20
+
+
+# just above 1 GiB of sums: two parts; even and odd
+@pytest.mark.parametrize("n,precision", [(11600, "fp64"), (11701, "fp64"), (16500, "fp32")])
+def test_unweighted_in_parts(n, precision):
+    import torch
+    emb = _embedding(n, 60, n)
+    full, rm, gm = uf.dm(emb, "unweighted", precision, row_means=True)
+    s = n // 2
+    buf = torch.full_like(full, -1.0)
+    for k in range(4):
+        uf.dm_stripes(emb, "unweighted", precision, s * k // 4, s * (k + 1) // 4, layout="condensed", out=buf)
+    assert torch.equal(buf, full)
+    stripes, _ = uf.dm_stripes(emb, "unweighted", precision, 0, s, out_dtype=torch.float64)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    a = torch.randint(0, s, (1 << 20,), generator=g, device="cuda")
+    i = torch.randint(0, n, (1 << 20,), generator=g, device="cuda")
+    j = (i + a + 1) % n
+    lo, hi = torch.minimum(i, j), torch.maximum(i, j)
+    assert torch.equal(stripes[a, i], full[lo * n - lo * (lo + 1) // 2 + hi - lo - 1])
+    # row means of -d^2/2 from the stripes: n terms of at most 1/2, each rounded, in any order
+    q = -0.5 * stripes * stripes
+    if n % 2 == 0:
+        q[-1, s:] = 0.0
+    sums = q.sum(0)
+    for k in range(0, s, 64):
+        for t in range(k, min(s, k + 64)):
+            sums += torch.roll(q[t], t + 1)
+    assert torch.max(torch.abs(sums / n - rm)).item() <= 2.0 ** -53 * (n + 4)
+    assert abs(float(gm) - float(rm.mean())) <= 2.0 ** -53 * (n + 4)
