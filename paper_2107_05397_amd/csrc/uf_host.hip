@@ -1470,6 +1470,7 @@ struct uf_batch {
     int32_t* d_tab_of = nullptr;
     int4* d_items = nullptr;
     int64_t max_plane = 0;
+    bool side_by_side = true;                 // segments, each to its own plane
     size_t off_mask = 0, chunk_bytes = 0;     // of a chunk of all tables
     size_t off_E = 0, off_acc = 0, ws_total = 0;
     hipStream_t cap = nullptr;                // capture stream (default priority)
@@ -1591,6 +1592,7 @@ const char* tune_path(const char* p) { return p ? p : std::getenv("UF_TUNE_CACHE
 // on XCD p mod 8: every table's list is cut in eighths, one per XCD (table -1: none), so
 // that each XCD reads its own part and has the same work; tables with the longest
 // segments come first.  wide: the tables of ufx::kPairWideN samples and more, else the rest.
+// A table of several segments that has one plane only takes them all in one item.
 std::vector<int4> batch_items(const std::vector<BatchTable>& tabs, bool wide) {
     constexpr int64_t G = 8;
     std::vector<size_t> order(tabs.size());
@@ -1602,7 +1604,8 @@ std::vector<int4> batch_items(const std::vector<BatchTable>& tabs, bool wide) {
         if (t.n < 2 || (t.n >= ufx::kPairWideN) != wide) continue;
         const int64_t nblk = (t.n + 63) / 64;
         own.clear();
-        for (int64_t g = 0; g < t.n_seg; ++g)
+        const bool all = t.n_seg == 1 && t.p_off != t.acc_off;
+        for (int64_t g = all ? -1 : 0; g < (all ? 0 : t.n_seg); ++g)
             for (int64_t r0 = 0; r0 < nblk; r0 += G)
                 for (int64_t c0 = r0; c0 < nblk; c0 += G)
                     for (int64_t bi = r0; bi < std::min(nblk, r0 + G); ++bi)
@@ -1620,11 +1623,12 @@ std::vector<int4> batch_items(const std::vector<BatchTable>& tabs, bool wide) {
 // samples i a wave, as single calls take them, the others as configured.
 hipError_t batch_tiles(const uf_batch* b, const void* chunk, int64_t k0, int64_t kc, float* acc, int ks, int w,
                        int ts, hipStream_t s) {
-    const hipError_t er = ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_wide, k0, kc, acc,
-                                           ks, w, 256, s);
+    const bool last = k0 + kc == b->emb->nb;
+    const hipError_t er = ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_wide, false, k0, kc,
+                                           last, acc, ks, w, 256, s);
     if (er != hipSuccess) return er;
-    return ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items + b->n_wide, b->n_items - b->n_wide, k0,
-                            kc, acc, ks, w, ts, s);
+    return ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items + b->n_wide, b->n_items - b->n_wide,
+                            !b->side_by_side, k0, kc, last, acc, ks, w, ts, s);
 }
 
 // enqueue the whole batch on stream s (also used under graph capture)
@@ -1768,11 +1772,28 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
         uf_status st = embed_impl(tree, &cat, stream, &b->emb);
         if (st != UF_OK) return st;
         b->n_tables = n_tables;
-        // chunk length: 16 GiB of embedding for all tables, or the process-wide setting
-        // (32-bit offsets inside a chunk)
+        // chunk length: 16 GiB of embedding for all tables (whose samples are padded to
+        // blocks of 64, each with its masks), or the process-wide setting (32-bit offsets
+        // inside a chunk)
         const int64_t n_all = std::max<int64_t>(cat.n_samples, 1);
+        int64_t n_blocks = 0;
+        double planes = 0.0;
+        auto segments = [&](int64_t n) {
+            const int64_t nb = std::max<int64_t>(b->emb->nb, 1), seg = ufx::pair_segment(n, nb);
+            return (nb + seg - 1) / seg;
+        };
+        for (int64_t r = 0; r < n_tables; ++r) {
+            const int64_t n = tables[r]->n_samples, n_seg = segments(n);
+            n_blocks += (n + 63) / 64;
+            if (n_seg > 1) planes += double(n_seg) * double(n / 2 * n) * 4.0;
+        }
+        // Segments have a plane each, to run side by side, while these come to 4 GiB at most
+        // (12 MB a table at most; hundreds of tables fill the chip without); else one plane,
+        // segment after segment, with the same sums.
+        b->side_by_side = planes <= 0x1p32;
         int64_t kc = g_chunk_nodes.load();
-        if (kc <= 0) kc = int64_t(16.0 * 1024 * 1024 * 1024 / (double(n_all) * 4.0));
+        if (kc <= 0)
+            kc = int64_t(16.0 * 1024 * 1024 * 1024 / (double(std::max<int64_t>(n_blocks, 1)) * (64 * 4 + 8)));
         kc = std::min<int64_t>(kc, int64_t(1) << 22);
         kc = std::min<int64_t>(std::max<int64_t>(kc, 32), std::max<int64_t>(b->emb->nb, 1));
         b->kc = kc;
@@ -1789,11 +1810,15 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
             t.m_off = moff;
             t.plane = (t.n / 2) * t.n;
             t.seg = ufx::pair_segment(t.n, b->emb->nb);
-            t.n_seg = (std::max<int64_t>(b->emb->nb, 1) + t.seg - 1) / t.seg;
+            t.n_seg = segments(t.n);
             const int64_t room = (t.plane + 63) / 64 * 64;
             t.acc_off = aoff;
             aoff += room;
             t.p_off = t.n_seg > 1 ? aoff : t.acc_off;
+            if (t.n_seg > 1 && !b->side_by_side) {
+                t.n_seg = 1;
+                aoff += room;
+            }
             if (t.n_seg > 1) aoff += (t.n_seg * t.plane + 63) / 64 * 64;
             b->tabs.push_back(t);
             b->max_plane = std::max(b->max_plane, t.n_seg > 1 ? t.plane : 0);

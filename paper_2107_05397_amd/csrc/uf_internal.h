@@ -173,10 +173,11 @@ struct BatchTable {
     int64_t e_off;    // element offset of its values in a chunk
     int64_t m_off;    // element offset of its masks
     int64_t acc_off;  // element offset of its stripe-major accumulator [n/2][n]
-    int64_t p_off;    // element offset of its segments' planes (n_seg == 1: acc_off)
+    int64_t p_off;    // element offset of its segments' planes (n_seg == 1: acc_off, or with
+                      // segments one after the other the running one's)
     int64_t plane;    // elements of a plane
     int64_t seg;      // branches per segment
-    int64_t n_seg;
+    int64_t n_seg;    // planes (1: sums end up at acc_off)
 };
 
 // ---------------------------------------------------------------------------

@@ -206,11 +206,13 @@ __device__ __forceinline__ void wave_sync() {
 // 6.4 ms; 5,000 x 40,000 33.5 -> 16.5 ms, there bound by the rows that miss the caches;
 // 10,000 x 2,000 5.4 -> 5.4.
 constexpr int kWin = kPairWin;
+// total (nullable): the sums go there instead, added to what it holds (more) or not.
 template <typename T, int A, int U, bool L1>
 __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
                                           const unsigned long long* __restrict__ mask, int kc,
                                           int64_t kcp, int n, int64_t bi, int64_t bj, int ig, int k_lo,
-                                          int k_hi, int sb, int se, bool load, T* out) {
+                                          int k_hi, int sb, int se, bool load, T* out,
+                                          T* total = nullptr, bool more = false) {
     constexpr int PER = 16 / A;             // branches per load of x_i
     constexpr int NI = U / PER;
     constexpr int ROW = 64 * int(sizeof(T));
@@ -309,8 +311,10 @@ __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
     for (int a = 0; a < A; ++a) {
         int64_t at, dup;
         if (!slot(a, &at, &dup)) continue;
-        out[at] = r[a];
-        if (dup >= 0) out[dup] = r[a];
+        T* to = total ? total : out;
+        const T v = more ? to[at] + r[a] : r[a];
+        to[at] = v;
+        if (dup >= 0) to[dup] = v;
     }
 }
 
@@ -338,8 +342,10 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
 }
 
 // The same tiles over every table of a batch in one launch: items of 64 x 64 pairs and one
-// segment, 64 / A waves each; block b runs on XCD b mod 8 and so does its item.
-// A segment that an earlier chunk began goes on from its plane.
+// segment, or (-1) all of the table's segments one after the other, 64 / A waves each; block
+// b runs on XCD b mod 8 and so does its item.  A segment that an earlier chunk began goes on
+// from its plane; last: the tree's branches end with this chunk.  ALL: items of all segments
+// occur (compiled apart: the loop over them cost a batch without such items 4%).
 // Every table's segments together fill the chip, so that its launches do not queue up
 // behind small ones.  Eight tables of 300-1,500 samples x 20,000 branches, a whole call:
 // 8.15 ms with 128 x 128 LDS tiles over all branches (about one workgroup of four waves
@@ -348,12 +354,12 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
 // all tables in one list, cut in eighths by count: 7.5 ms (segments differ in length).
 // Three tables of 4,500-9,000 samples x 40,000: 136 -> 87 ms, two of 9,000-16,000 x
 // 100,000: 634 -> 351.
-template <int A, int U>
+template <int A, int U, bool ALL>
 __global__ __launch_bounds__(256) void k_batch_pairs(const float* __restrict__ E,
                                                      const unsigned long long* __restrict__ mask,
                                                      const BatchTable* __restrict__ tabs,
                                                      const int4* __restrict__ items,
-                                                     int k0, int kc, float* __restrict__ acc) {
+                                                     int k0, int kc, int last, float* __restrict__ acc) {
     constexpr int SUB = 64 / (4 * A);       // workgroups per item
     __shared__ uint32_t queue[4][kWin + U];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -364,11 +370,18 @@ __global__ __launch_bounds__(256) void k_batch_pairs(const float* __restrict__ E
     const BatchTable t = tabs[it.x];
     const int n = int(t.n);
     if (it.z * 64 + ig >= n) return;
-    const int64_t s0 = int64_t(it.y) * t.seg;       // the segment's part in this chunk
-    const int k_lo = int(max<int64_t>(s0 - k0, 0)), k_hi = int(min<int64_t>(s0 + t.seg - k0, kc));
-    if (k_lo >= k_hi) return;
-    pair_wave<float, A, U, true>(queue[wave], E + t.e_off, mask + t.m_off, kc, kc, n, it.z, it.w, ig, k_lo,
-                                 k_hi, 0, n / 2, s0 < k0, acc + t.p_off + it.y * t.plane);
+    const bool all = ALL && it.y < 0;
+    const int64_t g_end = all ? (int64_t(k0) + kc - 1) / t.seg : it.y;
+    for (int64_t g = all ? k0 / t.seg : it.y; g <= g_end; ++g) {
+        const int64_t s0 = g * t.seg;               // the segment's part in this chunk
+        const int k_lo = int(max<int64_t>(s0 - k0, 0)), k_hi = int(min<int64_t>(s0 + t.seg - k0, kc));
+        if (k_lo >= k_hi) return;
+        const bool ends = all && (last || s0 + t.seg <= int64_t(k0) + kc);
+        pair_wave<float, A, U, true>(queue[wave], E + t.e_off, mask + t.m_off, kc, kc, n, it.z, it.w, ig, k_lo,
+                                     k_hi, 0, n / 2, s0 < k0, acc + t.p_off + (all ? 0 : g) * t.plane,
+                                     ends ? acc + t.acc_off : nullptr, ends && g > 0);
+        if constexpr (!ALL) break;
+    }
 }
 
 // Every table's sums: its segments' planes in order (tables of one segment have their
@@ -476,27 +489,27 @@ int batch_max_blocks(int stage_branches, int tile_stripes) {
 
 template <int A, int U>
 static hipError_t batch_pairs_as(const float* E, const unsigned long long* mask, const BatchTable* tabs,
-                                 const int4* items, int64_t n_items, int64_t k0, int64_t kc, float* acc,
-                                 int wgs_per_cu, hipStream_t st) {
+                                 const int4* items, int64_t n_items, bool all, int64_t k0, int64_t kc,
+                                 bool last, float* acc, int wgs_per_cu, hipStream_t st) {
     const int64_t blocks = (64 / (4 * A)) * n_items;
     if (blocks > 0x7fffffff || n_items % 8) return hipErrorInvalidValue;
     // one group of 16 waves per CU: each of its four workgroups holds a quarter of the LDS
     const unsigned lds = wgs_per_cu == 1 ? 34 * 1024 : 0;
-    hipLaunchKernelGGL((k_batch_pairs<A, U>), dim3(unsigned(blocks)), dim3(256), lds, st, E, mask, tabs, items,
-                       int(k0), int(kc), acc);
+    hipLaunchKernelGGL((all ? k_batch_pairs<A, U, true> : k_batch_pairs<A, U, false>), dim3(unsigned(blocks)),
+                       dim3(256), lds, st, E, mask, tabs, items, int(k0), int(kc), int(last), acc);
     return hipGetLastError();
 }
 
 hipError_t batch_pairs(const void* chunk, size_t off_mask, const BatchTable* tabs, const int4* items,
-                       int64_t n_items, int64_t k0, int64_t kc, float* acc, int stage_branches,
-                       int wgs_per_cu, int tile_stripes, hipStream_t st) {
+                       int64_t n_items, bool all, int64_t k0, int64_t kc, bool last, float* acc,
+                       int stage_branches, int wgs_per_cu, int tile_stripes, hipStream_t st) {
     const auto* E = static_cast<const float*>(chunk);
     const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + off_mask);
     if (n_items < 1 || kc < 1) return hipSuccess;
     if (wgs_per_cu < 1 || kc > 0x3fffffff) return hipErrorInvalidValue;
 #define UF_BP(KS_, TS_)                            \
     if (stage_branches == KS_ && tile_stripes == TS_) \
-        return batch_pairs_as<TS_ / 16, KS_ / 2>(E, mask, tabs, items, n_items, k0, kc, acc, wgs_per_cu, st);
+        return batch_pairs_as<TS_ / 16, KS_ / 2>(E, mask, tabs, items, n_items, all, k0, kc, last, acc, wgs_per_cu, st);
     UF_BP(8, 64)
     UF_BP(8, 128)
     UF_BP(8, 256)

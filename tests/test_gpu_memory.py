@@ -62,3 +62,53 @@ def test_unweighted_in_parts(n, precision):
             sums += torch.roll(q[t], t + 1)
     assert torch.max(torch.abs(sums / n - rm)).item() <= 2.0 ** -53 * (n + 4)
     assert abs(float(gm) - float(rm.mean())) <= 2.0 ** -53 * (n + 4)
+
+
+def _tables(tree, sizes, n_tips, seed):
+    rng = np.random.default_rng(seed)
+    out = []
+    for n in sizes:
+        x = make_table(random_rows(rng, np.arange(n_tips), n, max_nnz=60))
+        out.append(uf.Table(tree, x.indptr, x.tips, x.counts))
+    return out
+
+
+# (sizes, times, tips): tables of few samples, whose blocks of 64 are mostly padding: the
+# chunk is sized for these; tables whose segments side by side would take more than 4 GiB:
+# one plane each (2,049 tips: 16 segments)
+@pytest.mark.parametrize("sizes,times,n_tips", [((2, 3, 5), 1000, 20000), ((576, 575, 300), 190, 2049)])
+def test_batches_of_very_many_tables(sizes, times, n_tips):
+    import torch
+    tree = synth.gen_tree(n_tips, 0.05, n_tips)
+    t = uf.Tree(tree.parent, tree.length)
+    tabs = _tables(t, sizes, n_tips, n_tips)
+    few = uf.Batch(t, tabs)
+    want = [o.clone() for o in few.run()]
+    for tb, w in zip(tabs, want):
+        d, _, _ = uf.dm(uf.Embedding(t, tb), "weighted_normalized", "fp32", out_dtype=torch.float32)
+        assert torch.equal(d, w)
+    pairs = sum(n // 2 * n for n in sizes) * times
+    try:
+        for nodes in (0, 900):
+            uf.set_chunk_nodes(nodes)
+            b = uf.Batch(t, tabs * times)
+            uf.set_chunk_nodes(0)
+            if nodes == 0:
+                chunk = sum((n + 63) // 64 for n in sizes) * times * (tree.n_nodes + 1) * (64 * 4 + 8)
+                assert b.workspace_size() <= min(chunk, 17 * GIB) + 2 * 4 * pairs + (64 << 20)
+            got = b.run()
+            torch.cuda.synchronize()
+            for k, g in enumerate(got):
+                assert torch.equal(g, want[k % len(sizes)]), (nodes, k)
+            for cfg in ((8, 1, 64), (16, 2, 256)):
+                b.set_config(*cfg)
+                got = b.run()
+                torch.cuda.synchronize()
+                assert all(torch.equal(g, want[k % len(sizes)]) for k, g in enumerate(got)), cfg
+            if nodes == 0:
+                assert b.autotune() > 0
+            b.close()
+            del b, got
+            torch.cuda.empty_cache()
+    finally:
+        uf.set_chunk_nodes(0)
