@@ -963,15 +963,40 @@ __global__ __launch_bounds__(256) void k_rerank(SparseView q, SparseView rf,
 // samples touch the branch, the count and the bits below give the value's place.
 // Groups of W waves take one candidate each, so nothing is reduced over the block for
 // every candidate.  blockIdx.y: a share of the candidates (few queries).
+// A list's entries fall into kRrClasses classes (64 consecutive ones to a class, class after
+// class), whose sums are formed and added in one order whatever W, so that a pair's distance
+// does not depend on the queries and candidates it is asked for with.  A wave takes 16 / W
+// neighbouring classes.
 // With a dense row of the query in memory instead, every entry was a gather of 8
 // bytes from a 1.6 MB row (200,000 branches): 1,500 queries x 100 candidates of 6,000
 // branches 6.5 -> 1.35 ms (zeroing of the rows included). What is left is one pass over
 // each candidate's list, 12 bytes an entry; its cache traffic was not counted.
-constexpr int kRrThreads = 1024, kRrWaves = kRrThreads / 64, kRrU = 8;
+constexpr int kRrThreads = 1024, kRrWaves = kRrThreads / 64, kRrU = 8, kRrClasses = 16;
+
+// Sums of N values over the wave's lanes, value m in the lanes whose top bits are m: steps of
+// OFF, OFF / 2, ... lanes for every value, the first ones on the values that a lane keeps.
+template <int N, int OFF>
+__device__ __forceinline__ double lane_sums(const double* a, int lane) {
+    if constexpr (N == 1) {
+        double v = a[0];
+#pragma unroll
+        for (int off = OFF; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        return v;
+    } else {
+        const bool up = (lane & OFF) != 0;
+        double k[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i)
+            k[i] = (up ? a[i + N / 2] : a[i]) + __shfl_xor(up ? a[i] : a[i + N / 2], OFF, 64);
+        return lane_sums<N / 2, OFF / 2>(k, lane);
+    }
+}
+
+template <int W>
 __global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, SparseView rf,
                                                             const int32_t* __restrict__ qids,
                                                             const int32_t* __restrict__ cand,
-                                                            int64_t nq, int kc, int share, int W,
+                                                            int64_t nq, int kc, int share,
                                                             int words, int64_t nb, int vals_lds,
                                                             double* __restrict__ scratch,
                                                             double* __restrict__ out) {
@@ -984,7 +1009,8 @@ __global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, Sparse
                             : scratch + int64_t(blockIdx.x) * nb;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int groups = kRrWaves / W, group = wave / W, part = wave % W;
+    constexpr int groups = kRrWaves / W, PER = kRrClasses / W, U = PER < kRrU ? PER : kRrU;
+    const int group = wave / W, part = wave % W;
     const int c_lo = int(blockIdx.y) * share, c_hi = min(kc, c_lo + share);
     for (int64_t qi = blockIdx.x; qi < nq; qi += gridDim.x) {
         const int64_t qs = qids[qi];
@@ -1031,31 +1057,48 @@ __global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, Sparse
             if (c < c_hi) {
                 r = cand[qi * kc + c];
                 const int64_t ra = rf.off[r], rb = rf.off[r + 1];
-                for (int64_t t0 = ra + part * 64; t0 < rb; t0 += 64 * W * kRrU) {
-                    int32_t p[kRrU];
-                    double v[kRrU];
+                double a[PER];
 #pragma unroll
-                    for (int u = 0; u < kRrU; ++u) {
-                        const int64_t t = t0 + int64_t(64 * W) * u + lane;
-                        p[u] = t < rb ? rf.pos[t] : -1;
-                        v[u] = t < rb ? rf.val[t] : 0.0;
+                for (int m = 0; m < PER; ++m) a[m] = 0.0;
+                // kRrU loads of 64 entries in flight: of several rounds of the wave's classes,
+                // or of half of them
+                constexpr int ROUNDS = kRrU / U;
+                for (int64_t t0 = ra + part * PER * 64; t0 < rb; t0 += 64 * kRrClasses * ROUNDS)
+#pragma unroll
+                    for (int m0 = 0; m0 < PER; m0 += U) {
+                        int32_t p[kRrU];
+                        double v[kRrU];
+#pragma unroll
+                        for (int u = 0; u < kRrU; ++u) {
+                            const int64_t t = t0 + 64 * (kRrClasses * (u / U) + m0 + u % U) + lane;
+                            p[u] = t < rb ? rf.pos[t] : -1;
+                            v[u] = t < rb ? rf.val[t] : 0.0;
+                        }
+#pragma unroll
+                        for (int u = 0; u < kRrU; ++u) {
+                            if (p[u] < 0) continue;
+                            const unsigned long long word = bits[p[u] >> 6];
+                            if ((word >> (p[u] & 63)) & 1ull)
+                                a[m0 + u % U] += fmin(vals[place(p[u], word)], v[u]);
+                        }
                     }
+                acc = lane_sums<PER, 32>(a, lane);
+                // neighbouring classes, then neighbouring pairs of them, ...
 #pragma unroll
-                    for (int u = 0; u < kRrU; ++u) {
-                        if (p[u] < 0) continue;
-                        const unsigned long long word = bits[p[u] >> 6];
-                        if ((word >> (p[u] & 63)) & 1ull) acc += fmin(vals[place(p[u], word)], v[u]);
-                    }
-                }
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+                for (int off = 64 / PER; off < 64; off <<= 1) acc += __shfl_xor(acc, off, 64);
             }
-            if (W > 1) {                     // block-uniform
+            if constexpr (W > 1) {
                 if (lane == 0) red[wave] = acc;
                 __syncthreads();
-                acc = 0.0;
-                for (int w = 0; w < W; ++w) acc += red[group * W + w];
+                double r16[W];
+#pragma unroll
+                for (int w = 0; w < W; ++w) r16[w] = red[group * W + w];
                 __syncthreads();
+#pragma unroll
+                for (int x = 1; x < W; x <<= 1)
+#pragma unroll
+                    for (int w = 0; w < W; w += 2 * x) r16[w] += r16[w + x];
+                acc = r16[0];
             }
             if (c < c_hi && part == 0 && lane == 0) {
                 const double den = q.s[qs] + rf.s[r];
@@ -1357,21 +1400,28 @@ hipError_t rerank(const SparseView& q, const SparseView& r, const int32_t* qids,
     const size_t tables = size_t(words + (words + 3) / 4) * 8, with_vals = tables + size_t(q_longest) * 8;
     constexpr size_t kMost = 158 * 1024;     // beside the static arrays
     if (q_longest < 65536 && tables <= kMost) {
-        static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_rerank_bits),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                        int(kMost)) == hipSuccess;
+        using Kernel = decltype(&k_rerank_bits<1>);
+        static const Kernel kernels[] = {&k_rerank_bits<1>, &k_rerank_bits<2>, &k_rerank_bits<4>,
+                                         &k_rerank_bits<8>, &k_rerank_bits<16>};
+        static const bool attr_ok = [] {
+            for (Kernel k : kernels)
+                if (hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                        int(kMost)) != hipSuccess)
+                    return false;
+            return true;
+        }();
         if (!attr_ok) return hipErrorInvalidValue;
         const bool vals_lds = with_vals <= kMost;
         // shares of the candidates while the queries alone leave CUs idle (each share lays
         // the query out again, so at least 8 candidates)
         const int64_t shares = vals_lds ? std::max<int64_t>(1, std::min<int64_t>((kc + 7) / 8, 512 / nq)) : 1;
         const int share = int((kc + shares - 1) / shares);
-        int W = 1;
-        while (W < kRrWaves && share * W < kRrWaves) W *= 2;
+        int w2 = 0;                          // log2 W
+        while ((1 << w2) < kRrWaves && share << w2 < kRrWaves) ++w2;
         const int64_t gx = vals_lds ? std::min<int64_t>(nq, 1 << 20) : std::min(nq, n_rows);
-        hipLaunchKernelGGL(k_rerank_bits, dim3(unsigned(gx), unsigned((kc + share - 1) / share)),
+        hipLaunchKernelGGL(kernels[w2], dim3(unsigned(gx), unsigned((kc + share - 1) / share)),
                            dim3(kRrThreads), vals_lds ? with_vals : tables, st, q, r, qids, cand, nq, kc,
-                           share, W, int(words), nb, vals_lds ? 1 : 0, scratch, out);
+                           share, int(words), nb, vals_lds ? 1 : 0, scratch, out);
         return hipGetLastError();
     }
     hipError_t e = zero_f64(scratch, n_rows * nb, st);
