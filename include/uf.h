@@ -270,9 +270,10 @@ uf_status uf_batch_plan_create(const uf_tree* tree, const uf_table* const* table
                                uf_batch** out);
 int64_t uf_batch_n_tables(const uf_batch* batch);
 uf_status uf_batch_workspace_size(const uf_batch* batch, size_t* bytes);
-/* Current launch configuration: branches in flight per wave (8, 16 or 32), groups of
- * 16 waves per CU (2 and more: as many as fit), pairs per tile (64, 128 or 256 stand
- * for 4, 8 or 16 samples by 64) and branches per chunk (each pointer nullable). */
+/* Current launch configuration: branches in flight per wave (8, 16 or 32), wgs_per_cu
+ * (kept as set; as many waves run as fit), pairs per tile (64, 128 or 256 stand for 4, 8
+ * or 16 samples by 64; tables of 4,096 samples and more always take 16) and branches per
+ * chunk (each pointer nullable). */
 uf_status uf_batch_config(const uf_batch* batch, int* stage_branches, int* wgs_per_cu,
                           int* tile_stripes, int64_t* chunk_nodes);
 /* Set the launch configuration.  wgs_per_cu may be 1 up to, for stage_branches 8: 5, 3
@@ -301,10 +302,10 @@ uf_status uf_batch_set_precision(uf_batch* batch, uf_precision prec, const uf_ta
  * instead of launching kernel by kernel.  Asynchronous on hip_stream. */
 uf_status uf_batch_run(uf_batch* batch, float* const* outs, int use_graph, void* ws,
                        size_t ws_bytes, void* hip_stream);
-/* The self-written tile/stripe autotuner: time every tile size (64, 128, 256
- * stripes) x stage size (8, 16, 32 branches) at the two highest wgs_per_cu that
- * configuration allows, on the first 16,384 branches of the batch's first chunk; keep the fastest (results are identical for all) and record it
- * in the JSON cache at tune_cache (nullable; else $UF_TUNE_CACHE; no file if
+/* The self-written autotuner: time every tile size (64, 128, 256) x stage size (8, 16,
+ * 32 branches) once, on the first 16,384 branches of the batch's first chunk; keep the
+ * fastest (results are identical for all) and record it, with the largest wgs_per_cu it
+ * may name, in the JSON cache at tune_cache (nullable; else $UF_TUNE_CACHE; no file if
  * neither), keyed by the size bucket.
  * best_ms (nullable) receives the winner's time.  Synchronises hip_stream. */
 uf_status uf_autotune(uf_batch* batch, void* ws, size_t ws_bytes, const char* tune_cache,

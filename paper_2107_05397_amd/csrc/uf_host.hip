@@ -1521,7 +1521,7 @@ namespace {
 const int kBatchStages[] = {8, 16, 32};
 const int kBatchTiles[] = {64, 128, 256};
 
-// (branches in flight, groups of waves per CU, tile) is one that recorded files may hold
+// (branches in flight, waves as recorded, tile) is one that recorded files may hold
 bool config_valid(int ks, int w, int ts) {
     return w >= 1 && w <= ufx::batch_max_blocks(ks, ts);
 }
@@ -1621,14 +1621,14 @@ std::vector<int4> batch_items(const std::vector<BatchTable>& tabs, bool wide) {
 
 // The pair tiles of every table on one chunk: the wide tables (first in d_items) with 16
 // samples i a wave, as single calls take them, the others as configured.
-hipError_t batch_tiles(const uf_batch* b, const void* chunk, int64_t k0, int64_t kc, float* acc, int ks, int w,
+hipError_t batch_tiles(const uf_batch* b, const void* chunk, int64_t k0, int64_t kc, float* acc, int ks,
                        int ts, hipStream_t s) {
     const bool last = k0 + kc == b->emb->nb;
     const hipError_t er = ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_wide, false, k0, kc,
-                                           last, acc, ks, w, 256, s);
+                                           last, acc, ks, 256, s);
     if (er != hipSuccess) return er;
     return ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items + b->n_wide, b->n_items - b->n_wide,
-                            !b->side_by_side, k0, kc, last, acc, ks, w, ts, s);
+                            !b->side_by_side, k0, kc, last, acc, ks, ts, s);
 }
 
 // enqueue the whole batch on stream s (also used under graph capture)
@@ -1641,7 +1641,7 @@ uf_status batch_enqueue(uf_batch* b, float* const* outs, char* base, hipStream_t
         const int64_t kc = std::min<int64_t>(b->kc, e.nb - k0);
         UF_HIP(ufx::batch_fill(emb_view(e), b->d_tabs, b->d_tab_of, k0, kc, chunk, b->off_mask,
                                b->chunk_bytes, s));
-        UF_HIP(batch_tiles(b, chunk, k0, kc, acc, b->stage_branches, b->wgs_per_cu, b->tile_stripes, s));
+        UF_HIP(batch_tiles(b, chunk, k0, kc, acc, b->stage_branches, b->tile_stripes, s));
     }
     if (b->n_chunks > 0) UF_HIP(ufx::batch_planes(b->d_tabs, b->n_tables, b->max_plane, acc, s));
     for (int64_t r = 0; r < b->n_tables; ++r) {
@@ -2058,22 +2058,20 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
         } ev{e0, e1};
         TuneEntry best{b->stage_branches, b->wgs_per_cu, b->tile_stripes, 1e300};
         for (int ts : kBatchTiles) {
+            // (tables of ufx::kPairWideN samples and more have their own tile)
+            if (b->n_items == b->n_wide && ts != b->tile_stripes) continue;
             for (int ks : kBatchStages) {
-                // the two highest occupancies the configuration allows
-                const int wmax = ufx::batch_max_blocks(ks, ts);
-                for (int w = std::max(1, wmax - 1); w <= wmax; ++w) {
-                    double tmin = 1e300;
-                    for (int rep = 0; rep < 2; ++rep) {
-                        UF_HIP(hipEventRecord(e0, s));
-                        UF_HIP(batch_tiles(b, chunk, 0, kc, acc, ks, w, ts, s));
-                        UF_HIP(hipEventRecord(e1, s));
-                        UF_HIP(hipEventSynchronize(e1));
-                        float ms = 0;
-                        UF_HIP(hipEventElapsedTime(&ms, e0, e1));
-                        tmin = std::min(tmin, double(ms));
-                    }
-                    if (tmin < best.ms) best = TuneEntry{ks, w, ts, tmin};
+                double tmin = 1e300;
+                for (int rep = 0; rep < 2; ++rep) {
+                    UF_HIP(hipEventRecord(e0, s));
+                    UF_HIP(batch_tiles(b, chunk, 0, kc, acc, ks, ts, s));
+                    UF_HIP(hipEventRecord(e1, s));
+                    UF_HIP(hipEventSynchronize(e1));
+                    float ms = 0;
+                    UF_HIP(hipEventElapsedTime(&ms, e0, e1));
+                    tmin = std::min(tmin, double(ms));
                 }
+                if (tmin < best.ms) best = TuneEntry{ks, ufx::batch_max_blocks(ks, ts), ts, tmin};
             }
         }
         if (best_ms) *best_ms = best.ms;

@@ -74,14 +74,14 @@ hipError_t batch_fill(const ufp::Emb& e, const BatchTable* tabs, const int32_t* 
 // plane at p_off.  items: (table, segment, block of 64 samples i, block of 64 samples
 // j >= i), eight at a time, item p for XCD p mod 8 (table -1: none; segment -1, with `all`
 // only: all, one after the other, their sums to acc_off as they end).  last: the chunk ends
-// with the tree's branches.  Configuration: stage_branches (8, 16 or 32) branches in flight per wave;
-// wgs_per_cu groups of 16 waves per CU (two and more: as many as fit); tiles of
-// tile_stripes / 16 samples i (tile_stripes 64, 128 or 256) by 64 samples j.
+// with the tree's branches.  Configuration: stage_branches (8, 16 or 32) branches in flight
+// per wave; tiles of tile_stripes / 16 samples i (tile_stripes 64, 128 or 256) by 64 j.
 hipError_t batch_pairs(const void* chunk, size_t off_mask, const BatchTable* tabs, const int4* items,
                        int64_t n_items, bool all, int64_t k0, int64_t kc, bool last, float* acc,
-                       int stage_branches, int wgs_per_cu, int tile_stripes, hipStream_t st);
-// The largest wgs_per_cu that a configuration may ask for (0: no such configuration): a
-// fixed table, so that recorded configurations stay valid.
+                       int stage_branches, int tile_stripes, hipStream_t st);
+// The largest wgs_per_cu that a configuration may name (0: no such configuration): a
+// fixed table, so that recorded configurations stay valid.  It sets nothing: as many waves
+// run as fit (fewer, kept away by unused LDS, were slower by up to a fifth or the same).
 int batch_max_blocks(int stage_branches, int tile_stripes);
 // acc_off (=) the planes of each table, in order.
 hipError_t batch_planes(const BatchTable* tabs, int64_t n_tables, int64_t max_plane, float* acc,

@@ -490,26 +490,24 @@ int batch_max_blocks(int stage_branches, int tile_stripes) {
 template <int A, int U>
 static hipError_t batch_pairs_as(const float* E, const unsigned long long* mask, const BatchTable* tabs,
                                  const int4* items, int64_t n_items, bool all, int64_t k0, int64_t kc,
-                                 bool last, float* acc, int wgs_per_cu, hipStream_t st) {
+                                 bool last, float* acc, hipStream_t st) {
     const int64_t blocks = (64 / (4 * A)) * n_items;
     if (blocks > 0x7fffffff || n_items % 8) return hipErrorInvalidValue;
-    // one group of 16 waves per CU: each of its four workgroups holds a quarter of the LDS
-    const unsigned lds = wgs_per_cu == 1 ? 34 * 1024 : 0;
     hipLaunchKernelGGL((all ? k_batch_pairs<A, U, true> : k_batch_pairs<A, U, false>), dim3(unsigned(blocks)),
-                       dim3(256), lds, st, E, mask, tabs, items, int(k0), int(kc), int(last), acc);
+                       dim3(256), 0, st, E, mask, tabs, items, int(k0), int(kc), int(last), acc);
     return hipGetLastError();
 }
 
 hipError_t batch_pairs(const void* chunk, size_t off_mask, const BatchTable* tabs, const int4* items,
                        int64_t n_items, bool all, int64_t k0, int64_t kc, bool last, float* acc,
-                       int stage_branches, int wgs_per_cu, int tile_stripes, hipStream_t st) {
+                       int stage_branches, int tile_stripes, hipStream_t st) {
     const auto* E = static_cast<const float*>(chunk);
     const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + off_mask);
     if (n_items < 1 || kc < 1) return hipSuccess;
-    if (wgs_per_cu < 1 || kc > 0x3fffffff) return hipErrorInvalidValue;
+    if (kc > 0x3fffffff) return hipErrorInvalidValue;
 #define UF_BP(KS_, TS_)                            \
     if (stage_branches == KS_ && tile_stripes == TS_) \
-        return batch_pairs_as<TS_ / 16, KS_ / 2>(E, mask, tabs, items, n_items, all, k0, kc, last, acc, wgs_per_cu, st);
+        return batch_pairs_as<TS_ / 16, KS_ / 2>(E, mask, tabs, items, n_items, all, k0, kc, last, acc, st);
     UF_BP(8, 64)
     UF_BP(8, 128)
     UF_BP(8, 256)
