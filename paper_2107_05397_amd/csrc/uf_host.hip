@@ -483,7 +483,7 @@ struct Plan {
     int64_t n_parts = 0;
     // touched-branch pair tiles: segment length, segments held side by side, elements
     // of one plane of sums
-    bool pairs = false;
+    bool pairs = false, band = false;   // band: LDS tiles over all branches instead
     int form = ufx::kPairMin;
     int64_t seg = 0, n_planes = 0, plane = 0;
     // Gram product on presence bits: length digits (4 or 8; 0: not taken), length kind,
@@ -549,6 +549,9 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
         p->sr_part = (p->sr + parts - 1) / parts;
     p->plane = bits ? bits_plane() : p->sr * n;
     const int64_t n_seg = p->pairs ? (std::max<int64_t>(nb, 1) + p->seg - 1) / p->seg : 0;
+    // (a split's dense branches are those that many samples touch)
+    p->band = fit == 0 && p->form == ufx::kPairL1 && prec != UF_FP64 && n_seg == 1 && ufk::band_chunk(n) >= 32 &&
+              ufk::band_wins(ufk::band_tiles(n, p->sr), split ? 1.0 : e->touched);
     // workspace layout for a chunk of kc branches; planes: segments held side by side
     auto layout = [&](int64_t kc, int64_t planes) {
         p->kc = kc;
@@ -613,6 +616,7 @@ uf_status make_plan(const uf_embedding* e, int weighted, uf_precision prec, int6
     }
     // 32-bit offsets and sums inside a chunk
     if (p->pairs || bits) kc = std::min<int64_t>(kc, int64_t(1) << 22);
+    if (p->band) kc = std::min<int64_t>(kc, ufk::band_chunk(n));
     kc = shape(kc);
     layout(kc, kc >= nb ? n_seg : kc / std::max<int64_t>(p->seg, 1));
     return UF_OK;
@@ -635,6 +639,11 @@ uf_status run_pairs(const Plan& p, int64_t nb, const char* name, char* base, hip
             UF_HIP(fill(k0, kc, chunk));
         }
         ProfScope ps(name, s);
+        if constexpr (std::is_same<T, float>::value)
+            if (p.band) {
+                UF_HIP(ufk::band_f32(static_cast<const float*>(chunk), kc, p.n, p.sb, p.se, c == 0, acc, s));
+                continue;
+            }
         if (p.n_planes == 0) {
             UF_HIP(ufx::pairs<T>(p.form, chunk, p.n, kc, 0, kc, kc, 1, p.sb, p.se, c > 0, acc, p.plane, s));
             continue;
@@ -1188,7 +1197,7 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         const size_t o_d32 = c.take(size_t(m) * 8);
         const size_t o_dbf = c.take(size_t(m) * 8);
         const size_t o_above = c.take(size_t(m) * 4);
-        const size_t o_mean = c.take(8);
+        const size_t o_touched = c.take(16);
         void* arena = nullptr;
         hipError_t he = hipMalloc(&arena, c.off + 256);
         if (he != hipSuccess) return fail(UF_ERR_NOMEM, "device allocation of the embedding failed");
@@ -1258,22 +1267,26 @@ uf_status embed_impl(const uf_tree* t, const uf_table* tb, void* stream, uf_embe
         if (rc == hipSuccess) rc = H2D(ddbf, dbf.data(), size_t(m) * 8);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "upload of the embedding inputs"));
         int32_t* dabove = reinterpret_cast<int32_t*>(b + o_above);
-        unsigned long long* mean_min = reinterpret_cast<unsigned long long*>(b + o_mean);
+        unsigned long long* dtouched = reinterpret_cast<unsigned long long*>(b + o_touched);
         const double infinite = HUGE_VAL;   // no sample touches a branch of nonzero length
+        unsigned long long touched[2] = {0, 0};
+        std::memcpy(&touched[0], &infinite, 8);
         rc = H2D(dabove, above.data(), size_t(m) * 4);
-        if (rc == hipSuccess) rc = H2D(mean_min, &infinite, 8);
+        if (rc == hipSuccess) rc = H2D(dtouched, touched, 16);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "upload of the embedding inputs"));
         rc = ufk::pack_nodes(*e, dabove, s);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "node record kernel launch"));
         if (n > 0) {
-            rc = ufk::sample_scalars(*e, ppos, tpos, dd64, dd32, ddbf, mean_min, s);
+            rc = ufk::sample_scalars(*e, ppos, tpos, dd64, dd32, ddbf, dtouched, s);
             if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel launch"));
         }
         rc = hipStreamSynchronize(s);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalar kernel"));
-        double mean = 0.0;
-        rc = hipMemcpy(&mean, mean_min, 8, hipMemcpyDeviceToHost);
+        rc = hipMemcpy(touched, dtouched, 16, hipMemcpyDeviceToHost);
         if (rc != hipSuccess) return cleanup(hip_fail(rc, "sample scalars"));
+        double mean = 0.0;
+        std::memcpy(&mean, &touched[0], 8);
+        e->touched = double(touched[1]) / std::max(double(n) * double(nb), 1.0);
         e->len_exp = t->len_exp;
         choose_digits(e, mean);
         *out = guard.release();
@@ -1462,6 +1475,7 @@ struct uf_batch {
     std::vector<BatchTable> tabs;        // host copy
     std::vector<int64_t> acc_elems;           // per table
     int64_t n_items = 0, n_wide = 0;          // of them, of wide tables (first)
+    int64_t n_band = 0;                       // or LDS tiles of the wide tables
     int64_t kc = 0, n_chunks = 0;
     int stage_branches = 16, wgs_per_cu = 2, tile_stripes = 128;
     int64_t n_bucket = 0;
@@ -1469,6 +1483,7 @@ struct uf_batch {
     BatchTable* d_tabs = nullptr;
     int32_t* d_tab_of = nullptr;
     int4* d_items = nullptr;
+    int2* d_band = nullptr;
     int64_t max_plane = 0;
     bool side_by_side = true;                 // segments, each to its own plane
     size_t off_mask = 0, chunk_bytes = 0;     // of a chunk of all tables
@@ -1619,13 +1634,17 @@ std::vector<int4> batch_items(const std::vector<BatchTable>& tabs, bool wide) {
     return items;
 }
 
-// The pair tiles of every table on one chunk: the wide tables (first in d_items) with 16
-// samples i a wave, as single calls take them, the others as configured.
+// The tiles of every table on one chunk: the wide tables (first in d_items) with 16 samples
+// i a wave and 32 branches in flight (8 and 16 in flight: 29.8 and 28.5 ms for 6,000 and
+// 8,000 samples x 10,000 branches, 26.7 with 32), or as LDS tiles; the others as configured.
 hipError_t batch_tiles(const uf_batch* b, const void* chunk, int64_t k0, int64_t kc, float* acc, int ks,
                        int ts, hipStream_t s) {
     const bool last = k0 + kc == b->emb->nb;
-    const hipError_t er = ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_wide, false, k0, kc,
-                                           last, acc, ks, 256, s);
+    const hipError_t er =
+        b->n_band ? ufk::band_batch_f32(static_cast<const float*>(chunk), kc, b->d_tabs, b->d_band, b->n_band,
+                                        k0 == 0, acc, s)
+                  : ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items, b->n_wide, false, k0, kc, last,
+                                     acc, 32, 256, s);
     if (er != hipSuccess) return er;
     return ufx::batch_pairs(chunk, b->off_mask, b->d_tabs, b->d_items + b->n_wide, b->n_items - b->n_wide,
                             !b->side_by_side, k0, kc, last, acc, ks, ts, s);
@@ -1795,6 +1814,17 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
         if (kc <= 0)
             kc = int64_t(16.0 * 1024 * 1024 * 1024 / (double(std::max<int64_t>(n_blocks, 1)) * (64 * 4 + 8)));
         kc = std::min<int64_t>(kc, int64_t(1) << 22);
+        // wide tables together as LDS tiles, where these win
+        int64_t tiles = 0, widest = 0;
+        for (int64_t r = 0; r < n_tables; ++r) {
+            const int64_t n = tables[r]->n_samples;
+            if (n < ufx::kPairWideN) continue;
+            tiles += ufk::band_tiles(n, n / 2);
+            widest = std::max(widest, n);
+        }
+        const bool band = tiles > 0 && tiles < 0x7fffffff && ufk::band_chunk(widest) >= 32 &&
+                          ufk::band_wins(tiles, b->emb->touched);
+        if (band) kc = std::min<int64_t>(kc, ufk::band_chunk(widest));
         kc = std::min<int64_t>(std::max<int64_t>(kc, 32), std::max<int64_t>(b->emb->nb, 1));
         b->kc = kc;
         b->n_chunks = b->emb->nb > 0 ? (b->emb->nb + kc - 1) / kc : 0;
@@ -1829,7 +1859,13 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
             moff += nblk * kc;
             mean_n += double(t.n) / double(n_tables);
         }
-        std::vector<int4> items = batch_items(b->tabs, true);
+        std::vector<int2> band_items;
+        for (int64_t r = 0; band && r < n_tables; ++r)
+            if (b->tabs[size_t(r)].n >= ufx::kPairWideN)
+                for (int64_t l = 0; l < ufk::band_tiles(b->tabs[size_t(r)].n, b->tabs[size_t(r)].n / 2); ++l)
+                    band_items.push_back(make_int2(int(r), int(l)));
+        b->n_band = int64_t(band_items.size());
+        std::vector<int4> items = band ? std::vector<int4>() : batch_items(b->tabs, true);
         b->n_wide = int64_t(items.size());
         const std::vector<int4> rest = batch_items(b->tabs, false);
         items.insert(items.end(), rest.begin(), rest.end());
@@ -1839,11 +1875,15 @@ uf_status uf_batch_create(const uf_tree* tree, const uf_table* const* tables, in
         const size_t o_tabs = c.take(sizeof(BatchTable) * size_t(n_tables));
         const size_t o_tabof = c.take(size_t(n_all) * 4);
         const size_t o_items = c.take(sizeof(int4) * size_t(std::max<int64_t>(b->n_items, 1)));
+        const size_t o_band = c.take(sizeof(int2) * size_t(b->n_band));
         if (hipMalloc(&b->arena, c.off + 256) != hipSuccess) return fail(UF_ERR_NOMEM, "batch descriptors");
         char* base = static_cast<char*>(b->arena);
         b->d_tabs = reinterpret_cast<BatchTable*>(base + o_tabs);
         b->d_tab_of = reinterpret_cast<int32_t*>(base + o_tabof);
         b->d_items = reinterpret_cast<int4*>(base + o_items);
+        b->d_band = reinterpret_cast<int2*>(base + o_band);
+        if (b->n_band)
+            UF_HIP(hipMemcpy(b->d_band, band_items.data(), sizeof(int2) * band_items.size(), hipMemcpyHostToDevice));
         UF_HIP(hipMemcpy(b->d_tabs, b->tabs.data(), sizeof(BatchTable) * size_t(n_tables), hipMemcpyHostToDevice));
         if (b->n_items)
             UF_HIP(hipMemcpy(b->d_items, items.data(), sizeof(int4) * items.size(), hipMemcpyHostToDevice));
@@ -2040,7 +2080,7 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
         void* chunk = base + b->off_E;
         float* acc = reinterpret_cast<float*>(base + b->off_acc);
         const uf_embedding& e = *b->emb;
-        if (b->n_chunks == 0 || b->n_items == 0) return UF_OK;
+        if (b->n_chunks == 0 || b->n_items + b->n_band == 0) return UF_OK;
         // timed on the first 16,384 branches of the first chunk: every configuration
         // pays the same per-branch work, so a part of the chunk ranks them
         const int64_t kc = std::min<int64_t>(std::min<int64_t>(b->kc, e.nb), 16384);
@@ -2058,9 +2098,9 @@ uf_status uf_autotune(uf_batch* b, void* ws, size_t ws_bytes, const char* tune_c
         } ev{e0, e1};
         TuneEntry best{b->stage_branches, b->wgs_per_cu, b->tile_stripes, 1e300};
         for (int ts : kBatchTiles) {
-            // (tables of ufx::kPairWideN samples and more have their own tile)
-            if (b->n_items == b->n_wide && ts != b->tile_stripes) continue;
             for (int ks : kBatchStages) {
+                // (wide tables have their own: nothing to choose for them alone)
+                if (b->n_items == b->n_wide && (ts != b->tile_stripes || ks != b->stage_branches)) continue;
                 double tmin = 1e300;
                 for (int rep = 0; rep < 2; ++rep) {
                     UF_HIP(hipEventRecord(e0, s));

@@ -107,6 +107,7 @@ struct uf_embedding {
     // digits below that serve (0: none do)
     int len_exp = 0;
     int len_digits[3] = {0, 0, 0};
+    double touched = 0.0;   // of the branches, by a sample on average
     // table
     int64_t* row_ptr = nullptr;   // [n+1]
     int32_t* rank = nullptr;      // [nnz]
@@ -187,18 +188,20 @@ struct BatchTable {
 namespace ufk {
 
 constexpr int kBandI = 128;       // samples per band tile
+constexpr int kBandTS = 256;      // stripes per band tile
+constexpr int kBandWgs = 512;     // two workgroups (64 KiB of LDS) on each of 256 CUs
 constexpr int kGramT = 256;       // square tile of the MFMA Gram kernel
 constexpr int kGramK = 128;        // K step of the MFMA Gram kernel
 constexpr int kGramKPad = 256;    // K of its presence matrix is padded to this (steps go in pairs)
 
 // e.nodes; above: branches of nonzero length from each position to the root.
 hipError_t pack_nodes(const uf_embedding& e, const int32_t* above, hipStream_t st);
-// Per-sample scalars from the postorder leaf intervals (one wave per sample).  mean_min
-// (nullable): lowered to the smallest mean length of the branches a sample touches (those
-// of nonzero length), as the bits of a double.
+// Per-sample scalars from the postorder leaf intervals (one wave per sample).  touched
+// (nullable): [0] lowered to the smallest mean length of the branches a sample touches (those
+// of nonzero length), as the bits of a double, [1] raised by their number for each sample.
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos,
                           const int32_t* tip_pos, const double* d64, const double* d32,
-                          const double* dbf, unsigned long long* mean_min, hipStream_t st);
+                          const double* dbf, unsigned long long* touched, hipStream_t st);
 
 // Sample-major presence P[s][k]: FP8 e4m3 -2.0 (0xC0) where present, else 0, k < kpad (zero beyond
 // kc), for positions [k0, k0+kc), or for positions list[k0 .. k0+kc) when list is
@@ -210,6 +213,29 @@ hipError_t embed_presence_fp8(const uf_embedding& e, int64_t k0, int64_t kc, int
 // acc += sum_k |E[k][i] - E[k][j]| (exact integers; the caller keeps the sum below 2^32).
 hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first,
                     uint32_t* acc, hipStream_t st);
+// The same in FP32 over a chunk in the layout of the pair tiles (ufx::PairChunk), kc <=
+// band_chunk(n): the sums of its L1 tiles over one segment, bit for bit.
+hipError_t band_f32(const float* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first, float* acc,
+                    hipStream_t st);
+// For tables of a batch, all stripes.  items: (table, tile below band_tiles(n, n / 2)).
+hipError_t band_batch_f32(const float* E, int64_t kc, const BatchTable* tabs, const int2* items, int64_t n_items,
+                          int first, float* acc, hipStream_t st);
+inline int64_t band_tiles(int64_t n, int64_t stripes) {
+    return ((n + kBandI - 1) / kBandI) * ((stripes + kBandTS - 1) / kBandTS);
+}
+// 32-bit offsets inside a chunk
+inline int64_t band_chunk(int64_t n) { return (int64_t(1) << 32) / ((n + 63) / 64 * 256) - 2; }
+// Whether LDS tiles over all branches beat FP32 pair tiles over those a tile touches, which
+// leave out ever less the more branches a sample touches and reread the rows of large
+// matrices: from 4.5 rounds of tiles on (12,300 samples; the last round is part empty) with
+// an eighth of the branches touched, from 3 (10,000 samples) with a quarter.  Pair and LDS
+// tiles, 2,000 branches: 30,000 samples touching 0.16 of them 36.8 and 32.9 ms, 0.33 41.7
+// and 33.2, 0.84 42.2 and 34.7; 20,000: 16.5 and 15.3, 18.7 and 15.6, 19.1 and 16.4;
+// 10,000: 4.4 and 4.8, 5.0 and 4.9, 5.2 and 5.3; 5,000 (0.8 rounds): 1.3 and 1.3, 1.5 and
+// 1.4, 1.7 and 1.5; 2,500: 0.49 and 1.17, 0.57 and 1.22, 0.66 and 1.29.
+inline bool band_wins(int64_t tiles, double touched) {
+    return tiles >= 9 * kBandWgs / 2 ? touched >= 0.125 : tiles >= 3 * kBandWgs && touched >= 0.25;
+}
 
 // MFMA Gram over one chunk: for every upper-triangle 256x256 tile (bi <= bj) that holds
 // a pair of stripes [sb, se), G_ij (+)= sum_k [P_ik != 0][P_jk != 0] (hi_k + lo_k), scattered

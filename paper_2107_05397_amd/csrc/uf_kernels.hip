@@ -42,9 +42,9 @@ __device__ __forceinline__ double wave_sum(double v) {
 //      = sum_k D(t_k) - sum_k D(lca(t_k, t_{k+1}))  for tips in rank order,
 // which is sum_v l_v a_v.  D is the root distance with FP64, FP32-rounded or
 // BF16 hi+lo lengths.  Lane sums and the wave reduction run in a fixed order.
-//   MEAN: *mean_min = min(itself, w / touched branches of nonzero length), likewise from
-// the numbers of such branches up to the root (nodes[v].w); as bits, which order as the
-// values do.
+//   MEAN: the branches of nonzero length that the sample touches, K, likewise from their
+// numbers up to the root (nodes[v].w): touched[0] = min(itself, w / K), as bits, which order
+// as the values do; touched[1] += K.
 // ----------------------------------------------------------------------------
 template <bool MEAN>
 __global__ __launch_bounds__(256) void k_sample_scalars(
@@ -54,7 +54,7 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
     const int32_t* __restrict__ tip_pos, const double* __restrict__ d64,
     const double* __restrict__ d32, const double* __restrict__ dbf, double* __restrict__ sw,
     double* __restrict__ wu, double* __restrict__ wu32, double* __restrict__ wub,
-    const int4* __restrict__ nodes, unsigned long long* __restrict__ mean_min) {
+    const int4* __restrict__ nodes, unsigned long long* __restrict__ touched) {
     const int lane = threadIdx.x & 63;
     const int64_t s = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (s >= n) return;
@@ -91,8 +91,10 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
     }
     if constexpr (MEAN) {
         k = wave_sum(k);
-        if (lane == 0 && k > 0.0)
-            atomicMin(mean_min, (unsigned long long)__double_as_longlong(fmax(w, 0.0) / k));
+        if (lane == 0 && k > 0.0) {
+            atomicMin(&touched[0], (unsigned long long)__double_as_longlong(fmax(w, 0.0) / k));
+            atomicAdd(&touched[1], (unsigned long long)k);
+        }
     }
 }
 
@@ -187,8 +189,7 @@ __global__ __launch_bounds__(256) void k_embed_pres_fp8(
 // ----------------------------------------------------------------------------
 constexpr int kBandKS = 16;                  // branches per LDS stage
 constexpr int kBandMS = 16;                  // stripes per thread
-constexpr int kBandTS = 16 * kBandMS;        // stripes per tile
-constexpr int kBandWgs = 512;                // two workgroups (64 KiB of LDS) on each of 256 CUs
+static_assert(kBandTS == 16 * kBandMS, "");
 
 // |a - b| + c on unsigned 32-bit integers in one VALU op
 __device__ __forceinline__ uint32_t sad_u32(uint32_t a, uint32_t b, uint32_t c) {
@@ -247,9 +248,13 @@ struct BandLds {
 // i0 + s0 + 1 + 8ti + MS*ts.  mode: store the sums, add to what acc holds, or (a part of
 // the tile's branches) add atomically.
 constexpr int kBandStore = 0, kBandAdd = 1, kBandAtomic = 2;
-__device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict__ E, int64_t ka,
+// T = uint32_t: E is row-major, [branches][n].  T = float: E is the pair tiles' chunk of kc
+// branches, blocks of 64 samples [kc + 1][64] one after the other (below 4 GiB).
+template <typename T>
+__device__ __forceinline__ void band_tile(BandLds& L, const T* __restrict__ E, int64_t kc, int64_t ka,
                                           int64_t kb, int64_t n, int64_t sb, int64_t se, int64_t i0,
-                                          int64_t s0, int mode, uint32_t* __restrict__ acc) {
+                                          int64_t s0, int mode, T* __restrict__ acc) {
+    constexpr bool BLOCKED = std::is_same<T, float>::value;
     constexpr int KS = kBandKS, MS = kBandMS;
     constexpr int SEG_I = kBandI / 64, SEG_J = (kBandI + kBandTS) / 64;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -257,11 +262,17 @@ __device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict
 
     // lane -> the element of segment p it fills (its quad at band_swz)
     auto seg_elem = [&](int p) { return 4 * band_swz(16 * p + (lane >> 2)) + (lane & 3); };
-    int coli[SEG_I], colj[SEG_J];   // in bytes
+    // where sample s (modulo n) is in a row, in bytes; 4 bytes from one row to the next
+    auto col = [&](int64_t s) {
+        s %= n;
+        return BLOCKED ? int(uint32_t(4 * ((s >> 6) * (kc + 1) * 64 + (s & 63)))) : int(4 * s);
+    };
+    const int64_t row_len = BLOCKED ? 64 : n;
+    int coli[SEG_I], colj[SEG_J];
 #pragma unroll
-    for (int p = 0; p < SEG_I; ++p) coli[p] = 4 * int((i0 + seg_elem(p)) % n);
+    for (int p = 0; p < SEG_I; ++p) coli[p] = col(i0 + seg_elem(p));
 #pragma unroll
-    for (int p = 0; p < SEG_J; ++p) colj[p] = 4 * int((i0 + s0 + 1 + seg_elem(p)) % n);
+    for (int p = 0; p < SEG_J; ++p) colj[p] = col(i0 + s0 + 1 + seg_elem(p));
     // this thread's fragment quads: 2 from its 8 samples, NQJ from its 7+MS partners
     constexpr int NQI = 2, NQJ = (7 + MS + 3) / 4;
     int oi[NQI], oj[NQJ];
@@ -272,14 +283,14 @@ __device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict
 
     auto stage = [&](int buf, int64_t k0) {
         const __amdgpu_buffer_rsrc_t rs =
-            __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(E + k0 * n), 0, -4, 0x00027000);
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(E + k0 * row_len), 0, -4, 0x00027000);
 #pragma unroll
         for (int kk = wave; kk < KS; kk += 4) {
             const int64_t row = k0 + kk;
             uint32_t* di = &L.wi[buf][kk][0];
             uint32_t* dj = &L.wj[buf][kk][0];
             if (row < kb) {
-                const int so = kk * int(n) * 4;
+                const int so = kk * int(row_len) * 4;
 #pragma unroll
                 for (int p = 0; p < SEG_I; ++p)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, di + p * 64, 4, coli[p], so, 0, 0);
@@ -295,14 +306,14 @@ __device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict
         }
     };
 
-    uint32_t r[8][MS];
+    T r[8][MS];
 #pragma unroll
     for (int b = 0; b < MS; ++b) {
         const int64_t s = s0 + ts * MS + b;
 #pragma unroll
         for (int a = 0; a < 8; ++a) {
             const int64_t i = i0 + ti * 8 + a;
-            r[a][b] = (mode == kBandAdd && s < se && i < n) ? acc[(s - sb) * n + i] : 0u;
+            r[a][b] = (mode == kBandAdd && s < se && i < n) ? acc[(s - sb) * n + i] : T(0);
         }
     }
 
@@ -325,7 +336,10 @@ __device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict
 #pragma unroll
             for (int a = 0; a < 8; ++a)
 #pragma unroll
-                for (int b = 0; b < MS; ++b) r[a][b] = sad_u32(xi[a], xj[a + b], r[a][b]);
+                for (int b = 0; b < MS; ++b) {
+                    if constexpr (BLOCKED) r[a][b] += fabsf(__uint_as_float(xi[a]) - __uint_as_float(xj[a + b]));
+                    else r[a][b] = sad_u32(xi[a], xj[a + b], r[a][b]);
+                }
         }
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -338,7 +352,7 @@ __device__ __forceinline__ void band_tile(BandLds& L, const uint32_t* __restrict
         for (int a = 0; a < 8; ++a) {
             const int64_t i = i0 + ti * 8 + a;
             if (i >= n) continue;
-            if (mode == kBandAtomic) atomicAdd(&acc[(s - sb) * n + i], r[a][b]);
+            if (!BLOCKED && mode == kBandAtomic) atomicAdd(&acc[(s - sb) * n + i], r[a][b]);
             else acc[(s - sb) * n + i] = r[a][b];
         }
     }
@@ -382,8 +396,31 @@ __global__ __launch_bounds__(256, 2) void k_band(const uint32_t* __restrict__ E,
         int64_t ib = 0, sblk = 0;
         band_patch_tile(t, n_iblk, n_sblk, &ib, &sblk);
         const int mode = kb - ka < kc ? kBandAtomic : first ? kBandStore : kBandAdd;
-        band_tile(L, E, ka, kb, n, sb, se, ib * kBandI, sb + sblk * kBandTS, mode, acc);
+        band_tile<uint32_t>(L, E, kc, ka, kb, n, sb, se, ib * kBandI, sb + sblk * kBandTS, mode, acc);
     }
+}
+
+// FP32: a workgroup a tile, of one matrix, or (items: table, tile) of those of a batch.
+// Bound by the issue of its two operations an update (20,000 samples x 2,000 branches: 4e11
+// updates in 15.3 to 16.4 ms, whole call; with tiles of 128 x 128 16.1 to 18.6).
+__global__ __launch_bounds__(256, 2) void k_band_f32(const float* __restrict__ E, int64_t kc, int64_t n,
+                                                     int64_t sb, int64_t se, const BatchTable* __restrict__ tabs,
+                                                     const int2* __restrict__ items, int first,
+                                                     float* __restrict__ acc) {
+    __shared__ __attribute__((aligned(16))) BandLds L;
+    int64_t l = xcd_tile(int64_t(blockIdx.x), int64_t(gridDim.x));
+    if (items) {
+        const int2 it = items[l];
+        const BatchTable& t = tabs[it.x];
+        l = it.y;
+        n = t.n;
+        se = n / 2;
+        E += t.e_off;
+        acc += t.acc_off;
+    }
+    int64_t ib = 0, sblk = 0;
+    band_patch_tile(l, (n + kBandI - 1) / kBandI, (se - sb + kBandTS - 1) / kBandTS, &ib, &sblk);
+    band_tile<float>(L, E, kc, 0, kc, n, sb, se, ib * kBandI, sb + sblk * kBandTS, first ? kBandStore : kBandAdd, acc);
 }
 
 // ----------------------------------------------------------------------------
@@ -948,11 +985,11 @@ hipError_t pack_nodes(const uf_embedding& e, const int32_t* above, hipStream_t s
 
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos, const int32_t* tip_pos,
                           const double* d64, const double* d32, const double* dbf,
-                          unsigned long long* mean_min, hipStream_t st) {
+                          unsigned long long* touched, hipStream_t st) {
     const unsigned blocks = unsigned((e.n + 3) / 4);
-    hipLaunchKernelGGL(mean_min ? k_sample_scalars<true> : k_sample_scalars<false>, dim3(blocks), dim3(256),
+    hipLaunchKernelGGL(touched ? k_sample_scalars<true> : k_sample_scalars<false>, dim3(blocks), dim3(256),
                        0, st, e.n, e.row_ptr, e.rank, e.cum, e.total, parent_pos, e.hi, tip_pos, d64, d32,
-                       dbf, e.sw, e.wu, e.wu32, e.wub, e.nodes, mean_min);
+                       dbf, e.sw, e.wu, e.wu32, e.wub, e.nodes, touched);
     return hipGetLastError();
 }
 
@@ -981,6 +1018,27 @@ hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_
     const int64_t whole = n_tiles / kBandWgs * kBandWgs;
     const unsigned blocks = unsigned(whole + (n_tiles > whole ? kBandWgs : 0));
     hipLaunchKernelGGL(k_band, dim3(blocks), dim3(256), 0, st, E, kc, n, sb, se, n_iblk, first, acc);
+    return hipGetLastError();
+}
+
+hipError_t band_f32(const float* E, int64_t kc, int64_t n, int64_t sb, int64_t se, int first, float* acc,
+                    hipStream_t st) {
+    if (se <= sb || n <= 0 || kc <= 0) return hipSuccess;
+    const int64_t n_tiles = band_tiles(n, se - sb);
+    if (n_tiles > 0x7fffffff || kc > band_chunk(n)) return hipErrorInvalidValue;
+    const BatchTable* no_tabs = nullptr;
+    const int2* no_items = nullptr;
+    hipLaunchKernelGGL(k_band_f32, dim3(unsigned(n_tiles)), dim3(256), 0, st, E, kc, n, sb, se, no_tabs, no_items,
+                       first, acc);
+    return hipGetLastError();
+}
+
+hipError_t band_batch_f32(const float* E, int64_t kc, const BatchTable* tabs, const int2* items, int64_t n_items,
+                          int first, float* acc, hipStream_t st) {
+    if (n_items <= 0 || kc <= 0) return hipSuccess;
+    if (n_items > 0x7fffffff) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_band_f32, dim3(unsigned(n_items)), dim3(256), 0, st, E, kc, int64_t(0), int64_t(0),
+                       int64_t(0), tabs, items, first, acc);
     return hipGetLastError();
 }
 
