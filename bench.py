@@ -128,7 +128,7 @@ def cpu_baseline(tree, table, target_s: float, variants=("weighted_normalized", 
 
 def bench_batch(args) -> int:
     """Batching workload: many rarefied tables of uneven size on one tree,
-    weighted normalized FP32, one persistent launch per chunk, one graph."""
+    weighted normalized FP32, one launch of tiles per chunk, one graph."""
     import numpy as np
     import synth
     log(f"generating {args.tables} rarefied tables")

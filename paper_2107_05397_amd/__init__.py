@@ -483,7 +483,7 @@ class Batch(_Handle):
                                          int(tile_stripes)))
 
     def set_precision(self, precision: str = "fp32", stream=None) -> None:
-        """"fp32" (persistent stripe kernel) or "fp32_split" (per-table sparse split on
+        """"fp32" (pair tiles of all tables) or "fp32_split" (per-table sparse split on
         forked streams); the workspace is re-sized on the next run."""
         arr = (_vp * len(self.tables))(*[t.handle.value for t in self.tables])
         _check(lib().uf_batch_set_precision(self._h, PRECISION[precision], arr, _stream_ptr(stream)))

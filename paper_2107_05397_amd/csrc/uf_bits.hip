@@ -22,12 +22,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 typedef unsigned long long u64;
 
-__global__ __launch_bounds__(256) void k_zero16(uint4* __restrict__ p, int64_t n16) {
-    const int64_t step = int64_t(gridDim.x) * 256;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n16; i += step)
-        p[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
 // one block per sample: its bit at the rank of each of its tips
 __global__ __launch_bounds__(256) void k_tip_bits(int64_t pyr, const int64_t* __restrict__ row_ptr,
                                                   const int32_t* __restrict__ rank,
@@ -106,45 +100,6 @@ __global__ __launch_bounds__(256) void k_digits(int kind, const double* __restri
     dig[k] = d;
 }
 
-// Tile t of the upper triangle of nblk x nblk blocks (see k_gram_bits): super-tiles of
-// G x G blocks, super-row-major, the diagonal super-tile first in its super-row.
-// Workgroups are dealt to the 8 XCDs round-robin and XCD x takes the x-th eighth of
-// that order, so its CUs share rows and columns of bits in its L2.
-constexpr int kGroup = 8;
-__device__ __forceinline__ bool tri_tile(int64_t b, int64_t nblk, int64_t& bi, int64_t& bj) {
-    constexpr int64_t G = kGroup;
-    const int64_t L = nblk * (nblk + 1) / 2;
-    const int64_t per = (L + 7) / 8;
-    int64_t v = (b & 7) * per + (b >> 3);
-    if ((b >> 3) >= per || v >= L) return false;
-    for (int64_t r0 = 0;;) {
-        const int64_t r = min(G, nblk - r0);
-        const int64_t diag = r * (r + 1) / 2, cnt = diag + r * (nblk - r0 - r);
-        if (v >= cnt) {
-            v -= cnt;
-            r0 += r;
-            continue;
-        }
-        if (v < diag) {
-            int64_t a = 0;
-            while (v >= r - a) {
-                v -= r - a;
-                ++a;
-            }
-            bi = r0 + a;
-            bj = bi + v;
-        } else {
-            v -= diag;
-            const int64_t c0 = r0 + r + (v / (r * G)) * G;
-            const int64_t c = min(G, nblk - c0);
-            const int64_t w = v % (r * G);
-            bi = r0 + w / c;
-            bj = c0 + w % c;
-        }
-        return true;
-    }
-}
-
 // bytes 0-3 (lo) or 4-7 (hi) of four words, transposed: out[c] holds byte c of each
 __device__ __forceinline__ void transpose4(const uint32_t w[4], uint32_t out[4]) {
     const uint32_t a = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);   // w0.0 w1.0 w0.1 w1.1
@@ -192,7 +147,7 @@ __global__ __launch_bounds__(256, 2) void k_gram_bits(const u64* __restrict__ an
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int64_t nblk = (n + 63) / 64;
     int64_t bi, bj;
-    if (!tri_tile(blockIdx.x, nblk, bi, bj)) return;
+    if (!ufd::tri_tile(blockIdx.x, nblk, bi, bj)) return;
     {
         // pairs of the tile in the stripe range: partner offset d = j - i; stripe d-1
         // if d <= S, else n-d-1
@@ -339,9 +294,7 @@ hipError_t tip_bits(const ufp::Emb& e, int64_t n_tips, void* ws, hipStream_t st)
     if (p.nblk > 65535 || p.levels > 16) return hipErrorInvalidValue;
     u64* tips = static_cast<u64*>(ws);
     const int64_t n16 = (p.nblk * p.pyr * 8 + 15) / 16;   // (the bits of a chunk follow)
-    hipLaunchKernelGGL(k_zero16, dim3(unsigned(std::min<int64_t>((n16 + 255) / 256, 16384))), dim3(256),
-                       0, st, static_cast<uint4*>(ws), n16);
-    hipError_t er = hipGetLastError();
+    hipError_t er = ufk::zero16(ws, n16, st);
     if (er != hipSuccess) return er;
     hipLaunchKernelGGL(k_tip_bits, dim3(unsigned(e.n)), dim3(256), 0, st, p.pyr, e.row_ptr, e.rank, tips);
     er = hipGetLastError();

@@ -138,4 +138,43 @@ __device__ __forceinline__ void for_each_counted_row_branch(const ufp::Emb& e, c
     }
 }
 
+// Tile t of the upper triangle of nblk x nblk blocks: super-tiles of G x G blocks,
+// super-row-major, the diagonal super-tile first in its super-row, row-major inside.
+// Workgroups are dealt to the 8 XCDs round-robin and XCD x takes the x-th eighth of
+// that order, so its CUs walk neighbouring tiles (shared rows and columns in its L2).
+constexpr int kTriGroup = 8;
+__device__ __forceinline__ bool tri_tile(int64_t b, int64_t nblk, int64_t& bi, int64_t& bj) {
+    constexpr int64_t G = kTriGroup;
+    const int64_t L = nblk * (nblk + 1) / 2;
+    const int64_t per = (L + 7) / 8;
+    int64_t v = (b & 7) * per + (b >> 3);
+    if ((b >> 3) >= per || v >= L) return false;
+    for (int64_t r0 = 0;;) {
+        const int64_t r = min(G, nblk - r0);
+        const int64_t diag = r * (r + 1) / 2, cnt = diag + r * (nblk - r0 - r);
+        if (v >= cnt) {
+            v -= cnt;
+            r0 += r;
+            continue;
+        }
+        if (v < diag) {
+            int64_t a = 0;
+            while (v >= r - a) {
+                v -= r - a;
+                ++a;
+            }
+            bi = r0 + a;
+            bj = bi + v;
+        } else {
+            v -= diag;
+            const int64_t c0 = r0 + r + (v / (r * G)) * G;
+            const int64_t c = min(G, nblk - c0);
+            const int64_t w = v % (r * G);
+            bi = r0 + w / c;
+            bj = c0 + w % c;
+        }
+        return true;
+    }
+}
+
 }  // namespace ufd

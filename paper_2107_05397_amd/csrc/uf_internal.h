@@ -267,5 +267,7 @@ hipError_t grand_mean(const double* row_means, int64_t n, double* out, hipStream
 
 // Zero n unsigned counters (a kernel, so that graph replays stay valid).
 hipError_t zero_u32(unsigned* p, int64_t n, hipStream_t st);
+// and n16 times 16 bytes.
+hipError_t zero16(void* p, int64_t n16, hipStream_t st);
 
 }  // namespace ufk

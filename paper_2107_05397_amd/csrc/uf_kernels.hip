@@ -964,6 +964,12 @@ __global__ __launch_bounds__(256) void k_pack_nodes(const int32_t* __restrict__ 
     if (v < m) nodes[v] = make_int4(lo[v], hi[v], parent[v], above[v]);
 }
 
+__global__ __launch_bounds__(256) void k_zero16(uint4* __restrict__ p, int64_t n16) {
+    const int64_t step = int64_t(gridDim.x) * 256;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n16; i += step)
+        p[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 __global__ void k_zero_u32(unsigned* __restrict__ p, int64_t n) {
     const int64_t i = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
@@ -1105,6 +1111,13 @@ hipError_t row_sums(const double* q, int64_t n, int64_t sb, int64_t se, double* 
 
 hipError_t grand_mean(const double* row_means, int64_t n, double* out, hipStream_t st) {
     hipLaunchKernelGGL(k_grand_mean, dim3(1), dim3(256), 0, st, row_means, n, out);
+    return hipGetLastError();
+}
+
+hipError_t zero16(void* p, int64_t n16, hipStream_t st) {
+    if (n16 <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_zero16, dim3(unsigned(std::min<int64_t>((n16 + 255) / 256, 16384))), dim3(256), 0, st,
+                       static_cast<uint4*>(p), n16);
     return hipGetLastError();
 }
 

@@ -24,13 +24,11 @@ constexpr int64_t kPairWideN = 4096;
 
 // Workspace of one chunk of kc branches of n samples: values, then masks.
 struct PairChunk {
-    int64_t kcp = 0;             // masks per block
     size_t off_mask = 0, bytes = 0;
 };
 inline PairChunk pair_chunk(int64_t n, int64_t kc, size_t elem) {
     PairChunk c;
     const size_t nblk = size_t((n + 63) / 64);
-    c.kcp = kc;
     c.off_mask = nblk * size_t(kc + 1) * 64 * elem;
     c.bytes = (c.off_mask + nblk * size_t(kc) * 8 + 15) / 16 * 16;
     return c;

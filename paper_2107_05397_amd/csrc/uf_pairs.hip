@@ -10,7 +10,6 @@
 // branch k of the chunk (row kc is all zeros), mask[b][k] the bit of every sample
 // of the block that touches it.
 //
-//   k_pair_zero    clears a chunk
 //   k_pair_fill    one walk over the branches every sample touches writes both
 //   k_pairs        the tiles
 //   k_pair_planes  adds the segments' sums in branch order
@@ -27,19 +26,13 @@
 namespace ufx {
 namespace {
 
-__global__ __launch_bounds__(256) void k_pair_zero(uint4* __restrict__ p, int64_t n16) {
-    const int64_t step = int64_t(gridDim.x) * 256;
-    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < n16; i += step)
-        p[i] = make_uint4(0u, 0u, 0u, 0u);
-}
-
 // One block per sample (tabs: of a batch of tables): every branch of [k0, k0 + kc) that the sample touches, once.
 // Weighted: x = l c / T with the exact count c; unweighted: x = l.  Bound by the chain of
 // the walks and by their scattered reads and writes.  With the row searched in memory and
 // the node fields apart: 7,495 samples of eight tables, 20,000 branches 685 -> 547 us;
 // 1,500 samples x 300 tips, 40,000 branches (FP64) 299 -> 204.
 template <typename T, bool W>
-__global__ __launch_bounds__(256) void k_pair_fill(ufp::Emb e, int32_t k0, int32_t kc, int64_t kcp,
+__global__ __launch_bounds__(256) void k_pair_fill(ufp::Emb e, int32_t k0, int32_t kc,
                                                    const BatchTable* __restrict__ tabs,
                                                    const int32_t* __restrict__ tab_of,
                                                    T* __restrict__ E,
@@ -58,7 +51,7 @@ __global__ __launch_bounds__(256) void k_pair_fill(ufp::Emb e, int32_t k0, int32
     const int64_t a = e.row_ptr[s], b = e.row_ptr[s + 1];
     const double tot = e.total[s];
     T* Es = E + (ls >> 6) * (int64_t(kc) + 1) * 64 + (ls & 63);
-    unsigned long long* ms = mask + (ls >> 6) * kcp;
+    unsigned long long* ms = mask + (ls >> 6) * kc;
     const unsigned long long bit = 1ull << (ls & 63);
     if constexpr (W) {
         __shared__ ufd::RowLds row;
@@ -76,45 +69,6 @@ __global__ __launch_bounds__(256) void k_pair_fill(ufp::Emb e, int32_t k0, int32
                 Es[int64_t(k) * 64] = T(e.len[v]);
                 atomicOr(&ms[k], bit);
             });
-    }
-}
-
-// Tile t of the upper triangle of nblk x nblk blocks: super-tiles of G x G blocks,
-// super-row-major, the diagonal super-tile first in its super-row, row-major inside.
-// Workgroups are dealt to the 8 XCDs round-robin and XCD x takes the x-th eighth of
-// that order, so its CUs walk neighbouring tiles (shared rows and columns in its L2).
-constexpr int kGroup = 8;
-__device__ __forceinline__ bool tri_tile(int64_t b, int64_t nblk, int64_t& bi, int64_t& bj) {
-    constexpr int64_t G = kGroup;
-    const int64_t L = nblk * (nblk + 1) / 2;
-    const int64_t per = (L + 7) / 8;
-    int64_t v = (b & 7) * per + (b >> 3);
-    if ((b >> 3) >= per || v >= L) return false;
-    for (int64_t r0 = 0;;) {
-        const int64_t r = min(G, nblk - r0);
-        const int64_t diag = r * (r + 1) / 2, cnt = diag + r * (nblk - r0 - r);
-        if (v >= cnt) {
-            v -= cnt;
-            r0 += r;
-            continue;
-        }
-        if (v < diag) {
-            int64_t a = 0;
-            while (v >= r - a) {
-                v -= r - a;
-                ++a;
-            }
-            bi = r0 + a;
-            bj = bi + v;
-        } else {
-            v -= diag;
-            const int64_t c0 = r0 + r + (v / (r * G)) * G;
-            const int64_t c = min(G, nblk - c0);
-            const int64_t w = v % (r * G);
-            bi = r0 + w / c;
-            bj = c0 + w % c;
-        }
-        return true;
     }
 }
 
@@ -210,7 +164,7 @@ constexpr int kWin = kPairWin;
 template <typename T, int A, int U, bool L1>
 __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
                                           const unsigned long long* __restrict__ mask, int kc,
-                                          int64_t kcp, int n, int64_t bi, int64_t bj, int ig, int k_lo,
+                                          int n, int64_t bi, int64_t bj, int ig, int k_lo,
                                           int k_hi, int sb, int se, bool load, T* out,
                                           T* total = nullptr, bool more = false) {
     constexpr int PER = 16 / A;             // branches per load of x_i
@@ -239,8 +193,8 @@ __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
     }
     const T* Ei = E + bi * (int64_t(kc) + 1) * 64;
     const T* Ej = E + bj * (int64_t(kc) + 1) * 64;
-    const uint32_t* mi = reinterpret_cast<const uint32_t*>(mask + bi * kcp) + (ig >> 5);
-    const unsigned long long* mj = mask + bj * kcp;
+    const uint32_t* mi = reinterpret_cast<const uint32_t*>(mask + bi * kc) + (ig >> 5);
+    const unsigned long long* mj = mask + bj * kc;
     const unsigned ibits = ((1u << A) - 1u) << (ig & 31);
     const unsigned kl = unsigned(lane & 15) / A;
     const unsigned oi = unsigned(ig + (lane & (A - 1))) * unsigned(sizeof(T));
@@ -321,7 +275,7 @@ __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
 template <typename T, int A, bool L1>
 __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
                                                const unsigned long long* __restrict__ mask, int kc,
-                                               int64_t kcp, int n, int sb, int se, int ka, int kb,
+                                               int n, int sb, int se, int ka, int kb,
                                                int seg, int load, T* __restrict__ out,
                                                int64_t plane) {
     constexpr int SUB = 64 / (4 * A);
@@ -331,13 +285,13 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
     const int64_t nblk = (n + 63) / 64;
     int64_t bi, bj;
     const int64_t tb = blockIdx.x;
-    if (!tri_tile(((tb >> 3) / SUB) * 8 + (tb & 7), nblk, bi, bj)) return;
+    if (!ufd::tri_tile(((tb >> 3) / SUB) * 8 + (tb & 7), nblk, bi, bj)) return;
     const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;     // first i inside its block
     const int i0 = int(bi) * 64 + ig, j0 = int(bj) * 64;
     if (i0 >= n) return;
     if (!pairs_in_range(i0, min(i0 + A, n), j0, min(j0 + 64, n), n, sb, se)) return;
     const int k_lo = ka + seg * int(blockIdx.y), k_hi = min(kb, k_lo + seg);
-    pair_wave<T, A, U, L1>(queue[wave], E, mask, kc, kcp, n, bi, bj, ig, k_lo, k_hi, sb, se, load != 0,
+    pair_wave<T, A, U, L1>(queue[wave], E, mask, kc, n, bi, bj, ig, k_lo, k_hi, sb, se, load != 0,
                            out + int64_t(blockIdx.y) * plane);
 }
 
@@ -377,7 +331,7 @@ __global__ __launch_bounds__(256) void k_batch_pairs(const float* __restrict__ E
         const int k_lo = int(max<int64_t>(s0 - k0, 0)), k_hi = int(min<int64_t>(s0 + t.seg - k0, kc));
         if (k_lo >= k_hi) return;
         const bool ends = all && (last || s0 + t.seg <= int64_t(k0) + kc);
-        pair_wave<float, A, U, true>(queue[wave], E + t.e_off, mask + t.m_off, kc, kc, n, it.z, it.w, ig, k_lo,
+        pair_wave<float, A, U, true>(queue[wave], E + t.e_off, mask + t.m_off, kc, n, it.z, it.w, ig, k_lo,
                                      k_hi, 0, n / 2, s0 < k0, acc + t.p_off + (all ? 0 : g) * t.plane,
                                      ends ? acc + t.acc_off : nullptr, ends && g > 0);
         if constexpr (!ALL) break;
@@ -423,16 +377,14 @@ hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, vo
     const BatchTable* no_tabs = nullptr;
     const int32_t* no_tab_of = nullptr;
     const int64_t n16 = int64_t(c.bytes / 16);
-    const unsigned zb = unsigned(std::min<int64_t>((n16 + 255) / 256, 16384));
-    hipLaunchKernelGGL(k_pair_zero, dim3(zb), dim3(256), 0, st, static_cast<uint4*>(chunk), n16);
-    hipError_t er = hipGetLastError();
+    const hipError_t er = ufk::zero16(chunk, n16, st);
     if (er != hipSuccess) return er;
     if (weighted)
         hipLaunchKernelGGL((k_pair_fill<T, true>), dim3(fill_blocks(e.n)), dim3(256), 0, st, e,
-                           int32_t(k0), int32_t(kc), c.kcp, no_tabs, no_tab_of, E, mask);
+                           int32_t(k0), int32_t(kc), no_tabs, no_tab_of, E, mask);
     else
         hipLaunchKernelGGL((k_pair_fill<T, false>), dim3(fill_blocks(e.n)), dim3(256), 0, st, e,
-                           int32_t(k0), int32_t(kc), c.kcp, no_tabs, no_tab_of, E, mask);
+                           int32_t(k0), int32_t(kc), no_tabs, no_tab_of, E, mask);
     return hipGetLastError();
 }
 
@@ -447,7 +399,7 @@ static hipError_t pairs_as(const void* chunk, int64_t n, int64_t kc, int64_t ka,
         return hipErrorInvalidValue;
     const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + c.off_mask);
     hipLaunchKernelGGL((k_pairs<T, A, L1>), dim3(unsigned(blocks), unsigned(count)), dim3(256), 0, st,
-                       static_cast<const T*>(chunk), mask, int(kc), c.kcp, int(n), int(sb), int(se),
+                       static_cast<const T*>(chunk), mask, int(kc), int(n), int(sb), int(se),
                        int(ka), int(kb), int(std::min<int64_t>(seg, 0x3fffffff)), load, out, plane);
     return hipGetLastError();
 }
@@ -470,12 +422,10 @@ hipError_t batch_fill(const ufp::Emb& e, const BatchTable* tabs, const int32_t* 
     if (e.n <= 0 || kc <= 0) return hipSuccess;
     if (kc > 0x3fffffff) return hipErrorInvalidValue;
     const int64_t n16 = int64_t((bytes + 15) / 16);
-    hipLaunchKernelGGL(k_pair_zero, dim3(unsigned(std::min<int64_t>((n16 + 255) / 256, 16384))), dim3(256),
-                       0, st, static_cast<uint4*>(chunk), n16);
-    const hipError_t er = hipGetLastError();
+    const hipError_t er = ufk::zero16(chunk, n16, st);
     if (er != hipSuccess) return er;
     hipLaunchKernelGGL((k_pair_fill<float, true>), dim3(fill_blocks(e.n)), dim3(256), 0, st, e, int32_t(k0),
-                       int32_t(kc), kc, tabs, tab_of, static_cast<float*>(chunk),
+                       int32_t(kc), tabs, tab_of, static_cast<float*>(chunk),
                        reinterpret_cast<unsigned long long*>(static_cast<char*>(chunk) + off_mask));
     return hipGetLastError();
 }
