@@ -363,6 +363,7 @@ __device__ __forceinline__ void band_tile(BandLds& L, const T* __restrict__ E, i
 // fewer than a round, are cut along the branches into kBandWgs equal shares (multiples of
 // 4 stages), taken first by as many workgroups, so that all end at about the same time.
 // The sums are integers: a tile's parts add up in any order to the same bits.
+// shares: 0 where the left-over tiles take a workgroup each instead (band_u32).
 // One workgroup per tile left CUs empty in the last (or only) round: 300 samples x 2,912
 // branches 1,030 -> 109 us, 1,000 x 3,838 1.36 -> 0.67 ms, 3,333 x 6,849 2.44 -> 1.68,
 // 10,000 x 14,873 27.5 -> 23.7; 30,000 samples, 200,000 tips 209 -> 198 (resident
@@ -370,13 +371,12 @@ __device__ __forceinline__ void band_tile(BandLds& L, const T* __restrict__ E, i
 // 50,000 samples).  On touched-branch pair tiles (min and add) these took
 // 2.2 (3,333) and 56 ms: most of a split's dense branches are touched in every tile.
 __global__ __launch_bounds__(256, 2) void k_band(const uint32_t* __restrict__ E, int64_t kc, int64_t n,
-                                              int64_t sb, int64_t se, int64_t n_iblk, int first,
+                                              int64_t sb, int64_t se, int64_t n_iblk, int shares, int first,
                                               uint32_t* __restrict__ acc) {
     __shared__ __attribute__((aligned(16))) BandLds L;
     const int64_t n_sblk = (se - sb + kBandTS - 1) / kBandTS;
-    const int64_t n_tiles = n_iblk * n_sblk, whole = n_tiles / kBandWgs * kBandWgs;
+    const int64_t n_tiles = n_iblk * n_sblk, whole = shares ? n_tiles / kBandWgs * kBandWgs : n_tiles;
     const int64_t stages = (kc + kBandKS - 1) / kBandKS, work = (n_tiles - whole) * stages;
-    const int64_t shares = n_tiles > whole ? kBandWgs : 0;      // (a multiple of 8: XCDs as below)
     const bool share = int64_t(blockIdx.x) < shares;
     const int64_t rank = int64_t(blockIdx.x & 7) * (kBandWgs / 8) + (blockIdx.x >> 3);
     int64_t w = share ? (rank * work / kBandWgs) & ~int64_t(3) : 0;
@@ -1017,13 +1017,19 @@ hipError_t band_u32(const uint32_t* E, int64_t kc, int64_t n, int64_t sb, int64_
     const int64_t n_iblk = (n + kBandI - 1) / kBandI;
     const int64_t n_tiles = n_iblk * ((se - sb + kBandTS - 1) / kBandTS);
     if (n_tiles > 0x7ffff000) return hipErrorInvalidValue;
-    if (first && n_tiles % kBandWgs) {   // the tiles cut in parts add to it
+    // A workgroup spared g stages (6 to 8 us each) ends sooner by them; every share adds its
+    // 32,768 sums atomically (0.65 us of the chip).  3,000 samples x 398 branches (144 tiles of
+    // 25 stages) in shares 0.63 ms, a workgroup a tile 0.30; 12,000 x 118 1.33 and 1.11.
+    const int64_t left = n_tiles % kBandWgs, stages = (kc + kBandKS - 1) / kBandKS, work = left * stages;
+    const int64_t parts = std::min<int64_t>(kBandWgs, (work + 3) / 4);      // (the others are empty)
+    const bool cut = left > 0 && 9 * (stages - (work + parts - 1) / parts) > parts;
+    if (first && cut) {   // the tiles cut in parts add to it
         const hipError_t er = zero_u32(acc, (se - sb) * n, st);
         if (er != hipSuccess) return er;
     }
-    const int64_t whole = n_tiles / kBandWgs * kBandWgs;
-    const unsigned blocks = unsigned(whole + (n_tiles > whole ? kBandWgs : 0));
-    hipLaunchKernelGGL(k_band, dim3(blocks), dim3(256), 0, st, E, kc, n, sb, se, n_iblk, first, acc);
+    const unsigned blocks = unsigned(cut ? n_tiles - left + kBandWgs : n_tiles);
+    hipLaunchKernelGGL(k_band, dim3(blocks), dim3(256), 0, st, E, kc, n, sb, se, n_iblk, cut ? kBandWgs : 0, first,
+                       acc);
     return hipGetLastError();
 }
 
