@@ -197,11 +197,10 @@ constexpr int kGramKPad = 256;    // K of its presence matrix is padded to this 
 // e.nodes; above: branches of nonzero length from each position to the root.
 hipError_t pack_nodes(const uf_embedding& e, const int32_t* above, hipStream_t st);
 // Per-sample scalars from the postorder leaf intervals (one wave per sample).  touched
-// (nullable): [0] lowered to the smallest mean length of the branches a sample touches (those
-// of nonzero length), as the bits of a double, [1] raised by their number for each sample.
+// (nullable, [n]): the branches of nonzero length that a sample touches.
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos,
                           const int32_t* tip_pos, const double* d64, const double* d32,
-                          const double* dbf, unsigned long long* touched, hipStream_t st);
+                          const double* dbf, int32_t* touched, hipStream_t st);
 
 // Sample-major presence P[s][k]: FP8 e4m3 -2.0 (0xC0) where present, else 0, k < kpad (zero beyond
 // kc), for positions [k0, k0+kc), or for positions list[k0 .. k0+kc) when list is

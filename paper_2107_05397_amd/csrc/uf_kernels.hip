@@ -42,9 +42,8 @@ __device__ __forceinline__ double wave_sum(double v) {
 //      = sum_k D(t_k) - sum_k D(lca(t_k, t_{k+1}))  for tips in rank order,
 // which is sum_v l_v a_v.  D is the root distance with FP64, FP32-rounded or
 // BF16 hi+lo lengths.  Lane sums and the wave reduction run in a fixed order.
-//   MEAN: the branches of nonzero length that the sample touches, K, likewise from their
-// numbers up to the root (nodes[v].w): touched[0] = min(itself, w / K), as bits, which order
-// as the values do; touched[1] += K.
+//   MEAN: the branches of nonzero length that the sample touches, likewise from their
+// numbers up to the root (nodes[v].w).
 // ----------------------------------------------------------------------------
 template <bool MEAN>
 __global__ __launch_bounds__(256) void k_sample_scalars(
@@ -54,7 +53,7 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
     const int32_t* __restrict__ tip_pos, const double* __restrict__ d64,
     const double* __restrict__ d32, const double* __restrict__ dbf, double* __restrict__ sw,
     double* __restrict__ wu, double* __restrict__ wu32, double* __restrict__ wub,
-    const int4* __restrict__ nodes, unsigned long long* __restrict__ touched) {
+    const int4* __restrict__ nodes, int32_t* __restrict__ touched) {
     const int lane = threadIdx.x & 63;
     const int64_t s = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (s >= n) return;
@@ -91,10 +90,7 @@ __global__ __launch_bounds__(256) void k_sample_scalars(
     }
     if constexpr (MEAN) {
         k = wave_sum(k);
-        if (lane == 0 && k > 0.0) {
-            atomicMin(&touched[0], (unsigned long long)__double_as_longlong(fmax(w, 0.0) / k));
-            atomicAdd(&touched[1], (unsigned long long)k);
-        }
+        if (lane == 0) touched[s] = int32_t(k);
     }
 }
 
@@ -991,7 +987,7 @@ hipError_t pack_nodes(const uf_embedding& e, const int32_t* above, hipStream_t s
 
 hipError_t sample_scalars(const uf_embedding& e, const int32_t* parent_pos, const int32_t* tip_pos,
                           const double* d64, const double* d32, const double* dbf,
-                          unsigned long long* touched, hipStream_t st) {
+                          int32_t* touched, hipStream_t st) {
     const unsigned blocks = unsigned((e.n + 3) / 4);
     hipLaunchKernelGGL(touched ? k_sample_scalars<true> : k_sample_scalars<false>, dim3(blocks), dim3(256),
                        0, st, e.n, e.row_ptr, e.rank, e.cum, e.total, parent_pos, e.hi, tip_pos, d64, d32,
