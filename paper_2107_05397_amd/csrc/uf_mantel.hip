@@ -714,8 +714,10 @@ uf_status uf_mantel(const double* x, const double* y, int64_t n, int method, con
         UFM_HIP(hipMemcpyAsync(&hbad, bad, 4, hipMemcpyDeviceToHost, s));
         UFM_HIP(hipStreamSynchronize(s));
         if (hbad & 1u) return fail(UF_ERR_ARG, "permutation entries must lie in [0, n)");
-        // a row that names a sample twice has no inverse: the general kernel takes it
-        lds_rows = p.lds && !hbad;
+        // a row that names a sample twice has no inverse: the general kernel takes it, and
+        // one permutation of long rows, too few for the rows' staging to pay (19,000 samples:
+        // 4.7 ms with the rows in LDS, 4.4 without; 8,000: 0.96 and 1.30)
+        lds_rows = p.lds && !hbad && (n_perm > 1 || n <= 16384);
     }
 
     const double* xs = x;
