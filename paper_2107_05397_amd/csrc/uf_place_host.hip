@@ -130,9 +130,17 @@ uf_status uf_project(const uf_tree* tree, const uf_embedding* emb, const int32_t
         int8_t* dsigns = reinterpret_cast<int8_t*>(buf + bd);
         int32_t* dnode = reinterpret_cast<int32_t*>(buf + bd + bs);
         int32_t* dent = reinterpret_cast<int32_t*>(buf + bd + bs + bn);
-        UF_HIP(hipMemcpy(ddims, dims, size_t(cnt) * 4, hipMemcpyHostToDevice));
-        UF_HIP(hipMemcpy(dsigns, signs, size_t(cnt), hipMemcpyHostToDevice));
-        UF_HIP(hipMemcpy(dnode, tree->node_at32.data(), size_t(m) * 4, hipMemcpyHostToDevice));
+        if (bd + bs + bn <= size_t(1) << 16) {   // one copy: its call costs more than its bytes
+            std::vector<char> all(bd + bs + bn);
+            std::memcpy(all.data(), dims, size_t(cnt) * 4);
+            std::memcpy(all.data() + bd, signs, size_t(cnt));
+            std::memcpy(all.data() + bd + bs, tree->node_at32.data(), size_t(m) * 4);
+            UF_HIP(hipMemcpy(buf, all.data(), all.size(), hipMemcpyHostToDevice));
+        } else {
+            UF_HIP(hipMemcpy(ddims, dims, size_t(cnt) * 4, hipMemcpyHostToDevice));
+            UF_HIP(hipMemcpy(dsigns, signs, size_t(cnt), hipMemcpyHostToDevice));
+            UF_HIP(hipMemcpy(dnode, tree->node_at32.data(), size_t(m) * 4, hipMemcpyHostToDevice));
+        }
         hipStream_t s = static_cast<hipStream_t>(stream);
         UF_HIP(ufp::project(view(*emb), ddims, dsigns, dnode, m, int(per_node), dent, int(out_dim), scale,
                             static_cast<uint16_t*>(out_bf16), s));
