@@ -325,7 +325,9 @@ void uf_free_batch(uf_batch* batch);
  * j < per_node (scale > 0 sets the input scale of the network); dims/signs are HOST arrays indexed by node id
  * ([n_nodes][per_node]; the root's row is ignored).  out_bf16: device
  * [N][out_dim] bfloat16.  Sums are exact fixed point (2^-40), so the result
- * is deterministic.  Synchronises hip_stream. */
+ * is deterministic.  Synchronises hip_stream.  The uploaded arrays stay in the
+ * embedding's device scratch (9 bytes a node and output, 4 a node), which later calls
+ * reuse and freeing the embedding gives back. */
 uf_status uf_project(const uf_tree* tree, const uf_embedding* emb, const int32_t* dims,
                      const int8_t* signs, int64_t per_node, int64_t out_dim, double scale,
                      void* out_bf16, void* hip_stream);

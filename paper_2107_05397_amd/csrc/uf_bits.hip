@@ -126,12 +126,12 @@ __device__ __forceinline__ void transpose4(const uint32_t w[4], uint32_t out[4])
 // Why so.  The bits are 1/64 of FP64 values, so the operands of all tiles stay in L2;
 // of the branches, 20 to 40% are touched on both sides of a 64 x 64 tile, and at int8
 // rates a listed branch costs a tile 32 (nd 8) or 16 SIMD cycles, an eighth of what
-// the vector units need.  It is bound by building operands beside the products (VALU
-// issue 55%, matrix cores 36% of the time at 5,000 samples x 100,000 tips).  Measured
-// with events: FP64 2,001 samples x 20,000 tips 23.4 ms (vector kernel over all
-// branches), 3.2 ms (pair tiles over touched branches) -> 0.34 ms; BF16 hi + lo lengths
-// 5,000 x 100,000 7.4 ms (dense BF16 product over all branches) -> 2.2 ms.  Listing
-// with a ballot per 64 branches and byte stores per listed branch took 3.9 ms.
+// the vector units need.  It is bound by building operands beside the products: the matrix
+// cores are busy in 48% of the SIMDs' busy cycles (nd 4, 5,000 samples x 100,000 tips; nd 8,
+// 2,001 x 20,000: 47%).  Measured with events: FP64 2,001 samples x 20,000 tips 23.4 ms
+// (vector kernel over all branches), 3.2 ms (pair tiles over touched branches) -> 0.32 ms;
+// BF16 hi + lo lengths 5,000 x 100,000 7.4 ms (dense BF16 product over all branches) -> 2.2
+// ms.  Listing with a ballot per 64 branches and byte stores per listed branch took 3.9 ms.
 template <int ND>
 __global__ __launch_bounds__(256, 2) void k_gram_bits(const u64* __restrict__ any,
                                                       const u64* __restrict__ bits,

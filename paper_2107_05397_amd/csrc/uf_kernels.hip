@@ -5,7 +5,8 @@
 //   k_embed_pres_fp8  sample-major FP8 (e4m3) 0/1 presence for the MFMA Gram path (merge)
 //   k_band             weighted stripe-band accumulation of a split's dense set on the
 //                      vector ALUs (LDS-tiled): 32-bit fixed point, one v_sad_u32
-//                      (|a - b| + acc) per update
+//                      (|a - b| + acc) per update; k_band_f32: large FP32 matrices over
+//                      all branches, where most are touched
 //   k_gram_mfma        unweighted Gram product on MFMA (split-precision lengths)
 //   k_finalize         FP64 division, output layouts, -d^2/2 for PCoA
 //   k_rowsum_*         fixed-order two-stage row sums; k_grand_mean

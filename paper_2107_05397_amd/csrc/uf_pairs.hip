@@ -303,11 +303,11 @@ __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
 // Every table's segments together fill the chip, so that its launches do not queue up
 // behind small ones.  Eight tables of 300-1,500 samples x 20,000 branches, a whole call:
 // 8.15 ms with 128 x 128 LDS tiles over all branches (about one workgroup of four waves
-// per CU), now 4.1; three tables of 70-150 x 2,000: 0.77 -> 0.09 ms.  Waves that took
+// per CU), now 3.9; three tables of 70-150 x 2,000: 0.78 -> 0.09 ms.  Waves that took
 // their tiles from counters instead spent 0.37 ms per 4,096 waves on them.  The items of
 // all tables in one list, cut in eighths by count: 7.5 ms (segments differ in length).
-// Three tables of 4,500-9,000 samples x 40,000: 136 -> 87 ms, two of 9,000-16,000 x
-// 100,000: 634 -> 351.
+// Three tables of 4,500-9,000 samples x 40,000: 136 -> 84 ms, two of 9,000-16,000 x
+// 100,000: 634 -> 340; 64 of 2,215-19,953 x 200,000: 33.6 -> 21.4 s.
 template <int A, int U, bool ALL>
 __global__ __launch_bounds__(256) void k_batch_pairs(const float* __restrict__ E,
                                                      const unsigned long long* __restrict__ mask,
