@@ -136,8 +136,9 @@ template <int ND>
 __global__ __launch_bounds__(256, 2) void k_gram_bits(const u64* __restrict__ any,
                                                       const u64* __restrict__ bits,
                                                       const u64* __restrict__ dig, int64_t kc,
-                                                      int64_t words, int64_t seg, int64_t n, int64_t sb,
-                                                      int64_t se, int load, double* __restrict__ out) {
+                                                      int64_t words, int64_t seg, ufd::TileSet tiles,
+                                                      int64_t n, int64_t sb, int64_t se, int load,
+                                                      double* __restrict__ out) {
     constexpr int NB = ND == 8 ? 2 : 1;     // 32-column blocks per wave
     constexpr int PITCH = kBatch + 32;      // rows 32 bytes apart modulo the banks
     __shared__ __attribute__((aligned(16))) uint8_t bi8[8][PITCH], bj8[8][PITCH], d8[ND][PITCH];
@@ -145,9 +146,8 @@ __global__ __launch_bounds__(256, 2) void k_gram_bits(const u64* __restrict__ an
     __shared__ int wave_count[4];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int64_t nblk = (n + 63) / 64;
     int64_t bi, bj;
-    if (!ufd::tri_tile(blockIdx.x, nblk, bi, bj)) return;
+    if (!ufd::tile_of(tiles, blockIdx.x, bi, bj)) return;
     {
         // pairs of the tile in the stripe range: partner offset d = j - i; stripe d-1
         // if d <= S, else n-d-1
@@ -331,7 +331,8 @@ hipError_t gram_bits(int nd, int64_t n, int64_t n_tips, int64_t kc, int64_t spli
                      int64_t se, int load, double* out, const void* ws, hipStream_t st) {
     if (n <= 0 || kc <= 0 || se <= sb) return hipSuccess;
     const BitsPlan p = bits_plan(n, n_tips, kc);
-    const int64_t blocks = 8 * ((p.nblk * (p.nblk + 1) / 2 + 7) / 8);
+    const ufd::TileSet tiles = ufd::tile_set(n, sb, se, true);
+    const int64_t blocks = 8 * ((tiles.total + 7) / 8);
     const int64_t seg = ((kc + splits - 1) / splits + kSplit - 1) / kSplit * kSplit;
     // int32 sums: 127 per branch
     if (blocks > 0x7fffffff || splits < 1 || splits > 65535 || kc > (int64_t(1) << 23)) return hipErrorInvalidValue;
@@ -341,11 +342,11 @@ hipError_t gram_bits(int nd, int64_t n, int64_t n_tips, int64_t kc, int64_t spli
     const u64* dig = reinterpret_cast<const u64*>(base + p.off_dig);
     const dim3 grid{unsigned(blocks), unsigned(splits)};
     if (nd == 8)
-        hipLaunchKernelGGL(k_gram_bits<8>, grid, dim3(256), 0, st, any, bits, dig, kc, p.words, seg, n, sb, se,
-                           load, out);
+        hipLaunchKernelGGL(k_gram_bits<8>, grid, dim3(256), 0, st, any, bits, dig, kc, p.words, seg, tiles, n, sb,
+                           se, load, out);
     else if (nd == 4)
-        hipLaunchKernelGGL(k_gram_bits<4>, grid, dim3(256), 0, st, any, bits, dig, kc, p.words, seg, n, sb, se,
-                           load, out);
+        hipLaunchKernelGGL(k_gram_bits<4>, grid, dim3(256), 0, st, any, bits, dig, kc, p.words, seg, tiles, n, sb,
+                           se, load, out);
     else
         return hipErrorInvalidValue;
     return hipGetLastError();

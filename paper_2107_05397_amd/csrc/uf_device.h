@@ -177,4 +177,59 @@ __device__ __forceinline__ bool tri_tile(int64_t b, int64_t nblk, int64_t& bi, i
     }
 }
 
+// The tiles of stripes [sb, se) of n samples: all of the triangle, or, where these are few,
+// the diagonals bj - bi that the stripes' partner offsets [sb + 1, se] and [n - se, n - sb - 1]
+// fall in (and, `self`, the tiles with bi = bj), 8 rows at a time.  Launching a workgroup for
+// every tile of the triangle, most of them to end at once, took 0.3 ms at 20,000 samples.
+struct TileSet {
+    int64_t nblk = 0, total = 0;
+    int64_t lo[3] = {0, 0, 0}, count[3] = {0, 0, 0};   // first diagonal and diagonals of each run
+    bool all = true;
+};
+inline TileSet tile_set(int64_t n, int64_t sb, int64_t se, bool self) {
+    TileSet t;
+    t.nblk = (n + 63) / 64;
+    t.total = t.nblk * (t.nblk + 1) / 2;
+    // diagonal D holds offsets 64 D - 63 .. 64 D + 63
+    int64_t from = 0, total = 0;
+    auto run = [&](int k, int64_t first, int64_t last) {
+        const int64_t a = first - 63 <= 0 ? 0 : first / 64;   // ceil((first - 63) / 64)
+        t.lo[k] = a < from ? from : a;
+        const int64_t hi = (last + 63) / 64 < t.nblk - 1 ? (last + 63) / 64 : t.nblk - 1;
+        t.count[k] = hi >= t.lo[k] ? hi - t.lo[k] + 1 : 0;
+        if (t.count[k] > 0) {
+            from = hi + 1;
+            total += t.count[k] * (t.nblk - t.lo[k]);
+        }
+    };
+    if (self) run(0, 0, -63);
+    run(1, sb + 1, se);
+    run(2, n - se, n - sb - 1);
+    if (2 * total <= t.total) {
+        t.all = false;
+        t.total = total;
+    }
+    return t;
+}
+// Tile b of 8 ceil(total / 8) workgroups (XCD b mod 8, as above); false: none.
+__device__ __forceinline__ bool tile_of(const TileSet& t, int64_t b, int64_t& bi, int64_t& bj) {
+    if (t.all) return tri_tile(b, t.nblk, bi, bj);
+    const int64_t per = (t.total + 7) / 8;
+    int64_t v = (b & 7) * per + (b >> 3);
+    if ((b >> 3) >= per || v >= t.total) return false;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const int64_t rows = t.nblk - t.lo[k], cnt = t.count[k] * rows;
+        if (v < cnt) {
+            const int64_t g = v / (kTriGroup * t.count[k]), r = v % (kTriGroup * t.count[k]);
+            const int64_t h = min<int64_t>(kTriGroup, rows - g * kTriGroup);
+            bi = g * kTriGroup + r % h;
+            bj = bi + t.lo[k] + r / h;
+            return bj < t.nblk;
+        }
+        v -= cnt;
+    }
+    return false;
+}
+
 }  // namespace ufd

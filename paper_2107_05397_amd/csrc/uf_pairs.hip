@@ -275,17 +275,16 @@ __device__ __forceinline__ void pair_wave(uint32_t* q, const T* __restrict__ E,
 template <typename T, int A, bool L1>
 __global__ __launch_bounds__(256) void k_pairs(const T* __restrict__ E,
                                                const unsigned long long* __restrict__ mask, int kc,
-                                               int n, int sb, int se, int ka, int kb,
-                                               int seg, int load, T* __restrict__ out,
+                                               ufd::TileSet tiles, int n, int sb, int se, int ka,
+                                               int kb, int seg, int load, T* __restrict__ out,
                                                int64_t plane) {
     constexpr int SUB = 64 / (4 * A);
     constexpr int U = kPairU;
     __shared__ uint32_t queue[4][kWin + U];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t nblk = (n + 63) / 64;
     int64_t bi, bj;
     const int64_t tb = blockIdx.x;
-    if (!ufd::tri_tile(((tb >> 3) / SUB) * 8 + (tb & 7), nblk, bi, bj)) return;
+    if (!ufd::tile_of(tiles, ((tb >> 3) / SUB) * 8 + (tb & 7), bi, bj)) return;
     const int ig = (int((tb >> 3) % SUB) * 4 + wave) * A;     // first i inside its block
     const int i0 = int(bi) * 64 + ig, j0 = int(bj) * 64;
     if (i0 >= n) return;
@@ -389,17 +388,16 @@ hipError_t pair_fill(const ufp::Emb& e, int weighted, int64_t k0, int64_t kc, vo
 }
 
 template <typename T, int A, bool L1>
-static hipError_t pairs_as(const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
+static hipError_t pairs_as(const ufd::TileSet& tiles, const void* chunk, int64_t n, int64_t kc, int64_t ka, int64_t kb, int64_t seg,
                            int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
                            hipStream_t st) {
     const PairChunk c = pair_chunk(n, kc, sizeof(T));
-    const int64_t nblk = (n + 63) / 64;
-    const int64_t blocks = 8 * (64 / (4 * A)) * ((nblk * (nblk + 1) / 2 + 7) / 8);
+    const int64_t blocks = 8 * (64 / (4 * A)) * ((tiles.total + 7) / 8);
     if (blocks > 0x7fffffff || n > 0x7fffff00 || kc > 0x3fffffff || count > 65535)
         return hipErrorInvalidValue;
     const auto* mask = reinterpret_cast<const unsigned long long*>(static_cast<const char*>(chunk) + c.off_mask);
     hipLaunchKernelGGL((k_pairs<T, A, L1>), dim3(unsigned(blocks), unsigned(count)), dim3(256), 0, st,
-                       static_cast<const T*>(chunk), mask, int(kc), int(n), int(sb), int(se),
+                       static_cast<const T*>(chunk), mask, int(kc), tiles, int(n), int(sb), int(se),
                        int(ka), int(kb), int(std::min<int64_t>(seg, 0x3fffffff)), load, out, plane);
     return hipGetLastError();
 }
@@ -409,12 +407,14 @@ hipError_t pairs(int form, const void* chunk, int64_t n, int64_t kc, int64_t ka,
                  int64_t count, int64_t sb, int64_t se, int load, T* out, int64_t plane,
                  hipStream_t st) {
     if (n <= 0 || kb <= ka) return hipSuccess;
+    const ufd::TileSet t = ufd::tile_set(n, sb, se, false);
+    // (few stripes of a wide table: the narrower tiles, for twice the waves)
+    const bool wide = n >= kPairWideN && t.total >= kPairWideN / 64 * (kPairWideN / 64) / 2;
     if (form == kPairL1)
-        return n >= kPairWideN
-                   ? pairs_as<T, 2 * kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st)
-                   : pairs_as<T, kPairA, true>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
+        return wide ? pairs_as<T, 2 * kPairA, true>(t, chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st)
+                    : pairs_as<T, kPairA, true>(t, chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
     if (form != kPairMin) return hipErrorInvalidValue;
-    return pairs_as<T, kPairA, false>(chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
+    return pairs_as<T, kPairA, false>(t, chunk, n, kc, ka, kb, seg, count, sb, se, load, out, plane, st);
 }
 
 hipError_t batch_fill(const ufp::Emb& e, const BatchTable* tabs, const int32_t* tab_of, int64_t k0,
