@@ -34,18 +34,20 @@ def test_unweighted_workspace_holds_one_sum_per_pair():
     assert few <= 64 << 20
 
 
-# just above 1 GiB of sums: two parts; even and odd
-@pytest.mark.parametrize("n,precision", [(11600, "fp64"), (11701, "fp64"), (16500, "fp32")])
+# just above 16 GiB of sums: two parts; even and odd
+@pytest.mark.parametrize("n,precision", [(46400, "fp64"), (46501, "fp64"), (65700, "fp32")])
 def test_unweighted_in_parts(n, precision):
     import torch
     emb = _embedding(n, 60, n)
-    full, rm, gm = uf.dm(emb, "unweighted", precision, row_means=True)
+    dtype = torch.float64 if precision == "fp64" else torch.float32
+    full, rm, gm = uf.dm(emb, "unweighted", precision, out_dtype=dtype, row_means=True)
     s = n // 2
     buf = torch.full_like(full, -1.0)
     for k in range(4):
         uf.dm_stripes(emb, "unweighted", precision, s * k // 4, s * (k + 1) // 4, layout="condensed", out=buf)
     assert torch.equal(buf, full)
-    stripes, _ = uf.dm_stripes(emb, "unweighted", precision, 0, s, out_dtype=torch.float64)
+    del buf
+    stripes, _ = uf.dm_stripes(emb, "unweighted", precision, 0, s, out_dtype=dtype)
     g = torch.Generator(device="cuda").manual_seed(n)
     a = torch.randint(0, s, (1 << 20,), generator=g, device="cuda")
     i = torch.randint(0, n, (1 << 20,), generator=g, device="cuda")
@@ -53,14 +55,15 @@ def test_unweighted_in_parts(n, precision):
     lo, hi = torch.minimum(i, j), torch.maximum(i, j)
     assert torch.equal(stripes[a, i], full[lo * n - lo * (lo + 1) // 2 + hi - lo - 1])
     # row means of -d^2/2 from the stripes: n terms of at most 1/2, each rounded, in any order
-    q = -0.5 * stripes * stripes
-    if n % 2 == 0:
-        q[-1, s:] = 0.0
-    sums = q.sum(0)
-    for k in range(0, s, 64):
-        for t in range(k, min(s, k + 64)):
-            sums += torch.roll(q[t], t + 1)
-    assert torch.max(torch.abs(sums / n - rm)).item() <= 2.0 ** -53 * (n + 4)
+    # (from FP32 distances: each of d <= 1 rounded to 2^-25)
+    sums = torch.zeros(n, dtype=torch.float64, device="cuda")
+    for t in range(s):
+        q = -0.5 * stripes[t].double() ** 2
+        if n % 2 == 0 and t == s - 1:
+            q[s:] = 0.0
+        sums += q + torch.roll(q, t + 1)
+    tol = 2.0 ** -53 * (n + 4) + (0.0 if dtype == torch.float64 else 2.0 ** -25)
+    assert torch.max(torch.abs(sums / n - rm)).item() <= tol
     assert abs(float(gm) - float(rm.mean())) <= 2.0 ** -53 * (n + 4)
 
 
