@@ -971,7 +971,7 @@ __global__ __launch_bounds__(256) void k_rerank(SparseView q, SparseView rf,
 // bytes from a 1.6 MB row (200,000 branches): 1,500 queries x 100 candidates of 6,000
 // branches 6.5 -> 1.35 ms (zeroing of the rows included). What is left is one pass over
 // each candidate's list, 12 bytes an entry; its cache traffic was not counted.
-constexpr int kRrThreads = 1024, kRrWaves = kRrThreads / 64, kRrU = 8, kRrClasses = 16;
+constexpr int kRrU = 8, kRrClasses = 16;
 
 // Sums of N values over the wave's lanes, value m in the lanes whose top bits are m: steps of
 // OFF, OFF / 2, ... lanes for every value, the first ones on the values that a lane keeps.
@@ -992,8 +992,9 @@ __device__ __forceinline__ double lane_sums(const double* a, int lane) {
     }
 }
 
-template <int W>
-__global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, SparseView rf,
+// THREADS: of a block.
+template <int W, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_rerank_bits(SparseView q, SparseView rf,
                                                             const int32_t* __restrict__ qids,
                                                             const int32_t* __restrict__ cand,
                                                             int64_t nq, int kc, int share,
@@ -1001,29 +1002,30 @@ __global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, Sparse
                                                             double* __restrict__ scratch,
                                                             double* __restrict__ out) {
     extern __shared__ unsigned long long sh[];
-    __shared__ double red[kRrWaves];
-    __shared__ int wave_tot[kRrWaves];
+    constexpr int WAVES = THREADS / 64;
+    __shared__ double red[WAVES];
+    __shared__ int wave_tot[WAVES];
     unsigned long long* bits = sh;                                      // [words]
     uint16_t* below = reinterpret_cast<uint16_t*>(sh + words);          // [words]
     double* vals = vals_lds ? reinterpret_cast<double*>(sh + words + (words + 3) / 4)
                             : scratch + int64_t(blockIdx.x) * nb;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    constexpr int groups = kRrWaves / W, PER = kRrClasses / W, U = PER < kRrU ? PER : kRrU;
+    constexpr int groups = WAVES / W, PER = kRrClasses / W, U = PER < kRrU ? PER : kRrU;
     const int group = wave / W, part = wave % W;
     const int c_lo = int(blockIdx.y) * share, c_hi = min(kc, c_lo + share);
     for (int64_t qi = blockIdx.x; qi < nq; qi += gridDim.x) {
         const int64_t qs = qids[qi];
         const int64_t qa = q.off[qs], qb = q.off[qs + 1];
         __syncthreads();                     // the previous query's tables are consumed
-        for (int w = tid; w < words; w += kRrThreads) bits[w] = 0ull;
+        for (int w = tid; w < words; w += THREADS) bits[w] = 0ull;
         __syncthreads();
-        for (int64_t t = qa + tid; t < qb; t += kRrThreads) {
+        for (int64_t t = qa + tid; t < qb; t += THREADS) {
             const int32_t p = q.pos[t];
             atomicOr(&bits[p >> 6], 1ull << (p & 63));
         }
         __syncthreads();
-        const int per = (words + kRrThreads - 1) / kRrThreads;
+        const int per = (words + THREADS - 1) / THREADS;
         const int w0 = min(words, tid * per), w1 = min(words, w0 + per);
         int own = 0;
         for (int w = w0; w < w1; ++w) own += int(__popcll(bits[w]));
@@ -1045,7 +1047,7 @@ __global__ __launch_bounds__(kRrThreads) void k_rerank_bits(SparseView q, Sparse
         auto place = [&](int32_t p, unsigned long long word) {
             return int(below[p >> 6]) + int(__popcll(word & ((1ull << (p & 63)) - 1ull)));
         };
-        for (int64_t t = qa + tid; t < qb; t += kRrThreads) {
+        for (int64_t t = qa + tid; t < qb; t += THREADS) {
             const int32_t p = q.pos[t];
             vals[place(p, bits[p >> 6])] = q.val[t];
         }
@@ -1400,9 +1402,10 @@ hipError_t rerank(const SparseView& q, const SparseView& r, const int32_t* qids,
     const size_t tables = size_t(words + (words + 3) / 4) * 8, with_vals = tables + size_t(q_longest) * 8;
     constexpr size_t kMost = 158 * 1024;     // beside the static arrays
     if (q_longest < 65536 && tables <= kMost) {
-        using Kernel = decltype(&k_rerank_bits<1>);
-        static const Kernel kernels[] = {&k_rerank_bits<1>, &k_rerank_bits<2>, &k_rerank_bits<4>,
-                                         &k_rerank_bits<8>, &k_rerank_bits<16>};
+        using Kernel = decltype(&k_rerank_bits<1, 1024>);
+        static const Kernel kernels[] = {&k_rerank_bits<1, 1024>, &k_rerank_bits<2, 1024>, &k_rerank_bits<4, 1024>,
+                                         &k_rerank_bits<8, 1024>, &k_rerank_bits<16, 1024>,
+                                         &k_rerank_bits<1, 256>, &k_rerank_bits<2, 256>, &k_rerank_bits<4, 256>};
         static const bool attr_ok = [] {
             for (Kernel k : kernels)
                 if (hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1416,11 +1419,17 @@ hipError_t rerank(const SparseView& q, const SparseView& r, const int32_t* qids,
         // the query out again, so at least 8 candidates)
         const int64_t shares = vals_lds ? std::max<int64_t>(1, std::min<int64_t>((kc + 7) / 8, 512 / nq)) : 1;
         const int share = int((kc + shares - 1) / shares);
+        // Blocks of 256 threads where several fit on a CU and there are enough of them: a block
+        // of 1,024 lays out a short query no faster (20,000 pairs of samples with 100 of 2,000
+        // tips and with 200 of 10,000: 0.37 and 0.48 ms with 1,024 threads, 0.11 and 0.18 with
+        // 256, the dense-row kernel 0.22 and 0.59; 500 of 100,000: 0.85, 1.73 and 4.05).
+        const bool small = with_vals <= 32 * 1024 && nq * shares >= 512;
+        const int waves = small ? 4 : 16;
         int w2 = 0;                          // log2 W
-        while ((1 << w2) < kRrWaves && share << w2 < kRrWaves) ++w2;
+        while ((1 << w2) < waves && share << w2 < waves) ++w2;
         const int64_t gx = vals_lds ? std::min<int64_t>(nq, 1 << 20) : std::min(nq, n_rows);
-        hipLaunchKernelGGL(kernels[w2], dim3(unsigned(gx), unsigned((kc + share - 1) / share)),
-                           dim3(kRrThreads), vals_lds ? with_vals : tables, st, q, r, qids, cand, nq, kc,
+        hipLaunchKernelGGL(kernels[w2 + (small ? 5 : 0)], dim3(unsigned(gx), unsigned((kc + share - 1) / share)),
+                           dim3(64 * waves), vals_lds ? with_vals : tables, st, q, r, qids, cand, nq, kc,
                            share, int(words), nb, vals_lds ? 1 : 0, scratch, out);
         return hipGetLastError();
     }

@@ -1,5 +1,5 @@
 """A pair's re-ranked distance has the same bits whichever queries and candidates it is asked
-for with (one to sixteen waves a candidate)."""
+for with (one to sixteen waves a candidate, blocks of 256 and 1,024 threads)."""
 import numpy as np
 import pytest
 
@@ -35,6 +35,8 @@ def test_distance_is_a_function_of_the_pair(n_tips, nnz):
     want = run(ids, cand)
     big = np.tile(ids, 600 // nq + 1)                          # more queries than workgroups' share
     assert torch.equal(run(big, cand[big])[:nq], want)
+    for k in (1, 3, 5):                                        # many, with few candidates
+        assert torch.equal(run(big, cand[big, :k])[:nq], want[:, :k].contiguous()), k
     for k in (1, 2, 3, 5, 9, 16, nr):                          # one query, and all, with k candidates
         assert torch.equal(run(ids, cand[:, :k]), want[:, :k].contiguous()), k
         assert torch.equal(run(ids[:1], cand[:1, :k]), want[:1, :k].contiguous()), k
